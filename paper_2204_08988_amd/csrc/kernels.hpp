@@ -110,7 +110,16 @@ hipError_t launch_label_gauss(int d, const float* x, long long n, const float* p
 constexpr int SORTED_MIN_D = 5;
 hipError_t launch_label_gauss_z(int d, const float* x, long long n, int G, long long per_block, const float* packed,
                                 int K, uint32_t t, uint64_t seed, int* z, int* hist, int* tot, hipStream_t s);
-hipError_t sorted_plan(long long n, int K, long long hist_cap, int* G, long long* per_block);
+// the same draw on the FP32 matrix cores, used from MX_MIN_D up.  The line lies
+// where the two cross: 5e5 points, K = 16, us per launch at d = 16 / 20 / 24 /
+// 26 / 27 / 28: vector ALUs 63 / 75 / 100 / 127 / 139 / 147, matrix cores (a
+// 16-row block costs the same however many of its rows are there) 63 / 119 /
+// 130 / 140 / 138 / 139
+constexpr int MX_MIN_D = 27;
+hipError_t launch_label_gauss_mx(int d, const float* x, long long n, int G, long long per_block, const float* packed,
+                                 int K, uint32_t t, uint64_t seed, int* z, int* hist, int* tot, hipStream_t s);
+// block_rows: rows per block while n allows at most 2048 blocks (256 or 512)
+hipError_t sorted_plan(long long n, int K, long long hist_cap, int* G, long long* per_block, int block_rows = 512);
 hipError_t launch_sort_by_z(const int* z, long long n, int K, int G, long long per_block, bool have_hist, int* hist,
                             int* tot, int* offs, int* perm, int* zsort, hipStream_t s);
 // waves of the d <= 32 statistics kernel.  In slot mode (cstart = the

@@ -19,7 +19,8 @@
 // z are gathered per lane; the logistic draw is skipped when the score gap
 // exceeds the logistic's range.  For d >= 5 the kernel draws z only and the
 // sub-labels are drawn in cluster-sorted order (sorted.hip), where the
-// sub-cluster records are wave-uniform.
+// sub-cluster records are wave-uniform; from d = MX_MIN_D on the draw runs on
+// the matrix cores (label_gauss_mx.hip).
 #include "kernels.hpp"
 #include "score.hpp"
 
@@ -84,29 +85,6 @@ __global__ __launch_bounds__(BLOCK) void k_label_gauss(const float* __restrict__
   }
 }
 
-__global__ __launch_bounds__(BLOCK) void k_label_gauss_dyn(const float* __restrict__ x, long long n, int d,
-                                                           const float* __restrict__ packed, int K,
-                                                           int k_max, uint32_t t, uint64_t seed,
-                                                           int* __restrict__ z,
-                                                           unsigned char* __restrict__ zsub) {
-  extern __shared__ float lds[];
-  float* dx = lds + threadIdx.x;
-  const int S = gauss_rec_stride(d);
-  const long long stride_pts = (long long)gridDim.x * BLOCK;
-  for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < n; i += stride_pts) {
-    const float* xi = x + i * d;
-    Top2 t2;
-    t2.init();
-    for (int k = 0; k < K; ++k) t2.push(score_rec_dyn(packed + (size_t)k * S, xi, dx, d), k);
-    const int zi = lazy_gumbel_max(t2, K, (uint32_t)i, t, seed,
-                                   [&](int k) { return score_rec_dyn(packed + (size_t)k * S, xi, dx, d); });
-    const float* ps = packed + (size_t)(k_max + 2 * zi) * S;
-    const float delta = score_rec_dyn(ps, xi, dx, d) - score_rec_dyn(ps + S, xi, dx, d);
-    z[i] = zi;
-    zsub[i] = draw_sub(delta, (uint32_t)i, t, seed, K);
-  }
-}
-
 // Cluster draw only, for the cluster-sorted path (d >= 5): block b labels the
 // contiguous points [b per_block, (b + 1) per_block) and writes its histogram
 // of z (hist[b][k]) and adds it to the cluster totals tot[k].
@@ -137,51 +115,6 @@ __global__ __launch_bounds__(BLOCK) void k_label_gauss_z(const float* __restrict
   for (int k = threadIdx.x; k < K; k += BLOCK) {
     hist[(size_t)blockIdx.x * K + k] = h[k];
     if (h[k]) atomicAdd(&tot[k], h[k]);
-  }
-}
-
-__global__ __launch_bounds__(BLOCK) void k_label_gauss_z_dyn(const float* __restrict__ x, long long n, int d,
-                                                             long long per_block, const float* __restrict__ packed,
-                                                             int K, uint32_t t, uint64_t seed, int* __restrict__ z,
-                                                             int* __restrict__ hist, int* __restrict__ tot) {
-  extern __shared__ float lds[];
-  float* dx = lds + threadIdx.x;
-  int* h = reinterpret_cast<int*>(lds + (size_t)d * BLOCK);
-  const int S = gauss_rec_stride(d);
-  for (int k = threadIdx.x; k < K; k += BLOCK) h[k] = 0;
-  __syncthreads();
-  const long long begin = (long long)blockIdx.x * per_block;
-  const long long end = begin + per_block < n ? begin + per_block : n;
-  for (long long i = begin + threadIdx.x; i < end; i += BLOCK) {
-    const float* xi = x + i * d;
-    Top2 t2;
-    t2.init();
-    for (int k = 0; k < K; ++k) t2.push(score_rec_dyn(packed + (size_t)k * S, xi, dx, d), k);
-    const int zi = lazy_gumbel_max(t2, K, (uint32_t)i, t, seed,
-                                   [&](int k) { return score_rec_dyn(packed + (size_t)k * S, xi, dx, d); });
-    z[i] = zi;
-    atomicAdd(&h[zi], 1);
-  }
-  __syncthreads();
-  for (int k = threadIdx.x; k < K; k += BLOCK) {
-    hist[(size_t)blockIdx.x * K + k] = h[k];
-    if (h[k]) atomicAdd(&tot[k], h[k]);
-  }
-}
-
-// All 3K weighted log-likelihoods per point (parity / inspection entry).
-__global__ __launch_bounds__(BLOCK) void k_loglik_gauss_dyn(const float* __restrict__ x, long long n, int d,
-                                                            const float* __restrict__ packed, int K,
-                                                            int k_max, float* __restrict__ out) {
-  extern __shared__ float lds[];
-  float* dx = lds + threadIdx.x;
-  const int S = gauss_rec_stride(d);
-  const long long stride_pts = (long long)gridDim.x * BLOCK;
-  for (long long i = (long long)blockIdx.x * BLOCK + threadIdx.x; i < n; i += stride_pts) {
-    const float* xi = x + i * d;
-    float* o = out + i * 3 * K;
-    for (int k = 0; k < K; ++k) o[k] = score_rec_dyn(packed + (size_t)k * S, xi, dx, d);
-    for (int j = 0; j < 2 * K; ++j) o[K + j] = score_rec_dyn(packed + (size_t)(k_max + j) * S, xi, dx, d);
   }
 }
 
@@ -220,75 +153,11 @@ hipError_t launch_label_gauss(int d, const float* x, long long n, const float* p
     DPMM_LABEL_CASE(2)
     DPMM_LABEL_CASE(3)
     DPMM_LABEL_CASE(4)
-    DPMM_LABEL_CASE(8)
-    DPMM_LABEL_CASE(16)
-    DPMM_LABEL_CASE(32)
     default:
-      hipLaunchKernelGGL(k_label_gauss_dyn, dim3(g), dim3(BLOCK), (size_t)d * BLOCK * sizeof(float), s,
-                         x, n, d, packed, K, k_max, t, seed, z, zsub);
+      return hipErrorInvalidValue;
   }
 #undef DPMM_LABEL_CASE
   return hipGetLastError();
-}
-
-// d = 128, FP32: a workgroup walks its point range in chunks of BLOCK rows,
-// gathered coalesced into LDS columns (stride BLOCK + 1); each thread centres
-// its column in registers and scores the clusters with wave-uniform records.
-// The Gumbel-max runs as one streaming pass: cluster k's Gumbel is drawn only
-// while l_k + G_max can still beat the running best perturbed score, which
-// gives the argmax of l_k + g_k over all k with the same counter-based g_k.
-constexpr int COL_LD = BLOCK + 1;
-
-template <int D>
-__global__ __launch_bounds__(BLOCK) void k_label_gauss_z_col(const float* __restrict__ x, long long n,
-                                                             long long per_block, const float* __restrict__ packed,
-                                                             int K, uint32_t t, uint64_t seed, int* __restrict__ z,
-                                                             int* __restrict__ hist, int* __restrict__ tot) {
-  constexpr int S = (4 + D + D * (D + 1) / 2 + 3) & ~3;
-  extern __shared__ float xs[];  // [D][COL_LD], then the histogram
-  int* h = reinterpret_cast<int*>(xs + D * COL_LD);
-  for (int k = threadIdx.x; k < K; k += BLOCK) h[k] = 0;
-  const long long begin = (long long)blockIdx.x * per_block;
-  const long long end = begin + per_block < n ? begin + per_block : n;
-  for (long long chunk = begin; chunk < end; chunk += BLOCK) {
-    const int rows = (int)(end - chunk < BLOCK ? end - chunk : BLOCK);
-    __syncthreads();  // the previous chunk's columns are read
-    for (int e = threadIdx.x; e < rows * D; e += BLOCK) {
-      const int r = e / D, c = e - r * D;
-      xs[c * COL_LD + r] = x[(size_t)(chunk + r) * D + c];
-    }
-    __syncthreads();
-    const int r = threadIdx.x;
-    if (r < rows) {
-      const long long i = chunk + r;
-      const float* xc = xs + r;
-      float best = -INFINITY;
-      int win = 0, cached = -1;
-      u32x4 blk{0u, 0u, 0u, 0u};
-      for (int k = 0; k < K; ++k) {
-        const float l = score_col<D, COL_LD>(packed + (size_t)k * S, xc);
-        if (l + GUMBEL_MAX_F > best) {
-          const int b = k >> 2;
-          if (b != cached) {
-            blk = rng_block(seed, t, (uint32_t)i, TAG_GUMBEL, (uint32_t)b);
-            cached = b;
-          }
-          const float v = l + gumbel_f(word_of(blk, k & 3));
-          if (v > best) {
-            best = v;
-            win = k;
-          }
-        }
-      }
-      z[i] = win;
-      atomicAdd(&h[win], 1);
-    }
-  }
-  __syncthreads();
-  for (int k = threadIdx.x; k < K; k += BLOCK) {
-    hist[(size_t)blockIdx.x * K + k] = h[k];
-    if (h[k]) atomicAdd(&tot[k], h[k]);
-  }
 }
 
 hipError_t launch_label_gauss_z(int d, const float* x, long long n, int G, long long per_block, const float* packed,
@@ -296,6 +165,7 @@ hipError_t launch_label_gauss_z(int d, const float* x, long long n, int G, long 
   if (n == 0) return hipSuccess;
   hipError_t e = launch_zero64(tot, (size_t)(K + 1) / 2 + 1, s);
   if (e != hipSuccess) return e;
+  if (d >= MX_MIN_D) return launch_label_gauss_mx(d, x, n, G, per_block, packed, K, t, seed, z, hist, tot, s);
   const size_t lh = (size_t)K * sizeof(int);
 #define DPMM_LABELZ_CASE(DD)                                                                                  \
   case DD:                                                                                                    \
@@ -303,35 +173,32 @@ hipError_t launch_label_gauss_z(int d, const float* x, long long n, int G, long 
                        hist, tot);                                                                            \
     break;
   switch (d) {
+    DPMM_LABELZ_CASE(5)
+    DPMM_LABELZ_CASE(6)
+    DPMM_LABELZ_CASE(7)
     DPMM_LABELZ_CASE(8)
+    DPMM_LABELZ_CASE(9)
+    DPMM_LABELZ_CASE(10)
+    DPMM_LABELZ_CASE(11)
+    DPMM_LABELZ_CASE(12)
+    DPMM_LABELZ_CASE(13)
+    DPMM_LABELZ_CASE(14)
+    DPMM_LABELZ_CASE(15)
     DPMM_LABELZ_CASE(16)
-    DPMM_LABELZ_CASE(32)
-    DPMM_LABELZ_CASE(64)
-    case 128: {
-      static bool attr_set = false;
-      if (!attr_set) {  // the row block takes more than 64 KB of LDS
-        e = hipFuncSetAttribute((const void*)k_label_gauss_z_col<128>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                160 * 1024);
-        if (e != hipSuccess) return e;
-        attr_set = true;
-      }
-      hipLaunchKernelGGL(k_label_gauss_z_col<128>, dim3(G), dim3(BLOCK), (size_t)128 * COL_LD * sizeof(float) + lh, s,
-                         x, n, per_block, packed, K, t, seed, z, hist, tot);
-      break;
-    }
+    DPMM_LABELZ_CASE(17)
+    DPMM_LABELZ_CASE(18)
+    DPMM_LABELZ_CASE(19)
+    DPMM_LABELZ_CASE(20)
+    DPMM_LABELZ_CASE(21)
+    DPMM_LABELZ_CASE(22)
+    DPMM_LABELZ_CASE(23)
+    DPMM_LABELZ_CASE(24)
+    DPMM_LABELZ_CASE(25)
+    DPMM_LABELZ_CASE(26)
     default:
-      hipLaunchKernelGGL(k_label_gauss_z_dyn, dim3(G), dim3(BLOCK), (size_t)d * BLOCK * sizeof(float) + lh, s, x, n,
-                         d, per_block, packed, K, t, seed, z, hist, tot);
+      return hipErrorInvalidValue;
   }
 #undef DPMM_LABELZ_CASE
-  return hipGetLastError();
-}
-
-hipError_t launch_loglik_gauss(int d, const float* x, long long n, const float* packed, int K, int k_max,
-                               float* out, hipStream_t s) {
-  if (n == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_loglik_gauss_dyn, dim3(grid_for(n)), dim3(BLOCK), (size_t)d * BLOCK * sizeof(float),
-                     s, x, n, d, packed, K, k_max, out);
   return hipGetLastError();
 }
 

@@ -1,0 +1,149 @@
+// FP32 component scores of 64 points per wave on the FP32 matrix cores, bit for
+// bit the scores of score_rec (score.hpp).
+//
+// v_mfma_f32_16x16x4_f32 adds its four products to an accumulator one after the
+// other in increasing k, each as a fused multiply-add rounded to FP32 (checked
+// against fmaf over 300 000 results with exponents from 2^-70 to 2^70, denormal
+// results included).  A chain of these instructions over k is therefore the
+// chain y = fma(w[c], dx[c], y), c = 0, 1, ..., of the vector-ALU form, and the
+// zeros that pad W above its diagonal and below its last row leave a finite
+// chain unchanged (fma(0, dx, y) = y).  The squared norm q = fma(y_r, y_r, q)
+// runs over increasing r as there: after the rows of a 16-row block are formed,
+// a 4 x 4 transpose over the lane groups (v_permlane32_swap, v_permlane16_swap)
+// gives every lane all 16 rows of one point.
+//
+// Layout: the wave's 64 points are four tiles of 16.  Lane l = 16 g + c holds,
+// for point c of every tile t, the coordinates 4 s + g (x[t][s]); it supplies
+// W[i][4 s + g], i = c, as the A operand (one LDS read for four tiles) and owns
+// point 16 g + c = l of the 64 at the end.
+//
+// Cost at dimension d: sum over the 16-row blocks of 4 tiles x min(4 (rb + 1),
+// d / 4) instructions of 32 cycles: 18 432 cycles per 64 points at d = 128
+// (the vector ALUs: 8 384 FMAs = 33 536 cycles), 1 536 at d = 32 (2 368), 512
+// at d = 16 (608 to 672).  Blocks of 32 rows (32x32x2) would spend 20 480 and
+// 2 048 on the wider diagonal blocks.
+#pragma once
+#include "common.hpp"
+
+namespace dpmm {
+namespace mx {
+
+typedef float f32x4 __attribute__((ext_vector_type(4)));
+constexpr int BUF_DWORD3 = 0x00020000;  // raw buffer descriptor word 3 (gfx9 family)
+// floats that may be read past the end of the last staged record (masked)
+constexpr int REC_PAD = 16;
+
+__host__ __device__ constexpr int row_blocks(int d) { return (d + 15) / 16; }
+
+// x[t][s] of the wave's rows [0, rows) at xr (rows past them, and coordinates
+// past d, are zero).  The loads go through one buffer descriptor per wave:
+// every address is a lane offset plus a constant.
+template <int RB>
+__device__ __forceinline__ void load_rows(const float* xr, int rows, int d, float (&x)[4][4 * RB]) {
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const __amdgpu_buffer_rsrc_t rx =
+      __builtin_amdgcn_make_buffer_rsrc((void*)xr, (short)0, rows * d * 4, BUF_DWORD3);
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int o = ((16 * t + c) * d + g) * 4;
+#pragma unroll
+    for (int s = 0; s < 4 * RB; ++s) {
+      const float v = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, o + 16 * s, 0, 0));
+      x[t][s] = s < 4 * (RB - 1) || 4 * s + g < d ? v : 0.0f;
+    }
+  }
+}
+
+// Four rows (registers v0 .. v3 of tiles 0 .. 3, row 4 g + r of lane group g)
+// transposed: v_j becomes row 4 j + r of the lane's own tile.
+__device__ __forceinline__ void transpose4(float& v0, float& v1, float& v2, float& v3) {
+  const auto a = __builtin_amdgcn_permlane32_swap(__float_as_uint(v0), __float_as_uint(v2), false, false);
+  const auto b = __builtin_amdgcn_permlane32_swap(__float_as_uint(v1), __float_as_uint(v3), false, false);
+  const auto e = __builtin_amdgcn_permlane16_swap(a[0], b[0], false, false);
+  const auto f = __builtin_amdgcn_permlane16_swap(a[1], b[1], false, false);
+  v0 = __uint_as_float(e[0]);
+  v1 = __uint_as_float(e[1]);
+  v2 = __uint_as_float(f[0]);
+  v3 = __uint_as_float(f[1]);
+}
+
+// Squared norm q of the lane's own point under the record p (in LDS, REC_PAD
+// floats readable past it).  `go(q)` is asked after every 16-row block but the
+// last whether the wave still needs the rest: q only grows from block to block,
+// so the score of the partial norm bounds the full one from above, also in
+// rounded arithmetic.  Returns false when it stopped.
+//
+// The steps of a block are pipelined by hand: W and the mean PF steps ahead of
+// their use, x - mu one step ahead, so that neither an LDS read nor the wait
+// from a vector instruction to the matrix instruction that reads it stands
+// between two matrix instructions.
+typedef __attribute__((address_space(3))) const float lds_cfloat;
+
+template <int RB, typename GoFn>
+__device__ __forceinline__ bool sq_norm(lds_cfloat* p, int d, const float (&x)[4][4 * RB], float& q, GoFn go) {
+  constexpr int PF = 3;
+  const int lane = threadIdx.x & 63, g = lane >> 4, i = lane & 15;
+  q = 0.0f;
+  const int ext = d - 16 * (RB - 1);  // rows of the last block
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const bool last = rb == RB - 1;
+    const int NS = 4 * (rb + 1);
+    const int r = 16 * rb + i;
+    const bool rok = !last || i < ext;
+    const int rr = rok ? r : d - 1;
+    lds_cfloat* wr = p + 4 + d + rr * (rr + 1) / 2 + g;
+    lds_cfloat* mu = p + 4 + g;
+    asm volatile("" : "+v"(mu));  // read again per block, not held across the blocks
+    float w[4 * RB], m[4 * RB], b[2][4];
+    auto load = [&](int s) __attribute__((always_inline)) {
+      w[s] = wr[4 * s];
+      m[s] = mu[4 * s];
+    };
+    // the operands of step s: zero above the diagonal, below the last row and past the dimension
+    auto ready = [&](int s) __attribute__((always_inline)) {
+      if (s >= 4 * rb) w[s] = 4 * s + g <= r && rok ? w[s] : 0.0f;
+      else if (last) w[s] = rok ? w[s] : 0.0f;
+      if (last && s >= 4 * rb) m[s] = 4 * s + g < d ? m[s] : 0.0f;
+#pragma unroll
+      for (int t = 0; t < 4; ++t) b[s & 1][t] = x[t][s] - m[s];
+    };
+#pragma unroll
+    for (int s = 0; s < PF && s < NS; ++s) load(s);
+    ready(0);
+    f32x4 a[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) a[t] = f32x4{0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int s = 0; s < 4 * RB; ++s) {
+      if (s >= NS) continue;
+      if (s + PF < NS) load(s + PF);
+      if (s + 1 < NS) ready(s + 1);
+      __builtin_amdgcn_sched_barrier(0);
+      // the last block's steps past the dimension are skipped (uniform)
+      if (!(last && s > 4 * rb) || 4 * (s - 4 * rb) < ext) {
+#pragma unroll
+        for (int t = 0; t < 4; ++t) a[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], b[s & 1][t], a[t], 0, 0, 0);
+      }
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float y0 = a[0][u], y1 = a[1][u], y2 = a[2][u], y3 = a[3][u];
+      transpose4(y0, y1, y2, y3);
+      a[0][u] = y0;
+      a[1][u] = y1;
+      a[2][u] = y2;
+      a[3][u] = y3;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; ++j)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) q = fmaf(a[j][u], a[j][u], q);
+    if (!last && !go(q)) return false;
+  }
+  return true;
+}
+
+}  // namespace mx
+}  // namespace dpmm

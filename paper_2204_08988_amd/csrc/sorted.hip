@@ -727,8 +727,8 @@ struct SortedPlan {
   long long per_block;
 };
 
-SortedPlan plan_blocks(long long n, int K, long long hist_cap) {
-  long long G = (n + 511) / 512;
+SortedPlan plan_blocks(long long n, int K, long long hist_cap, int block_rows) {
+  long long G = (n + block_rows - 1) / block_rows;
   if (G > 2048) G = 2048;
   while (G > 1 && G * K > hist_cap) G = (G + 1) / 2;
   if (G < 1) G = 1;
@@ -1343,8 +1343,8 @@ hipError_t launch_sub_stats_t(int d, const float* x, long long n, const int* per
 
 }  // namespace
 
-hipError_t sorted_plan(long long n, int K, long long hist_cap, int* G, long long* per_block) {
-  const SortedPlan p = plan_blocks(n, K, hist_cap);
+hipError_t sorted_plan(long long n, int K, long long hist_cap, int* G, long long* per_block, int block_rows) {
+  const SortedPlan p = plan_blocks(n, K, hist_cap, block_rows);
   *G = p.G;
   *per_block = p.per_block;
   return hipSuccess;

@@ -1,0 +1,42 @@
+"""GPU: the FP32 cluster draw on the FP32 matrix cores, the log-likelihoods and
+the vector-ALU draw of the dimensions around it, against the FP64 oracle under
+the rules of parity_util.  Dimensions sit on both sides of every 16-row block
+and of the switch between the two draws; row counts on both sides of a wave and
+a workgroup step; K on both sides of one and several record groups in LDS."""
+import numpy as np
+import pytest
+
+from oracle import niw, sampler
+from tests import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+CASES = [  # d, K, n, spread: 4 well apart; 0.2 most clusters within the Gumbel range of every point
+    (6, 5, 300, 4.0), (11, 30, 257, 0.2), (17, 9, 255, 4.0), (26, 40, 300, 0.2), (27, 40, 257, 0.2),
+    (31, 3, 65, 4.0), (32, 33, 513, 0.2), (33, 1, 1, 4.0), (47, 12, 64, 0.2), (48, 13, 63, 4.0), (49, 20, 300, 0.2),
+    (63, 9, 255, 4.0), (65, 10, 256, 0.2), (80, 6, 257, 4.0), (81, 6, 200, 0.2), (96, 5, 300, 4.0), (97, 4, 300, 0.2),
+    (112, 3, 300, 4.0), (113, 2, 300, 0.2), (127, 5, 700, 0.2), (128, 7, 513, 0.2)]
+
+
+@pytest.mark.parametrize("d,K,n,spread", CASES)
+def test_fp32_draw_and_loglik(d, K, n, spread):
+    import torch
+
+    from paper_2204_08988_amd.sampler import Sampler
+    seed = 50 + 3 * d + K
+    params = pu.random_gauss_params(K, d, seed, spread=spread)
+    x = pu.gauss_points(params, n, seed + 1)
+    S = Sampler("gaussian", d, K + 2, 2.0, seed, kappa=1.0, nu=d + 3.0, m=np.zeros(d), psi=np.eye(d))
+    S.set_params(params.log_pi, params.log_pisub, pu.comp_array(params))
+    xt = torch.from_numpy(x).cuda()
+    model = sampler.Model("gaussian", 2.0, niw.NIWPrior(1.0, np.zeros(d), d + 3, np.eye(d)), seed=seed)
+    lc, ls = sampler.loglik(model, x.astype(np.float64), params)
+    Mc, Ms = pu.gauss_scale(x, params)
+    ll = S.loglik(xt).cpu().numpy().astype(np.float64)
+    assert pu.check_loglik(ll, lc, ls, Mc, Ms) <= 1e-5
+    for t in (1, 2):
+        z, zs = S.sample_labels(xt, t)
+        bad_c, bad_s, tie_c, tie_s = pu.label_mismatches(seed, t, z.cpu().numpy(), zs.cpu().numpy(), lc, ls, Mc, Ms)
+        assert bad_c.size == 0 and bad_s.size == 0, (bad_c[:10], bad_s[:10])
+        assert tie_c <= max(2, n // 1000) and tie_s <= max(2, n // 1000)
+    S.close()
