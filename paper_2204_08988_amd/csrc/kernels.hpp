@@ -135,6 +135,17 @@ hipError_t launch_sub_stats(int d, bool sample, const float* x, long long n, con
                             const int* zrow, unsigned char* zsub, const float* packed, int K, int k_max, uint32_t t,
                             uint64_t seed, long long* counts, double* moments, const int* cstart, const int* ctot,
                             double* part, hipStream_t s, const SubX3* x3 = nullptr);
+// k_sub_stats_w for the dimensions up to 31 that sorted.hip does not hold
+// (sub_stats_any.hip); arguments as there
+hipError_t launch_sub_stats_w_any(int d, bool sample, const float* x, long long npts, long long n, long long rpw,
+                                  const int* perm, const int* z, const int* zrow, unsigned char* zsub,
+                                  const float* packed, int K, int k_max, uint32_t t, uint64_t seed, long long* counts,
+                                  double* moments, const int* cstart, const int* ctot, int kbase, double* part,
+                                  hipStream_t s);
+// sub-labels of cluster-sorted rows, d = 33 .. 127, FP32 on the matrix cores
+hipError_t launch_sub_labels_mx(int d, const float* x, long long n, const int* perm, const int* z, const int* zrow,
+                                unsigned char* zsub, const float* packed, int K, int k_max, uint32_t t, uint64_t seed,
+                                hipStream_t s);
 // statistics of a listed set of cluster k1's points split by side[i] into
 // segments slot, slot + 1 (slot >= 2 k1; d in {8, 16, 32, 64, 128});
 // cspan: device int[2] = {0, nsel}; part: sub_stats_part_doubles(d, nsel)

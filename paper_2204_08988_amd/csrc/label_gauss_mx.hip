@@ -30,19 +30,7 @@ namespace {
 
 using namespace score;
 
-typedef __attribute__((address_space(3))) void lds_void;
 constexpr int MX_BLOCK = 256;
-
-// Copies `words` floats (a multiple of 4) from src to LDS by LDS DMA, the whole
-// workgroup taking part; landed after a wait and a barrier.
-__device__ __forceinline__ void stage(float* dst, const float* src, int words) {
-  const int n4 = words >> 2;
-  for (int f0 = 0; f0 < n4; f0 += MX_BLOCK) {
-    const int f = f0 + threadIdx.x;
-    if (f < n4)
-      __builtin_amdgcn_global_load_lds((const void*)(src + 4 * (size_t)f), (lds_void*)(dst + 4 * (f & ~63)), 16, 0, 0);
-  }
-}
 
 // Lazy Gumbel-max in one pass over the clusters in increasing k.  Clusters
 // within the Gumbel range of the running maximum wait in a queue of four; a new
@@ -99,6 +87,21 @@ struct StreamDraw {
   }
 };
 
+// the wave's rows [base, base + rows) of x (row 0 read in the place of the others)
+template <int RB>
+__device__ __forceinline__ void load_chunk(const float* __restrict__ x, long long base, int rows, int d,
+                                           float (&xv)[4][4 * RB]) {
+  const float* xr[4];
+  bool ok[4];
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+    const int r = 16 * t + (threadIdx.x & 15);
+    ok[t] = r < rows;
+    xr[t] = x + (ok[t] ? (size_t)(base + r) * d : 0);
+  }
+  mx::load_rows<RB>(xr, ok, d, xv);
+}
+
 // Block b labels the points [b per_block, (b + 1) per_block), writes its
 // histogram of z and adds it to the totals.  cg: records per LDS buffer; one
 // buffer when it holds all K.
@@ -120,7 +123,7 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_label_gauss_mx(const float* __r
   const long long begin = (long long)blockIdx.x * per_block;
   const long long end = begin + per_block < n ? begin + per_block : n;
   const int c0 = cg < K ? cg : K;
-  if (begin < end) stage(buf0, packed, c0 * S);
+  if (begin < end) mx::stage<MX_BLOCK>(buf0, packed, c0 * S);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   bool odd = false;  // which buffer holds the current group
@@ -128,7 +131,7 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_label_gauss_mx(const float* __r
     const long long base = chunk + wave * 64;
     const int rows = (int)(end - base < 64 ? (end - base > 0 ? end - base : 0) : 64);
     float xv[4][4 * RB];
-    mx::load_rows<RB>(x + (rows > 0 ? base : 0) * d, rows, d, xv);
+    load_chunk<RB>(x, base, rows, d, xv);
     const uint32_t i = (uint32_t)(base + lane);
     StreamDraw dr;
     dr.init();
@@ -138,7 +141,7 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_label_gauss_mx(const float* __r
         const bool wrap = g0 + cg >= K;
         const int gn = wrap ? 0 : g0 + cg;
         if (!wrap || chunk + MX_BLOCK < end)
-          stage(odd ? buf0 : buf1, packed + (size_t)gn * S, (K - gn < cg ? K - gn : cg) * S);
+          mx::stage<MX_BLOCK>(odd ? buf0 : buf1, packed + (size_t)gn * S, (K - gn < cg ? K - gn : cg) * S);
       }
       mx::lds_cfloat* rec = (mx::lds_cfloat*)(odd ? buf1 : buf0);
       for (int c = 0; c < nk; ++c, rec += S) {
@@ -192,8 +195,8 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_loglik_gauss_mx(const float* __
   // components [j0, j0 + nj) into dst: the clusters' records, then the sub-clusters'
   auto fetch = [&](float* dst, int j0, int nj) {
     const int a = j0 < K ? (K - j0 < nj ? K - j0 : nj) : 0;
-    if (a) stage(dst, packed + (size_t)j0 * S, a * S);
-    if (nj > a) stage(dst + (size_t)a * S, packed + (size_t)(k_max + j0 + a - K) * S, (nj - a) * S);
+    if (a) mx::stage<MX_BLOCK>(dst, packed + (size_t)j0 * S, a * S);
+    if (nj > a) mx::stage<MX_BLOCK>(dst + (size_t)a * S, packed + (size_t)(k_max + j0 + a - K) * S, (nj - a) * S);
   };
   const long long step = (long long)gridDim.x * MX_BLOCK;
   long long chunk = (long long)blockIdx.x * MX_BLOCK;
@@ -205,7 +208,7 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_loglik_gauss_mx(const float* __
     const long long base = chunk + wave * 64;
     const int rows = (int)(n - base < 64 ? (n - base > 0 ? n - base : 0) : 64);
     float xv[4][4 * RB];
-    mx::load_rows<RB>(x + (rows > 0 ? base : 0) * d, rows, d, xv);
+    load_chunk<RB>(x, base, rows, d, xv);
     for (int g0 = jb; g0 < je; g0 += cg) {
       const int nj = je - g0 < cg ? je - g0 : cg;
       const bool wrap = g0 + cg >= je;
@@ -214,7 +217,7 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_loglik_gauss_mx(const float* __
       mx::lds_cfloat* rec = (mx::lds_cfloat*)(odd ? buf1 : buf0);
       for (int c = 0; c < nj; ++c, rec += S) {
         float q;
-        mx::sq_norm<RB>(rec, d, xv, q, [](float) { return true; });
+        mx::sq_norm<RB>(rec, d, xv, q, mx::Always());
         const int j = g0 + c, o = j % LL_GRP;
         tile[lane * (LL_GRP + 1) + o] = fmaf(-0.5f, q, rec[0]);
         if (o == LL_GRP - 1 || j == je - 1) {
@@ -290,11 +293,11 @@ hipError_t launch_loglik_gauss(int d, const float* x, long long n, const float* 
   if (n == 0) return hipSuccess;
   const size_t rec = (size_t)gauss_rec_stride(d) * sizeof(float);
   int cg = (int)(MX_LDS_RECORDS / 2 / rec);
-  // about 1024 workgroups: the components in groups of whole LL_GRPs where n is small
+  // about 2048 workgroups: the components in groups of whole LL_GRPs where n is small
   const int J = 3 * K, grps = (J + LL_GRP - 1) / LL_GRP;
   long long g = (n + MX_BLOCK - 1) / MX_BLOCK;
   if (g > 4096) g = 4096;
-  const int ny = (int)std::min<long long>(grps, std::max<long long>(1, 1024 / g));
+  const int ny = (int)std::min<long long>(grps, std::max<long long>(1, 2048 / g));
   const int jper = (grps + ny - 1) / ny * LL_GRP;
   if (cg > jper) cg = jper;
   const size_t lds = rec * cg * 2 + mx::REC_PAD * sizeof(float) + (size_t)MX_BLOCK * (LL_GRP + 1) * sizeof(float);

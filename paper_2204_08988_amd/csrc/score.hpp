@@ -27,21 +27,6 @@ __device__ __forceinline__ float score_rec(const float* __restrict__ p, const fl
   return fmaf(-0.5f, q, p[0]);
 }
 
-// Generic dimension: the centred vector lives in a per-thread LDS column.
-__device__ __forceinline__ float score_rec_dyn(const float* __restrict__ p, const float* __restrict__ x,
-                                               float* dx, int d) {
-  for (int j = 0; j < d; ++j) dx[j * BLOCK] = x[j] - p[4 + j];
-  const float* w = p + 4 + d;
-  float q = 0.0f;
-  for (int r = 0; r < d; ++r) {
-    const float* wr = w + r * (r + 1) / 2;
-    float y = 0.0f;
-    for (int c = 0; c <= r; ++c) y = fmaf(wr[c], dx[c * BLOCK], y);
-    q = fmaf(y, y, q);
-  }
-  return fmaf(-0.5f, q, p[0]);
-}
-
 struct Top2 {
   float m1, m2;
   int arg;

@@ -29,28 +29,22 @@ namespace dpmm {
 namespace mx {
 
 typedef float f32x4 __attribute__((ext_vector_type(4)));
-constexpr int BUF_DWORD3 = 0x00020000;  // raw buffer descriptor word 3 (gfx9 family)
 // floats that may be read past the end of the last staged record (masked)
 constexpr int REC_PAD = 16;
 
 __host__ __device__ constexpr int row_blocks(int d) { return (d + 15) / 16; }
 
-// x[t][s] of the wave's rows [0, rows) at xr (rows past them, and coordinates
-// past d, are zero).  The loads go through one buffer descriptor per wave:
-// every address is a lane offset plus a constant.
-template <int RB>
-__device__ __forceinline__ void load_rows(const float* xr, int rows, int d, float (&x)[4][4 * RB]) {
-  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
-  const __amdgpu_buffer_rsrc_t rx =
-      __builtin_amdgcn_make_buffer_rsrc((void*)xr, (short)0, rows * d * 4, BUF_DWORD3);
-#pragma unroll
-  for (int t = 0; t < 4; ++t) {
-    const int o = ((16 * t + c) * d + g) * 4;
-#pragma unroll
-    for (int s = 0; s < 4 * RB; ++s) {
-      const float v = __int_as_float(__builtin_amdgcn_raw_buffer_load_b32(rx, o + 16 * s, 0, 0));
-      x[t][s] = s < 4 * (RB - 1) || 4 * s + g < d ? v : 0.0f;
-    }
+typedef __attribute__((address_space(3))) void lds_void;
+
+// Copies `words` floats (a multiple of 4) from src to LDS by LDS DMA, every
+// thread of a workgroup of BLK taking part; landed after a wait and a barrier.
+template <int BLK>
+__device__ __forceinline__ void stage(float* dst, const float* src, int words) {
+  const int n4 = words >> 2;
+  for (int f0 = 0; f0 < n4; f0 += BLK) {
+    const int f = f0 + threadIdx.x;
+    if (f < n4)
+      __builtin_amdgcn_global_load_lds((const void*)(src + 4 * (size_t)f), (lds_void*)(dst + 4 * (f & ~63)), 16, 0, 0);
   }
 }
 
@@ -67,6 +61,43 @@ __device__ __forceinline__ void transpose4(float& v0, float& v1, float& v2, floa
   v3 = __uint_as_float(f[1]);
 }
 
+// x[t][s] of the rows xr[t] (the lane's row 16 t + c of each tile), zero where !ok[t]
+// (xr[t] must be readable all the same) and past the dimension.  The four lanes
+// of a row read 64 consecutive bytes of it at a time and trade them by
+// transpose4; 4-byte loads would touch every line of the row eight times, with
+// the wave's 64 rows larger than the L1.  Rows need not be 16-byte aligned.
+template <int RB>
+__device__ __forceinline__ void load_rows(const float* const (&xr)[4], const bool (&ok)[4], int d,
+                                          float (&x)[4][4 * RB]) {
+  typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+  const int g = (threadIdx.x & 63) >> 4;
+#pragma unroll
+  for (int t = 0; t < 4; ++t) {
+#pragma unroll
+    for (int j = 0; j < RB; ++j) {
+      float v[4];
+      if (j < RB - 1 || d == 16 * RB) {
+        const f32x4u u = *reinterpret_cast<const f32x4u*>(xr[t] + 16 * j + 4 * g);
+        v[0] = u.x, v[1] = u.y, v[2] = u.z, v[3] = u.w;
+      } else {
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const int c = 16 * j + 4 * g + q;
+          const float u = xr[t][c < d ? c : 0];
+          v[q] = c < d ? u : 0.0f;
+        }
+      }
+#pragma unroll
+      for (int q = 0; q < 4; ++q) x[t][4 * j + q] = ok[t] ? v[q] : 0.0f;
+    }
+  }
+#pragma unroll
+  for (int t = 0; t < 4; ++t)
+#pragma unroll
+    for (int j = 0; j < RB; ++j)
+      transpose4(x[t][4 * j], x[t][4 * j + 1], x[t][4 * j + 2], x[t][4 * j + 3]);
+}
+
 // Squared norm q of the lane's own point under the record p (in LDS, REC_PAD
 // floats readable past it).  `go(q)` is asked after every 16-row block but the
 // last whether the wave still needs the rest: q only grows from block to block,
@@ -78,6 +109,17 @@ __device__ __forceinline__ void transpose4(float& v0, float& v1, float& v2, floa
 // from a vector instruction to the matrix instruction that reads it stands
 // between two matrix instructions.
 typedef __attribute__((address_space(3))) const float lds_cfloat;
+
+// `go` of a caller that always wants the whole norm: a branch that the compiler
+// cannot fold, so that the row blocks stay separate basic blocks (in one block it
+// loads the operands of all of them first and spills)
+struct Always {
+  __device__ __forceinline__ bool operator()(float) const {
+    int one = 1;
+    asm volatile("" : "+s"(one));
+    return one != 0;
+  }
+};
 
 template <int RB, typename GoFn>
 __device__ __forceinline__ bool sq_norm(lds_cfloat* p, int d, const float (&x)[4][4 * RB], float& q, GoFn go) {

@@ -7,26 +7,27 @@
 //   k_scan_hist  per-(block, cluster) output offsets;
 //   k_scatter_z  perm[offset] = i, zsort[offset] = z_i (the cluster of each
 //                sorted row, read coalesced by the kernels below).
-// Then k_sub_stats walks the sorted order in tiles of TR rows.  A tile holds
-// one or a few clusters, so sub-cluster scoring reads the two sub-cluster
-// records of a cluster with wave-uniform (scalar) loads instead of per-lane
-// gathers.  The tile's rows are then placed in LDS grouped by segment
-// s = 2 z + zsub, and every lane accumulates a 2x2 block of sum x x^T (or two
-// entries of sum x) in float64 registers over each segment's rows, with one
-// global atomic per entry, segment and tile.
+// Then, over the sorted order (a cluster is a run of rows):
+//   d <= 31      k_sub_stats_w: sub-labels and statistics in one pass;
+//   d = 32       k_sub_labels_mfma, then k_sub_stats_w;
+//   d = 64, 128  k_sub_labels_mfma (with BF16 tables behind the bf16x3 pass),
+//                then k_sub_stats_big;
+//   other d      k_sub_labels_mx, then k_sub_stats_big over rows padded with
+//                zero columns to 64 or 128.
+// Each walks contiguous ranges of rows, keeps the current cluster's sums and
+// leaves those of clusters that span ranges to k_sub_stats_fix.
 #include <utility>
 
 #include "kernels.hpp"
 #include "score.hpp"
+#include "sub_stats_w.hpp"
 
 namespace dpmm {
 
 namespace {
 
 using score::BLOCK;
-using score::score_rec;
-using score::score_rec_dyn;
-constexpr int IPT_MAX = 9;  // 2x2 work items per lane for d <= 128
+using subw::k_sub_stats_w;
 typedef __attribute__((__vector_size__(4 * sizeof(double)))) double f64x4;
 
 // Inclusive scan over a workgroup of `NT` threads (integer: exact in any
@@ -172,512 +173,6 @@ __global__ __launch_bounds__(BLOCK) void k_scatter_z(const int* __restrict__ z, 
   }
 }
 
-// 2x2 work items of one lane for dimension D (0: the generic bound, d <= 128)
-__host__ __device__ constexpr int items_per_lane(int D) {
-  return D == 0 ? IPT_MAX : ((((D + 1) / 2) * ((D + 1) / 2 + 1) / 2 + (D + 1) / 2) + 255) / 256;
-}
-
-// D > 0: a lane's row stays in registers for sub-cluster scoring and is then
-// stored straight to its segment-sorted LDS position; D == 0 (generic d): rows
-// are staged in LDS and reached through an index list.  SAMPLE: draw zsub
-// (else read it).  Workgroup g walks the tiles [g tpw, (g + 1) tpw) of TR
-// sorted rows each (TR <= BLOCK: one row per lane).  Clusters are contiguous
-// in sorted order, so the lanes keep float64 accumulators of the current
-// cluster's two segments across tiles; each segment keeps the rows' sorted
-// order.  Slot mode (part != nullptr, cstart / ctot indexed by cluster -
-// kbase): a cluster inside the workgroup's rows is written to its final
-// place, the first and last clusters that reach beyond them to partial slots
-// 2 g, 2 g + 1 that k_sub_stats_fix adds in a fixed order.  Otherwise the
-// sums are added with global atomics when the cluster changes.
-template <int D, bool SAMPLE>
-__global__ __launch_bounds__(BLOCK) void k_sub_stats(const float* __restrict__ x, int d, int TR, int tpw,
-                                                     long long n_sorted, const int* __restrict__ perm,
-                                                     const int* __restrict__ z, unsigned char* __restrict__ zsub,
-                                                     const float* __restrict__ packed, int K, int k_max, uint32_t t,
-                                                     uint64_t seed, long long* __restrict__ counts,
-                                                     double* __restrict__ moments, const int* __restrict__ cstart,
-                                                     const int* __restrict__ ctot, int kbase,
-                                                     double* __restrict__ part) {
-  constexpr int IPT = items_per_lane(D);
-  extern __shared__ float lds[];
-  const int tid = threadIdx.x;
-  const int dp = (d + 1) & ~1;  // even, padded with a zero column
-  const int ld = dp + 1;        // odd row stride: lanes touching their own rows hit distinct banks
-  float* xs = lds;                                         // [TR][ld]
-  int* rk = reinterpret_cast<int*>(xs + (size_t)TR * ld);  // [TR] cluster of the row
-  int* order = rk + TR;                                    // [TR] (generic d) row of each sorted slot
-  int* lcount = order + TR;                                // [2 TR]
-  int* lstart = lcount + 2 * TR;                           // [2 TR]
-  int* rinfo = lstart + 2 * TR;                            // [2 TR]: run start row, right rows before it
-  int* buf = rinfo + 2 * TR;                               // [BLOCK]
-  int* rcl = buf + BLOCK;                                  // [TR] cluster of each run
-  float* dxc = reinterpret_cast<float*>(rcl + TR);         // [d][BLOCK] (generic d, SAMPLE only)
-  const int S = gauss_rec_stride(d);
-  const int E = d + d * (d + 1) / 2;
-  // this lane's 2x2 work items: blocks (I, J), I <= J, of sum x x^T over the
-  // even-padded dimension, then pairs I of sum x (J = -2)
-  const int hb = dp / 2;
-  const int n_tri = hb * (hb + 1) / 2;
-  const int n_items = n_tri + hb;
-  short iI[IPT], iJ[IPT];
-#pragma unroll
-  for (int j = 0; j < IPT; ++j) {
-    const int it = tid + j * BLOCK;
-    iI[j] = -1;
-    iJ[j] = -1;
-    if (it < n_tri) {
-      int u = it, a = 0;
-      while (u >= hb - a) {
-        u -= hb - a;
-        ++a;
-      }
-      iI[j] = (short)a;
-      iJ[j] = (short)(a + u);
-    } else if (it < n_items) {
-      iI[j] = (short)(it - n_tri);
-      iJ[j] = -2;
-    }
-  }
-  const long long tiles = (n_sorted + TR - 1) / TR;
-  const long long tile_beg = (long long)blockIdx.x * tpw;
-  const long long tile_end = tile_beg + tpw < tiles ? tile_beg + tpw : tiles;
-  const long long r_begin = tile_beg * TR;
-  const long long r_end = tile_end * TR < n_sorted ? tile_end * TR : n_sorted;
-  // running sums of the current cluster's left (accL) and right (accR)
-  // segments; indexed statically so they stay in registers
-  double accL[IPT][4], accR[IPT][4];
-  long long cntL = 0, cntR = 0;
-  int cur_k = -1, k_first = -1;
-  auto zero_acc = [&]() {
-#pragma unroll
-    for (int j = 0; j < IPT; ++j) {
-      accL[j][0] = accL[j][1] = accL[j][2] = accL[j][3] = 0.0;
-      accR[j][0] = accR[j][1] = accR[j][2] = accR[j][3] = 0.0;
-    }
-    cntL = cntR = 0;
-  };
-  // atomic: added to M / C; else stored to M and C (or the slot's count Cd)
-  auto flush_one = [&](double (&acc)[IPT][4], long long cnt, double* M, long long* C, double* Cd, bool atomic) {
-#pragma unroll
-    for (int j = 0; j < IPT; ++j) {
-      const int I = iI[j], J = iJ[j];
-      if (I < 0) continue;
-      if (J == -2) {
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-          if (2 * I + u < d) {
-            if (atomic)
-              atomicAdd(&M[2 * I + u], acc[j][u]);
-            else
-              M[2 * I + u] = acc[j][u];
-          }
-      } else {
-#pragma unroll
-        for (int u = 0; u < 2; ++u)
-#pragma unroll
-          for (int v = 0; v < 2; ++v) {
-            const int a = 2 * I + u, b = 2 * J + v;
-            if (a < d && b < d && a <= b) {
-              double* dst = &M[d + a * d - (a * (a - 1)) / 2 + (b - a)];
-              if (atomic)
-                atomicAdd(dst, acc[j][2 * u + v]);
-              else
-                *dst = acc[j][2 * u + v];
-            }
-          }
-      }
-    }
-    if (tid == 0) {
-      if (atomic)
-        atomicAdd((unsigned long long*)C, (unsigned long long)cnt);
-      else if (C)
-        *C = cnt;
-      else
-        *Cd = (double)cnt;
-    }
-  };
-  auto flush = [&]() {
-    if (cur_k < 0) return;
-    const int sL = 2 * cur_k, sR = sL + 1;
-    if (!part) {
-      if (cntL) flush_one(accL, cntL, moments + (size_t)sL * E, counts + sL, nullptr, true);
-      if (cntR) flush_one(accR, cntR, moments + (size_t)sR * E, counts + sR, nullptr, true);
-      return;
-    }
-    const long long cs = cstart[cur_k - kbase], ce = cs + ctot[cur_k - kbase];
-    if (cs >= r_begin && ce <= r_end) {
-      flush_one(accL, cntL, moments + (size_t)sL * E, counts + sL, nullptr, false);
-      flush_one(accR, cntR, moments + (size_t)sR * E, counts + sR, nullptr, false);
-    } else {
-      double* P = part + (size_t)(2 * blockIdx.x + (cur_k == k_first ? 0 : 1)) * 2 * (E + 1);
-      flush_one(accL, cntL, P + 1, nullptr, P, false);
-      flush_one(accR, cntR, P + (E + 1) + 1, nullptr, P + (E + 1), false);
-    }
-  };
-  auto accumulate = [&](double (&acc)[IPT][4], int st, int cnt) {
-#pragma unroll 4
-    for (int p = st; p < st + cnt; ++p) {
-      const float* xr = xs + (size_t)(D > 0 ? p : order[p]) * ld;
-#pragma unroll
-      for (int j = 0; j < IPT; ++j) {
-        const int I = iI[j], J = iJ[j];
-        if (I < 0) continue;
-        const double a0 = xr[2 * I], a1 = xr[2 * I + 1];
-        if (J == -2) {
-          acc[j][0] += a0;
-          acc[j][1] += a1;
-        } else {
-          const double b0 = xr[2 * J], b1 = xr[2 * J + 1];
-          acc[j][0] = fma(a0, b0, acc[j][0]);
-          acc[j][1] = fma(a0, b1, acc[j][1]);
-          acc[j][2] = fma(a1, b0, acc[j][2]);
-          acc[j][3] = fma(a1, b1, acc[j][3]);
-        }
-      }
-    }
-  };
-  zero_acc();
-  for (long long tile = tile_beg; tile < tile_end; ++tile) {
-    const long long tile0 = tile * TR;
-    const int rows = (int)((n_sorted - tile0) < TR ? (n_sorted - tile0) : TR);
-    const int r = tid;
-    const bool valid = r < rows;
-    // ---- phase A: load the row, draw or read its sub-label
-    long long i = 0;
-    int k = -1;
-    float xv[D > 0 ? D : 1];
-    if (valid) {
-      i = perm[tile0 + r];
-      k = z[i];
-      rk[r] = k;
-      if constexpr (D > 0) {
-#pragma unroll
-        for (int j = 0; j < D; ++j) xv[j] = x[i * D + j];
-      } else {
-        // eight loads in flight at a time (d is not known at compile time)
-        float* xr = xs + (size_t)r * ld;
-        for (int j0 = 0; j0 < d; j0 += 8) {
-          float tv[8];
-#pragma unroll
-          for (int u = 0; u < 8; ++u) tv[u] = j0 + u < d ? x[i * d + j0 + u] : 0.0f;
-#pragma unroll
-          for (int u = 0; u < 8; ++u)
-            if (j0 + u < d) xr[j0 + u] = tv[u];
-        }
-        for (int j = d; j < dp; ++j) xr[j] = 0.0f;
-      }
-    }
-    for (int q = tid; q < 2 * TR; q += BLOCK) lcount[q] = 0;
-    int zs = 0;
-    if (SAMPLE) {
-      float delta = 0.0f;
-      unsigned long long pending = __ballot(valid);
-      while (pending) {
-        const int lane0 = __ffsll((long long)pending) - 1;
-        const int kk = __shfl(k, lane0);
-        const bool mine = valid && k == kk;
-        if (mine) {
-          const float* ps = packed + (size_t)(k_max + 2 * kk) * S;
-          if constexpr (D > 0) {
-            delta = score_rec<D>(ps, xv) - score_rec<D>(ps + S, xv);
-          } else {
-            const float* xr = xs + (size_t)r * ld;
-            delta = score_rec_dyn(ps, xr, dxc + tid, d) - score_rec_dyn(ps + S, xr, dxc + tid, d);
-          }
-        }
-        pending &= ~__ballot(mine);
-      }
-      if (valid) {
-        zs = sub_label_draw(delta, seed, t, (uint32_t)i, K);
-        zsub[i] = (unsigned char)zs;
-      }
-    } else if (valid) {
-      zs = zsub[i] ? 1 : 0;
-    }
-    __syncthreads();
-    // ---- group rows by segment: run of the cluster (rows are sorted by z),
-    // then the sub-label; one scan gives the run of each row (high half) and
-    // the right rows up to it (low half)
-    const int flag = (valid && (r == 0 || rk[r] != rk[r - 1])) ? 1 : 0;
-    const int sc = block_inclusive_scan((flag << 16) | zs, buf);
-    const int run = (sc >> 16) - 1, ones_ex = (sc & 0xFFFF) - zs;
-    const int nruns = buf[BLOCK - 1] >> 16;
-    const int lid = 2 * run + zs;
-    if (flag) {
-      rinfo[2 * run] = r;
-      rinfo[2 * run + 1] = ones_ex;
-      rcl[run] = k;
-    }
-    if (valid) atomicAdd(&lcount[lid], 1);  // integer counts: exact in any order
-    __syncthreads();
-    if (tid == 0) {
-      int a = 0;
-      for (int q = 0; q < 2 * nruns; ++q) {
-        lstart[q] = a;
-        a += lcount[q];
-      }
-    }
-    __syncthreads();
-    // slot within the segment: the row's rank among the run's rows of the same
-    // sub-label, so each segment keeps the sorted order
-    if (valid) {
-      const int ones_run = ones_ex - rinfo[2 * run + 1];
-      const int pos = lstart[lid] + (zs ? ones_run : (r - rinfo[2 * run]) - ones_run);
-      if constexpr (D > 0) {
-        float* xr = xs + (size_t)pos * ld;
-#pragma unroll
-        for (int j = 0; j < D; ++j) xr[j] = xv[j];
-        if (D & 1) xr[D] = 0.0f;
-      } else {
-        order[pos] = r;
-      }
-    }
-    __syncthreads();
-    // ---- phase B: every run in order into the running sums
-    for (int j = 0; j < nruns; ++j) {
-      const int kq = rcl[j];
-      if (kq != cur_k) {
-        flush();
-        zero_acc();
-        if (cur_k < 0) k_first = kq;
-        cur_k = kq;
-      }
-      const int cl = lcount[2 * j], cr = lcount[2 * j + 1];
-      cntL += cl;
-      cntR += cr;
-      accumulate(accL, lstart[2 * j], cl);
-      accumulate(accR, lstart[2 * j + 1], cr);
-    }
-    __syncthreads();
-  }
-  flush();
-}
-
-// Wave-independent kernel for D in {8, 16, 32}: each wave walks its own
-// contiguous range of sorted rows in chunks of 64 (one row per lane), with no
-// workgroup barriers.  Per chunk:
-//   (1) sub-cluster scores: for each run of lanes with the same cluster (rows
-//       are sorted by z, so a cluster is a run of lanes) every lane scores the
-//       run's two sub-cluster records; control flow stays wave-uniform, so the
-//       records are read with scalar loads, and each lane keeps the result of
-//       its own run;
-//   (2) each row is stored to LDS at its segment-sorted slot: within a run the
-//       left rows first, then the right rows;
-//   (3) per segment, four rows at a time, v_mfma_f64_16x16x4_f64 adds the
-//       16x16 blocks (I <= J) of sum x x^T (dimensions padded to a multiple
-//       of 16 with zeros); the same operands give sum x.
-// The current cluster's two segments are carried across chunks and flushed
-// with global atomics when the cluster changes or the range ends.
-template <int D, bool SAMPLE>
-__global__ __launch_bounds__(BLOCK) void k_sub_stats_w(const float* __restrict__ x, long long npts, long long n_sorted,
-                                                       long long rows_per_wave, const int* __restrict__ perm,
-                                                       const int* __restrict__ z, const int* __restrict__ zrow,
-                                                       unsigned char* __restrict__ zsub,
-                                                       const float* __restrict__ packed, int K, int k_max, uint32_t t,
-                                                       uint64_t seed, long long* __restrict__ counts,
-                                                       double* __restrict__ moments, const int* __restrict__ cstart,
-                                                       const int* __restrict__ ctot, int kbase,
-                                                       double* __restrict__ part) {
-  constexpr int NB = (D + 15) / 16;  // 16-wide blocks of dimensions
-  constexpr int NBLK = NB * (NB + 1) / 2;
-  constexpr int LDW = D + 1;  // odd row stride
-  constexpr int S = (4 + D + D * (D + 1) / 2 + 3) & ~3;
-  constexpr int E = D + D * (D + 1) / 2;
-  extern __shared__ float lds[];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  float* xs = lds + wave * 64 * LDW;
-  const unsigned long long below = (1ull << lane) - 1ull;
-  const int col = lane & 15;
-  f64x4 cL[NBLK], cR[NBLK];
-  double sL[NB], sR[NB];
-  long long nL = 0, nR = 0;
-  int cur_k = -1;
-  auto zero_acc = [&]() {
-#pragma unroll
-    for (int b = 0; b < NBLK; ++b) cL[b] = cR[b] = f64x4{0.0, 0.0, 0.0, 0.0};
-#pragma unroll
-    for (int b = 0; b < NB; ++b) sL[b] = sR[b] = 0.0;
-    nL = nR = 0;
-  };
-  const long long gw = (long long)blockIdx.x * (BLOCK / 64) + wave;
-  const long long w_begin = gw * rows_per_wave;
-  const long long w_end = w_begin + rows_per_wave < n_sorted ? w_begin + rows_per_wave : n_sorted;
-  int k_first = -1;  // cluster of the wave's first row (partial-slot mode)
-  // lane l holds element j of block (I, J) at row 16 I + l / 16 + 4 j, column 16 J + l % 16.
-  // Atomic mode (part == nullptr): added to counts[seg], moments[seg].  Slot mode:
-  // stored to M (moments layout) and *cnt_out, either the final arrays (the
-  // cluster lies in this wave's rows) or a partial slot that k_sub_stats_fix sums.
-  auto flush_one = [&](f64x4 (&c)[NBLK], double (&sx)[NB], long long cnt, double* M, long long* cnt_out,
-                       double* cnt_d, bool atomic) {
-    int blk = 0;
-#pragma unroll
-    for (int I = 0; I < NB; ++I)
-#pragma unroll
-      for (int J = I; J < NB; ++J, ++blk)
-#pragma unroll
-        for (int j = 0; j < 4; ++j) {
-          const int a = 16 * I + (lane >> 4) + 4 * j, b = 16 * J + col;
-          if (a <= b && b < D) {
-            double* dst = &M[D + a * D - (a * (a - 1)) / 2 + (b - a)];
-            if (atomic)
-              atomicAdd(dst, c[blk][j]);
-            else
-              *dst = c[blk][j];
-          }
-        }
-#pragma unroll
-    for (int b = 0; b < NB; ++b) {
-      double v = sx[b];
-      v += __shfl_xor(v, 16);
-      v += __shfl_xor(v, 32);
-      if (lane < 16 && 16 * b + lane < D) {
-        if (atomic)
-          atomicAdd(&M[16 * b + lane], v);
-        else
-          M[16 * b + lane] = v;
-      }
-    }
-    if (lane == 0) {
-      if (atomic)
-        atomicAdd((unsigned long long*)cnt_out, (unsigned long long)cnt);
-      else if (cnt_out)
-        *cnt_out = cnt;
-      else
-        *cnt_d = (double)cnt;
-    }
-  };
-  auto flush = [&]() {
-    if (cur_k < 0) return;
-    if (!part) {
-      if (nL) flush_one(cL, sL, nL, moments + (size_t)(2 * cur_k) * E, &counts[2 * cur_k], nullptr, true);
-      if (nR) flush_one(cR, sR, nR, moments + (size_t)(2 * cur_k + 1) * E, &counts[2 * cur_k + 1], nullptr, true);
-      return;
-    }
-    const long long cs = cstart[cur_k - kbase], ce = cs + ctot[cur_k - kbase];
-    if (cs >= w_begin && ce <= w_end) {
-      // the whole cluster is this wave's: final values, both segments
-      flush_one(cL, sL, nL, moments + (size_t)(2 * cur_k) * E, &counts[2 * cur_k], nullptr, false);
-      flush_one(cR, sR, nR, moments + (size_t)(2 * cur_k + 1) * E, &counts[2 * cur_k + 1], nullptr, false);
-    } else {
-      // slot 2 gw: the wave's first cluster; 2 gw + 1: its last (when different); each [2][1 + E]
-      double* P = part + (size_t)(2 * gw + (cur_k == k_first ? 0 : 1)) * 2 * (E + 1);
-      flush_one(cL, sL, nL, P + 1, nullptr, P, false);
-      flush_one(cR, sR, nR, P + (E + 1) + 1, nullptr, P + (E + 1), false);
-    }
-  };
-  // rows [s0, e0) of the wave's LDS tile, four at a time: A = B = the rows' block of dimensions
-  auto mfma_rows = [&](f64x4 (&c)[NBLK], double (&sx)[NB], int s0, int e0) {
-    for (int g = s0; g < e0; g += 4) {
-      // unconditional LDS reads of an element inside the tile (row s0, column 0 for a
-      // lane past the rows or the dimensions), then zeroed: no branches, so the reads
-      // of the next step can overlap the matrix-core work of this one
-      const int rr = g + (lane >> 4);
-      const bool ok = rr < e0;
-      const int rs = ok ? rr : s0;
-      double a[NB];
-#pragma unroll
-      for (int b = 0; b < NB; ++b) {
-        const int cc = 16 * b + col;
-        const float v = xs[rs * LDW + (cc < D ? cc : 0)];
-        a[b] = (ok && cc < D) ? (double)v : 0.0;
-      }
-#pragma unroll
-      for (int b = 0; b < NB; ++b) sx[b] += a[b];
-      int blk = 0;
-#pragma unroll
-      for (int I = 0; I < NB; ++I)
-#pragma unroll
-        for (int J = I; J < NB; ++J, ++blk) c[blk] = __builtin_amdgcn_mfma_f64_16x16x4f64(a[I], a[J], c[blk], 0, 0, 0);
-    }
-  };
-  zero_acc();
-  for (long long c0 = w_begin; c0 < w_end; c0 += 64) {
-    const long long r = c0 + lane;
-    bool valid = r < w_end;
-    long long i = 0;
-    int k = -1;
-    float xv[D];
-    if (valid) {
-      i = perm[r];
-      // a label outside [0, K) leaves its row out (and never reaches memory)
-      valid = (unsigned long long)i < (unsigned long long)npts;
-      if (valid) k = zrow ? zrow[r] : z[i];
-      valid = valid && (unsigned)k < (unsigned)K;
-    }
-    if (valid) {
-#pragma unroll
-      for (int j = 0; j < D; ++j) xv[j] = x[i * D + j];
-    } else {
-      i = 0;
-#pragma unroll
-      for (int j = 0; j < D; ++j) xv[j] = 0.0f;
-    }
-    // ---- (1) sub-labels
-    int zs = 0;
-    if (SAMPLE) {
-      float delta = 0.0f;
-      unsigned long long pend = __ballot(valid);
-      while (pend) {
-        const int lane0 = __ffsll((long long)pend) - 1;
-        const int kk = __builtin_amdgcn_readlane(k, lane0);
-        const bool mine = valid && k == kk;
-        const float* ps = packed + (size_t)(k_max + 2 * kk) * S;
-        const float dl = score_rec<D>(ps, xv) - score_rec<D>(ps + S, xv);
-        if (mine) delta = dl;
-        pend &= ~__ballot(mine);
-      }
-      if (valid) {
-        zs = sub_label_draw(delta, seed, t, (uint32_t)i, K);
-        zsub[i] = (unsigned char)zs;
-      }
-    } else if (valid) {
-      zs = zsub[i] ? 1 : 0;
-    }
-    // ---- (2) segment-sorted slot of each row
-    const unsigned long long right = __ballot(valid && zs == 1);
-    int pos = 0;
-    unsigned long long rem = __ballot(valid);
-    while (rem) {
-      const int lane0 = __ffsll((long long)rem) - 1;
-      const int kk = __builtin_amdgcn_readlane(k, lane0);
-      const bool mine = valid && k == kk;
-      const unsigned long long mk = __ballot(mine);
-      const unsigned long long mR = mk & right, mL = mk & ~right;
-      if (mine) pos = lane0 + (zs ? __popcll(mL) + __popcll(mR & below) : __popcll(mL & below));
-      rem &= ~mk;
-    }
-    // the previous chunk's reads of xs are done: same wave, in order
-    __builtin_amdgcn_wave_barrier();
-    if (valid) {
-#pragma unroll
-      for (int j = 0; j < D; ++j) xs[pos * LDW + j] = xv[j];
-    }
-    __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
-    __builtin_amdgcn_wave_barrier();
-    __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
-    // ---- (3) each run's two segments into the running sums
-    rem = __ballot(valid);
-    while (rem) {
-      const int lane0 = __ffsll((long long)rem) - 1;
-      const int kk = __builtin_amdgcn_readlane(k, lane0);
-      const unsigned long long mk = __ballot(valid && k == kk);
-      if (kk != cur_k) {
-        flush();
-        zero_acc();
-        if (cur_k < 0) k_first = kk;
-        cur_k = kk;
-      }
-      const int cl = __popcll(mk & ~right), cr = __popcll(mk & right);
-      nL += cl;
-      nR += cr;
-      mfma_rows(cL, sL, lane0, lane0 + cl);
-      mfma_rows(cR, sR, lane0 + cl, lane0 + cl + cr);
-      rem &= ~mk;
-    }
-  }
-  flush();
-}
-
 // Slot mode of the sorted-order statistics kernels: the counts and moments of
 // every cluster whose rows span several row ranges (rpw rows each: a wave of
 // k_sub_stats_w, a workgroup of the other kernels) are the sums of those
@@ -738,20 +233,6 @@ SortedPlan plan_blocks(long long n, int K, long long hist_cap, int block_rows) {
   if (G < 1) G = 1;
   return SortedPlan{(int)G, per};
 }
-
-int tile_rows(int d) {
-  if (d <= 32) return 256;
-  if (d <= 64) return 128;
-  return 32;  // generic d up to 128: the per-lane centred columns take d x 1 KB of LDS
-}
-
-size_t sub_stats_lds(int d, int TR, bool generic) {
-  const int dp = (d + 1) & ~1;
-  size_t b = (size_t)TR * (dp + 1) * sizeof(float) + (size_t)(9 * TR + BLOCK) * sizeof(int);
-  if (generic) b += (size_t)d * BLOCK * sizeof(float);
-  return b;
-}
-
 
 constexpr int BIG_THREADS = 512;  // 8 waves: 0-3 own the left segment, 4-7 the right
 // sorted rows per tile: 64 KB of FP32 rows, so that two tiles fit in LDS
@@ -1024,8 +505,13 @@ __device__ __forceinline__ void big_rows(f64x4 (&acc)[TPW], double (&sx)[D / 64]
 // k_sub_stats_fix adds in a fixed order: no float atomics, so the sums do not
 // depend on timing.  cstart / ctot are indexed by cluster - kbase.  Otherwise
 // the segments are added to counts / moments with atomics.
-template <int D>
-__global__ __launch_bounds__(BIG_THREADS) void k_sub_stats_big(const float* __restrict__ x, long long n_sorted,
+// PAD: rows of d < D columns, copied four bytes per lane (a row need not be a
+// multiple of 16 bytes); the columns from d on stay zero in LDS and their sums
+// are dropped.  The generic kernel that this replaced kept 2 x 2 entries per
+// lane and read two LDS operands per FMA: d = 100, N = 1e5, K = 32, sub-labels
+// and statistics together 9.48 -> 0.17 ms; d = 127, N = 5e5, K = 16: 68.6 -> 0.52 ms.
+template <int D, bool PAD>
+__global__ __launch_bounds__(BIG_THREADS) void k_sub_stats_big(const float* __restrict__ x, int d, long long n_sorted,
                                                                int tpb, const int* __restrict__ perm,
                                                                const int* __restrict__ z,
                                                                const int* __restrict__ zrow,
@@ -1037,7 +523,8 @@ __global__ __launch_bounds__(BIG_THREADS) void k_sub_stats_big(const float* __re
                                                                double* __restrict__ part) {
   constexpr int R = big_rows_of(D);
   constexpr int NB = D / 16, NT = NB * (NB + 1) / 2, TPW = (NT + 3) / 4;
-  constexpr int E = D + D * (D + 1) / 2;
+  const int dd = PAD ? d : D;  // columns of a row
+  const int E = dd + dd * (dd + 1) / 2;
   constexpr int SB = D / 64;       // column blocks of sum x per wave
   constexpr int C4 = D / 4;        // 16-byte pieces per row
   constexpr int RPI = 64 / C4;     // rows per wave DMA instruction
@@ -1123,7 +610,8 @@ __global__ __launch_bounds__(BIG_THREADS) void k_sub_stats_big(const float* __re
         if (bI == bJ && ra > rb) continue;  // a diagonal block holds both orders
         const int c1 = big_col<D>(bI, ra), c2 = big_col<D>(bJ, rb);
         const int a = c1 < c2 ? c1 : c2, b = c1 < c2 ? c2 : c1;
-        double* dst = &M[D + a * D - (a * (a - 1)) / 2 + (b - a)];
+        if (PAD && b >= dd) continue;
+        double* dst = &M[dd + a * dd - (a * (a - 1)) / 2 + (b - a)];
         if (atomic)
           atomicAdd(dst, acc[j][e]);
         else
@@ -1136,7 +624,7 @@ __global__ __launch_bounds__(BIG_THREADS) void k_sub_stats_big(const float* __re
       double v = sx[j];
       v += __shfl_xor(v, 16);
       v += __shfl_xor(v, 32);
-      if (lane < 16) {
+      if (lane < 16 && (!PAD || big_col<D>(wq + 4 * j, lane) < dd)) {
         double* dst = &M[big_col<D>(wq + 4 * j, lane)];
         if (atomic)
           atomicAdd(dst, v);
@@ -1157,6 +645,17 @@ __global__ __launch_bounds__(BIG_THREADS) void k_sub_stats_big(const float* __re
   auto issue_rows = [&](int lt, float* dst) __attribute__((always_inline)) {
     const int rows = tile_rows(lt);
     const int* np = nperm[lt & 1];
+    if constexpr (PAD) {
+      // 64 columns of a row per instruction; lanes past the columns copy nothing
+#pragma unroll 8
+      for (int i = 0; i < R * SB / 8; ++i) {
+        const int r = (wave * (R * SB / 8) + i) / SB, c = (i % SB) * 64 + lane;
+        if (c < dd)
+          __builtin_amdgcn_global_load_lds((const void*)(x + (size_t)np[r < rows ? r : 0] * dd + c),
+                                           (lds_void*)(dst + r * D + (i % SB) * 64), 4, 0, 0);
+      }
+      return;
+    }
 #pragma unroll
     for (int i = 0; i < NI; ++i) {
       // rows past the tile's end copy its first row (never read): no branches,
@@ -1174,9 +673,9 @@ __global__ __launch_bounds__(BIG_THREADS) void k_sub_stats_big(const float* __re
   unsigned char zb = 0;
   if (nt > 0) {
     if (tid < tile_rows(0)) nperm[0][tid] = perm[r_begin + tid];
-    for (int c = tid; c < D; c += BIG_THREADS) {
-      xa[R * D + c] = 0.0f;
-      xb[R * D + c] = 0.0f;
+    for (int c = PAD ? tid : R * D + tid; c < (R + 1) * D; c += BIG_THREADS) {
+      xa[c] = 0.0f;
+      xb[c] = 0.0f;
     }
     __syncthreads();
     const int r = tid < tile_rows(0) ? tid : 0;
@@ -1287,60 +786,6 @@ __global__ __launch_bounds__(BIG_THREADS) void k_sub_stats_big(const float* __re
   flush();
 }
 
-// workgroups of the generic statistics kernel: about four per CU, fewer
-// above d = 64 (each range's partial slots hold 2 (1 + E) doubles per side)
-long long generic_groups(int d, long long n) {
-  const int TR = tile_rows(d);
-  const long long tiles = (n + TR - 1) / TR;
-  const long long cap = d <= 64 ? 1024 : 256;
-  const long long g = tiles < cap ? tiles : cap;
-  const long long tpw = g > 0 ? (tiles + g - 1) / g : 1;
-  return tiles > 0 ? (tiles + tpw - 1) / tpw : 0;
-}
-
-template <bool SAMPLE>
-hipError_t launch_sub_stats_t(int d, const float* x, long long n, const int* perm, const int* z, unsigned char* zsub,
-                              const float* packed, int K, int k_max, uint32_t t, uint64_t seed, long long* counts,
-                              double* moments, const int* cstart, const int* ctot, int kbase, int ncl, double* part,
-                              hipStream_t s) {
-  const int TR = tile_rows(d);
-  static bool attr_set = false;
-  if (!attr_set) {  // above d = 64 the per-lane centred columns take more than 64 KB
-    hipError_t e = hipFuncSetAttribute((const void*)k_sub_stats<0, SAMPLE>,
-                                       hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
-    if (e != hipSuccess) return e;
-    attr_set = true;
-  }
-  // contiguous tile ranges
-  const long long tiles = (n + TR - 1) / TR;
-  const long long g = generic_groups(d, n);
-  const int tpw = (int)((tiles + g - 1) / g);
-  const unsigned grid = (unsigned)((tiles + tpw - 1) / tpw);
-#define DPMM_SUB_CASE(DD)                                                                                 \
-  case DD:                                                                                                \
-    hipLaunchKernelGGL((k_sub_stats<DD, SAMPLE>), dim3(grid), dim3(BLOCK), sub_stats_lds(d, TR, false), s, x, d, \
-                       TR, tpw, n, perm, z, zsub, packed, K, k_max, t, seed, counts, moments, cstart, ctot, kbase,\
-                       part);                                                                             \
-    break;
-  switch (d) {
-    DPMM_SUB_CASE(8)
-    DPMM_SUB_CASE(16)
-    DPMM_SUB_CASE(32)
-    DPMM_SUB_CASE(64)
-    default:
-      hipLaunchKernelGGL((k_sub_stats<0, SAMPLE>), dim3(grid), dim3(BLOCK), sub_stats_lds(d, TR, SAMPLE), s, x, d,
-                         TR, tpw, n, perm, z, zsub, packed, K, k_max, t, seed, counts, moments, cstart, ctot, kbase,
-                         part);
-  }
-#undef DPMM_SUB_CASE
-  hipError_t e = hipGetLastError();
-  if (e != hipSuccess || !part) return e;
-  const int E = d + d * (d + 1) / 2;
-  hipLaunchKernelGGL(k_sub_stats_fix, dim3((2 * (E + 1) + FIX_EN - 1) / FIX_EN, ncl), dim3(FIX_PH * FIX_EN),
-                     0, s, E, (long long)tpw * TR, cstart, ctot, part, counts, moments, kbase);
-  return hipGetLastError();
-}
-
 }  // namespace
 
 hipError_t sorted_plan(long long n, int K, long long hist_cap, int* G, long long* per_block, int block_rows) {
@@ -1371,16 +816,24 @@ hipError_t launch_sort_by_z(const int* z, long long n, int K, int G, long long p
 
 namespace {
 
-// rows per wave of k_sub_stats_w (whole 64-row chunks, at most SUBW_WAVES waves)
-long long subw_rpw(long long n) {
-  long long rpw = (n + SUBW_WAVES - 1) / SUBW_WAVES;
+// waves of k_sub_stats_w: the partial slots of 1024 ranges is what the other
+// dimensions have always taken of the static scratch
+int subw_waves(int d) { return d == 8 || d == 16 || d == 32 ? SUBW_WAVES : SUBW_WAVES / 2; }
+
+// rows per wave of k_sub_stats_w (whole 64-row chunks, at most subw_waves(d) waves)
+long long subw_rpw(int d, long long n) {
+  long long rpw = (n + subw_waves(d) - 1) / subw_waves(d);
   return ((rpw + 63) / 64) * 64;
 }
 
-// tiles per workgroup of k_sub_stats_big (at most 512 workgroups at d = 64, 256 at d = 128)
+// columns of a row of k_sub_stats_big, zero-padded (d > 32)
+int big_dim(int d) { return d <= 64 ? 64 : 128; }
+
+// tiles per workgroup of k_sub_stats_big (at most 512 workgroups at d <= 64, 256 above)
 int big_tpb(int d, long long n) {
-  const long long tiles = (n + big_rows_of(d) - 1) / big_rows_of(d);
-  const long long gmax = d == 128 ? 256 : 512;
+  const int R = big_rows_of(big_dim(d));
+  const long long tiles = (n + R - 1) / R;
+  const long long gmax = d > 64 ? 256 : 512;
   const long long g = tiles < gmax ? tiles : gmax;
   return g > 0 ? (int)((tiles + g - 1) / g) : 1;
 }
@@ -1445,26 +898,36 @@ hipError_t sub_stats_kernels(int d, bool sample, const float* x, long long npts,
     }
     sample = false;
   }
-  if (d == 64 || d == 128) {
-    const int R = big_rows_of(d);
+  if (sample && d > 32) {
+    e = launch_sub_labels_mx(d, x, n, perm, z, zrow, zsub, packed, K, k_max, t, seed, s);
+    if (e != hipSuccess) return e;
+  }
+  if (d > 32) {
+    const int R = big_rows_of(big_dim(d));
     const long long tiles = (n + R - 1) / R;
     const int tpb = big_tpb(d, n);
     const unsigned grid = (unsigned)((tiles + tpb - 1) / tpb);
     const size_t lds = 0;  // all of its LDS is static (two tiles' rows, 129 KB)
+#define DPMM_BIG(DD, PP)                                                                                          \
+  hipLaunchKernelGGL((k_sub_stats_big<DD, PP>), dim3(grid), dim3(BIG_THREADS), lds, s, x, d, n, tpb, perm, z, zrow, \
+                     zsub, counts, moments, cstart, ctot, kbase, part)
     if (d == 64)
-      hipLaunchKernelGGL(k_sub_stats_big<64>, dim3(grid), dim3(BIG_THREADS), lds, s, x, n, tpb, perm, z, zrow, zsub,
-                         counts, moments, cstart, ctot, kbase, part);
+      DPMM_BIG(64, false);
+    else if (d == 128)
+      DPMM_BIG(128, false);
+    else if (d < 64)
+      DPMM_BIG(64, true);
     else
-      hipLaunchKernelGGL(k_sub_stats_big<128>, dim3(grid), dim3(BIG_THREADS), lds, s, x, n, tpb, perm, z, zrow, zsub,
-                         counts, moments, cstart, ctot, kbase, part);
+      DPMM_BIG(128, true);
+#undef DPMM_BIG
     if ((e = hipGetLastError()) != hipSuccess || !part) return e;
     hipLaunchKernelGGL(k_sub_stats_fix, fix_grid, dim3(FIX_PH * FIX_EN), 0, s, E, (long long)tpb * R, cstart,
                        ctot, part, counts, moments, kbase);
     return hipGetLastError();
   }
-  if (d == 8 || d == 16 || d == 32) {
-    // about eight waves per CU, each on a contiguous range of whole 64-row chunks
-    const long long rpw = subw_rpw(n);
+  {
+    // four to eight waves per CU, each on a contiguous range of whole 64-row chunks
+    const long long rpw = subw_rpw(d, n);
     const long long nw = (n + rpw - 1) / rpw;
     const unsigned grid = (unsigned)((nw + 3) / 4);
     const size_t lds = (size_t)4 * 64 * (d + 1) * sizeof(float);
@@ -1481,6 +944,10 @@ hipError_t sub_stats_kernels(int d, bool sample, const float* x, long long npts,
       DPMM_SUBW_CASE(8)
       DPMM_SUBW_CASE(16)
       DPMM_SUBW_CASE(32)
+      default:
+        e = launch_sub_stats_w_any(d, sample, x, npts, n, rpw, perm, z, zrow, zsub, packed, K, k_max, t, seed, counts,
+                                   moments, cstart, ctot, kbase, part, s);
+        if (e != hipSuccess) return e;
     }
 #undef DPMM_SUBW_CASE
     if ((e = hipGetLastError()) != hipSuccess || !part) return e;
@@ -1488,10 +955,6 @@ hipError_t sub_stats_kernels(int d, bool sample, const float* x, long long npts,
                        moments, kbase);
     return hipGetLastError();
   }
-  return sample ? launch_sub_stats_t<true>(d, x, n, perm, z, zsub, packed, K, k_max, t, seed, counts, moments,
-                                           cstart, ctot, kbase, ncl, part, s)
-                : launch_sub_stats_t<false>(d, x, n, perm, z, zsub, packed, K, k_max, t, seed, counts, moments,
-                                            cstart, ctot, kbase, ncl, part, s);
 }
 
 }  // namespace
@@ -1500,28 +963,21 @@ size_t sub_stats_part_doubles(int d, long long n) {
   const int E = d + d * (d + 1) / 2;
   long long ranges;
   if (n <= 0) return 0;
-  if (d == 8 || d == 16 || d == 32) {
-    const long long rpw = subw_rpw(n);
+  if (d <= 32) {
+    const long long rpw = subw_rpw(d, n);
     ranges = (n + rpw - 1) / rpw;
-  } else if (d == 64 || d == 128) {
-    const long long tiles = (n + big_rows_of(d) - 1) / big_rows_of(d);
+  } else {
+    const int R = big_rows_of(big_dim(d));
+    const long long tiles = (n + R - 1) / R;
     const int tpb = big_tpb(d, n);
     ranges = (tiles + tpb - 1) / tpb;
-  } else {
-    ranges = generic_groups(d, n);
   }
   return (size_t)2 * ranges * 2 * (E + 1);
 }
 
 size_t sub_stats_part_doubles_max(int d) {
   const int E = d + d * (d + 1) / 2;
-  long long ranges;
-  if (d == 8 || d == 16 || d == 32)
-    ranges = SUBW_WAVES;
-  else if (d == 64 || d == 128)
-    ranges = d == 128 ? 256 : 512;
-  else
-    ranges = d <= 64 ? 1024 : 256;
+  const long long ranges = d <= 32 ? subw_waves(d) : (d > 64 ? 256 : 512);
   return (size_t)2 * ranges * 2 * (E + 1);
 }
 

@@ -1,0 +1,205 @@
+// Sub-labels and statistics of the dimensions without a kernel of their own in
+// sorted.hip: Sec. 4.1 step (f) and Sec. 4.4 over cluster-sorted rows.
+//
+//   d <= 31       k_sub_stats_w, one instantiation per dimension (the generic
+//                 kernel before it read both operands of every FMA from LDS:
+//                 N = 5e5, K = 16: d = 6 551 -> 30 us, 20 742 -> 61, 31 1035 -> 120);
+//   33 <= d < 128 k_sub_labels_mx: the two sub-cluster scores of a row on the
+//                 FP32 matrix cores (score_mx.hpp), with the bits of the
+//                 vector-ALU form.  The statistics follow in k_sub_stats_big.
+#include "kernels.hpp"
+#include "score.hpp"
+#include "score_mx.hpp"
+#include "sub_stats_w.hpp"
+
+namespace dpmm {
+
+namespace {
+
+constexpr int SLX_BLOCK = 256;
+
+// A workgroup walks a contiguous range of sorted rows, 256 at a time; the two
+// records of the current cluster are staged in LDS whenever the cluster changes
+// (rows are sorted, so a range holds few; the clusters of the chunk's rows are
+// kept in LDS to find the next), and a wave scores its 64 rows if any of them has
+// that cluster.  Bound by the matrix cores and the vector ALUs together, as the
+// cluster draw; two of its K + 2 evaluations per point.
+template <int RB>
+__global__ __launch_bounds__(SLX_BLOCK, 2) void k_sub_labels_mx(const float* __restrict__ x, int d, long long n_sorted,
+                                                                long long per_block, const int* __restrict__ perm,
+                                                                const int* __restrict__ z,
+                                                                const int* __restrict__ zrow,
+                                                                unsigned char* __restrict__ zsub,
+                                                                const float* __restrict__ packed, int K, int k_max,
+                                                                uint32_t t, uint64_t seed) {
+  extern __shared__ __align__(16) float s_rec[];  // the two records, then REC_PAD floats
+  __shared__ int s_k[SLX_BLOCK];                  // clusters of the chunk's rows
+  const int S = gauss_rec_stride(d);
+  const int lane = threadIdx.x & 63, c = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long long begin = (long long)blockIdx.x * per_block;
+  const long long end = begin + per_block < n_sorted ? begin + per_block : n_sorted;
+  int staged = -1;
+  for (long long chunk = begin; chunk < end; chunk += SLX_BLOCK) {
+    const long long cend = chunk + SLX_BLOCK < end ? chunk + SLX_BLOCK : end;
+    const long long mine = chunk + threadIdx.x;
+    const int i = mine < cend ? perm[mine] : 0;
+    const int k = mine < cend ? (zrow ? zrow[mine] : z[i]) : 0x7fffffff;
+    float xv[4][4 * RB];
+    const float* xr[4];
+    bool ok[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      // row 16 q + c of the wave belongs to lane 16 q + c
+      const int r = __shfl(i, 16 * q + c);
+      ok[q] = chunk + wave * 64 + 16 * q + c < cend;
+      xr[q] = x + (size_t)r * d;
+    }
+    mx::load_rows<RB>(xr, ok, d, xv);
+    __syncthreads();  // the previous chunk's clusters are read
+    s_k[threadIdx.x] = k;
+    __syncthreads();
+    float delta = 0.0f;
+    int cur = __builtin_amdgcn_readfirstlane(s_k[0]);
+    for (;;) {
+      if (cur != staged) {
+        __syncthreads();  // every wave is done with the previous records
+        mx::stage<SLX_BLOCK>(s_rec, packed + (size_t)(k_max + 2 * cur) * S, 2 * S);
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        staged = cur;
+      }
+      if (__ballot(k == cur)) {
+        mx::lds_cfloat* rec = (mx::lds_cfloat*)s_rec;
+        float sc = 0.0f, dl = 0.0f;
+#pragma unroll 1
+        for (int sub = 0; sub < 2; ++sub, rec += S) {
+          float q;
+          mx::sq_norm<RB>(rec, d, xv, q, mx::Always());
+          const float l = fmaf(-0.5f, q, rec[0]);
+          dl = sc - l;
+          sc = l;
+        }
+        if (k == cur) delta = dl;
+      }
+      // the next cluster of the chunk: the smallest above cur (every wave finds the same)
+      int nx = 0x7fffffff;
+#pragma unroll
+      for (int q = 0; q < SLX_BLOCK; q += 64) {
+        const int v = s_k[q + lane];
+        nx = v > cur && v < nx ? v : nx;
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) nx = min(nx, __shfl_xor(nx, o));
+      if (nx == 0x7fffffff) break;
+      cur = __builtin_amdgcn_readfirstlane(nx);
+    }
+    if (mine < cend) zsub[i] = (unsigned char)sub_label_draw(delta, seed, t, (uint32_t)i, K);
+  }
+}
+
+}  // namespace
+
+hipError_t launch_sub_labels_mx(int d, const float* x, long long n, const int* perm, const int* z, const int* zrow,
+                                unsigned char* zsub, const float* packed, int K, int k_max, uint32_t t, uint64_t seed,
+                                hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  const size_t lds = (size_t)(2 * gauss_rec_stride(d) + mx::REC_PAD) * sizeof(float);
+  static bool attr_set = false;
+  if (!attr_set) {
+    const void* fns[6] = {(const void*)k_sub_labels_mx<3>, (const void*)k_sub_labels_mx<4>,
+                          (const void*)k_sub_labels_mx<5>, (const void*)k_sub_labels_mx<6>,
+                          (const void*)k_sub_labels_mx<7>, (const void*)k_sub_labels_mx<8>};
+    for (const void* f : fns) {
+      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 80 * 1024);
+      if (e != hipSuccess) return e;
+    }
+    attr_set = true;
+  }
+  // at most four workgroups per CU, each on a range of whole steps
+  long long per = (n + 1023) / 1024;
+  per = (per + SLX_BLOCK - 1) / SLX_BLOCK * SLX_BLOCK;
+  const unsigned G = (unsigned)((n + per - 1) / per);
+#define DPMM_SLX_CASE(RB)                                                                                             \
+  case RB:                                                                                                            \
+    hipLaunchKernelGGL(k_sub_labels_mx<RB>, dim3(G), dim3(SLX_BLOCK), lds, s, x, d, n, per, perm, z, zrow, zsub, packed, \
+                       K, k_max, t, seed);                                                                            \
+    break;
+  switch (mx::row_blocks(d)) {
+    DPMM_SLX_CASE(3)
+    DPMM_SLX_CASE(4)
+    DPMM_SLX_CASE(5)
+    DPMM_SLX_CASE(6)
+    DPMM_SLX_CASE(7)
+    DPMM_SLX_CASE(8)
+    default:
+      return hipErrorInvalidValue;
+  }
+#undef DPMM_SLX_CASE
+  return hipGetLastError();
+}
+
+hipError_t launch_sub_stats_w_any(int d, bool sample, const float* x, long long npts, long long n, long long rpw,
+                                  const int* perm, const int* z, const int* zrow, unsigned char* zsub,
+                                  const float* packed, int K, int k_max, uint32_t t, uint64_t seed, long long* counts,
+                                  double* moments, const int* cstart, const int* ctot, int kbase, double* part,
+                                  hipStream_t s) {
+  const long long nw = (n + rpw - 1) / rpw;
+  const unsigned grid = (unsigned)((nw + 3) / 4);
+  const size_t lds = (size_t)4 * 64 * (d + 1) * sizeof(float);
+#define DPMM_ANY(DD, SS)                                                                                              \
+  hipLaunchKernelGGL((subw::k_sub_stats_w<DD, SS>), dim3(grid), dim3(score::BLOCK), lds, s, x, npts, n, rpw, perm, z, \
+                     zrow, zsub, packed, K, k_max, t, seed, counts, moments, cstart, ctot, kbase, part)
+#define DPMM_ANY_CASE(DD)  \
+  case DD:                 \
+    if (sample)            \
+      DPMM_ANY(DD, true);  \
+    else                   \
+      DPMM_ANY(DD, false); \
+    break;
+// d <= 4 draws its sub-labels with its labels
+#define DPMM_ANY_SMALL(DD)                   \
+  case DD:                                   \
+    if (sample) return hipErrorInvalidValue; \
+    DPMM_ANY(DD, false);                     \
+    break;
+  switch (d) {
+    DPMM_ANY_SMALL(1)
+    DPMM_ANY_SMALL(2)
+    DPMM_ANY_SMALL(3)
+    DPMM_ANY_SMALL(4)
+    DPMM_ANY_CASE(5)
+    DPMM_ANY_CASE(6)
+    DPMM_ANY_CASE(7)
+    DPMM_ANY_CASE(9)
+    DPMM_ANY_CASE(10)
+    DPMM_ANY_CASE(11)
+    DPMM_ANY_CASE(12)
+    DPMM_ANY_CASE(13)
+    DPMM_ANY_CASE(14)
+    DPMM_ANY_CASE(15)
+    DPMM_ANY_CASE(17)
+    DPMM_ANY_CASE(18)
+    DPMM_ANY_CASE(19)
+    DPMM_ANY_CASE(20)
+    DPMM_ANY_CASE(21)
+    DPMM_ANY_CASE(22)
+    DPMM_ANY_CASE(23)
+    DPMM_ANY_CASE(24)
+    DPMM_ANY_CASE(25)
+    DPMM_ANY_CASE(26)
+    DPMM_ANY_CASE(27)
+    DPMM_ANY_CASE(28)
+    DPMM_ANY_CASE(29)
+    DPMM_ANY_CASE(30)
+    DPMM_ANY_CASE(31)
+    default:
+      return hipErrorInvalidValue;
+  }
+#undef DPMM_ANY_SMALL
+#undef DPMM_ANY_CASE
+#undef DPMM_ANY
+  return hipGetLastError();
+}
+
+}  // namespace dpmm

@@ -40,3 +40,25 @@ def test_fp32_draw_and_loglik(d, K, n, spread):
         assert bad_c.size == 0 and bad_s.size == 0, (bad_c[:10], bad_s[:10])
         assert tie_c <= max(2, n // 1000) and tie_s <= max(2, n // 1000)
     S.close()
+
+
+# the statistics over sorted rows by themselves: on both sides of the switch from one row per lane to padded
+# tiles (32 | 33), of the padded widths (64 | 65), at the smallest and largest dimension of each, with empty
+# sub-clusters; d < 5 with more clusters than the per-lane sums hold
+@pytest.mark.parametrize("d,K,n", [(1, 900, 3000), (3, 300, 2001), (5, 4, 1), (7, 3, 65), (15, 2, 700), (17, 9, 1300),
+                                   (31, 5, 4097), (33, 3, 513), (63, 2, 257), (65, 4, 130), (99, 2, 129), (127, 3, 700)])
+def test_stats_of_any_dimension(d, K, n):
+    import torch
+
+    from paper_2204_08988_amd.sampler import Sampler
+    from tests.test_gpu_parity import _check_stats
+    g = np.random.Generator(np.random.PCG64(d * 31 + K))
+    x = (g.standard_normal((n, d)) * 3 + 1).astype(np.float32)
+    z = g.integers(0, K, n).astype(np.int32)
+    zs = g.integers(0, 2, n).astype(np.uint8)
+    zs[z == 0] = 1
+    S = Sampler("gaussian", d, K, 2.0, 5, m=np.zeros(d), psi=np.eye(d))
+    S.set_state(K)
+    S.suffstats(torch.from_numpy(x).cuda(), torch.from_numpy(z).cuda(), torch.from_numpy(zs).cuda())
+    _check_stats(S.get_stats(), x, z, zs, K, d)
+    S.close()
