@@ -275,9 +275,9 @@ struct RelabelEntry {
 };
 hipError_t launch_relabel(long long n, const RelabelEntry* table, int n_entries, uint32_t t, uint64_t seed, int* z,
                           unsigned char* zsub, hipStream_t s);
-// zero a buffer of 8-byte words with a kernel (no memset nodes, so the call
-// stays safe inside captured graphs)
-hipError_t launch_zero64(void* p, size_t n_words, hipStream_t s);
+// zero a buffer of 8-byte words, or two in one launch, with a kernel (no memset
+// nodes, so the call stays safe inside captured graphs)
+hipError_t launch_zero64(void* p, size_t n_words, hipStream_t s, void* q = nullptr, size_t q_words = 0);
 hipError_t launch_init_labels(long long n, uint64_t seed, int* z, unsigned char* zsub, hipStream_t s);
 
 }  // namespace dpmm

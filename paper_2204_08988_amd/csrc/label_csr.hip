@@ -267,10 +267,6 @@ __global__ __launch_bounds__(BLOCK) void k_stats_csr(const long long* __restrict
     if (hist[s]) atomicAdd(counts + s, (unsigned long long)hist[s]);
 }
 
-__global__ void k_zero_u64(unsigned long long* __restrict__ p, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x) p[i] = 0;
-}
-
 // Word-major tables from the component records of k_pack_mult (slot k for
 // cluster k, k_max + 2k + h for its sub-clusters; value 0 the constant c,
 // values 4 .. 4 + V - 1 the log parameters): a 64 x 64 tile of (component,
@@ -343,10 +339,8 @@ hipError_t launch_loglik_csr(const SparseRows& x, long long n, int V, const floa
 
 hipError_t launch_stats_csr(const SparseRows& x, long long n, int V, const int* z, const unsigned char* zsub, int K,
                             long long* counts, long long* sums, int* err, hipStream_t s) {
-  const size_t ns = 2 * (size_t)K * V;
-  hipLaunchKernelGGL(k_zero_u64, dim3(std::min<size_t>((ns + 255) / 256, 4096)), dim3(256), 0, s,
-                     (unsigned long long*)sums, ns);
-  hipLaunchKernelGGL(k_zero_u64, dim3(1), dim3(256), 0, s, (unsigned long long*)counts, 2 * (size_t)K);
+  hipError_t e = launch_zero64(sums, 2 * (size_t)K * V, s, counts, 2 * (size_t)K);
+  if (e != hipSuccess) return e;
   if (n > 0)
     hipLaunchKernelGGL(k_stats_csr, dim3(waves_grid(n)), dim3(BLOCK), 2 * (size_t)K * sizeof(int), s, x.row_ptr,
                        x.col, x.val, x.nnz, n, V, z, zsub, K, (unsigned long long*)counts, (unsigned long long*)sums,

@@ -8,6 +8,7 @@
 // scalar loads.  Label and sub-label draws as in the Gaussian kernel: top-2
 // screen, lazy Gumbel-max, logistic skipped outside its range.
 #include "kernels.hpp"
+#include "score_mx.hpp"
 
 namespace dpmm {
 
@@ -15,8 +16,14 @@ namespace {
 
 constexpr int BLOCK = 256;
 constexpr float RGAP = GUMBEL_MAX_F - GUMBEL_MIN_F;
-constexpr size_t MULT_MFMA_LDS_MAX = 96 * 1024;  // log theta staged for every cluster (two workgroups per CU)
-constexpr int BUF_DWORD3 = 0x00020000;            // raw buffer descriptor word 3 (gfx9 family)
+constexpr size_t MULT_MFMA_LDS_MAX = 96 * 1024;  // log theta staged for every cluster
+
+// orders the wave's own LDS accesses (no workgroup barrier)
+__device__ __forceinline__ void wave_sync() {
+  __builtin_amdgcn_fence(__ATOMIC_RELEASE, "wavefront");
+  __builtin_amdgcn_wave_barrier();
+  __builtin_amdgcn_fence(__ATOMIC_ACQUIRE, "wavefront");
+}
 
 template <int VT>
 __device__ __forceinline__ float score_mult(const float* __restrict__ p, const float (&x)[VT]) {
@@ -87,199 +94,274 @@ __global__ __launch_bounds__(BLOCK) void k_label_mult(const int* __restrict__ x,
   }
 }
 
-// The same draw with the scores on the FP32 matrix cores (v_mfma_f32_32x32x2_f32):
-// a wave takes 64 points (two 32-point tiles) against blocks of 32 clusters,
-// A = log theta of the block (staged in LDS for all K clusters once per
-// workgroup, zero past V, row stride odd), B = the counts (word 2 s + h at step
-// s on lane half h), and the accumulators start at log w (-inf for the padding
-// clusters of the last block).  A lane ends with 16 of a point's K scores per
-// block; the top-2 screen runs over the lane and its partner (lane ^ 32).  Only
-// a wave holding a point whose runner-up lies within the Gumbel range computes
-// its scores again and draws every cluster above m1 - RGAP: the winner of
-// max (l_k + g_k), smaller k on ties, with the Philox words of the vector-ALU
-// kernel (the same winner as its streaming draw, which skips only clusters
-// that cannot beat the running best).  The sub-label then comes from the two
-// sub-cluster scores of the point's cluster on the vector ALUs.
-template <int VH>
-__global__ __launch_bounds__(BLOCK) void k_label_mult_mfma(const int* __restrict__ x, long long n, int V,
-                                                           const float* __restrict__ packed, int K, int k_max,
-                                                           uint32_t t, uint64_t seed, int* __restrict__ z,
-                                                           unsigned char* __restrict__ zsub) {
-  typedef float f32x16 __attribute__((ext_vector_type(16)));
-  constexpr int LDV = 2 * VH + 1;  // odd row stride
-  const int S = mult_rec_stride(V);
-  const int KB = (K + 31) / 32;
-  extern __shared__ float th[];  // [32 KB][LDV] log theta, then [32 KB] log w
-  float* cw = th + (size_t)KB * 32 * LDV;
-  // eight loads in flight per thread (clamped addresses, zeroed afterwards)
-  for (int i0 = threadIdx.x; i0 < KB * 32 * LDV; i0 += 8 * BLOCK) {
-    float tv[8];
-#pragma unroll
-    for (int u = 0; u < 8; ++u) {
-      const int idx = i0 + u * BLOCK, k = idx / LDV, v = idx - k * LDV;
-      const bool in = idx < KB * 32 * LDV && k < K && v < V;
-      const float val = packed[in ? (size_t)k * S + 4 + v : 0];
-      tv[u] = in ? val : 0.0f;
+// The same draw with the scores on the FP32 matrix cores: v_mfma_f32_16x16x4_f32
+// adds its products one after the other in increasing word order (score_mx.hpp),
+// so a score is the chain l = fma(x_v, log theta_v, l) from l = log w.  A wave
+// takes 64 points (four 16-point tiles, rows in registers as in score_mx.hpp)
+// against groups of 64 clusters: A = log theta (staged in LDS for all K clusters
+// once per workgroup, rows of 4 x odd floats: the sixteen rows x four words of a
+// read fall on 64 banks), B = the counts.  Lane 16 g + c of a tile ends with the
+// clusters 4 g .. 4 g + 3 of every 16 for point c.
+//
+// Clusters within the Gumbel range of the running maximum are listed per wave in
+// LDS (point, cluster, score); with a single group only those of points that have
+// several.  The list's Gumbels are drawn one entry per lane, whatever points they
+// belong to, and each point's winner (largest l_k + g_k, smaller k on ties) is a
+// 64-bit LDS maximum: a wave with a few doubtful points pays for their clusters,
+// not for every cluster of 64 points.  The sub-label needs the point's whole row
+// on one lane: a 4 x 4 lane transpose of the registers.  The two sub-cluster
+// records come from LDS while they fit beside the clusters'.
+//
+// Bound by the FP32 matrix cores, and HBM behind them.  N = 1e6, V = 100, K = 50:
+// 646 us (32-row tiles, rows read with a stride, the whole wave scored twice for
+// one doubtful point, sub-cluster records gathered from memory) -> 196 us; its 400
+// matrix instructions per 64 points take 95.
+constexpr int MM_BLOCK = 512;
+constexpr int MM_LIST = 1024;  // candidates listed per wave: those of one tile and group always fit
+constexpr int MM_WAVES = MM_BLOCK / 64;
+constexpr size_t MM_LDS_MAX = 150 * 1024;
+
+__host__ __device__ constexpr int mm_ldv(int V) { return 4 * (((V + 3) / 4) | 1); }
+
+// A float in an order-preserving 32-bit key.
+__device__ __forceinline__ uint32_t order_key(float v) {
+  const uint32_t b = __float_as_uint(v);
+  return b & 0x80000000u ? ~b : b | 0x80000000u;
+}
+
+template <int RB, bool SUB>
+__global__ __launch_bounds__(MM_BLOCK, 2) void k_label_mult_mfma(const int* __restrict__ x, long long n, int V,
+                                                                 const float* __restrict__ packed, int K, int k_max,
+                                                                 uint32_t t, uint64_t seed,
+                                                                 int* __restrict__ z, unsigned char* __restrict__ zsub) {
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int S = mult_rec_stride(V), LDV = mm_ldv(V), Q = LDV / 4;
+  extern __shared__ __align__(16) float th[];  // [K][LDV] clusters, then (SUB) [2K][LDV] sub-clusters
+  float* cw = th + (size_t)(SUB ? 3 : 1) * K * LDV;  // [K rounded up to 64] log w (-inf past K), [2K] sub-clusters'
+  const int KP = (K + 63) & ~63;
+  float* csub = cw + KP;
+  unsigned long long* best_all = reinterpret_cast<unsigned long long*>(cw + KP + 2 * K);  // [waves][64]
+  float* lists = reinterpret_cast<float*>(best_all + MM_WAVES * 64);  // [waves][MM_LIST] scores
+  unsigned short* listk = reinterpret_cast<unsigned short*>(lists + MM_WAVES * MM_LIST);  // point << 10 | cluster
+  {
+    const int rows = SUB ? 3 * K : K;
+    for (int e = threadIdx.x; e < rows * Q; e += MM_BLOCK) {
+      const int r = e / Q, q = e - r * Q;
+      const float* src = packed + (size_t)(r < K ? r : k_max + (r - K)) * S + 4;
+      float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
+      if (4 * q < V) v = *reinterpret_cast<const float4*>(src + 4 * q);
+      v.x = 4 * q < V ? v.x : 0.0f;
+      v.y = 4 * q + 1 < V ? v.y : 0.0f;
+      v.z = 4 * q + 2 < V ? v.z : 0.0f;
+      v.w = 4 * q + 3 < V ? v.w : 0.0f;
+      *reinterpret_cast<float4*>(th + (size_t)r * LDV + 4 * q) = v;
     }
-#pragma unroll
-    for (int u = 0; u < 8; ++u)
-      if (i0 + u * BLOCK < KB * 32 * LDV) th[i0 + u * BLOCK] = tv[u];
+    for (int k = threadIdx.x; k < KP; k += MM_BLOCK) cw[k] = k < K ? packed[(size_t)k * S] : -INFINITY;
+    for (int k = threadIdx.x; k < 2 * K; k += MM_BLOCK) csub[k] = packed[(size_t)(k_max + k) * S];
   }
-  for (int k = threadIdx.x; k < KB * 32; k += BLOCK) cw[k] = k < K ? packed[(size_t)k * S] : -INFINITY;
   __syncthreads();
-  const int lane = threadIdx.x & 63, h = lane >> 5, col = lane & 31;
-  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);  // scalar: the buffer descriptors below are too
-  auto scores = [&](int b, const float (&xa)[VH], const float (&xb)[VH], f32x16& acca, f32x16& accb) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const float c0 = cw[32 * b + 8 * (r >> 2) + 4 * h + (r & 3)];
-      acca[r] = c0;
-      accb[r] = c0;
+  const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  unsigned long long* best = best_all + wave * 64;
+  float* ll = lists + wave * MM_LIST;
+  unsigned short* lk = listk + wave * MM_LIST;
+  const int ext = V - 16 * (RB - 1);  // words of the last 16
+  // Gumbels of the listed candidates above their point's floor; the winners into best
+  auto draw_list = [&](int cnt, const float (&fl)[4], long long base) __attribute__((always_inline)) {
+    wave_sync();
+    for (int e0 = 0; e0 < cnt; e0 += 64) {
+      const int e = e0 + lane;
+      const float l = ll[e < cnt ? e : 0];
+      const int pk = lk[e < cnt ? e : 0], p = pk >> 10, k = pk & 1023;
+      // the floor of point p: lane p % 16 holds it for tile p / 16
+      const float f0 = __shfl(fl[0], p & 15), f1 = __shfl(fl[1], p & 15), f2 = __shfl(fl[2], p & 15),
+                  f3 = __shfl(fl[3], p & 15);
+      const float f = p < 32 ? (p < 16 ? f0 : f1) : (p < 48 ? f2 : f3);
+      if (e < cnt && l > f) {
+        const u32x4 blk = rng_block(seed, t, (uint32_t)(base + p), TAG_GUMBEL, (uint32_t)(k >> 2));
+        const float sv = l + gumbel_f(word_of(blk, k & 3));
+        atomicMax(&best[p], (unsigned long long)order_key(sv) << 32 | (uint32_t)(0x7fffffff - k));
+      }
     }
-    const float* ar = th + (size_t)(32 * b + col) * LDV + h;
-#pragma unroll
-    for (int st = 0; st < VH; ++st) {
-      const float a = ar[2 * st];
-      acca = __builtin_amdgcn_mfma_f32_32x32x2f32(a, xa[st], acca, 0, 0, 0);
-      accb = __builtin_amdgcn_mfma_f32_32x32x2f32(a, xb[st], accb, 0, 0, 0);
-    }
+    wave_sync();
   };
-  for (long long chunk = (long long)blockIdx.x * BLOCK; chunk < n; chunk += (long long)gridDim.x * BLOCK) {
+  for (long long chunk = (long long)blockIdx.x * MM_BLOCK; chunk < n; chunk += (long long)gridDim.x * MM_BLOCK) {
     const long long base = chunk + wave * 64;
-    const long long pA = base + col, pB = base + 32 + col;
-    // the wave's 64 rows through a buffer descriptor that covers only rows below n
-    // (loads past it return 0): one offset per lane, the word as an immediate, no
-    // branches, so every load is in flight at once; words past V are zeroed
-    const long long rows = n - base < 64 ? (n - base > 0 ? n - base : 0) : 64;
-    const __amdgpu_buffer_rsrc_t rx = __builtin_amdgcn_make_buffer_rsrc(
-        (void*)(x + (rows > 0 ? base : 0) * V), (short)0, (int)(rows * V * 4), BUF_DWORD3);
-    const int oA = (col * V + h) * 4, oB = ((32 + col) * V + h) * 4;
-    float xa[VH], xb[VH];
+    if (base >= n) continue;  // (no workgroup barrier in the loop)
+    float xv[4][4 * RB];
+    {
+      const float* xr[4];
+      bool ok[4];
 #pragma unroll
-    for (int st = 0; st < VH; ++st) {
-      const int ia = __builtin_amdgcn_raw_buffer_load_b32(rx, oA + 8 * st, 0, 0);
-      const int ib = __builtin_amdgcn_raw_buffer_load_b32(rx, oB + 8 * st, 0, 0);
-      xa[st] = 2 * st + h < V ? (float)ia : 0.0f;
-      xb[st] = 2 * st + h < V ? (float)ib : 0.0f;
-    }
-    // top-2 over this lane's clusters of each tile's point, then with the partner lane
-    float a1 = -INFINITY, a2 = -INFINITY, b1 = -INFINITY, b2 = -INFINITY;
-    int ka = 0, kb = 0;
-    for (int b = 0; b < KB; ++b) {
-      f32x16 acca, accb;
-      scores(b, xa, xb, acca, accb);
-#pragma unroll
-      for (int r = 0; r < 16; ++r) {
-        const int k = 32 * b + 8 * (r >> 2) + 4 * h + (r & 3);
-        const float la = acca[r], lb = accb[r];
-        if (la > a1) {
-          a2 = a1;
-          a1 = la;
-          ka = k;
-        } else if (la > a2) {
-          a2 = la;
-        }
-        if (lb > b1) {
-          b2 = b1;
-          b1 = lb;
-          kb = k;
-        } else if (lb > b2) {
-          b2 = lb;
-        }
+      for (int q = 0; q < 4; ++q) {
+        const long long p = base + 16 * q + c;
+        ok[q] = p < n;
+        xr[q] = reinterpret_cast<const float*>(x) + (ok[q] ? (size_t)p * V : 0);
       }
+      mx::load_rows<RB>(xr, ok, V, xv);
+#pragma unroll
+      for (int q = 0; q < 4; ++q)
+#pragma unroll
+        for (int s = 0; s < 4 * RB; ++s) xv[q][s] = (float)__float_as_int(xv[q][s]);
     }
-    auto merge2 = [&](float& m1, float& m2, int& kk) {
-      const float o1 = __shfl_xor(m1, 32), o2 = __shfl_xor(m2, 32);
-      const int ok = __shfl_xor(kk, 32);
-      const float s2 = fmaxf(fminf(m1, o1), fmaxf(m2, o2));
-      if (o1 > m1 || (o1 == m1 && ok < kk)) {
-        m1 = o1;
-        kk = ok;
+    best[lane] = 0ull;  // below the key of every score
+    float m1[4] = {-INFINITY, -INFINITY, -INFINITY, -INFINITY};  // maxima of point c of each tile
+    float fl[4];
+    int arg[4] = {0, 0, 0, 0};  // the leader, the smallest k on ties
+    bool many[4] = {false, false, false, false};
+    int cnt = 0;
+    for (int k0 = 0; k0 < K; k0 += 64) {
+      f32x4 a[4][4];  // [row block][tile]
+#pragma unroll
+      for (int rb = 0; rb < 4; ++rb) {
+        const f32x4 c0 = *reinterpret_cast<const f32x4*>(cw + k0 + 16 * rb + 4 * g);
+#pragma unroll
+        for (int q = 0; q < 4; ++q) a[rb][q] = c0;
       }
-      m2 = s2;
-    };
-    merge2(a1, a2, ka);
-    merge2(b1, b2, kb);
-    const bool da = pA < n && a2 > a1 - RGAP, db = pB < n && b2 > b1 - RGAP;
-    int za = ka, zb = kb;
-    if (__ballot(da || db)) {
-      // exact draw over the clusters above m1 - RGAP
-      const float ta = a1 - RGAP, tb = b1 - RGAP;
-      float sa = -INFINITY, sb = -INFINITY;
-      int wa = 0x7fffffff, wb = 0x7fffffff;
-      for (int b = 0; b < KB; ++b) {
-        f32x16 acca, accb;
-        scores(b, xa, xb, acca, accb);
+      // row block by row block; W is read PF steps ahead of its use
+      constexpr int PF = 4;
 #pragma unroll
-        for (int g = 0; g < 4; ++g) {
-          const int k0 = 32 * b + 8 * g + 4 * h;
-          bool ca = false, cb = false;
+      for (int rb = 0; rb < 4; ++rb) {
+        if (rb > 0 && k0 + 16 * rb >= K) continue;
+        const int r = k0 + 16 * rb + c;
+        mx::lds_cfloat* wr = (mx::lds_cfloat*)th + (r < K ? r : K - 1) * LDV + g;
+        float w[4 * RB];
 #pragma unroll
-          for (int j = 0; j < 4; ++j) {
-            ca = ca || (k0 + j < K && acca[4 * g + j] > ta);
-            cb = cb || (k0 + j < K && accb[4 * g + j] > tb);
+        for (int s = 0; s < PF && s < 4 * RB; ++s) w[s] = wr[4 * s];
+#pragma unroll
+        for (int s = 0; s < 4 * RB; ++s) {
+          // (rows are padded to LDV >= V; reads past them stay inside LDS and are not used)
+          if (s + PF < 4 * RB) w[s + PF] = wr[4 * (s + PF)];
+          __builtin_amdgcn_sched_barrier(0);
+          if (s <= 4 * (RB - 1) || 4 * (s - 4 * (RB - 1)) < ext) {  // steps past the last word: skipped (uniform)
+#pragma unroll
+            for (int q = 0; q < 4; ++q)
+              a[rb][q] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], xv[q][s], a[rb][q], 0, 0, 0);
           }
-          if (da && ca) {
-            const u32x4 blk = rng_block(seed, t, (uint32_t)pA, TAG_GUMBEL, (uint32_t)(k0 >> 2));
+          __builtin_amdgcn_sched_barrier(0);
+        }
+      }
 #pragma unroll
-            for (int j = 0; j < 4; ++j)
-              if (k0 + j < K && acca[4 * g + j] > ta) {
-                const float sv = acca[4 * g + j] + gumbel_f(word_of(blk, j));
-                if (sv > sa || (sv == sa && k0 + j < wa)) {
-                  sa = sv;
-                  wa = k0 + j;
-                }
+      for (int q = 0; q < 4; ++q) {
+        // the point's maximum over this lane's 16 clusters, then over the four lane groups
+        float b = -INFINITY;
+#pragma unroll
+        for (int rb = 0; rb < 4; ++rb) b = fmaxf(b, fmaxf(fmaxf(a[rb][q][0], a[rb][q][1]), fmaxf(a[rb][q][2], a[rb][q][3])));
+        b = fmaxf(b, __shfl_xor(b, 16));
+        b = fmaxf(b, __shfl_xor(b, 32));
+        const bool higher = b > m1[q];
+        m1[q] = fmaxf(m1[q], b);
+        fl[q] = m1[q] - RGAP;
+        int in = 0, kk = 0x7fffffff;
+#pragma unroll
+        for (int rb = 3; rb >= 0; --rb)
+#pragma unroll
+          for (int u = 3; u >= 0; --u) {
+            in += a[rb][q][u] > fl[q] ? 1 : 0;
+            kk = a[rb][q][u] == m1[q] ? k0 + 16 * rb + 4 * g + u : kk;
+          }
+        kk = min(kk, __shfl_xor(kk, 16));
+        kk = min(kk, __shfl_xor(kk, 32));
+        arg[q] = higher ? kk : arg[q];
+        if (K <= 64) {  // the only group: clusters in range of the point
+          int tot = in + __shfl_xor(in, 16);
+          tot += __shfl_xor(tot, 32);
+          many[q] = tot > 1;
+        } else {
+          many[q] = true;
+        }
+        const bool list_it = many[q] && in > 0 && base + 16 * q + c < n;
+        if (__ballot(list_it)) {
+          int add = 0;
+#pragma unroll
+          for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) add += __popcll(__ballot(list_it && a[rb][q][u] > fl[q]));
+          if (cnt + add > MM_LIST) {
+            draw_list(cnt, fl, base);
+            cnt = 0;
+          }
+#pragma unroll
+          for (int rb = 0; rb < 4; ++rb)
+#pragma unroll
+            for (int u = 0; u < 4; ++u) {
+              const bool up = list_it && a[rb][q][u] > fl[q];
+              const unsigned long long m = __ballot(up);
+              if (up) {
+                const int o = cnt + __popcll(m & ((1ull << lane) - 1ull));
+                ll[o] = a[rb][q][u];
+                lk[o] = (unsigned short)((16 * q + c) << 10 | (k0 + 16 * rb + 4 * g + u));
               }
-          }
-          if (db && cb) {
-            const u32x4 blk = rng_block(seed, t, (uint32_t)pB, TAG_GUMBEL, (uint32_t)(k0 >> 2));
-#pragma unroll
-            for (int j = 0; j < 4; ++j)
-              if (k0 + j < K && accb[4 * g + j] > tb) {
-                const float sv = accb[4 * g + j] + gumbel_f(word_of(blk, j));
-                if (sv > sb || (sv == sb && k0 + j < wb)) {
-                  sb = sv;
-                  wb = k0 + j;
-                }
-              }
-          }
+              cnt += __popcll(m);
+            }
         }
       }
-      auto merge_best = [&](float& sv, int& w) {
-        const float os = __shfl_xor(sv, 32);
-        const int ow = __shfl_xor(w, 32);
-        if (os > sv || (os == sv && ow < w)) {
-          sv = os;
-          w = ow;
-        }
-      };
-      merge_best(sa, wa);
-      merge_best(sb, wb);
-      if (da) za = wa;
-      if (db) zb = wb;
     }
-    // the lane's own point: tile A on the lower half, tile B on the upper
-    const long long i = h ? pB : pA;
+    if (cnt) draw_list(cnt, fl, base);
+    // the lane's own point: tile g, point c
+    int zi = g == 0 ? arg[0] : (g == 1 ? arg[1] : (g == 2 ? arg[2] : arg[3]));
+    const bool drew = g == 0 ? many[0] : (g == 1 ? many[1] : (g == 2 ? many[2] : many[3]));
+    if (drew) {
+      const unsigned long long bk = best[lane];
+      if (bk) zi = 0x7fffffff - (int)(uint32_t)bk;  // (0: scores so large that the range vanishes in them)
+    }
+    wave_sync();  // best is reset by the next rows
+    // its sub-label: word v on even and odd chains, as score_mult
+#pragma unroll
+    for (int s = 0; s < 4 * RB; ++s) mx::transpose4(xv[0][s], xv[1][s], xv[2][s], xv[3][s]);  // word 4 s + q in xv[q][s]
+    const long long i = base + lane;
+    float sc[2];
+#pragma unroll
+    for (int hh = 0; hh < 2; ++hh) {
+      float a0 = csub[2 * zi + hh], a1 = 0.0f;
+      if constexpr (SUB) {
+        // (words past V: zeros on both sides, which leave the chains as they are)
+        typedef __attribute__((address_space(3))) const f32x4 lds_f32x4;
+        lds_f32x4* ps = (lds_f32x4*)(th + (size_t)(K + 2 * zi + hh) * LDV);
+#pragma unroll
+        for (int s = 0; s < 4 * RB; ++s) {
+          if (s > 4 * (RB - 1) && 4 * (s - 4 * (RB - 1)) >= ext) continue;
+          const f32x4 w = ps[s];
+          a0 = fmaf(xv[0][s], w[0], a0);
+          a1 = fmaf(xv[1][s], w[1], a1);
+          a0 = fmaf(xv[2][s], w[2], a0);
+          a1 = fmaf(xv[3][s], w[3], a1);
+        }
+      } else {
+        const float* ps = packed + (size_t)(k_max + 2 * zi + hh) * S + 4;
+#pragma unroll
+        for (int s = 0; s < 4 * RB; ++s) {
+          if (s > 4 * (RB - 1) && 4 * (s - 4 * (RB - 1)) >= ext) continue;
+          const float4 w = *reinterpret_cast<const float4*>(ps + 4 * s);
+          const bool tail = s >= 4 * (RB - 1);  // words past V are not the record's
+          a0 = fmaf(xv[0][s], w.x, a0);
+          a1 = !tail || 4 * s + 1 < V ? fmaf(xv[1][s], w.y, a1) : a1;
+          a0 = !tail || 4 * s + 2 < V ? fmaf(xv[2][s], w.z, a0) : a0;
+          a1 = !tail || 4 * s + 3 < V ? fmaf(xv[3][s], w.w, a1) : a1;
+        }
+      }
+      sc[hh] = a0 + a1;
+    }
     if (i < n) {
-      const int zi = h ? zb : za;
-      float xv[2 * VH];
-#pragma unroll
-      for (int v = 0; v < 2 * VH; ++v) {
-        const int c = __builtin_amdgcn_raw_buffer_load_b32(rx, lane * V * 4 + 4 * v, 0, 0);
-        xv[v] = v < V ? (float)c : 0.0f;
-      }
-      const float* ps = packed + (size_t)(k_max + 2 * zi) * S;
-      const float delta = score_mult<2 * VH>(ps, xv) - score_mult<2 * VH>(ps + S, xv);
       z[i] = zi;
-      zsub[i] = (unsigned char)sub_label_draw(delta, seed, t, (uint32_t)i, K);
+      zsub[i] = (unsigned char)sub_label_draw(sc[0] - sc[1], seed, t, (uint32_t)i, K);
     }
   }
 }
 
-size_t label_mult_mfma_lds(int V, int K) {
+size_t label_mult_mfma_lds(int V, int K, bool sub) {
+  return ((size_t)(sub ? 3 : 1) * K * mm_ldv(V) + ((K + 63) & ~63) + 2 * (size_t)K) * sizeof(float) +
+         (size_t)MM_WAVES * (64 * sizeof(unsigned long long) + MM_LIST * (sizeof(float) + sizeof(unsigned short)));
+}
+
+// The matrix-core draw takes the calls whose log theta, in rows of 32, 64 or 128
+// words and blocks of 32 clusters, fits 96 KB (K <= 704, 352, 160).  The two
+// draws round their scores differently, so the line stays where it has been: a
+// call keeps its labels.
+bool mult_on_matrix_cores(int V, int K) {
   const int VH = V <= 32 ? 16 : (V <= 64 ? 32 : 64);
   const size_t kb = (size_t)(K + 31) / 32;
-  return (kb * 32 * (2 * VH + 1) + kb * 32) * sizeof(float);
+  return V <= 128 && (kb * 32 * (2 * VH + 1) + kb * 32) * sizeof(float) <= MULT_MFMA_LDS_MAX;
 }
 
 __global__ __launch_bounds__(BLOCK) void k_loglik_mult(const int* __restrict__ x, long long n, int V,
@@ -312,30 +394,51 @@ int grid_for(long long n) {
 hipError_t launch_label_mult(int V, const int* x, long long n, const float* packed, int K, int k_max,
                              uint32_t t, uint64_t seed, int* z, unsigned char* zsub, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  // the matrix-core kernel while log theta of every cluster fits in LDS
-  const size_t lds = label_mult_mfma_lds(V, K);
-  if (V <= 128 && lds <= MULT_MFMA_LDS_MAX) {
+  if (mult_on_matrix_cores(V, K)) {
+    const bool sub = label_mult_mfma_lds(V, K, true) <= MM_LDS_MAX;
+    const size_t lds = label_mult_mfma_lds(V, K, sub);
     static bool attr_set = false;
     if (!attr_set) {
-      const void* fns[3] = {(const void*)k_label_mult_mfma<16>, (const void*)k_label_mult_mfma<32>,
-                            (const void*)k_label_mult_mfma<64>};
+      const void* fns[16] = {
+          (const void*)k_label_mult_mfma<1, true>,  (const void*)k_label_mult_mfma<2, true>,
+          (const void*)k_label_mult_mfma<3, true>,  (const void*)k_label_mult_mfma<4, true>,
+          (const void*)k_label_mult_mfma<5, true>,  (const void*)k_label_mult_mfma<6, true>,
+          (const void*)k_label_mult_mfma<7, true>,  (const void*)k_label_mult_mfma<8, true>,
+          (const void*)k_label_mult_mfma<1, false>, (const void*)k_label_mult_mfma<2, false>,
+          (const void*)k_label_mult_mfma<3, false>, (const void*)k_label_mult_mfma<4, false>,
+          (const void*)k_label_mult_mfma<5, false>, (const void*)k_label_mult_mfma<6, false>,
+          (const void*)k_label_mult_mfma<7, false>, (const void*)k_label_mult_mfma<8, false>};
       for (const void* f : fns) {
-        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, (int)MULT_MFMA_LDS_MAX);
+        const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
         if (e != hipSuccess) return e;
       }
       attr_set = true;
     }
-    long long g = (n + BLOCK - 1) / BLOCK;
-    if (g > 1024) g = 1024;
-    if (V <= 32)
-      hipLaunchKernelGGL(k_label_mult_mfma<16>, dim3(g), dim3(BLOCK), lds, s, x, n, V, packed, K, k_max, t, seed, z,
-                         zsub);
-    else if (V <= 64)
-      hipLaunchKernelGGL(k_label_mult_mfma<32>, dim3(g), dim3(BLOCK), lds, s, x, n, V, packed, K, k_max, t, seed, z,
-                         zsub);
-    else
-      hipLaunchKernelGGL(k_label_mult_mfma<64>, dim3(g), dim3(BLOCK), lds, s, x, n, V, packed, K, k_max, t, seed, z,
-                         zsub);
+    // one workgroup of eight waves per CU, which stages the tables once
+    long long g = (n + MM_BLOCK - 1) / MM_BLOCK;
+    if (g > 256) g = 256;
+#define DPMM_MM_CASE(RB)                                                                                              \
+  case RB:                                                                                                            \
+    if (sub)                                                                                                          \
+      hipLaunchKernelGGL((k_label_mult_mfma<RB, true>), dim3(g), dim3(MM_BLOCK), lds, s, x, n, V, packed, K, k_max, t, \
+                         seed, z, zsub);                                                                              \
+    else                                                                                                              \
+      hipLaunchKernelGGL((k_label_mult_mfma<RB, false>), dim3(g), dim3(MM_BLOCK), lds, s, x, n, V, packed, K, k_max, t, \
+                         seed, z, zsub);                                                                              \
+    break;
+    switch (mx::row_blocks(V)) {
+      DPMM_MM_CASE(1)
+      DPMM_MM_CASE(2)
+      DPMM_MM_CASE(3)
+      DPMM_MM_CASE(4)
+      DPMM_MM_CASE(5)
+      DPMM_MM_CASE(6)
+      DPMM_MM_CASE(7)
+      DPMM_MM_CASE(8)
+      default:
+        return hipErrorInvalidValue;
+    }
+#undef DPMM_MM_CASE
     return hipGetLastError();
   }
   const int g = grid_for(n);

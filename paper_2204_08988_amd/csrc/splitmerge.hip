@@ -45,9 +45,10 @@ __device__ double reduce_sum(double v, double* red) {
   return r;
 }
 
-__global__ void k_zero64(unsigned long long* p, size_t n) {
-  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n; i += (size_t)gridDim.x * blockDim.x)
-    p[i] = 0ull;
+// two buffers in one launch (q may be null with m = 0)
+__global__ void k_zero64(unsigned long long* p, size_t n, unsigned long long* q, size_t m) {
+  for (size_t i = (size_t)blockIdx.x * blockDim.x + threadIdx.x; i < n + m; i += (size_t)gridDim.x * blockDim.x)
+    (i < n ? p[i] : q[i - n]) = 0ull;
 }
 
 __global__ void k_set_pair(int* p, int a, int b) {
@@ -623,11 +624,12 @@ hipError_t launch_set_pair(int* p, int a, int b, hipStream_t s) {
   return hipGetLastError();
 }
 
-hipError_t launch_zero64(void* p, size_t n_words, hipStream_t s) {
-  if (n_words == 0) return hipSuccess;
-  size_t g = (n_words + BLOCK - 1) / BLOCK;
+hipError_t launch_zero64(void* p, size_t n_words, hipStream_t s, void* q, size_t q_words) {
+  if (n_words + q_words == 0) return hipSuccess;
+  size_t g = (n_words + q_words + BLOCK - 1) / BLOCK;
   if (g > 4096) g = 4096;
-  hipLaunchKernelGGL(k_zero64, dim3((unsigned)g), dim3(BLOCK), 0, s, (unsigned long long*)p, n_words);
+  hipLaunchKernelGGL(k_zero64, dim3((unsigned)g), dim3(BLOCK), 0, s, (unsigned long long*)p, n_words,
+                     (unsigned long long*)q, q_words);
   return hipGetLastError();
 }
 

@@ -17,6 +17,8 @@
 // Multinomial: lanes over points, uint32 LDS accumulators (at most 65536
 // points per workgroup, so count entries below 65536 cannot overflow), int64
 // flush; all integer, so the result is exact and independent of the order.
+#include <algorithm>
+
 #include "kernels.hpp"
 
 namespace dpmm {
@@ -219,8 +221,13 @@ __global__ __launch_bounds__(64) void k_stats_small_reduce(const double* __restr
 // takes 64 consecutive rows: lane r reads row r's label, then the lanes span
 // the words of one row at a time (a coalesced load through a buffer descriptor
 // that covers only rows below n, eight rows in flight) and add them to the
-// row's segment, distinct addresses within each LDS instruction.
-__global__ __launch_bounds__(BLOCK) void k_stats_mult_lds(const int* __restrict__ x, long long n, int V,
+// row's segment, distinct addresses within each LDS instruction.  Bound by the
+// reads of x; one workgroup of 16 waves per CU, because each workgroup adds its
+// 2K (V + 1) sums to the totals with 64-bit atomics (N = 1e6, V = 100, K = 50:
+// 379 us with 122 workgroups of four waves, 116 us so; 400 MB at a copy's rate
+// take 85).
+constexpr int MS_BLOCK = 1024;
+__global__ __launch_bounds__(MS_BLOCK) void k_stats_mult_lds(const int* __restrict__ x, long long n, int V,
                                                           const int* __restrict__ z,
                                                           const unsigned char* __restrict__ zsub, int K,
                                                           long long* __restrict__ counts,
@@ -228,12 +235,12 @@ __global__ __launch_bounds__(BLOCK) void k_stats_mult_lds(const int* __restrict_
   extern __shared__ unsigned int lds_u[];
   unsigned int* acc = lds_u;           // [2K][V]
   unsigned int* cnt = acc + 2 * K * V;  // [2K]
-  for (int idx = threadIdx.x; idx < 2 * K * V + 2 * K; idx += BLOCK) lds_u[idx] = 0u;
+  for (int idx = threadIdx.x; idx < 2 * K * V + 2 * K; idx += MS_BLOCK) lds_u[idx] = 0u;
   __syncthreads();
   const int lane = threadIdx.x & 63;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
-  const long long wstep = (long long)gridDim.x * (BLOCK / 64) * 64;
-  for (long long base = ((long long)blockIdx.x * (BLOCK / 64) + wave) * 64; base < n; base += wstep) {
+  const long long wstep = (long long)gridDim.x * (MS_BLOCK / 64) * 64;
+  for (long long base = ((long long)blockIdx.x * (MS_BLOCK / 64) + wave) * 64; base < n; base += wstep) {
     const long long i = base + lane;
     int seg = -1;
     if (i < n) {
@@ -259,9 +266,9 @@ __global__ __launch_bounds__(BLOCK) void k_stats_mult_lds(const int* __restrict_
     }
   }
   __syncthreads();
-  for (int idx = threadIdx.x; idx < 2 * K * V; idx += BLOCK)
+  for (int idx = threadIdx.x; idx < 2 * K * V; idx += MS_BLOCK)
     if (acc[idx]) atomicAdd((unsigned long long*)&sums[idx], (unsigned long long)acc[idx]);
-  for (int idx = threadIdx.x; idx < 2 * K; idx += BLOCK)
+  for (int idx = threadIdx.x; idx < 2 * K; idx += MS_BLOCK)
     if (cnt[idx]) atomicAdd((unsigned long long*)&counts[idx], (unsigned long long)cnt[idx]);
 }
 
@@ -377,18 +384,19 @@ hipError_t launch_stats_gauss(int d, const float* x, long long n, const int* z, 
 
 hipError_t launch_stats_mult(int V, const int* x, long long n, const int* z, const unsigned char* zsub,
                              int K, long long* counts, long long* sums, hipStream_t s) {
-  hipError_t err = launch_zero64(counts, (size_t)2 * K, s);
-  if (err != hipSuccess) return err;
-  err = launch_zero64(sums, (size_t)2 * K * V, s);
+  hipError_t err = launch_zero64(counts, (size_t)2 * K, s, sums, (size_t)2 * K * V);
   if (err != hipSuccess) return err;
   if (n == 0) return hipSuccess;
   const size_t lds = ((size_t)2 * K * V + 2 * K) * sizeof(unsigned int);
   if (lds <= LDS_BUDGET) {
-    // uint32 partial sums: at most 65536 points per workgroup, so entries below
-    // 65536 cannot overflow a partial sum
-    long long g = stats_grid(n, (long long)BLOCK * 32);
-    if ((n + g - 1) / g > 65536) g = (n + 65535) / 65536;
-    hipLaunchKernelGGL(k_stats_mult_lds, dim3((unsigned)g), dim3(BLOCK), lds, s, x, n, V, z, zsub, K, counts,
+    // a workgroup per CU; more beyond 7168 points each, up to 2048 of them (a
+    // workgroup takes at most 1023 points more than its share).  uint32 partial
+    // sums: at most 65536 points per workgroup, so entries below 65536 cannot
+    // overflow a partial sum at any n
+    long long g = std::max<long long>(std::min<long long>((n + MS_BLOCK - 1) / MS_BLOCK, 256), (n + 7167) / 7168);
+    if (g > 2048) g = 2048;
+    if ((n + g - 1) / g > 65536 - MS_BLOCK) g = (n + 65536 - MS_BLOCK - 1) / (65536 - MS_BLOCK);
+    hipLaunchKernelGGL(k_stats_mult_lds, dim3((unsigned)g), dim3(MS_BLOCK), lds, s, x, n, V, z, zsub, K, counts,
                        sums);
   } else {
     hipLaunchKernelGGL(k_stats_mult_global, dim3(stats_grid(n, (long long)BLOCK * 4)), dim3(BLOCK), 0, s, x, n,
