@@ -217,44 +217,39 @@ dpmm_status ensure_items(dpmm_ctx* ctx, size_t count) {
   if (ctx->items_cap) DPMM_HIP(ctx, hipStreamSynchronize(ctx->stream), "synchronise");
   hipFree(ctx->d_items);
   hipFree(ctx->d_logml);
-  hipFree(ctx->d_mflag);
-  hipFree(ctx->d_plist);
   hipHostFree(ctx->h_items);
   hipHostFree(ctx->h_lml);
-  hipHostFree(ctx->h_mflag);
-  hipFree(ctx->d_rb);
   hipHostFree(ctx->h_rb);
-  ctx->d_plist = nullptr;
   ctx->d_rb = nullptr;
   ctx->h_rb = nullptr;
   ctx->d_items = nullptr;
   ctx->d_logml = nullptr;
-  ctx->d_mflag = nullptr;
   ctx->h_items = nullptr;
   ctx->h_lml = nullptr;
-  ctx->h_mflag = nullptr;
   ctx->items_cap = 0;
+  ctx->items_held = 0;
   DPMM_HIP(ctx, hipMalloc(&ctx->d_items, cap * sizeof(LogmlItem)), "allocate items");
   DPMM_HIP(ctx, hipMalloc(&ctx->d_logml, cap * sizeof(double)), "allocate items");
-  DPMM_HIP(ctx, hipMalloc(&ctx->d_mflag, cap), "allocate items");
-  DPMM_HIP(ctx, hipMalloc(&ctx->d_plist, cap * sizeof(int)), "allocate items");
   DPMM_HIP(ctx, hipHostMalloc((void**)&ctx->h_items, cap * sizeof(LogmlItem), hipHostMallocDefault), "pin items");
   DPMM_HIP(ctx, hipHostMalloc((void**)&ctx->h_lml, cap * sizeof(double), hipHostMallocDefault), "pin items");
-  DPMM_HIP(ctx, hipHostMalloc((void**)&ctx->h_mflag, cap, hipHostMallocDefault), "pin items");
   const size_t rb = readback_bytes(ctx->cfg.k_max, (int)cap);
-  DPMM_HIP(ctx, hipMalloc(&ctx->d_rb, rb), "allocate read-back");
   DPMM_HIP(ctx, hipHostMalloc((void**)&ctx->h_rb, rb, hipHostMallocDefault), "pin read-back");
+  DPMM_HIP(ctx, hipHostGetDevicePointer((void**)&ctx->d_rb, ctx->h_rb, 0), "map read-back");
   ctx->items_cap = cap;
   return DPMM_OK;
 }
 
-// copy items to d_items (through pinned staging)
+// copy items to d_items (through pinned staging), unless it holds them already:
+// an iteration without moves asks for the same items as the one before
 dpmm_status logml_upload(dpmm_ctx* ctx, const LogmlItem* items, size_t count) {
   DPMM_TRY(ensure_items(ctx, count));
   if (count == 0) return DPMM_OK;
+  if (count <= ctx->items_held && std::memcmp(ctx->h_items, items, count * sizeof(LogmlItem)) == 0) return DPMM_OK;
+  ctx->items_held = 0;
   std::memcpy(ctx->h_items, items, count * sizeof(LogmlItem));
   DPMM_HIP(ctx, hipMemcpyAsync(ctx->d_items, ctx->h_items, count * sizeof(LogmlItem), hipMemcpyHostToDevice,
                                ctx->stream), "copy items");
+  ctx->items_held = count;
   return DPMM_OK;
 }
 
@@ -265,8 +260,8 @@ dpmm_status logml_range(dpmm_ctx* ctx, size_t first, size_t count) {
   hipError_t e;
   if (ctx->gaussian())
     e = launch_logml_gauss((int)count, ctx->d_items + first, ctx->d, prior_dev(ctx), ctx->logdet_psi, ctx->d_counts,
-                           ctx->d_moments, ctx->d_scratch, ctx->d_logml + first, ctx->d_err, ctx->stream, nullptr,
-                           nullptr, 0, ctx->d_cmom, ctx->K);
+                           ctx->d_moments, ctx->d_scratch, ctx->d_logml + first, ctx->d_err, ctx->stream, ctx->d_cmom,
+                           ctx->K);
   else if (ctx->poisson())
     e = launch_logml_pois((int)count, ctx->d_items + first, ctx->d, ctx->d_gshape, ctx->d_grate, ctx->pois_const,
                           ctx->d_counts, ctx->d_sums, ctx->d_logml + first, ctx->stream);
@@ -486,7 +481,6 @@ dpmm_status dpmm_create(const dpmm_config* cfg, void* hip_stream, dpmm_ctx** out
   ok = ok && chk(c->alloc(&c->d_packed, 3 * (size_t)km * c->stride));
   ok = ok && chk(c->alloc(&c->d_err, 1));
   ok = ok && chk(c->alloc(&c->d_table, 4 * (size_t)km));
-  ok = ok && chk(c->alloc(&c->d_pcount, 2));
   if (c->gaussian()) {
     ok = ok && chk(c->alloc(&c->d_m, (size_t)d));
     ok = ok && chk(c->alloc(&c->d_psi, (size_t)d * d));
@@ -596,12 +590,8 @@ void dpmm_destroy(dpmm_ctx* ctx) {
   if (ctx->h_back) hipHostFree(ctx->h_back);
   hipFree(ctx->d_items);
   hipFree(ctx->d_logml);
-  hipFree(ctx->d_mflag);
-  hipFree(ctx->d_plist);
   hipHostFree(ctx->h_items);
   hipHostFree(ctx->h_lml);
-  hipHostFree(ctx->h_mflag);
-  hipFree(ctx->d_rb);
   hipHostFree(ctx->h_rb);
   hipHostFree(ctx->h_cnt);
   hipHostFree(ctx->h_flag);
@@ -850,6 +840,14 @@ dpmm_status label_phase(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t, int
   return DPMM_OK;
 }
 
+// Within dpmm_step: the end of the split / merge phase's device work so far (the
+// last of a phase stands), before the synchronisation that the phase makes
+// anyway: recorded after it, the event cost a wait of its own.
+dpmm_status phase_end(dpmm_ctx* ctx) {
+  if (ctx->step_timing) DPMM_HIP(ctx, hipEventRecord(ctx->ev[5], ctx->stream), "event");
+  return DPMM_OK;
+}
+
 // Second half on the sorted path: sort by cluster, sub-labels, statistics.
 dpmm_status sub_phase(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t, int32_t* z, uint8_t* zsub, int G,
                       long long per) {
@@ -886,12 +884,14 @@ dpmm_status dpmm_sample_params(dpmm_ctx* ctx, uint32_t t) {
   if (!ctx) return DPMM_E_ARG;
   if (!ctx->have_stats) return ctx->fail(DPMM_E_STATE, "no statistics yet");
   const int K = ctx->K;
-  hipLaunchKernelGGL(k_weights, dim3(1), dim3(256), 0, ctx->stream, K, ctx->cfg.alpha, ctx->d_counts, ctx->cfg.seed, t,
-                     ctx->d_log_pi, ctx->d_log_pisub, ctx->d_tmp);
-  DPMM_HIP(ctx, hipGetLastError(), "weights kernel");
+  if (!ctx->gaussian() || !niw_draws_weights(K, ctx->d)) {
+    hipLaunchKernelGGL(k_weights, dim3(1), dim3(256), 0, ctx->stream, K, ctx->cfg.alpha, ctx->d_counts, ctx->cfg.seed, t,
+                       ctx->d_log_pi, ctx->d_log_pisub, ctx->d_tmp);
+    DPMM_HIP(ctx, hipGetLastError(), "weights kernel");
+  }
   if (ctx->gaussian()) {
     DPMM_HIP(ctx, launch_niw_draw(K, ctx->d, ctx->cfg.k_max, prior_dev(ctx), ctx->d_counts, ctx->d_moments,
-                                  ctx->d_log_pi, ctx->d_log_pisub, ctx->cfg.seed, t, ctx->d_mu, ctx->d_sigma,
+                                  ctx->cfg.alpha, ctx->d_log_pi, ctx->d_log_pisub, ctx->cfg.seed, t, ctx->d_mu, ctx->d_sigma,
                                   ctx->d_scratch, ctx->d_packed, ctx->d_logdet, ctx->d_err, ctx->stream),
              "posterior draw kernel");
     if (ctx->d_whi)
@@ -947,44 +947,36 @@ dpmm_status dpmm_split_merge(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t
     for (int k1 = 0; k1 < K; ++k1) {
       if (ctx->age[k1] < burn) continue;
       for (int k2 = k1 + 1; k2 < K; ++k2)
-        if (ctx->age[k2] >= burn) {
-          pairs.emplace_back(k1, k2);
-          items.push_back(LogmlItem{{2 * k1, 2 * k1 + 1, 2 * k2, 2 * k2 + 1}});
-        }
+        if (ctx->age[k2] >= burn) pairs.emplace_back(k1, k2);
     }
     const int P = (int)pairs.size();
     const bool paper_form = ctx->cfg.merge_form == DPMM_MERGE_PAPER;
-    // the merge tests on the device, one read-back: counts, the 3K cluster /
-    // sub-cluster marginals, the pair decisions and the error flag
-    if (ctx->gaussian() && P > 0 && ctx->d <= MERGE_BOUND_MAX_D) {
-      // Gaussian, small d: the bound items log|Psi / 2 + C_k| after the pairs;
-      // the merge bound rejects most pairs, and only the others get the union's
-      // Cholesky.  (Above MERGE_BOUND_MAX_D the bound is too loose to pay for
-      // its K extra factorisations on ill-conditioned covariances.)
+    // Gaussian, small d: the bound items log|Psi / 2 + C_k| before the pairs; the
+    // merge bound rejects most pairs, and only the others get the union's
+    // Cholesky.  (Above MERGE_BOUND_MAX_D the bound is too loose to pay for
+    // its K extra factorisations on ill-conditioned covariances.)
+    const bool bounded = ctx->gaussian() && P > 0 && ctx->d <= MERGE_BOUND_MAX_D;
+    if (bounded)
       for (int k = 0; k < K; ++k) items.push_back(LogmlItem{{2 * k, 2 * k + 1, -1, LOGML_BOUND}});
-      DPMM_TRY(logml_upload(ctx, items.data(), items.size()));
-      DPMM_TRY(logml_range(ctx, 0, 3 * (size_t)K));
-      DPMM_TRY(logml_range(ctx, 3 * (size_t)K + P, (size_t)K));
-      DPMM_HIP(ctx, launch_merge_prune(P, ctx->d_items + 3 * K, ctx->d, prior_dev(ctx), ctx->logdet_psi, ctx->lam_psi,
-                                       ctx->d_counts, ctx->d_moments, ctx->d_logml, ctx->d_logml + 3 * K + P, alpha,
-                                       paper_form, seed, t, ctx->d_mflag, ctx->d_plist, ctx->d_pcount, ctx->stream),
-               "merge bound kernel");
-      DPMM_HIP(ctx, launch_logml_gauss(P, ctx->d_items, ctx->d, prior_dev(ctx), ctx->logdet_psi, ctx->d_counts,
-                                       ctx->d_moments, ctx->d_scratch, ctx->d_logml, ctx->d_err, ctx->stream,
-                                       ctx->d_plist, ctx->d_pcount, 3 * K),
-               "log marginal likelihood kernel");
-      DPMM_HIP(ctx, launch_merge_decide(P, ctx->d_items + 3 * K, ctx->d_counts, ctx->d_logml, ctx->d_logml + 3 * K,
-                                        alpha, paper_form, seed, t, ctx->d_mflag, ctx->stream, ctx->d_plist,
-                                        ctx->d_pcount), "merge test kernel");
+    const size_t first_pair = items.size();
+    for (const auto& kk : pairs)
+      items.push_back(LogmlItem{{2 * kk.first, 2 * kk.first + 1, 2 * kk.second, 2 * kk.second + 1}});
+    // the merge tests on the device; their kernel writes the counts, the 3K cluster
+    // / sub-cluster marginals, the pair decisions and the error flag to pinned memory
+    DPMM_TRY(logml_upload(ctx, items.data(), items.size()));
+    if (bounded) {
+      DPMM_TRY(logml_range(ctx, 0, first_pair));
+      DPMM_HIP(ctx, launch_merge_pairs(P, ctx->d_items + first_pair, ctx->d, K, prior_dev(ctx), ctx->logdet_psi,
+                                       ctx->lam_psi, ctx->d_counts, ctx->d_moments, ctx->d_logml,
+                                       ctx->d_logml + 3 * K, alpha, paper_form, seed, t, ctx->d_err, ctx->d_rb,
+                                       ctx->stream), "merge test kernel");
     } else {
-      DPMM_TRY(logml_launch(ctx, items.data(), items.size()));
-      DPMM_HIP(ctx, launch_merge_decide(P, ctx->d_items + 3 * K, ctx->d_counts, ctx->d_logml, ctx->d_logml + 3 * K,
-                                        alpha, paper_form, seed, t, ctx->d_mflag, ctx->stream), "merge test kernel");
+      DPMM_TRY(logml_range(ctx, 0, items.size()));
+      DPMM_HIP(ctx, launch_merge_decide(P, ctx->d_items + first_pair, K, ctx->d_counts, ctx->d_logml,
+                                        ctx->d_logml + first_pair, alpha, paper_form, seed, t, ctx->d_err, ctx->d_rb,
+                                        ctx->stream), "merge test kernel");
     }
-    DPMM_HIP(ctx, launch_pack_readback(K, P, ctx->d_counts, ctx->d_logml, ctx->d_mflag, ctx->d_err, ctx->d_rb,
-                                       ctx->stream), "read-back kernel");
-    DPMM_HIP(ctx, hipMemcpyAsync(ctx->h_rb, ctx->d_rb, readback_bytes(K, P), hipMemcpyDeviceToHost, ctx->stream),
-             "copy read-back");
+    DPMM_TRY(phase_end(ctx));
     DPMM_HIP(ctx, hipStreamSynchronize(ctx->stream), "synchronise");
     const long long* rb_cnt = reinterpret_cast<const long long*>(ctx->h_rb + 8);
     const double* rb_lml = reinterpret_cast<const double*>(ctx->h_rb + 8 + 16 * (size_t)K);
@@ -992,7 +984,9 @@ dpmm_status dpmm_split_merge(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t
     cnt.assign(rb_cnt, rb_cnt + 2 * (size_t)K);
     lml.assign(rb_lml, rb_lml + 3 * (size_t)K);
     merge_ok.assign(rb_m, rb_m + P);
-    const int flag = (int)*reinterpret_cast<const long long*>(ctx->h_rb);
+    int flag = (int)*reinterpret_cast<const long long*>(ctx->h_rb);
+    for (int p = 0; p < P; ++p)
+      if (merge_ok[p] == 2) flag |= 4;  // the union's factorisation failed
     if (flag) return flag_fail(ctx, flag);
     // delete empty clusters (stable), then start over with the new K
     int kept = 0;
@@ -1085,6 +1079,7 @@ dpmm_status dpmm_split_merge(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t
     DPMM_TRY(logml(ctx, fitems, lml_cluster, &flag));
     if (flag) return flag_fail(ctx, flag);
   }
+  if (local.splits > 0 || local.merges > 0) DPMM_TRY(phase_end(ctx));
   local.K = ctx->K;
   local.logpost = log_posterior(ctx, cnt, lml_cluster);
   ctx->have_params = false;  // parameters refer to the clusters before the moves
@@ -1121,29 +1116,32 @@ dpmm_status dpmm_step(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t, int32
   const dpmm_status sp = sub_phase(ctx, x, n, t, z, zsub, G, per);
   ctx->timing = false;
   DPMM_TRY(sp);
-  if (!ctx->sorted_path()) DPMM_HIP(ctx, hipEventRecord(ctx->ev[3], ctx->stream), "event");
   if (!ctx->labels_gave_stats) DPMM_TRY(launch_stats(ctx, x, n, z, zsub));
   DPMM_HIP(ctx, hipEventRecord(ctx->ev[4], ctx->stream), "event");
   dpmm_iter_info local{};
-  DPMM_TRY(dpmm_split_merge(ctx, x, n, t, z, zsub, &local));
-  DPMM_HIP(ctx, hipEventRecord(ctx->ev[5], ctx->stream), "event");
+  ctx->step_timing = true;
+  const dpmm_status sm = dpmm_split_merge(ctx, x, n, t, z, zsub, &local);
+  ctx->step_timing = false;
+  DPMM_TRY(sm);
   dpmm_learned_info li{};
   if (ctx->lm > 0) {
+    DPMM_HIP(ctx, hipEventRecord(ctx->ev[5], ctx->stream), "event");
     DPMM_TRY(learned_move(ctx, x, n, t, z, zsub, nullptr, &li));
     local.K = ctx->K;
+    DPMM_HIP(ctx, hipEventRecord(ctx->ev[6], ctx->stream), "event");
   }
-  DPMM_HIP(ctx, hipEventRecord(ctx->ev[6], ctx->stream), "event");
   for (auto& a : ctx->age) ++a;
   if (info) {
     *info = local;
     info->learned_kind = li.kind;
     info->learned_accepted = li.accepted;
-    DPMM_HIP(ctx, hipEventSynchronize(ctx->ev[6]), "event sync");
-    hipEventElapsedTime(&info->ms_learned, ctx->ev[5], ctx->ev[6]);
+    DPMM_HIP(ctx, hipEventSynchronize(ctx->ev[ctx->lm > 0 ? 6 : 5]), "event sync");
+    info->ms_learned = info->ms_sort = 0.0f;
+    if (ctx->lm > 0) hipEventElapsedTime(&info->ms_learned, ctx->ev[5], ctx->ev[6]);
     hipEventElapsedTime(&info->ms_params, ctx->ev[0], ctx->ev[1]);
     hipEventElapsedTime(&info->ms_labels, ctx->ev[1], ctx->ev[2]);
-    hipEventElapsedTime(&info->ms_sort, ctx->ev[2], ctx->ev[3]);
-    hipEventElapsedTime(&info->ms_stats, ctx->ev[3], ctx->ev[4]);
+    if (ctx->sorted_path()) hipEventElapsedTime(&info->ms_sort, ctx->ev[2], ctx->ev[3]);
+    hipEventElapsedTime(&info->ms_stats, ctx->ev[ctx->sorted_path() ? 3 : 2], ctx->ev[4]);
     hipEventElapsedTime(&info->ms_splitmerge, ctx->ev[4], ctx->ev[5]);
     info->ms_label_kernel = info->ms_labels;
     if (ctx->label_kernel_timed) hipEventElapsedTime(&info->ms_label_kernel, ctx->ev[7], ctx->ev[8]);

@@ -55,9 +55,10 @@ struct dpmm_ctx {
   double *d_log_pi = nullptr, *d_log_pisub = nullptr, *d_tmp = nullptr;
   double *d_mu = nullptr, *d_sigma = nullptr, *d_log_theta = nullptr, *d_logdet = nullptr;
   float* d_packed = nullptr;
-  // one split/merge round's read-back: device buffer and its pinned copy (grown with the items)
-  unsigned char* d_rb = nullptr;
+  // one split/merge round's read-back: pinned host memory that the merge kernels
+  // write, and its device address (grown with the items)
   unsigned char* h_rb = nullptr;
+  unsigned char* d_rb = nullptr;
   double* d_scratch = nullptr;  // NIW_SCRATCH(d) per workgroup slot
   int scratch_slots = 0;
   int* d_err = nullptr;
@@ -65,14 +66,11 @@ struct dpmm_ctx {
   // ensure_items (outside bufs)
   LogmlItem* d_items = nullptr;
   double* d_logml = nullptr;
-  unsigned char* d_mflag = nullptr;
-  int* d_plist = nullptr;   // pairs the merge bound leaves for the exact test
-  int* d_pcount = nullptr;  // their number
   double lam_psi = 0.0;     // an upper bound on lambda_max(Psi) (Gershgorin)
   LogmlItem* h_items = nullptr;
   double* h_lml = nullptr;
-  unsigned char* h_mflag = nullptr;
   size_t items_cap = 0;
+  size_t items_held = 0;  // items that d_items holds as h_items has them
   long long* h_cnt = nullptr;  // pinned [2 k_max]
   int* h_flag = nullptr;       // pinned
   RelabelEntry* d_table = nullptr;
@@ -102,6 +100,7 @@ struct dpmm_ctx {
   int* d_cand = nullptr;   // [perm_cap][RESCORE_CAND] their candidate clusters
   float* d_cst = nullptr;  // [CAND_SPLIT_CAP][CAND_SPLIT_NG][CAND_STATE] split candidate pass lists (d = 64, 128)
   hipEvent_t ev[9] = {nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr, nullptr};
+  bool step_timing = false;  // dpmm_step is running its split / merge phase (records ev[5])
   bool timing = false;  // record ev[3] between the sort and the statistics kernel
   // record ev[7], ev[8] around the main cluster-draw kernel (matrix-core path);
   // label_kernel_timed tells whether the last label phase did

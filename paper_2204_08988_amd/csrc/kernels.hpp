@@ -35,9 +35,12 @@ __global__ void k_niw_draw(int K, int d, int k_max, NiwPriorDev prior, const lon
                            const double* moments, const double* log_pi, const double* log_pisub,
                            uint64_t seed, uint32_t t, double* mu_out, double* sigma_out, double* scratch,
                            float* packed, double* logdet_out, int* err);
-// k_niw_draw, with one wave per component for d <= 64
+// k_niw_draw, with one wave per component for d <= 64.  While niw_draws_weights the
+// kernel draws the weights too (the same values; one wave holds the K + 1 log-gamma
+// draws), else log_pi / log_pisub come from k_weights before it
+bool niw_draws_weights(int K, int d);
 hipError_t launch_niw_draw(int K, int d, int k_max, NiwPriorDev prior, const long long* counts,
-                           const double* moments, const double* log_pi, const double* log_pisub, uint64_t seed,
+                           const double* moments, double alpha, double* log_pi, double* log_pisub, uint64_t seed,
                            uint32_t t, double* mu_out, double* sigma_out, double* scratch, float* packed,
                            double* logdet_out, int* err, hipStream_t s);
 __global__ void k_dir_draw(int K, int V, const double* beta, const long long* sums, uint64_t seed,
@@ -235,31 +238,28 @@ constexpr int LOGML_BOUND = -3;
 // |X + Y|^(1/d) >= |X|^(1/d) + |Y|^(1/d), whose gap grows with d when the two
 // clusters' covariances are ill-conditioned in different directions
 constexpr int MERGE_BOUND_MAX_D = 16;
-// list mode (list != nullptr): the items list_base + list[q] for q < *list_count
-// (n_items bounds the grid)
 // cmom (may be null; 64 < d <= 128): (K + 1) x CMOM_TILE_ENTRIES doubles of
 // scratch for the clusters' summed scatter matrices, rebuilt by the call
 constexpr int CMOM_TILE_ENTRIES = 136 * 64;
 hipError_t launch_logml_gauss(int n_items, const LogmlItem* items, int d, NiwPriorDev prior,
                               double logdet_psi, const long long* counts, const double* moments,
-                              double* scratch, double* out, int* err, hipStream_t s, const int* list = nullptr,
-                              const int* list_count = nullptr, int list_base = 0, double* cmom = nullptr,
+                              double* scratch, double* out, int* err, hipStream_t s, double* cmom = nullptr,
                               int K = 0);
-// the merge bound: accept[p] = 0 for the pairs it rejects, the others listed
-// (list, *list_count) for their log marginal and k_merge_decide
-hipError_t launch_merge_prune(int n_pairs, const LogmlItem* pairs, int d, NiwPriorDev prior, double logdet_psi,
-                              double lam_psi, const long long* counts, const double* moments, const double* lml_cluster,
-                              const double* logdet_half, double alpha, bool paper_form, uint64_t seed, uint32_t t,
-                              unsigned char* accept, int* list, int* list_count, hipStream_t s);
-// accept[p] = merge test of pair item pairs[p] (see k_merge_decide); list mode as above
-hipError_t launch_merge_decide(int n_pairs, const LogmlItem* pairs, const long long* counts, const double* lml_cluster,
-                               const double* lml_pair, double alpha, bool paper_form, uint64_t seed, uint32_t t,
-                               unsigned char* accept, hipStream_t s, const int* list = nullptr,
-                               const int* list_count = nullptr);
-// [error flag, 8 bytes][counts 2K int64][3K log marginals float64][P merge decisions] in one buffer
+// One split/merge round's read-back, written by the kernels below to pinned host
+// memory: [int error flag, 8 bytes][counts 2K int64][3K log marginals
+// float64][P merge decisions, one byte each: 0, 1, or 2 for a union whose
+// factorisation failed]
 size_t readback_bytes(int K, int P);
-hipError_t launch_pack_readback(int K, int P, const long long* counts, const double* lml, const unsigned char* mflag,
-                                const int* err, unsigned char* out, hipStream_t s);
+// d <= MERGE_BOUND_MAX_D: the merge test of every pair, bound first (lml: the 3K
+// log marginals, logdet_half: the K bound items)
+hipError_t launch_merge_pairs(int P, const LogmlItem* pairs, int d, int K, NiwPriorDev prior, double logdet_psi,
+                              double lam_psi, const long long* counts, const double* moments, const double* lml,
+                              const double* logdet_half, double alpha, bool paper_form, uint64_t seed, uint32_t t,
+                              const int* err, unsigned char* out, hipStream_t s);
+// the merge test of every pair from its union marginal lml_pair (P may be 0)
+hipError_t launch_merge_decide(int P, const LogmlItem* pairs, int K, const long long* counts, const double* lml,
+                               const double* lml_pair, double alpha, bool paper_form, uint64_t seed, uint32_t t,
+                               const int* err, unsigned char* out, hipStream_t s);
 hipError_t launch_logml_mult(int n_items, const LogmlItem* items, int V, const double* beta,
                              double beta_sum, double lgamma_beta_sum, const double* lgamma_beta,
                              const long long* counts, const long long* sums, double* out, hipStream_t s);

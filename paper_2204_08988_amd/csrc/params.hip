@@ -426,9 +426,9 @@ __global__ __launch_bounds__(NIW_BIG_THREADS) void k_niw_draw_lds(
 template <int D>
 __global__ __launch_bounds__(128) void k_niw_draw_wave(int K, int d, int k_max, NiwPriorDev prior,
                                                        const long long* __restrict__ counts,
-                                                       const double* __restrict__ moments,
-                                                       const double* __restrict__ log_pi,
-                                                       const double* __restrict__ log_pisub, uint64_t seed,
+                                                       const double* __restrict__ moments, int own_weights,
+                                                       double alpha, double* __restrict__ log_pi,
+                                                       double* __restrict__ log_pisub, uint64_t seed,
                                                        uint32_t t, double* __restrict__ mu_out,
                                                        double* __restrict__ sigma_out, float* __restrict__ packed,
                                                        double* __restrict__ logdet_out, int* __restrict__ err) {
@@ -439,6 +439,7 @@ __global__ __launch_bounds__(128) void k_niw_draw_wave(int K, int d, int k_max, 
   static_assert(D % 4 == 0, "Sigma is formed four columns at a time");
   __shared__ double rdiag[D];    // 1 / A[j][j], then 1 / G[j][j]
   __shared__ double seps[D];     // the mean's normals
+  __shared__ double s_lw;        // the component's log weight
   const int e = blockIdx.x;
   if (e >= 3 * K) return;
   const int k = e / 3, c = e % 3;
@@ -583,10 +584,37 @@ __global__ __launch_bounds__(128) void k_niw_draw_wave(int K, int d, int k_max, 
     }
   } else {
     __syncthreads();
+    // the log weight, while wave 0 works: from k_weights, or (own_weights, K <= 63)
+    // drawn here with its draws, sums and order, one log-gamma draw per lane
+    double lw;
+    if (!own_weights) {
+      lw = c == 0 ? log_pi[k] : log_pisub[2 * k + (c - 1)];
+    } else if (c == 0) {
+      double lg = -INFINITY;
+      if (lane <= K)
+        lg = log_gamma_draw(seed, t, (uint32_t)lane, TAG_WEIGHTS, 0,
+                            lane < K ? (double)(counts[2 * lane] + counts[2 * lane + 1]) : alpha);
+      double mx = lg;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) mx = fmax(mx, __shfl_xor(mx, o));
+      const double lse = mx + log(wave_sum(lane <= K ? exp(lg - mx) : 0.0));
+      lw = readlane_d(lg, k) - lse;
+      if (lane == 0) log_pi[k] = lw;
+    } else {
+      const int h = lane & 1;
+      const double lg = log_gamma_draw(seed, t, (uint32_t)k, TAG_SUBWEIGHTS, (uint32_t)h,
+                                       (double)counts[2 * k + h] + 0.5 * alpha);
+      const double l0 = readlane_d(lg, 0), l1 = readlane_d(lg, 1);
+      const double m = fmax(l0, l1);
+      lw = (c == 1 ? l0 : l1) - (m + log(exp(l0 - m) + exp(l1 - m)));
+      if (lane == 0) log_pisub[2 * k + (c - 1)] = lw;
+    }
+    if (lane == 0) s_lw = lw;
   }
+  __syncthreads();
   if (wave != 0) return;
   const double ld = 2.0 * wave_sum(live ? log(diag) : 0.0);
-  const double lw = c == 0 ? log_pi[k] : log_pisub[2 * k + (c - 1)];
+  const double lw = s_lw;
   const int stride = gauss_rec_stride(d);
   float* rec = packed + (size_t)record_slot(k, c, k_max) * stride;
   if (lane == 0) {
@@ -745,14 +773,16 @@ __global__ void k_pack_mult(int K, int V, int k_max, const double* __restrict__ 
   for (int idx = 4 + V + threadIdx.x; idx < stride; idx += blockDim.x) rec[idx] = 0.0f;
 }
 
+bool niw_draws_weights(int K, int d) { return d <= 64 && K <= 63; }
+
 hipError_t launch_niw_draw(int K, int d, int k_max, NiwPriorDev prior, const long long* counts,
-                           const double* moments, const double* log_pi, const double* log_pisub, uint64_t seed,
+                           const double* moments, double alpha, double* log_pi, double* log_pisub, uint64_t seed,
                            uint32_t t, double* mu_out, double* sigma_out, double* scratch, float* packed,
                            double* logdet_out, int* err, hipStream_t s) {
   if (K <= 0) return hipSuccess;
 #define DPMM_NIW_WAVE(DD)                                                                                    \
   hipLaunchKernelGGL(k_niw_draw_wave<DD>, dim3(3 * K), dim3(128), 0, s, K, d, k_max, prior, counts, moments,  \
-                     log_pi, log_pisub, seed, t, mu_out, sigma_out, packed, logdet_out, err)
+                     niw_draws_weights(K, d) ? 1 : 0, alpha, log_pi, log_pisub, seed, t, mu_out, sigma_out, packed, logdet_out, err)
   if (d <= 16)
     DPMM_NIW_WAVE(16);
   else if (d <= 32)

@@ -58,23 +58,15 @@ __global__ void k_set_pair(int* p, int a, int b) {
   }
 }
 
-// Item it of a launch: it itself, or in list mode (list != nullptr) the
-// base + list[q]-th item for q < *list_count (the survivors of the merge bound).
-__device__ __forceinline__ int logml_item(int q, int n_items, const int* list, const int* list_count, int base) {
-  if (!list) return q < n_items ? q : -1;
-  return q < *list_count ? base + list[q] : -1;
-}
-
 __global__ void k_logml_gauss(int n_items, const LogmlItem* __restrict__ items, int d, NiwPriorDev prior,
                               double logdet_psi, const long long* __restrict__ counts,
                               const double* __restrict__ moments, double* __restrict__ scratch,
-                              double* __restrict__ out, int* __restrict__ err, const int* __restrict__ list,
-                              const int* __restrict__ list_count, int list_base) {
+                              double* __restrict__ out, int* __restrict__ err) {
   extern __shared__ double lds_p[];
   __shared__ double red[BLOCK];
   __shared__ int flag;
-  const int it = logml_item(blockIdx.x, n_items, list, list_count, list_base);
-  if (it < 0) return;
+  const int it = blockIdx.x;
+  if (it >= n_items) return;
   const int tid = threadIdx.x;
   const int E = d + d * (d + 1) / 2;
   const LogmlItem item = items[it];
@@ -123,28 +115,22 @@ __global__ void k_logml_gauss(int n_items, const LogmlItem* __restrict__ items, 
   }
 }
 
-// One wave per item, D >= d rows padded with an identity block (whose
-// pivots are 1 and add nothing to log|Psi_n|).  Lane i builds row i of Psi_n
-// (entries k <= i) from the item's statistics, staged in the wave's LDS
-// buffer in one round of loads, and factors it with the wave Cholesky (pivots
-// and column entries by v_readlane): no workgroup barrier.
+// Log marginal of one item by one wave, D >= d rows padded with an identity
+// block (whose pivots are 1 and add nothing to log|Psi_n|).  Lane i builds row i
+// of Psi_n (entries k <= i) from the item's statistics, staged in the wave's LDS
+// buffer sm in one round of loads, and factors it with the wave Cholesky (pivots
+// and column entries by v_readlane): no workgroup barrier.  lg: the item's
+// log Gamma_d(nu_n / 2) - log Gamma_d(nu / 2) if the caller has it, else null.
 template <int D>
-__global__ __launch_bounds__(BLOCK) void k_logml_gauss_wave(int n_items, const LogmlItem* __restrict__ items, int d,
-                                                            NiwPriorDev prior, double logdet_psi,
-                                                            const long long* __restrict__ counts,
-                                                            const double* __restrict__ moments,
-                                                            double* __restrict__ out, int* __restrict__ err,
-                                                            const int* __restrict__ list,
-                                                            const int* __restrict__ list_count, int list_base) {
+__device__ __forceinline__ double logml_wave(const LogmlItem& item, int d, const NiwPriorDev& prior, double logdet_psi,
+                                             const long long* __restrict__ counts, const double* __restrict__ moments,
+                                             double* sm, const double* lg_known, bool& ok) {
   constexpr int ED = D + D * (D + 1) / 2;
-  __shared__ double ssum[BLOCK / 64][ED];  // per wave: the item's summed statistics
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int it = logml_item(blockIdx.x * (BLOCK / 64) + wave, n_items, list, list_count, list_base);
-  if (it < 0) return;
+  const int lane = threadIdx.x & 63;
   const int E = d + d * (d + 1) / 2;
-  const LogmlItem item = items[it];
   const bool bound = item.seg[3] == LOGML_BOUND;  // log|Psi / 2 + C| (merge bound)
   const bool live = lane < d;
+  ok = true;
   // every load of the item in one round: its counts, the sum of its segments'
   // statistics (summed in segment order into the wave's LDS buffer) and the
   // prior's row of Psi (entries k <= lane)
@@ -160,7 +146,6 @@ __global__ __launch_bounds__(BLOCK) void k_logml_gauss_wave(int n_items, const L
     const long long c = counts[hq[q] ? item.seg[q] : 0];
     nq[q] = hq[q] ? (double)c : 0.0;
   }
-  double* sm = ssum[wave];
 #pragma unroll
   for (int i = 0; i < (ED + 63) / 64; ++i) {
     const int e = lane + 64 * i, ec = e < E ? e : 0;
@@ -179,10 +164,7 @@ __global__ __launch_bounds__(BLOCK) void k_logml_gauss_wave(int n_items, const L
   double n = 0.0;
 #pragma unroll
   for (int q = 0; q < 4; ++q) n += nq[q];
-  if (n == 0.0) {
-    if (lane == 0) out[it] = 0.0;
-    return;
-  }
+  if (n == 0.0) return 0.0;
   const double kn = prior.kappa + n, nun = prior.nu + n, cm = bound ? 0.0 : prior.kappa * n / kn;
   wave_sync();
   const double si = live ? sm[lane] : 0.0;
@@ -197,17 +179,36 @@ __global__ __launch_bounds__(BLOCK) void k_logml_gauss_wave(int n_items, const L
     r[k] = in ? v : (k == lane ? 1.0 : 0.0);
   }
   double mydiag;
-  const bool ok = wave_cholesky<D>(r, lane, mydiag);
+  ok = wave_cholesky<D>(r, lane, mydiag);
   // log|Psi_n| = 2 sum log L_ii; log Gamma_d(nu_n / 2) - log Gamma_d(nu / 2)
   const double ld = 2.0 * wave_sum(live ? log(mydiag) : 0.0);
-  const double lg = wave_sum(live ? lgamma_d(0.5 * nun - 0.5 * lane) - lgamma_d(0.5 * prior.nu - 0.5 * lane) : 0.0);
+  const double lg = lg_known ? *lg_known
+                             : wave_sum(live ? lgamma_d(0.5 * nun - 0.5 * lane) - lgamma_d(0.5 * prior.nu - 0.5 * lane)
+                                             : 0.0);
+  return bound ? ld
+               : -0.5 * n * d * 1.1447298858494002 + lg + 0.5 * prior.nu * logdet_psi - 0.5 * nun * ld +
+                     0.5 * d * (log(prior.kappa) - log(kn));
+}
+
+template <int D>
+__global__ __launch_bounds__(BLOCK) void k_logml_gauss_wave(int n_items, const LogmlItem* __restrict__ items, int d,
+                                                            NiwPriorDev prior, double logdet_psi,
+                                                            const long long* __restrict__ counts,
+                                                            const double* __restrict__ moments,
+                                                            double* __restrict__ out, int* __restrict__ err) {
+  constexpr int ED = D + D * (D + 1) / 2;
+  __shared__ double ssum[BLOCK / 64][ED];  // per wave: the item's summed statistics
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  const int it = blockIdx.x * (BLOCK / 64) + wave;
+  if (it >= n_items) return;
+  bool ok;
+  const double v = logml_wave<D>(items[it], d, prior, logdet_psi, counts, moments, ssum[wave], nullptr, ok);
   if (lane == 0) {
     if (!ok) atomicOr(err, 4);
-    out[it] = bound ? ld
-                    : -0.5 * n * d * 1.1447298858494002 + lg + 0.5 * prior.nu * logdet_psi - 0.5 * nun * ld +
-                          0.5 * d * (log(prior.kappa) - log(kn));
+    out[it] = v;
   }
 }
+
 // 64 < d <= 128: one workgroup per item, Psi_n held in registers as the
 // 136 lower 8 x 8 tiles of a 128 x 128 matrix (d padded with an identity
 // block, whose pivots are 1), one tile per thread of the first 136.  Blocked
@@ -228,8 +229,6 @@ __global__ __launch_bounds__(CHOL_T) void k_logml_gauss_tile(int n_items, const 
                                                              const long long* __restrict__ counts,
                                                              const double* __restrict__ moments,
                                                              double* __restrict__ out, int* __restrict__ err,
-                                                             const int* __restrict__ list,
-                                                             const int* __restrict__ list_count, int list_base,
                                                              const double* __restrict__ cmom, int K) {
   constexpr int DP = 128, T = 8, NTL = DP / T;
   __shared__ double xbar[DP];
@@ -237,8 +236,8 @@ __global__ __launch_bounds__(CHOL_T) void k_logml_gauss_tile(int n_items, const 
   __shared__ double dg[T][T];                 // dg[c][r] = L[8 jt + r][8 jt + c] of the diagonal tile
   __shared__ double red[CHOL_T / 64];
   __shared__ int bad;
-  const int it = logml_item(blockIdx.x, n_items, list, list_count, list_base);
-  if (it < 0) return;
+  const int it = blockIdx.x;
+  if (it >= n_items) return;
   const int tid = threadIdx.x;
   const int E = d + d * (d + 1) / 2;
   const LogmlItem item = items[it];
@@ -405,39 +404,47 @@ __global__ __launch_bounds__(CHOL_T) void k_logml_gauss_tile(int n_items, const 
   }
 }
 
-// Read-back of one split/merge round in a single buffer (one copy to the
-// host instead of four): [int error flag, padded to 8 bytes][counts, 2K
-// int64][log marginals of the 3K cluster / sub-cluster items, float64][P merge
-// decisions, bytes].
-__global__ void k_pack_readback(int K, int P, const long long* __restrict__ counts, const double* __restrict__ lml,
-                                const unsigned char* __restrict__ mflag, const int* __restrict__ err,
-                                unsigned char* __restrict__ out) {
-  const int i = blockIdx.x * blockDim.x + threadIdx.x;
-  if (i == 0) *reinterpret_cast<long long*>(out) = (long long)*err;
+// Read-back of one split/merge round in a single buffer, pinned host memory that
+// the kernels below write themselves: [int error flag, padded to 8 bytes][counts,
+// 2K int64][log marginals of the 3K cluster / sub-cluster items, float64][P merge
+// decisions, bytes].  The first workgroups of a merge kernel copy all but the
+// decisions (the flag as it stands before this kernel).
+__device__ __forceinline__ void pack_readback(int i, int K, const long long* __restrict__ counts,
+                                              const double* __restrict__ lml, const int* __restrict__ err,
+                                              unsigned char* __restrict__ out) {
   long long* oc = reinterpret_cast<long long*>(out + 8);
   double* ol = reinterpret_cast<double*>(out + 8 + 16 * (size_t)K);
-  unsigned char* om = out + 8 + 40 * (size_t)K;
+  if (i == 0) *reinterpret_cast<long long*>(out) = (long long)*err;
   if (i < 2 * K)
     oc[i] = counts[i];
   else if (i < 5 * K)
     ol[i - 2 * K] = lml[i - 2 * K];
-  else if (i < 5 * K + P)
-    om[i - 5 * K] = mflag[i - 5 * K];
 }
 
-// Merge test of every listed pair (Sec. 4.1 eq. sample_merges; with
-// paper_form = 0 the reciprocal of the split ratio of Sec. 2.3): pair p is the
-// item pairs[p] = (2 k1, 2 k1 + 1, 2 k2, 2 k2 + 1) with union marginal
-// lml_pair[p]; lml_cluster[3 k] is cluster k's marginal.  accept[p] = 1 when
-// log u < log H_merge with u the merge uniform of (k1, k2).
-// log Gamma_d(a) - log Gamma_d(b) = sum_{j < d} lgamma(a - j/2) - lgamma(b - j/2)
-__device__ double lmultigamma_diff(double a, double b, int d) {
-  double s = 0.0;
-  for (int j = 0; j < d; ++j) s += lgamma_d(a - 0.5 * j) - lgamma_d(b - 0.5 * j);
-  return s;
+// log H_merge without the marginals: one lgamma per lane, combined in one order.
+// Returned to every lane of the wave.
+__device__ double merge_gammas_wave(double n1, double n2, double alpha, int paper_form) {
+  const int lane = threadIdx.x & 63;
+  const double arg = lane == 0   ? n1 + n2
+                     : lane == 1 ? n1
+                     : lane == 2 ? n2
+                     : lane == 3 ? alpha
+                     : lane == 4 ? alpha + n1 + n2
+                     : lane == 5 ? 0.5 * alpha + n1
+                     : lane == 6 ? 0.5 * alpha + n2
+                                 : 0.5 * alpha;
+  const double l = lgamma_d(arg);
+  double g = readlane_d(l, 0) - log(alpha) - readlane_d(l, 1) - readlane_d(l, 2);
+  if (paper_form)
+    g += readlane_d(l, 3) - readlane_d(l, 4) + readlane_d(l, 5) + readlane_d(l, 6) - 2.0 * readlane_d(l, 7);
+  return g;
 }
 
-// The merge bound (Gaussian family): for the pair (k1, k2) with union U,
+// Merge tests of the Gaussian pairs for d <= MERGE_BOUND_MAX_D, one wave per pair
+// (Sec. 4.1 eq. sample_merges; with paper_form = 0 the reciprocal of the split
+// ratio of Sec. 2.3): first the merge bound, and for a pair that it leaves the
+// union's log marginal and the test itself, log u < log H_merge with u the merge
+// uniform of (k1, k2).  The bound: for the pair (k1, k2) with union U,
 //   Psi_n(U) >= X + Y + b b^T,  X = Psi/2 + C1, Y = Psi/2 + C2 (scatters about
 //   the clusters' means), b = sqrt(n1 n2 / n) (xbar1 - xbar2);
 //   log|X + Y| >= d log(|X|^(1/d) + |Y|^(1/d)) (Minkowski's determinant inequality),
@@ -445,16 +452,27 @@ __device__ double lmultigamma_diff(double a, double b, int d) {
 // give a lower bound LB on log|Psi_n(U)|, so an upper bound on the NIW
 // marginal of U and on log H_merge.  A pair whose bound (plus a rounding
 // margin) lies below log u is rejected here: exactly the decision its full
-// ratio would give.  Every other pair is listed for its log marginal and
-// k_merge_decide.  logdet_half[k] = log|Psi/2 + C_k|; lam_psi >= lambda_max(Psi).
-__global__ void k_merge_prune(int n_pairs, const LogmlItem* __restrict__ pairs, int d, NiwPriorDev prior,
-                              double logdet_psi, double lam_psi, const long long* __restrict__ counts,
-                              const double* __restrict__ moments, const double* __restrict__ lml_cluster,
-                              const double* __restrict__ logdet_half, double alpha, int paper_form, uint64_t seed,
-                              uint32_t t, unsigned char* __restrict__ accept, int* __restrict__ list,
-                              int* __restrict__ list_count) {
-  const int p = blockIdx.x * blockDim.x + threadIdx.x;
-  if (p >= n_pairs) return;
+// ratio would give.  logdet_half[k] = log|Psi/2 + C_k|; lam_psi >= lambda_max(Psi).
+// Decisions: 0, 1, or 2 when the union's Cholesky failed.  Latency of one wave; a
+// thread per pair and a launch each for the bound, its survivors' marginals, their
+// test and the read-back took 22 us and five gaps at d = 2, K = 6 and 58 us at
+// d = 16, K = 8; this kernel 9 and 16 us.
+template <int D>
+__global__ __launch_bounds__(BLOCK) void k_merge_pairs(int P, const LogmlItem* __restrict__ pairs, int d, int K,
+                                                       NiwPriorDev prior, double logdet_psi, double lam_psi,
+                                                       const long long* __restrict__ counts,
+                                                       const double* __restrict__ moments,
+                                                       const double* __restrict__ lml,
+                                                       const double* __restrict__ logdet_half, double alpha,
+                                                       int paper_form, uint64_t seed, uint32_t t,
+                                                       const int* __restrict__ err, unsigned char* __restrict__ out) {
+  constexpr int ED = D + D * (D + 1) / 2;
+  __shared__ double ssum[BLOCK / 64][ED];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+  for (int i = blockIdx.x * BLOCK + threadIdx.x; i < 5 * K; i += gridDim.x * BLOCK)
+    pack_readback(i, K, counts, lml, err, out);
+  const int p = blockIdx.x * (BLOCK / 64) + wave;
+  if (p >= P) return;
   const LogmlItem it = pairs[p];
   const int k1 = it.seg[0] >> 1, k2 = it.seg[2] >> 1;
   const int E = d + d * (d + 1) / 2;
@@ -465,62 +483,56 @@ __global__ void k_merge_prune(int n_pairs, const LogmlItem* __restrict__ pairs, 
   const double* A1 = A0 + E;
   const double* B0 = moments + (size_t)(2 * k2) * E;
   const double* B1 = B0 + E;
+  const bool live = lane < d;
   // tr C_k = sum_i S_ii - |s|^2 / n_k, and |xbar1 - xbar2|^2
-  double tr1 = 0.0, tr2 = 0.0, ss1 = 0.0, ss2 = 0.0, dx2 = 0.0;
-  for (int i = 0; i < d; ++i) {
-    const int di = d + tri_index(i, i, d);
-    const double s1 = A0[i] + A1[i], s2 = B0[i] + B1[i];
-    tr1 += A0[di] + A1[di];
-    tr2 += B0[di] + B1[di];
-    ss1 += s1 * s1;
-    ss2 += s2 * s2;
-    const double dd = s1 / n1 - s2 / n2;
-    dx2 += dd * dd;
-  }
-  tr1 = fmax(tr1 - ss1 / n1, 0.0);
-  tr2 = fmax(tr2 - ss2 / n2, 0.0);
+  const int li = live ? lane : 0, di = d + tri_index(li, li, d);
+  const double s1 = A0[li] + A1[li], s2 = B0[li] + B1[li];
+  const double dd = s1 / n1 - s2 / n2;
+  const double tr1 = fmax(wave_sum(live ? A0[di] + A1[di] : 0.0) - wave_sum(live ? s1 * s1 : 0.0) / n1, 0.0);
+  const double tr2 = fmax(wave_sum(live ? B0[di] + B1[di] : 0.0) - wave_sum(live ? s2 * s2 : 0.0) / n2, 0.0);
+  const double dx2 = wave_sum(live ? dd * dd : 0.0);
   const double a = logdet_half[k1] / d, c = logdet_half[k2] / d;
   const double lb = d * (fmax(a, c) + log1p(exp(-fabs(a - c)))) + log1p(n1 * n2 / n * dx2 / (lam_psi + tr1 + tr2));
   const double nun = prior.nu + n, kn = prior.kappa + n;
-  const double lmg = lmultigamma_diff(0.5 * nun, 0.5 * prior.nu, d);
+  const double lmg =
+      wave_sum(live ? lgamma_d(0.5 * nun - 0.5 * lane) - lgamma_d(0.5 * prior.nu - 0.5 * lane) : 0.0);
   const double ub_u = -0.5 * n * d * 1.1447298858494002 + lmg + 0.5 * prior.nu * logdet_psi - 0.5 * nun * lb +
                       0.5 * d * (log(prior.kappa) - log(kn));
-  double g = lgamma_d(n) - log(alpha) - lgamma_d(n1) - lgamma_d(n2);
-  if (paper_form)
-    g += lgamma_d(alpha) - lgamma_d(alpha + n) + lgamma_d(0.5 * alpha + n1) + lgamma_d(0.5 * alpha + n2) -
-         2.0 * lgamma_d(0.5 * alpha);
-  const double l1 = lml_cluster[3 * k1], l2 = lml_cluster[3 * k2];
+  const double g = merge_gammas_wave(n1, n2, alpha, paper_form);
+  const double l1 = lml[3 * k1], l2 = lml[3 * k2];
   const double ub = g + ub_u - l1 - l2;
   // float64 rounding of the terms above (and of the Cholesky factorisations behind them)
   const double margin = 1e-9 * (fabs(g) + fabs(lmg) + 0.5 * nun * fabs(lb) + 0.5 * n * d * 1.15 + fabs(l1) + fabs(l2) +
                                 0.5 * prior.nu * fabs(logdet_psi)) + 1e-6;
-  const double u = uniform_d(rng_block(seed, t, merge_entity(k1, k2), TAG_MERGE, 0).x);
-  if (ub + margin < log(u)) {
-    accept[p] = 0;
-  } else {
-    list[atomicAdd(list_count, 1)] = p;  // the order of the list does not matter: one result per pair
+  const double lu = log(uniform_d(rng_block(seed, t, merge_entity(k1, k2), TAG_MERGE, 0).x));
+  unsigned char dec = 0;
+  if (!(ub + margin < lu)) {  // the same for every lane
+    bool ok;
+    const double lp = logml_wave<D>(it, d, prior, logdet_psi, counts, moments, ssum[wave], &lmg, ok);
+    dec = !ok ? 2 : (lu < g + lp - l1 - l2 ? 1 : 0);
   }
+  if (lane == 0) out[8 + 40 * (size_t)K + p] = dec;
 }
 
-__global__ void k_merge_decide(int n_pairs, const LogmlItem* __restrict__ pairs, const long long* __restrict__ counts,
-                               const double* __restrict__ lml_cluster, const double* __restrict__ lml_pair,
-                               double alpha, int paper_form, uint64_t seed, uint32_t t,
-                               unsigned char* __restrict__ accept, const int* __restrict__ list,
-                               const int* __restrict__ list_count) {
-  const int q = blockIdx.x * blockDim.x + threadIdx.x;
-  const int p = list ? (q < *list_count ? list[q] : -1) : (q < n_pairs ? q : -1);
-  if (p < 0) return;
+// The merge test of every pair from the union marginals of a launch before
+// (other families, larger d), and the read-back.
+__global__ void k_merge_decide(int P, const LogmlItem* __restrict__ pairs, int K, const long long* __restrict__ counts,
+                               const double* __restrict__ lml, const double* __restrict__ lml_pair, double alpha,
+                               int paper_form, uint64_t seed, uint32_t t, const int* __restrict__ err,
+                               unsigned char* __restrict__ out) {
+  const int p = blockIdx.x * blockDim.x + threadIdx.x;
+  for (int i = p; i < 5 * K; i += gridDim.x * blockDim.x) pack_readback(i, K, counts, lml, err, out);
+  if (p >= P) return;
   const LogmlItem it = pairs[p];
   const int k1 = it.seg[0] >> 1, k2 = it.seg[2] >> 1;
   const double n1 = (double)(counts[2 * k1] + counts[2 * k1 + 1]);
   const double n2 = (double)(counts[2 * k2] + counts[2 * k2 + 1]);
-  double lh = lgamma_d(n1 + n2) - log(alpha) - lgamma_d(n1) - lgamma_d(n2) + lml_pair[p] - lml_cluster[3 * k1] -
-              lml_cluster[3 * k2];
+  double lh = lgamma_d(n1 + n2) - log(alpha) - lgamma_d(n1) - lgamma_d(n2) + lml_pair[p] - lml[3 * k1] - lml[3 * k2];
   if (paper_form)
     lh += lgamma_d(alpha) - lgamma_d(alpha + n1 + n2) + lgamma_d(0.5 * alpha + n1) + lgamma_d(0.5 * alpha + n2) -
           2.0 * lgamma_d(0.5 * alpha);
   const double u = uniform_d(rng_block(seed, t, merge_entity(k1, k2), TAG_MERGE, 0).x);
-  accept[p] = log(u) < lh ? 1 : 0;
+  out[8 + 40 * (size_t)K + p] = log(u) < lh ? 1 : 0;
 }
 
 // NT threads per item: 1024 for a large vocabulary (the log-Gamma calls of an
@@ -662,13 +674,12 @@ __global__ void k_cluster_scatter(int K, int d, NiwPriorDev prior, const double*
 
 hipError_t launch_logml_gauss(int n_items, const LogmlItem* items, int d, NiwPriorDev prior, double logdet_psi,
                               const long long* counts, const double* moments, double* scratch, double* out,
-                              int* err, hipStream_t s, const int* list, const int* list_count, int list_base,
-                              double* cmom, int K) {
+                              int* err, hipStream_t s, double* cmom, int K) {
   if (n_items == 0) return hipSuccess;
   const dim3 wg((n_items + BLOCK / 64 - 1) / (BLOCK / 64));
 #define DPMM_LOGML_WAVE(DD)                                                                                         \
   hipLaunchKernelGGL(k_logml_gauss_wave<DD>, wg, dim3(BLOCK), 0, s, n_items, items, d, prior, logdet_psi, counts, \
-                     moments, out, err, list, list_count, list_base);                                             \
+                     moments, out, err);                                                                          \
   return hipGetLastError();
   if (d <= 16) {
     DPMM_LOGML_WAVE(16)
@@ -685,24 +696,24 @@ hipError_t launch_logml_gauss(int n_items, const LogmlItem* items, int d, NiwPri
       hipLaunchKernelGGL(k_cluster_scatter, dim3((CMOM_TILE_ENTRIES + 255) / 256, K + 1), dim3(256), 0, s, K, d, prior,
                          moments, cmom);
     hipLaunchKernelGGL(k_logml_gauss_tile, dim3(n_items), dim3(CHOL_T), 0, s, n_items, items, d, prior, logdet_psi,
-                       counts, moments, out, err, list, list_count, list_base, cmom, cmom ? K : 0);
+                       counts, moments, out, err, cmom, cmom ? K : 0);
     return hipGetLastError();
   }
   const size_t lds = d <= LOGML_LDS_MAX_D ? (size_t)d * d * sizeof(double) : 0;
   hipLaunchKernelGGL(k_logml_gauss, dim3(n_items), dim3(BLOCK), lds, s, n_items, items, d, prior, logdet_psi,
-                     counts, moments, scratch, out, err, list, list_count, list_base);
+                     counts, moments, scratch, out, err);
   return hipGetLastError();
 }
 
-hipError_t launch_merge_prune(int n_pairs, const LogmlItem* pairs, int d, NiwPriorDev prior, double logdet_psi,
-                              double lam_psi, const long long* counts, const double* moments, const double* lml_cluster,
+hipError_t launch_merge_pairs(int P, const LogmlItem* pairs, int d, int K, NiwPriorDev prior, double logdet_psi,
+                              double lam_psi, const long long* counts, const double* moments, const double* lml,
                               const double* logdet_half, double alpha, bool paper_form, uint64_t seed, uint32_t t,
-                              unsigned char* accept, int* list, int* list_count, hipStream_t s) {
-  hipError_t e = launch_zero64(list_count, 1, s);
-  if (e != hipSuccess || n_pairs == 0) return e;
-  hipLaunchKernelGGL(k_merge_prune, dim3((n_pairs + 63) / 64), dim3(64), 0, s, n_pairs, pairs, d, prior, logdet_psi,
-                     lam_psi, counts, moments, lml_cluster, logdet_half, alpha, paper_form ? 1 : 0, seed, t, accept,
-                     list, list_count);
+                              const int* err, unsigned char* out, hipStream_t s) {
+  if (d > MERGE_BOUND_MAX_D) return hipErrorInvalidValue;
+  const int waves = BLOCK / 64;
+  hipLaunchKernelGGL(k_merge_pairs<MERGE_BOUND_MAX_D>, dim3((P + waves - 1) / waves), dim3(BLOCK), 0, s, P, pairs, d, K,
+                     prior, logdet_psi, lam_psi, counts, moments, lml, logdet_half, alpha, paper_form ? 1 : 0, seed, t,
+                     err, out);
   return hipGetLastError();
 }
 
@@ -728,23 +739,16 @@ hipError_t launch_logml_pois(int n_items, const LogmlItem* items, int V, const d
   return hipGetLastError();
 }
 
-hipError_t launch_merge_decide(int n_pairs, const LogmlItem* pairs, const long long* counts, const double* lml_cluster,
+hipError_t launch_merge_decide(int P, const LogmlItem* pairs, int K, const long long* counts, const double* lml,
                                const double* lml_pair, double alpha, bool paper_form, uint64_t seed, uint32_t t,
-                               unsigned char* accept, hipStream_t s, const int* list, const int* list_count) {
-  if (n_pairs == 0) return hipSuccess;
-  hipLaunchKernelGGL(k_merge_decide, dim3((n_pairs + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, n_pairs, pairs, counts,
-                     lml_cluster, lml_pair, alpha, paper_form ? 1 : 0, seed, t, accept, list, list_count);
+                               const int* err, unsigned char* out, hipStream_t s) {
+  const int n = P > 5 * K ? P : 5 * K;
+  hipLaunchKernelGGL(k_merge_decide, dim3((n + 63) / 64), dim3(64), 0, s, P, pairs, K, counts, lml, lml_pair, alpha,
+                     paper_form ? 1 : 0, seed, t, err, out);
   return hipGetLastError();
 }
 
 size_t readback_bytes(int K, int P) { return 8 + 40 * (size_t)K + (size_t)P; }
-
-hipError_t launch_pack_readback(int K, int P, const long long* counts, const double* lml, const unsigned char* mflag,
-                                const int* err, unsigned char* out, hipStream_t s) {
-  const int n = 5 * K + P;
-  hipLaunchKernelGGL(k_pack_readback, dim3((n + 255) / 256), dim3(256), 0, s, K, P, counts, lml, mflag, err, out);
-  return hipGetLastError();
-}
 
 hipError_t launch_relabel(long long n, const RelabelEntry* table, int n_entries, uint32_t t, uint64_t seed, int* z,
                           unsigned char* zsub, hipStream_t s) {

@@ -110,6 +110,24 @@ constexpr int REG_VALUES = 72;
 constexpr int REG_L = 256;
 constexpr int REG_G = 512;  // at most two workgroups per CU
 
+// Level LV of the lane tree below on M sums per lane (the first M of v)
+template <int M, int LV, int NV>
+__device__ __forceinline__ void half_tree(double (&v)[NV], int lane, int& first, int& held) {
+  if constexpr (LV < 6) {
+    constexpr int H = (M + 1) / 2;
+    const bool up = (lane >> LV) & 1;
+#pragma unroll
+    for (int j = 0; j < H; ++j) {
+      const double hi = H + j < M ? v[H + j < M ? H + j : 0] : 0.0;
+      const double give = up ? v[j] : hi, keep = up ? hi : v[j];
+      v[j] = keep + __shfl_xor(give, 1 << LV);
+    }
+    first += up ? H : 0;
+    held = up ? max(held - H, 0) : min(held, H);
+    half_tree<H, LV + 1>(v, lane, first, held);
+  }
+}
+
 template <int D>
 __global__ __launch_bounds__(REG_L) void k_stats_regs(const float* __restrict__ x, long long n,
                                                       const int* __restrict__ z,
@@ -174,16 +192,21 @@ __global__ __launch_bounds__(REG_L) void k_stats_regs(const float* __restrict__ 
           for (int f = 0; f < E1; ++f) acc[q][f] += v[f];
     }
   }
-  // the wave's lanes by a fixed xor tree, then its waves in order
+  // the wave's lanes by a fixed xor tree (1, 2, 4, ...), then its waves in order.
+  // At each level a lane keeps half of its sums and adds its partner's copy of
+  // them, so the tree moves about one value per sum instead of six
+  constexpr int NV = SM * E1;
+  double v[NV];
 #pragma unroll
   for (int q = 0; q < SM; ++q)
 #pragma unroll
-    for (int f = 0; f < E1; ++f) {
-      double a = acc[q][f];
+    for (int f = 0; f < E1; ++f) v[q * E1 + f] = acc[q][f];
+  int first = 0, held = NV;  // this lane's v[j] is sum first + j, j < held
+  half_tree<NV, 0>(v, lane, first, held);
+  constexpr int LEFT = (NV + 63) / 64;
 #pragma unroll
-      for (int o = 1; o < 64; o <<= 1) a += __shfl_xor(a, o);
-      if (lane == 0) wsum[wave][q * E1 + f] = a;
-    }
+  for (int j = 0; j < LEFT; ++j)
+    if (j < held) wsum[wave][first + j] = v[j];
   __syncthreads();
   const int NE = nseg * E1;
   for (int e = threadIdx.x; e < NE; e += REG_L) {
@@ -328,8 +351,10 @@ hipError_t launch_stats_gauss(int d, const float* x, long long n, const int* z, 
     return launch_zero64(moments, (size_t)2 * K * E, s);
   }
   if (stats_regs_ok(d, K)) {
-    // at least 16 points per lane before the grid grows (small n: few partial rows)
-    long long gl = (n + (long long)REG_L * 16 - 1) / ((long long)REG_L * 16);
+    // a workgroup per 256 points up to REG_G of them: at small n the pass is the
+    // latency of a lane's points one after the other (N = 1e4, K = 6: 26 us with
+    // 16 points per lane on three workgroups and the whole tree on every lane, 6.6 us so)
+    const long long gl = (n + REG_L - 1) / REG_L;
     const int G = (int)(gl < 1 ? 1 : (gl > REG_G ? REG_G : gl));
     if (d == 1)
       hipLaunchKernelGGL(k_stats_regs<1>, dim3(G), dim3(REG_L), 0, s, x, n, z, zsub, K, part);

@@ -1,0 +1,80 @@
+"""GPU: the short kernels of a small iteration against the FP64 oracle at the
+edges of their ranges: weights drawn by the posterior kernel (K <= 63) and by
+their own, the register statistics of d <= 2 around one workgroup and a full
+grid, the merge tests of one wave per pair up to the bound's last dimension."""
+import numpy as np
+import pytest
+
+from oracle import niw, sampler
+from tests import parity_util as pu
+
+pytestmark = pytest.mark.gpu
+
+
+@pytest.mark.parametrize("d,K", [(1, 1), (2, 63), (2, 64), (17, 63), (33, 64), (64, 5)])
+def test_weights_of_the_posterior_draw(d, K):
+    from paper_2204_08988_amd.sampler import Sampler
+    seed = 11 * d + K
+    g = np.random.Generator(np.random.PCG64(seed))
+    n = 40 * K + 3 * d
+    x = (g.standard_normal((n, d)) * 2).astype(np.float32)
+    z = np.concatenate([np.arange(K), g.integers(0, K, n - K)])
+    zs = g.integers(0, 2, n)
+    zs[z == 0] = 0
+    model = sampler.Model("gaussian", 3.0, niw.NIWPrior(1.0, np.zeros(d), d + 3.0, np.eye(d)), seed=seed)
+    st = sampler.suffstats(model, x, z, zs, K)
+    S = Sampler("gaussian", d, K, 3.0, seed, kappa=1.0, nu=d + 3.0, m=np.zeros(d), psi=np.eye(d))
+    S.set_stats(pu.stats_array(st, "gaussian"))
+    for t in (1, 2):
+        S.sample_params(t)
+        lp, lps, _ = S.get_params()
+        ref = sampler.sample_params(model, st, t)
+        assert np.allclose(lp, ref.log_pi, rtol=1e-10, atol=1e-12)
+        assert np.allclose(lps, ref.log_pisub, rtol=1e-10, atol=1e-12)
+    S.close()
+
+
+@pytest.mark.parametrize("d,K,n", [(1, 12, 1), (1, 1, 255), (2, 6, 256), (2, 6, 257), (2, 3, 131072), (1, 12, 131073),
+                                   (2, 6, 600001)])
+def test_register_statistics(d, K, n):
+    import torch
+
+    from paper_2204_08988_amd.sampler import Sampler
+    from tests.test_gpu_parity import _check_stats
+    g = np.random.Generator(np.random.PCG64(d + n))
+    x = (g.standard_normal((n, d)) * 3 + 1).astype(np.float32)
+    z = g.integers(0, K, n).astype(np.int32)
+    zs = g.integers(0, 2, n).astype(np.uint8)
+    S = Sampler("gaussian", d, K, 2.0, 5, m=np.zeros(d), psi=np.eye(d))
+    S.set_state(K)
+    S.suffstats(torch.from_numpy(x).cuda(), torch.from_numpy(z).cuda(), torch.from_numpy(zs).cuda())
+    _check_stats(S.get_stats(), x, z, zs, K, d)
+    S.close()
+
+
+@pytest.mark.parametrize("d,K,form", [(1, 4, "paper"), (2, 13, "inverse_split"), (16, 9, "paper"), (17, 9, "paper")])
+def test_merge_tests_of_close_and_distant_pairs(d, K, form):
+    import torch
+
+    from paper_2204_08988_amd.sampler import Sampler
+    seed = 3 + d + K
+    g = np.random.Generator(np.random.PCG64(seed))
+    n = 60 * K
+    z = np.arange(n) % K
+    centre = np.where(np.arange(K) % 2 == 0, 0.0, 9.0 * np.arange(K))  # the even clusters coincide
+    x = (g.standard_normal((n, d)) + centre[z][:, None]).astype(np.float32)
+    zs = g.integers(0, 2, n)
+    model = sampler.Model("gaussian", 2.0, niw.NIWPrior(1.0, np.zeros(d), d + 3.0, np.eye(d)), seed=seed, burn_out=0,
+                          merge_form=form)
+    S = Sampler("gaussian", d, 2 * K + 4, 2.0, seed, kappa=1.0, nu=d + 3.0, m=np.zeros(d), psi=np.eye(d), burn_out=0,
+                merge_form=form)
+    xt, zt = torch.from_numpy(x).cuda(), torch.from_numpy(z.astype(np.int32)).cuda()
+    zst = torch.from_numpy(zs.astype(np.uint8)).cuda()
+    S.set_state(K, [3] * K)
+    S.suffstats(xt, zt, zst)
+    info = S.split_merge(xt, 4, zt, zst)
+    st = sampler.State(K, z.astype(np.int64), zs.astype(np.int64), np.full(K, 3))
+    ref, ri = sampler.split_merge(model, st, sampler.suffstats(model, x, st.z, st.zsub, K), 4)
+    assert (info["K"], info["splits"], info["merges"]) == (ref.K, ri.splits, ri.merges) and info["merges"] > 0
+    assert np.array_equal(zt.cpu().numpy(), ref.z) and np.array_equal(zst.cpu().numpy(), ref.zsub)
+    S.close()
