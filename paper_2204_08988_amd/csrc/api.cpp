@@ -809,16 +809,14 @@ dpmm_status label_phase(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t, int
                         long long* per) {
   ctx->labels_gave_stats = false;
   if (ctx->sorted_path()) {
-    // the FP32 matrix-core draw takes 256 rows per workgroup step: blocks of as many fill more CUs at
-    // small n (the other draws are short enough for the longer histogram scan to cost more: d = 16,
-    // N = 4e5, K = 2: 66 us at 512 rows, 76 at 256)
-    sorted_plan(n, ctx->K, ctx->hist_cap, G, per, !ctx->d_whi && ctx->d >= MX_MIN_D ? 256 : 512);
+    // the FP32 kernels take 256 rows per workgroup step, the BF16 ones 512: blocks of as many
+    sorted_plan(n, ctx->K, ctx->hist_cap, G, per, ctx->d_whi ? 512 : 256);
     DPMM_TRY(ensure_perm(ctx, n));
     if (ctx->d_whi) {
       DPMM_HIP(ctx, launch_label_gauss_mfma(ctx->d, ctx->cfg.precision == DPMM_BF16X3, (const float*)x, n, *G, *per,
                                             ctx->d_packed, ctx->d_whi, ctx->d_wlo, ctx->d_wbias, ctx->K,
                                             ctx->cfg.k_max, t, ctx->cfg.seed, z,
-                                            ctx->d_hist, ctx->d_tot, ctx->d_perm, ctx->d_cand, ctx->d_nflag,
+                                            ctx->d_hist, ctx->d_perm, ctx->d_cand, ctx->d_nflag,
                                             ctx->stream, ctx->label_timing ? ctx->ev[7] : nullptr,
                                             ctx->label_timing ? ctx->ev[8] : nullptr, ctx->d_cst),
                "matrix-core label kernel");
@@ -826,7 +824,7 @@ dpmm_status label_phase(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t, int
       return DPMM_OK;
     }
     DPMM_HIP(ctx, launch_label_gauss_z(ctx->d, (const float*)x, n, *G, *per, ctx->d_packed, ctx->K, t, ctx->cfg.seed, z,
-                                       ctx->d_hist, ctx->d_tot, ctx->stream), "label kernel");
+                                       ctx->d_hist, ctx->stream), "label kernel");
     return DPMM_OK;
   }
   hipError_t e =

@@ -112,7 +112,7 @@ hipError_t launch_label_gauss(int d, const float* x, long long n, const float* p
 // and statistics over sorted tiles
 constexpr int SORTED_MIN_D = 5;
 hipError_t launch_label_gauss_z(int d, const float* x, long long n, int G, long long per_block, const float* packed,
-                                int K, uint32_t t, uint64_t seed, int* z, int* hist, int* tot, hipStream_t s);
+                                int K, uint32_t t, uint64_t seed, int* z, int* hist, hipStream_t s);
 // the same draw on the FP32 matrix cores, used from MX_MIN_D up.  The line lies
 // where the two cross: 5e5 points, K = 16, us per launch at d = 16 / 20 / 24 /
 // 26 / 27 / 28: vector ALUs 63 / 75 / 100 / 127 / 139 / 147, matrix cores (a
@@ -120,7 +120,7 @@ hipError_t launch_label_gauss_z(int d, const float* x, long long n, int G, long 
 // 130 / 140 / 138 / 139
 constexpr int MX_MIN_D = 27;
 hipError_t launch_label_gauss_mx(int d, const float* x, long long n, int G, long long per_block, const float* packed,
-                                 int K, uint32_t t, uint64_t seed, int* z, int* hist, int* tot, hipStream_t s);
+                                 int K, uint32_t t, uint64_t seed, int* z, int* hist, hipStream_t s);
 // block_rows: rows per block while n allows at most 2048 blocks (256 or 512)
 hipError_t sorted_plan(long long n, int K, long long hist_cap, int* G, long long* per_block, int block_rows = 512);
 hipError_t launch_sort_by_z(const int* z, long long n, int K, int G, long long per_block, bool have_hist, int* hist,
@@ -186,7 +186,7 @@ hipError_t launch_sub_labels_x3(int d, const float* x, long long n, const int* p
 // slot, -2 in slot 0: all clusters); n_flagged: one device int
 hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, int G, long long per_block,
                                    const float* packed, const void* whi, const void* wlo, const float* wbias, int K,
-                                   int k_max, uint32_t t, uint64_t seed, int* z, int* hist, int* tot, int* flagged,
+                                   int k_max, uint32_t t, uint64_t seed, int* z, int* hist, int* flagged,
                                    int* cand, int* n_flagged, hipStream_t s, hipEvent_t ev_main0 = nullptr,
                                    hipEvent_t ev_main1 = nullptr, float* cst = nullptr);
 hipError_t launch_loglik_gauss(int d, const float* x, long long n, const float* packed, int K, int k_max,

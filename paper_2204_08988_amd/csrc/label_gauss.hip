@@ -87,12 +87,11 @@ __global__ __launch_bounds__(BLOCK) void k_label_gauss(const float* __restrict__
 
 // Cluster draw only, for the cluster-sorted path (d >= 5): block b labels the
 // contiguous points [b per_block, (b + 1) per_block) and writes its histogram
-// of z (hist[b][k]) and adds it to the cluster totals tot[k].
+// of z (hist[b][k]).
 template <int D>
 __global__ __launch_bounds__(BLOCK) void k_label_gauss_z(const float* __restrict__ x, long long n, long long per_block,
                                                          const float* __restrict__ packed, int K, uint32_t t,
-                                                         uint64_t seed, int* __restrict__ z, int* __restrict__ hist,
-                                                         int* __restrict__ tot) {
+                                                         uint64_t seed, int* __restrict__ z, int* __restrict__ hist) {
   extern __shared__ int h[];
   constexpr int S = (4 + D + D * (D + 1) / 2 + 3) & ~3;
   for (int k = threadIdx.x; k < K; k += BLOCK) h[k] = 0;
@@ -114,7 +113,6 @@ __global__ __launch_bounds__(BLOCK) void k_label_gauss_z(const float* __restrict
   __syncthreads();
   for (int k = threadIdx.x; k < K; k += BLOCK) {
     hist[(size_t)blockIdx.x * K + k] = h[k];
-    if (h[k]) atomicAdd(&tot[k], h[k]);
   }
 }
 
@@ -161,16 +159,14 @@ hipError_t launch_label_gauss(int d, const float* x, long long n, const float* p
 }
 
 hipError_t launch_label_gauss_z(int d, const float* x, long long n, int G, long long per_block, const float* packed,
-                                int K, uint32_t t, uint64_t seed, int* z, int* hist, int* tot, hipStream_t s) {
+                                int K, uint32_t t, uint64_t seed, int* z, int* hist, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  hipError_t e = launch_zero64(tot, (size_t)(K + 1) / 2 + 1, s);
-  if (e != hipSuccess) return e;
-  if (d >= MX_MIN_D) return launch_label_gauss_mx(d, x, n, G, per_block, packed, K, t, seed, z, hist, tot, s);
+  if (d >= MX_MIN_D) return launch_label_gauss_mx(d, x, n, G, per_block, packed, K, t, seed, z, hist, s);
   const size_t lh = (size_t)K * sizeof(int);
 #define DPMM_LABELZ_CASE(DD)                                                                                  \
   case DD:                                                                                                    \
     hipLaunchKernelGGL(k_label_gauss_z<DD>, dim3(G), dim3(BLOCK), lh, s, x, n, per_block, packed, K, t, seed, z, \
-                       hist, tot);                                                                            \
+                       hist);                                                                            \
     break;
   switch (d) {
     DPMM_LABELZ_CASE(5)

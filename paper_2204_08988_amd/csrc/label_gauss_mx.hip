@@ -103,14 +103,13 @@ __device__ __forceinline__ void load_chunk(const float* __restrict__ x, long lon
 }
 
 // Block b labels the points [b per_block, (b + 1) per_block), writes its
-// histogram of z and adds it to the totals.  cg: records per LDS buffer; one
+// histogram of z.  cg: records per LDS buffer; one
 // buffer when it holds all K.
 template <int RB>
 __global__ __launch_bounds__(MX_BLOCK, 2) void k_label_gauss_mx(const float* __restrict__ x, long long n, int d,
                                                                 long long per_block, const float* __restrict__ packed,
                                                                 int K, int cg, uint32_t t, uint64_t seed,
-                                                                int* __restrict__ z, int* __restrict__ hist,
-                                                                int* __restrict__ tot) {
+                                                                int* __restrict__ z, int* __restrict__ hist) {
   extern __shared__ __align__(16) float smem[];
   const int S = gauss_rec_stride(d);
   const bool single = cg >= K;
@@ -169,7 +168,6 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_label_gauss_mx(const float* __r
   __syncthreads();
   for (int k = threadIdx.x; k < K; k += MX_BLOCK) {
     hist[(size_t)blockIdx.x * K + k] = h[k];
-    if (h[k]) atomicAdd(&tot[k], h[k]);
   }
 }
 
@@ -247,7 +245,7 @@ constexpr int MX_LDS_MAX = 160 * 1024;
 }  // namespace
 
 hipError_t launch_label_gauss_mx(int d, const float* x, long long n, int G, long long per_block, const float* packed,
-                                 int K, uint32_t t, uint64_t seed, int* z, int* hist, int* tot, hipStream_t s) {
+                                 int K, uint32_t t, uint64_t seed, int* z, int* hist, hipStream_t s) {
   const size_t rec = (size_t)gauss_rec_stride(d) * sizeof(float);
   int cg = K, bufs = 1;
   if (rec * K > MX_LDS_RECORDS) {
@@ -270,7 +268,7 @@ hipError_t launch_label_gauss_mx(int d, const float* x, long long n, int G, long
 #define DPMM_MX_CASE(RB)                                                                                          \
   case RB:                                                                                                        \
     hipLaunchKernelGGL(k_label_gauss_mx<RB>, dim3(G), dim3(MX_BLOCK), lds, s, x, n, d, per_block, packed, K, cg, t, \
-                       seed, z, hist, tot);                                                                       \
+                       seed, z, hist);                                                                       \
     break;
   switch (mx::row_blocks(d)) {
     DPMM_MX_CASE(1)

@@ -162,7 +162,7 @@ __device__ __forceinline__ void finish_main(bool valid, long long p, const Top2U
 // -2 in slot 0 when a cluster above T may be missing, for k_rescore_flagged.
 __device__ __forceinline__ void finish_cands(bool valid, long long r, long long p, const Cands& cd, float rel,
                                              int K, long long per_block, uint32_t t, uint64_t seed, int* z,
-                                             int* hist, int* tot, int* cand) {
+                                             int* hist, int* cand) {
   const float T = cd.threshold();
   const bool complete = !(cd.ev_max > T);
   bool sure = false;
@@ -203,7 +203,6 @@ __device__ __forceinline__ void finish_cands(bool valid, long long r, long long 
     }
   }
   wave_count_add(sure, sure ? (p / per_block) * K + kb : 0, hist);
-  wave_count_add(sure, sure ? kb : 0, tot);
 }
 
 // The split candidate pass's lists of deferred point r (one per cluster group)
@@ -216,7 +215,7 @@ __global__ __launch_bounds__(256) void k_cands_merge(const int* __restrict__ n_f
                                                      const float* __restrict__ cst, float rel, int K,
                                                      long long per_block, uint32_t t, uint64_t seed,
                                                      const int* __restrict__ flagged, int* __restrict__ z,
-                                                     int* __restrict__ hist, int* __restrict__ tot,
+                                                     int* __restrict__ hist,
                                                      int* __restrict__ cand) {
   const long long nf = *n_flagged;
   if (nf > cap) return;
@@ -240,7 +239,7 @@ __global__ __launch_bounds__(256) void k_cands_merge(const int* __restrict__ n_f
           if (kk >= 0) m.push_u(o[g * CAND_STATE + j], o[g * CAND_STATE + NCAND + j], kk);
         }
     }
-    finish_cands(valid, r, valid ? (long long)flagged[r] : 0, m, rel, K, per_block, t, seed, z, hist, tot, cand);
+    finish_cands(valid, r, valid ? (long long)flagged[r] : 0, m, rel, K, per_block, t, seed, z, hist, cand);
   }
 }
 
@@ -259,8 +258,7 @@ __global__ __launch_bounds__(BLOCK32) void k_label_gauss_mfma32(const float* __r
                                                                 long long per_block, const float* __restrict__ packed,
                                                                 const bf16x8* __restrict__ whi,
                                                                 const bf16x8* __restrict__ wlo, int K, uint32_t t,
-                                                                uint64_t seed, int* __restrict__ z, int* __restrict__ hist,
-                                                                int* __restrict__ tot, int* __restrict__ flagged,
+                                                                uint64_t seed, int* __restrict__ z, int* __restrict__ hist, int* __restrict__ flagged,
                                                                 int* __restrict__ cand, int* __restrict__ n_flagged) {
   constexpr int D = 32, KS = 2, NF = KS * 64;  // 16-byte fragments per cluster and table
   constexpr float REL = X3 ? BF16X3_TOL_REL : BF16_TOL_REL;
@@ -381,7 +379,7 @@ __global__ __launch_bounds__(BLOCK32) void k_label_gauss_mfma32(const float* __r
     }
     const long long r = base + lane;
     if (CANDS)
-      finish_cands(r < end, r, r < end ? (long long)flagged[r] : 0, cd, REL, K, per_block, t, seed, z, hist, tot,
+      finish_cands(r < end, r, r < end ? (long long)flagged[r] : 0, cd, REL, K, per_block, t, seed, z, hist,
                    cand);
     else
       finish_main(r < end, r, t2, z, h, flagged, n_flagged, lane);
@@ -390,7 +388,6 @@ __global__ __launch_bounds__(BLOCK32) void k_label_gauss_mfma32(const float* __r
   __syncthreads();
   for (int k = threadIdx.x; k < K; k += BLOCK32) {
     hist[(size_t)blockIdx.x * K + k] = h[k];
-    if (h[k]) atomicAdd(&tot[k], h[k]);
   }
 }
 
@@ -432,7 +429,7 @@ __global__ __launch_bounds__(BLOCK_W32) void k_label_gauss_mfma_w32(const float*
                                                                    const bf16x8* __restrict__ whi,
                                                                    const bf16x8* __restrict__ wlo, int K, uint32_t t,
                                                                    uint64_t seed, int* __restrict__ z,
-                                                                   int* __restrict__ hist, int* __restrict__ tot,
+                                                                   int* __restrict__ hist,
                                                                    int* __restrict__ flagged, int* __restrict__ cand,
                                                                    int* __restrict__ n_flagged, int ng, int cap,
                                                                    float* __restrict__ cst) {
@@ -612,7 +609,7 @@ __global__ __launch_bounds__(BLOCK_W32) void k_label_gauss_mfma_w32(const float*
         o[3 * NCAND + 1] = cd.ev_max;
       }
     } else if (CANDS) {
-      finish_cands(ok && half == 0, r, p, cd, REL, K, per_block, t, seed, z, hist, tot, cand);
+      finish_cands(ok && half == 0, r, p, cd, REL, K, per_block, t, seed, z, hist, cand);
     } else {
       finish_main(ok && half == 0, r, t2, z, h, flagged, n_flagged, lane);
     }
@@ -621,7 +618,6 @@ __global__ __launch_bounds__(BLOCK_W32) void k_label_gauss_mfma_w32(const float*
   __syncthreads();
   for (int k = threadIdx.x; k < K; k += BLOCK_W32) {
     hist[(size_t)blockIdx.x * K + k] = h[k];
-    if (h[k]) atomicAdd(&tot[k], h[k]);
   }
 }
 
@@ -680,8 +676,7 @@ __global__ __launch_bounds__(64 * NWAVE, 8 / NWAVE) void k_label_gauss_mfma_uc(c
                                                                      long long per_block,
                                                                      const bf16x8* __restrict__ whi,
                                                                      const float* __restrict__ wbias, int K, int k_max,
-                                                                     int* __restrict__ z, int* __restrict__ hist,
-                                                                     int* __restrict__ tot, int* __restrict__ flagged,
+                                                                     int* __restrict__ z, int* __restrict__ hist, int* __restrict__ flagged,
                                                                      int* __restrict__ n_flagged) {
   using TT = TriTiles<D>;
   constexpr int MT = TT::MT, KS = TT::KS, NF = MT * KS * 64, NT = TT::NT;
@@ -879,7 +874,6 @@ __global__ __launch_bounds__(64 * NWAVE, 8 / NWAVE) void k_label_gauss_mfma_uc(c
   __syncthreads();
   for (int k = threadIdx.x; k < K; k += BLK) {
     hist[(size_t)blockIdx.x * K + k] = h[k];
-    if (h[k]) atomicAdd(&tot[k], h[k]);
   }
 }
 
@@ -912,7 +906,7 @@ __global__ __launch_bounds__(RS_BLOCK) void k_rescore_flagged(const float* __res
                                                               const int* __restrict__ n_flagged, long long per_block,
                                                               const float* __restrict__ packed, int K, uint32_t t,
                                                               uint64_t seed, int* __restrict__ z,
-                                                              int* __restrict__ hist, int* __restrict__ tot) {
+                                                              int* __restrict__ hist) {
   constexpr int S = (4 + D + D * (D + 1) / 2 + 3) & ~3;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int nf = *n_flagged;
@@ -999,7 +993,6 @@ __global__ __launch_bounds__(RS_BLOCK) void k_rescore_flagged(const float* __res
     const bool drew = valid && !done;
     if (drew) z[p] = win;
     wave_count_add(drew, drew ? (p / per_block) * K + win : 0, hist);
-    wave_count_add(drew, drew ? win : 0, tot);
   }
 }
 
@@ -1389,16 +1382,14 @@ hipError_t launch_pack_wfrag(int K, int d, int k_max, const float* packed, void*
 
 hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, int G, long long per_block,
                                    const float* packed, const void* whi, const void* wlo, const float* wbias, int K,
-                                   int k_max, uint32_t t, uint64_t seed, int* z, int* hist, int* tot, int* flagged,
+                                   int k_max, uint32_t t, uint64_t seed, int* z, int* hist, int* flagged,
                                    int* cand, int* n_flagged, hipStream_t s, hipEvent_t ev_main0,
                                    hipEvent_t ev_main1, float* cst) {
   if (n == 0) return hipSuccess;
-  hipError_t e = launch_zero64(tot, (size_t)(K + 1) / 2 + 1, s);
-  if (e != hipSuccess) return e;
   const size_t lh = (size_t)K * sizeof(int);
   const bf16x8* hi = (const bf16x8*)whi;
   const bf16x8* lo = (const bf16x8*)wlo;
-  e = launch_zero64(n_flagged, 1, s);
+  hipError_t e = launch_zero64(n_flagged, 1, s);
   if (e != hipSuccess) return e;
   static bool attr_set = false;
   if (!attr_set) {  // d = 32 and the uncentred kernels: more than 64 KB of dynamic LDS (160 KB per CU)
@@ -1434,7 +1425,7 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
       const size_t luc = big ? l512 : l256;
 #define DPMM_UC(DD, PP, NWV)                                                                                     \
   hipExtLaunchKernelGGL((k_label_gauss_mfma_uc<DD, PP, NWV>), dim3(Gp), dim3(64 * NWV), luc, s, e0, e1, 0, x, n, \
-                        per_block, hi, wbias, K, k_max, z, hist, tot, flagged, n_flagged)
+                        per_block, hi, wbias, K, k_max, z, hist, flagged, n_flagged)
       if (d == 128) {
         if (big)
           DPMM_UC(128, 512, 8);
@@ -1453,7 +1444,7 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
       // static staging buffers; only the histogram is dynamic
 #define DPMM_MFMA_W32(DD, XX, CC)                                                                            \
   hipExtLaunchKernelGGL((k_label_gauss_mfma_w32<DD, XX, CC>), dim3(Gp), dim3(BLOCK_W32), lh, s, e0, e1, 0, x, n, \
-                        per_block, packed, hi, lo, K, t, seed, z, hist, tot, flagged, cand, n_flagged, 1,        \
+                        per_block, packed, hi, lo, K, t, seed, z, hist, flagged, cand, n_flagged, 1,        \
                         (CC) && cst ? CAND_SPLIT_CAP : 0, nullptr)
       // the candidate pass scores in bf16x3 whatever the main pass's form; while
       // few points are deferred its clusters are split over CAND_SPLIT_NG
@@ -1465,15 +1456,15 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
                                            : Gp);
         if (d == 128)
           hipLaunchKernelGGL((k_label_gauss_mfma_w32<128, true, true>), dim3(gx, CAND_SPLIT_NG), dim3(BLOCK_W32), lh, s,
-                             x, n, per_block, packed, hi, lo, K, t, seed, z, hist, tot, flagged, cand, n_flagged,
+                             x, n, per_block, packed, hi, lo, K, t, seed, z, hist, flagged, cand, n_flagged,
                              CAND_SPLIT_NG, CAND_SPLIT_CAP, cst);
         else
           hipLaunchKernelGGL((k_label_gauss_mfma_w32<64, true, true>), dim3(gx, CAND_SPLIT_NG), dim3(BLOCK_W32), lh, s,
-                             x, n, per_block, packed, hi, lo, K, t, seed, z, hist, tot, flagged, cand, n_flagged,
+                             x, n, per_block, packed, hi, lo, K, t, seed, z, hist, flagged, cand, n_flagged,
                              CAND_SPLIT_NG, CAND_SPLIT_CAP, cst);
         if ((e = hipGetLastError()) != hipSuccess) return e;
         hipLaunchKernelGGL(k_cands_merge, dim3(CAND_SPLIT_CAP / 256), dim3(256), 0, s, n_flagged, CAND_SPLIT_NG,
-                           CAND_SPLIT_CAP, cst, BF16X3_TOL_REL, K, per_block, t, seed, flagged, z, hist, tot, cand);
+                           CAND_SPLIT_CAP, cst, BF16X3_TOL_REL, K, per_block, t, seed, flagged, z, hist, cand);
         if ((e = hipGetLastError()) != hipSuccess) return e;
       }
       if (d == 128) {
@@ -1498,7 +1489,7 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
       const size_t lds = (size_t)65536 + (size_t)(x3 || cands ? 16 : 32) * (d + 4) * sizeof(float) + lh;
 #define DPMM_MFMA32(XX, CC)                                                                                  \
   hipExtLaunchKernelGGL((k_label_gauss_mfma32<XX, CC>), dim3(Gp), dim3(BLOCK32), lds, s, e0, e1, 0, x, n, per_block, \
-                        packed, hi, lo, K, t, seed, z, hist, tot, flagged, cand, n_flagged)
+                        packed, hi, lo, K, t, seed, z, hist, flagged, cand, n_flagged)
       if (cands)
         DPMM_MFMA32(true, true);
       else if (x3)
@@ -1514,7 +1505,7 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
   // the deferred points in FP32 (grid-strided; the count stays on the device)
 #define DPMM_RESCORE(DD)                                                                                 \
   hipLaunchKernelGGL(k_rescore_flagged<DD>, dim3(512), dim3(RS_BLOCK), 0, s, x, flagged, cand, n_flagged, \
-                     per_block, packed, K, t, seed, z, hist, tot)
+                     per_block, packed, K, t, seed, z, hist)
   if (d == 32)
     DPMM_RESCORE(32);
   else if (d == 64)

@@ -58,7 +58,7 @@ __device__ __forceinline__ int block_inclusive_scan(int v, int* buf) { return bl
 }  // namespace
 
 __global__ __launch_bounds__(BLOCK) void k_hist_z(const int* __restrict__ z, long long n, long long per_block, int K,
-                                                  int* __restrict__ hist, int* __restrict__ tot) {
+                                                  int* __restrict__ hist) {
   extern __shared__ int h[];
   for (int k = threadIdx.x; k < K; k += BLOCK) h[k] = 0;
   __syncthreads();
@@ -71,38 +71,33 @@ __global__ __launch_bounds__(BLOCK) void k_hist_z(const int* __restrict__ z, lon
   __syncthreads();
   for (int k = threadIdx.x; k < K; k += BLOCK) {
     hist[(size_t)blockIdx.x * K + k] = h[k];
-    if (h[k]) atomicAdd(&tot[k], h[k]);
   }
 }
 
-// One workgroup per cluster k: offs[b][k] = sum_{k' < k} tot[k'] + sum_{b' < b} hist[b'][k].
+// One workgroup per cluster k: offs[b][k] = sum_{b' < b} hist[b'][k] (0 in row 0)
+// and the total tot[k].  k_scatter_z adds the clusters' starts.  (The blocks of the
+// label kernels and k_hist_z used to add their counts to cleared totals: at N = 1e6,
+// K = 16 two thousand atomics on each of sixteen addresses, 24.8 us of k_hist_z
+// against 3.5 us now, and a launch to clear them.)
+constexpr int SORT_BLOCKS = 2048;  // plan_blocks makes no more
 __global__ __launch_bounds__(BLOCK) void k_scan_hist(const int* __restrict__ hist, int G, int K,
-                                                     const int* __restrict__ tot, int* __restrict__ offs) {
+                                                     int* __restrict__ tot, int* __restrict__ offs) {
+  constexpr int PER = SORT_BLOCKS / BLOCK;
   __shared__ int buf[BLOCK];
-  __shared__ long long base_sh;
-  const int k = blockIdx.x;
-  const int tid = threadIdx.x;
-  long long b0 = 0;
-  for (int q = tid; q < k; q += BLOCK) b0 += tot[q];
-  // reduce b0 over the block
-  buf[tid] = (int)b0;  // cluster totals are below 2^31 (n < 2^31 for this path)
-  __syncthreads();
-  if (tid == 0) {
-    long long s = 0;
-    for (int q = 0; q < BLOCK; ++q) s += buf[q];
-    base_sh = s;
-  }
-  __syncthreads();
-  const int per = (G + BLOCK - 1) / BLOCK;
-  const int g0 = tid * per;
-  int local = 0;
-  for (int g = g0; g < g0 + per && g < G; ++g) local += hist[(size_t)g * K + k];
+  const int k = blockIdx.x, g0 = threadIdx.x * PER;
+  int v[PER], local = 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) v[j] = g0 + j < G ? hist[(size_t)(g0 + j) * K + k] : 0;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) local += v[j];
   const int incl = block_inclusive_scan(local, buf);
-  int run = (int)base_sh + incl - local;
-  for (int g = g0; g < g0 + per && g < G; ++g) {
-    offs[(size_t)g * K + k] = run;
-    run += hist[(size_t)g * K + k];
+  int run = incl - local;
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    if (g0 + j < G) offs[(size_t)(g0 + j) * K + k] = run;
+    run += v[j];
   }
+  if (threadIdx.x == BLOCK - 1) tot[k] = incl;
 }
 
 // Stable scatter: within block b the rows of a cluster keep their index
@@ -114,11 +109,14 @@ __global__ __launch_bounds__(BLOCK) void k_scan_hist(const int* __restrict__ his
 // it then walks its quarter 64 rows at a time.  The lanes holding the same
 // cluster are found with one ballot per bit of the cluster index (the lanes
 // that agree with this lane on every bit); a lane's rank among them is the
-// count of those below it, and the highest of them moves the cursor.
+// count of those below it, and the highest of them moves the cursor.  The
+// clusters' starts are the exclusive sums of tot; block 0 leaves them in row 0 of
+// offs (whose own offsets are 0) for the kernels that follow.
 __global__ __launch_bounds__(BLOCK) void k_scatter_z(const int* __restrict__ z, long long n, long long per_block,
-                                                     int K, const int* __restrict__ offs, int* __restrict__ perm,
-                                                     int* __restrict__ zsort) {
+                                                     int K, const int* __restrict__ tot, int* __restrict__ offs,
+                                                     int* __restrict__ perm, int* __restrict__ zsort) {
   extern __shared__ int cur[];  // [4][K]
+  __shared__ int buf[BLOCK];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   for (int q = threadIdx.x; q < 4 * K; q += BLOCK) cur[q] = 0;
   __syncthreads();
@@ -132,9 +130,19 @@ __global__ __launch_bounds__(BLOCK) void k_scatter_z(const int* __restrict__ z, 
     const int zi = z[i];
     if ((unsigned)zi < (unsigned)K) atomicAdd(&mine[zi], 1);
   }
-  __syncthreads();
-  for (int k = threadIdx.x; k < K; k += BLOCK) {
-    int run = offs[(size_t)blockIdx.x * K + k];
+  // a contiguous share of the clusters per thread
+  const int per = (K + BLOCK - 1) / BLOCK;
+  const int ka = threadIdx.x * per < K ? threadIdx.x * per : K, kb = ka + per < K ? ka + per : K;
+  int local = 0;
+  for (int k = ka; k < kb; ++k) local += tot[k];
+  int start = block_inclusive_scan(local, buf) - local;  // (its barriers complete the counts above)
+  for (int k = ka; k < kb; ++k) {
+    int run = start;
+    if (blockIdx.x == 0)
+      offs[k] = start;
+    else
+      run += offs[(size_t)blockIdx.x * K + k];
+    start += tot[k];
 #pragma unroll
     for (int u = 0; u < 4; ++u) {
       const int c = cur[u * K + k];
@@ -224,7 +232,7 @@ struct SortedPlan {
 
 SortedPlan plan_blocks(long long n, int K, long long hist_cap, int block_rows) {
   long long G = (n + block_rows - 1) / block_rows;
-  if (G > 2048) G = 2048;
+  if (G > SORT_BLOCKS) G = SORT_BLOCKS;
   while (G > 1 && G * K > hist_cap) G = (G + 1) / 2;
   if (G < 1) G = 1;
   long long per = (n + G - 1) / G;
@@ -799,18 +807,23 @@ hipError_t launch_sort_by_z(const int* z, long long n, int K, int G, long long p
                             int* tot, int* offs, int* perm, int* zsort, hipStream_t s) {
   if (n == 0) return hipSuccess;
   hipError_t e;
+  if (G > SORT_BLOCKS) return hipErrorInvalidValue;
   if (!have_hist) {
-    e = launch_zero64(tot, (size_t)(K + 1) / 2 + 1, s);
-    if (e != hipSuccess) return e;
-    hipLaunchKernelGGL(k_hist_z, dim3(G), dim3(BLOCK), (size_t)K * sizeof(int), s, z, n, per_block, K, hist, tot);
+    hipLaunchKernelGGL(k_hist_z, dim3(G), dim3(BLOCK), (size_t)K * sizeof(int), s, z, n, per_block, K, hist);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   hipLaunchKernelGGL(k_scan_hist, dim3(K), dim3(BLOCK), 0, s, hist, G, K, tot, offs);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // per_block is a multiple of BLOCK: each wave's quarter is whole 64-row chunks
   if (per_block % BLOCK != 0 || 4 * (size_t)K * sizeof(int) > 64 * 1024) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_scatter_z, dim3(G), dim3(BLOCK), 4 * (size_t)K * sizeof(int), s, z, n, per_block, K, offs, perm,
-                     zsort);
+  static bool attr_set = false;
+  if (!attr_set) {  // the cursors of 4096 clusters take 64 KB beside the static scan buffer
+    e = hipFuncSetAttribute((const void*)k_scatter_z, hipFuncAttributeMaxDynamicSharedMemorySize, 64 * 1024);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(k_scatter_z, dim3(G), dim3(BLOCK), 4 * (size_t)K * sizeof(int), s, z, n, per_block, K, tot, offs,
+                     perm, zsort);
   return hipGetLastError();
 }
 
