@@ -490,6 +490,8 @@ dpmm_status dpmm_create(const dpmm_config* cfg, void* hip_stream, dpmm_ctx** out
     c->scratch_slots = std::max(3 * km, 256);
     ok = ok && chk(c->alloc(&c->d_scratch, (size_t)c->scratch_slots * NIW_SCRATCH(d)));
     if (d > 64 && d <= 128) ok = ok && chk(c->alloc(&c->d_cmom, ((size_t)km + 1) * CMOM_TILE_ENTRIES));
+    if (cfg->precision == DPMM_FP32 && guess_table_bytes(d, km))
+      ok = ok && chk(c->alloc(&c->d_gtab, guess_table_bytes(d, km)));
     if (cfg->precision != DPMM_FP32) {
       ok = ok && chk(c->alloc(&c->d_whi, (size_t)km * d * d));
       ok = ok && chk(c->alloc(&c->d_nflag, 2));
@@ -812,6 +814,17 @@ dpmm_status label_phase(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t, int
     // the FP32 kernels take 256 rows per workgroup step, the BF16 ones 512: blocks of as many
     sorted_plan(n, ctx->K, ctx->hist_cap, G, per, ctx->d_whi ? 512 : 256);
     DPMM_TRY(ensure_perm(ctx, n));
+    ctx->z_hist = true;
+    if (ctx->d_gtab && label_prune_pays(ctx->d, ctx->K, n)) {
+      DPMM_HIP(ctx, launch_guess(ctx->d, (const float*)x, n, *G, *per, ctx->d_packed, ctx->K, ctx->d_gtab, z,
+                                 ctx->d_hist, ctx->stream), "guess kernel");
+      DPMM_HIP(ctx, launch_sort_by_z(z, n, ctx->K, *G, *per, true, ctx->d_hist, ctx->d_tot, ctx->d_offs, ctx->d_perm,
+                                     ctx->d_zsort, ctx->stream), "sort by guess");
+      DPMM_HIP(ctx, launch_label_sorted(ctx->d, (const float*)x, n, ctx->d_packed, ctx->K, ctx->d_perm, ctx->d_zsort, t,
+                                        ctx->cfg.seed, z, ctx->stream), "label kernel");
+      ctx->z_hist = false;
+      return DPMM_OK;
+    }
     if (ctx->d_whi) {
       DPMM_HIP(ctx, launch_label_gauss_mfma(ctx->d, ctx->cfg.precision == DPMM_BF16X3, (const float*)x, n, *G, *per,
                                             ctx->d_packed, ctx->d_whi, ctx->d_wlo, ctx->d_wbias, ctx->K,
@@ -850,7 +863,7 @@ dpmm_status phase_end(dpmm_ctx* ctx) {
 dpmm_status sub_phase(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t, int32_t* z, uint8_t* zsub, int G,
                       long long per) {
   if (!ctx->sorted_path()) return DPMM_OK;
-  DPMM_TRY(sorted_pass(ctx, x, n, true, true, t, z, zsub, G, per));
+  DPMM_TRY(sorted_pass(ctx, x, n, ctx->z_hist, true, t, z, zsub, G, per));
   ctx->labels_gave_stats = true;
   return DPMM_OK;
 }

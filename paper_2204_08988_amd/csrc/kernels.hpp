@@ -121,6 +121,16 @@ hipError_t launch_label_gauss_z(int d, const float* x, long long n, int G, long 
 constexpr int MX_MIN_D = 27;
 hipError_t launch_label_gauss_mx(int d, const float* x, long long n, int G, long long per_block, const float* packed,
                                  int K, uint32_t t, uint64_t seed, int* z, int* hist, hipStream_t s);
+// the FP32 draw with clusters ruled out by their first rows (label_prune.hip): a
+// guess of every point's cluster into z with its histogram, and the draw over the
+// rows sorted by it.  tab: guess_table_bytes(d, k_max) bytes
+constexpr int PRUNE_MIN_D = 48;
+bool label_prune_pays(int d, int K, long long n);
+size_t guess_table_bytes(int d, int k_max);
+hipError_t launch_guess(int d, const float* x, long long n, int G, long long per_block, const float* packed, int K,
+                        void* tab, int* z, int* hist, hipStream_t s);
+hipError_t launch_label_sorted(int d, const float* x, long long n, const float* packed, int K, const int* perm,
+                               const int* guess, uint32_t t, uint64_t seed, int* z, hipStream_t s);
 // block_rows: rows per block while n allows at most 2048 blocks (256 or 512)
 hipError_t sorted_plan(long long n, int K, long long hist_cap, int* G, long long* per_block, int block_rows = 512);
 hipError_t launch_sort_by_z(const int* z, long long n, int K, int G, long long per_block, bool have_hist, int* hist,

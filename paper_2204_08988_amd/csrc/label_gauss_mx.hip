@@ -32,61 +32,6 @@ using namespace score;
 
 constexpr int MX_BLOCK = 256;
 
-// Lazy Gumbel-max in one pass over the clusters in increasing k.  Clusters
-// within the Gumbel range of the running maximum wait in a queue of four; a new
-// maximum that puts every earlier score out of range empties it.  Only a full
-// queue, and the end, draw Gumbels, so a point with one cluster in range draws
-// none.  The result is the argmax of l_k + g_k over all k, the smaller k on
-// ties: a cluster left out trails the leader by more than the range, or cannot
-// reach the best perturbed score.
-struct StreamDraw {
-  float m1, best, l[4];
-  int win, cnt, k[4];
-  __device__ __forceinline__ void init() {
-    m1 = best = -INFINITY;
-    win = 0;
-    cnt = 0;
-  }
-  __device__ __forceinline__ float floor() const { return m1 - RGAP; }
-  __device__ __forceinline__ void flush(uint32_t i, uint32_t t, uint64_t seed) {
-    int cached = -1;
-    u32x4 blk = {0u, 0u, 0u, 0u};
-#pragma unroll
-    for (int j = 3; j >= 0; --j) {  // entry 0 is the newest: increasing k
-      if (j < cnt && l[j] > floor() && l[j] + GUMBEL_MAX_F >= best) {
-        if ((k[j] >> 2) != cached) {
-          cached = k[j] >> 2;
-          blk = rng_block(seed, t, i, TAG_GUMBEL, (uint32_t)cached);
-        }
-        const float s = l[j] + gumbel_f(word_of(blk, k[j] & 3));
-        if (s > best || (s == best && k[j] < win)) {
-          best = s;
-          win = k[j];
-        }
-      }
-    }
-    cnt = 0;
-  }
-  __device__ __forceinline__ void push(float s, int kk, uint32_t i, uint32_t t, uint64_t seed) {
-    if (s > floor()) {
-      if (m1 <= s - RGAP) {
-        cnt = 0;
-        best = -INFINITY;
-      }
-      l[3] = l[2], l[2] = l[1], l[1] = l[0], l[0] = s;
-      k[3] = k[2], k[2] = k[1], k[1] = k[0], k[0] = kk;
-      ++cnt;
-      m1 = fmaxf(m1, s);
-      if (cnt == 4) flush(i, t, seed);
-    }
-  }
-  __device__ __forceinline__ int finish(uint32_t i, uint32_t t, uint64_t seed) {
-    if (cnt == 1 && best == -INFINITY) return k[0];
-    flush(i, t, seed);
-    return win;
-  }
-};
-
 // the wave's rows [base, base + rows) of x (row 0 read in the place of the others)
 template <int RB>
 __device__ __forceinline__ void load_chunk(const float* __restrict__ x, long long base, int rows, int d,

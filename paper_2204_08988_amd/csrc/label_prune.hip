@@ -1,0 +1,408 @@
+// Gaussian cluster draw in FP32 with clusters ruled out by their first 16
+// whitened coordinates: Sec. 4.1 step (e), eq. sample_labels, for larger d, K, n.
+//
+// A cluster's squared norm q = fma(y_r, y_r, q) only grows with r, also in
+// rounded arithmetic, so the score c - q / 2 of the first rows of W bounds the
+// whole score from above, bit for bit.  A cluster whose bound lies below the
+// leader's score by more than the Gumbel range cannot win, and its other rows
+// need not be formed: for separated clusters 16 of d rows (at d = 128 2.8% of the
+// work) settle all but the point's own cluster.  That needs the leader early, and
+// 64 points of one wave that share it:
+//   k_pack_guess, k_guess   a guess of every point's cluster: the marginal density
+//                 of the first 32 coordinates, in BF16 on the matrix cores.  It only
+//                 orders the work; no result depends on it;
+//   the counting sort of the rows by guess (sorted.hip);
+//   k_label_sorted  per 256 sorted rows: their guessed clusters in full, then every
+//                 cluster's first 16 rows, then in full the clusters still in range
+//                 for some point of the wave.  The draw of the points (score.hpp)
+//                 takes the clusters in that order and gives the argmax of
+//                 l_k + g_k with the smaller k on ties, as in increasing order.
+// Scores have the bits of the kernel that forms them all (label_gauss_mx.hip), so
+// the labels are the same whatever the data.
+//
+// Label step (with sub-labels and statistics), all rows of every cluster -> so, us,
+// means N(0, 9 I): d = 128, N = 1e6, K = 32 6154 -> 1664 (draw 5.5 -> 0.91 ms);
+// d = 128, N = 1e5, K = 64 1589 -> 522; d = 64, N = 5e5, K = 16 629 -> 368; d = 48,
+// N = 1e5, K = 64 348 -> 219.  Where nearly every cluster stays in range of every
+// point (means N(0, 0.01 I)) the two extra passes cost 6 to 9% at d = 128, 13 to 19%
+// at d = 64, 18 to 25% at d = 48.
+#include "kernels.hpp"
+#include "score.hpp"
+#include "score_mx.hpp"
+
+namespace dpmm {
+
+namespace {
+
+using namespace score;
+
+typedef __attribute__((__vector_size__(8 * sizeof(__bf16)))) __bf16 bf16x8;
+typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
+
+constexpr int GD = 32;  // coordinates of the guess
+// one cluster's entry of the guess table: the BF16 fragments of W's first 32 rows
+// ([2 k-steps][64 lanes][8]), the offsets -W (mu - c) in the accumulator layout
+// ([2 lane halves][16]) and the constant
+constexpr int GT_W = 2 * 64 * 8 * 2, GT_B = GD * 4, GT_BYTES = GT_W + GT_B + 16;
+constexpr int GBLOCK = 256;
+
+// The table of every cluster, and after the K entries the common centre c (the
+// mean of the first 64 cluster means: any centre will do, one near the data keeps
+// the rounded rows small).
+__global__ __launch_bounds__(128) void k_pack_guess(int K, int d, const float* __restrict__ packed,
+                                                    unsigned char* __restrict__ tab) {
+  __shared__ float cen[GD];
+  __shared__ float red[128];
+  const int S = gauss_rec_stride(d), k = blockIdx.x, tid = threadIdx.x;
+  if (tid < GD) {
+    const int m = K < 64 ? K : 64;
+    float s = 0.0f;
+    for (int q = 0; q < m; ++q) s += packed[(size_t)q * S + 4 + tid];
+    cen[tid] = s / (float)m;
+    if (k == 0) reinterpret_cast<float*>(tab + (size_t)K * GT_BYTES)[tid] = cen[tid];
+  }
+  __syncthreads();
+  const float* rec = packed + (size_t)k * S;
+  const float* w = rec + 4 + d;
+  unsigned char* out = tab + (size_t)k * GT_BYTES;
+  __bf16* fr = reinterpret_cast<__bf16*>(out);
+  for (int e = tid; e < 1024; e += 128) {
+    const int q = e & 7, lane = (e >> 3) & 63, ks = e >> 9;
+    const int r = lane & 31, c = 16 * ks + 8 * (lane >> 5) + q;
+    fr[e] = (__bf16)(c <= r ? w[r * (r + 1) / 2 + c] : 0.0f);
+  }
+  if (tid < GD) {
+    float b = 0.0f;
+    for (int c = 0; c <= tid; ++c) b = fmaf(w[tid * (tid + 1) / 2 + c], rec[4 + c] - cen[c], b);
+    const int hh = (tid >> 2) & 1, j = ((tid >> 3) << 2) | (tid & 3);
+    reinterpret_cast<float*>(out + GT_W)[hh * 16 + j] = -b;
+  }
+  // log|W| of the rows left out
+  float s = 0.0f;
+  for (int r = GD + tid; r < d; r += 128) s += logf(fabsf(w[r * (r + 1) / 2 + r]));
+  red[tid] = s;
+  __syncthreads();
+  if (tid == 0) {
+    for (int q = 1; q < 128; ++q) s += red[q];
+    reinterpret_cast<float*>(out + GT_W + GT_B)[0] = rec[0] - s;
+  }
+}
+
+// Block b guesses the points [b per_block, (b + 1) per_block) and writes its
+// histogram.  A wave takes 64 points (two 32-point tiles, rounded once), the
+// tables come through LDS (all of them once, or groups in two buffers).  Bound by
+// the matrix cores: 4 instructions per 64 points and cluster, 45 vector ones
+// beside them.
+__global__ __launch_bounds__(GBLOCK, 2) void k_guess(const float* __restrict__ x, long long n, int d,
+                                                     long long per_block, const unsigned char* __restrict__ tab, int K,
+                                                     int cg, int* __restrict__ z, int* __restrict__ hist) {
+  typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  extern __shared__ __align__(16) unsigned char smem_g[];
+  const bool single = cg >= K;
+  unsigned char* buf0 = smem_g;
+  unsigned char* buf1 = single ? smem_g : smem_g + cg * GT_BYTES;
+  int* h = reinterpret_cast<int*>(smem_g + (single ? 1 : 2) * cg * GT_BYTES);
+  for (int k = threadIdx.x; k < K; k += GBLOCK) h[k] = 0;
+  const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long long begin = (long long)blockIdx.x * per_block;
+  const long long end = begin + per_block < n ? begin + per_block : n;
+  auto fetch = [&](unsigned char* dst, int k0, int nk) {
+    mx::stage<GBLOCK>(reinterpret_cast<float*>(dst), reinterpret_cast<const float*>(tab + (size_t)k0 * GT_BYTES),
+                      nk * (GT_BYTES / 4));
+  };
+  float cen[2][8];
+  {
+    const float* c = reinterpret_cast<const float*>(tab + (size_t)K * GT_BYTES);
+#pragma unroll
+    for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+      for (int q = 0; q < 8; ++q) cen[ks][q] = c[16 * ks + 8 * half + q];
+  }
+  if (begin < end) fetch(buf0, 0, cg < K ? cg : K);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  bool odd = false;
+  for (long long chunk = begin; chunk < end; chunk += GBLOCK) {
+    const long long base = chunk + wave * 64;
+    bf16x8 b[2][2];  // [tile][k-step]
+#pragma unroll
+    for (int t = 0; t < 2; ++t) {
+      const long long p = base + 32 * t + col;
+      const bool ok = p < end;
+      const float* xr = x + (ok ? (size_t)p * d : 0) + 8 * half;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const f32x4u u = *reinterpret_cast<const f32x4u*>(xr + 16 * ks);
+        const f32x4u v = *reinterpret_cast<const f32x4u*>(xr + 16 * ks + 4);
+        const float f[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int q = 0; q < 8; ++q) b[t][ks][q] = (__bf16)(f[q] - cen[ks][q]);
+      }
+    }
+    float best = -INFINITY;
+    int arg = 0;
+    for (int g0 = 0; g0 < K; g0 += cg) {
+      const int nk = K - g0 < cg ? K - g0 : cg;
+      if (!single) {
+        const bool wrap = g0 + cg >= K;
+        const int gn = wrap ? 0 : g0 + cg;
+        if (!wrap || chunk + GBLOCK < end) fetch(odd ? buf0 : buf1, gn, K - gn < cg ? K - gn : cg);
+      }
+      typedef __attribute__((address_space(3))) const unsigned char lds_uchar;
+      typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
+      typedef __attribute__((address_space(3))) const f32x4 lds_f32x4;
+      lds_uchar* e = (lds_uchar*)(odd ? buf1 : buf0);
+#pragma unroll 2
+      for (int c = 0; c < nk; ++c, e += GT_BYTES) {
+        const bf16x8 a0 = ((lds_bf16x8*)e)[lane], a1 = ((lds_bf16x8*)e)[64 + lane];
+        f32x16 acc[2];
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 u = ((lds_f32x4*)(e + GT_W))[4 * half + q];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) acc[0][4 * q + j] = acc[1][4 * q + j] = u[j];
+        }
+        const float cst = *(mx::lds_cfloat*)(e + GT_W + GT_B);
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b[t][0], acc[t], 0, 0, 0);
+          acc[t] = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b[t][1], acc[t], 0, 0, 0);
+        }
+        float qs[2];
+#pragma unroll
+        for (int t = 0; t < 2; ++t) {
+          float q0 = 0.0f, q1 = 0.0f;
+#pragma unroll
+          for (int r = 0; r < 16; r += 2) {
+            q0 = fmaf(acc[t][r], acc[t][r], q0);
+            q1 = fmaf(acc[t][r + 1], acc[t][r + 1], q1);
+          }
+          qs[t] = q0 + q1;
+        }
+        // the lane's own point: tile 0 on the lower half, tile 1 on the upper
+        const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(qs[0]), __float_as_uint(qs[1]), false, false);
+        const float l = fmaf(-0.5f, __uint_as_float(sw[0]) + __uint_as_float(sw[1]), cst);
+        arg = l > best ? g0 + c : arg;
+        best = fmaxf(best, l);
+      }
+      if (!single) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        odd = !odd;
+      }
+    }
+    if (base + lane < end) {
+      z[base + lane] = arg;
+      atomicAdd(&h[arg], 1);
+    }
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < K; k += GBLOCK) hist[(size_t)blockIdx.x * K + k] = h[k];
+}
+
+constexpr int SBLOCK = 256;
+constexpr int HEAD = 16;                                    // rows of W in a head
+constexpr int HEAD_S = (4 + HEAD + HEAD * (HEAD + 1) / 2 + 3) & ~3;  // its record, as one of dimension 16
+constexpr int HEAD_GROUP = 64;
+
+// The draw of the rows sorted by guess, 256 per workgroup step.  LDS: one whole
+// record, the heads of up to hg clusters (constant, first 16 means, first 16 rows
+// of W), and per wave the clusters done and those still in range.  Bound by the
+// FP32 matrix cores and the vector ALUs: per 64 points about 0.8 k cycles per
+// cluster for the heads and a whole evaluation (26 k at d = 128) for the few left.
+template <int RB>
+__global__ __launch_bounds__(SBLOCK, 2) void k_label_sorted(const float* __restrict__ x, long long n, int d,
+                                                            const float* __restrict__ packed, int K, int hg,
+                                                            const int* __restrict__ perm,
+                                                            const int* __restrict__ guess, uint32_t t, uint64_t seed,
+                                                            int* __restrict__ z) {
+  extern __shared__ __align__(16) float smem_s[];
+  __shared__ int s_k[SBLOCK];
+  const int S = gauss_rec_stride(d), NW = (K + 31) >> 5;
+  float* s_rec = smem_s;                                // a whole record
+  float* s_head = smem_s + S + mx::REC_PAD;             // [hg] heads
+  uint32_t* need = reinterpret_cast<uint32_t*>(s_head + hg * HEAD_S + mx::REC_PAD);  // [4][NW]
+  uint32_t* done = need + 4 * NW;
+  const int lane = threadIdx.x & 63, c16 = lane & 15;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  uint32_t* my_need = need + wave * NW;
+  uint32_t* my_done = done + wave * NW;
+  mx::lds_cfloat* rec = (mx::lds_cfloat*)s_rec;
+  for (long long chunk = (long long)blockIdx.x * SBLOCK; chunk < n; chunk += (long long)gridDim.x * SBLOCK) {
+    const long long mine = chunk + threadIdx.x;
+    const int i = mine < n ? perm[mine] : 0;
+    const int k = mine < n ? guess[mine] : 0x7fffffff;
+    float xv[4][4 * RB];
+    const float* xr[4];
+    bool ok[4];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const int r = __shfl(i, 16 * q + c16);
+      ok[q] = chunk + wave * 64 + 16 * q + c16 < n;
+      xr[q] = x + (size_t)r * d;
+    }
+    mx::load_rows<RB>(xr, ok, d, xv);
+    __syncthreads();  // the previous rows' tables are read
+    s_k[threadIdx.x] = k;
+    for (int w = threadIdx.x; w < 8 * NW; w += SBLOCK) need[w] = 0u;
+    __syncthreads();
+    StreamDraw dr;
+    dr.init();
+    auto whole = [&](int kk) __attribute__((always_inline)) {
+      float q;
+      const float cst = rec[0], fl = dr.floor();
+      const bool full = mx::sq_norm<RB>(rec, d, xv, q, [&](float qp) {
+        return __ballot(mine < n && fmaf(-0.5f, qp, cst) > fl) != 0ull;
+      });
+      if (full) dr.push(fmaf(-0.5f, q, cst), kk, (uint32_t)i, t, seed);
+    };
+    auto fetch = [&](int kk) __attribute__((always_inline)) {
+      __syncthreads();  // every wave is done with the previous record
+      mx::stage<SBLOCK>(s_rec, packed + (size_t)kk * S, S);
+      __builtin_amdgcn_s_waitcnt(0);
+      __syncthreads();
+    };
+    // (1) the guessed clusters of the step's rows, then (3) those still in range:
+    // one loop, so that the whole evaluation is instantiated once
+    int w3 = -1;          // -1: phase (1); else the word of `need` being walked
+    uint32_t bits = 0u;   // its clusters left (every wave's together)
+    int cur = __builtin_amdgcn_readfirstlane(s_k[0]);
+    for (;;) {
+      bool eval;
+      if (w3 < 0) {
+        eval = __ballot(k == cur) != 0ull;
+        if (eval && lane == 0) my_done[cur >> 5] |= 1u << (cur & 31);
+      } else {
+        eval = (__builtin_amdgcn_readfirstlane(my_need[cur >> 5] & ~my_done[cur >> 5]) >> (cur & 31)) & 1u;
+      }
+      fetch(cur);
+      if (eval) whole(cur);
+      if (w3 < 0) {
+        // the next guessed cluster: the smallest above cur (every wave finds the same)
+        int nx = 0x7fffffff;
+#pragma unroll
+        for (int q = 0; q < SBLOCK; q += 64) {
+          const int v = s_k[q + lane];
+          nx = v > cur && v < nx ? v : nx;
+        }
+#pragma unroll
+        for (int o = 32; o > 0; o >>= 1) nx = min(nx, __shfl_xor(nx, o));
+        if (nx != 0x7fffffff) {
+          cur = __builtin_amdgcn_readfirstlane(nx);
+          continue;
+        }
+        // (2) the heads of all clusters
+        float xh[4][4];
+#pragma unroll
+        for (int q = 0; q < 4; ++q)
+#pragma unroll
+          for (int s = 0; s < 4; ++s) xh[q][s] = xv[q][s];
+        const float fl = dr.floor();
+        for (int g0 = 0; g0 < K; g0 += hg) {
+          const int nk = K - g0 < hg ? K - g0 : hg;
+          __syncthreads();  // the previous group is read
+          for (int e0 = 0; e0 < nk * HEAD_S; e0 += SBLOCK) {
+            const int e = e0 + threadIdx.x, q = e / HEAD_S, f = e - q * HEAD_S;
+            if (q < nk && (f == 0 || (f >= 4 && f < 4 + HEAD + HEAD * (HEAD + 1) / 2)))
+              __builtin_amdgcn_global_load_lds(
+                  (const void*)(packed + (size_t)(g0 + q) * S + (f < 4 + HEAD ? f : f - HEAD + d)),
+                  (mx::lds_void*)(s_head + (e & ~63)), 4, 0, 0);
+          }
+          __builtin_amdgcn_s_waitcnt(0);
+          __syncthreads();
+          mx::lds_cfloat* hp = (mx::lds_cfloat*)s_head;
+          for (int c = 0; c < nk; ++c, hp += HEAD_S) {
+            float q;
+            mx::sq_norm<1>(hp, HEAD, xh, q, mx::Always());
+            if (__ballot(mine < n && fmaf(-0.5f, q, hp[0]) > fl) != 0ull && lane == 0)
+              my_need[(g0 + c) >> 5] |= 1u << ((g0 + c) & 31);
+          }
+        }
+        __syncthreads();  // every wave's clusters are marked
+        w3 = 0;
+        bits = 0u;
+        cur = -1;
+      }
+      // the next cluster in range for some wave that has not had it
+      while (bits == 0u && w3 <= NW - 1) {
+        const int w = w3++;
+        bits = __builtin_amdgcn_readfirstlane((need[w] & ~done[w]) | (need[NW + w] & ~done[NW + w]) |
+                                              (need[2 * NW + w] & ~done[2 * NW + w]) |
+                                              (need[3 * NW + w] & ~done[3 * NW + w]));
+      }
+      if (bits == 0u) break;
+      const int bit = __builtin_ctz(bits);
+      bits &= bits - 1;
+      cur = 32 * (w3 - 1) + bit;
+    }
+    if (mine < n) z[i] = dr.finish((uint32_t)i, t, seed);
+  }
+}
+
+}  // namespace
+
+size_t guess_table_bytes(int d, int k_max) { return d >= PRUNE_MIN_D ? (size_t)k_max * GT_BYTES + GD * 4 : 0; }
+
+// From the same comparison, us without and with, means N(0, 9 I): d = 40, N = 3e4,
+// K = 16 86 and 89; d = 48, N = 3e4, K = 16 89 and 89, N = 8000, K = 32 133 and 119;
+// N = 65536, K = 4: d = 64 97 and 111, d = 128 229 and 229.
+bool label_prune_pays(int d, int K, long long n) {
+  return d >= PRUNE_MIN_D && K >= (d >= 96 ? 8 : 12) && n * K >= 250000;
+}
+
+hipError_t launch_guess(int d, const float* x, long long n, int G, long long per_block, const float* packed, int K,
+                        void* tab, int* z, int* hist, hipStream_t s) {
+  hipLaunchKernelGGL(k_pack_guess, dim3(K), dim3(128), 0, s, K, d, packed, (unsigned char*)tab);
+  const int cg = K <= 32 ? K : 16;
+  const size_t lds = (size_t)(K <= 32 ? 1 : 2) * cg * GT_BYTES + (size_t)K * sizeof(int);
+  static bool attr_set = false;
+  if (!attr_set) {
+    const hipError_t e = hipFuncSetAttribute((const void*)k_guess, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+    if (e != hipSuccess) return e;
+    attr_set = true;
+  }
+  hipLaunchKernelGGL(k_guess, dim3(G), dim3(GBLOCK), lds, s, x, n, d, per_block, (const unsigned char*)tab, K, cg, z,
+                     hist);
+  return hipGetLastError();
+}
+
+hipError_t launch_label_sorted(int d, const float* x, long long n, const float* packed, int K, const int* perm,
+                               const int* guess, uint32_t t, uint64_t seed, int* z, hipStream_t s) {
+  if (n == 0) return hipSuccess;
+  const int hg = K < HEAD_GROUP ? K : HEAD_GROUP;
+  const size_t lds = (size_t)(gauss_rec_stride(d) + hg * HEAD_S + 2 * mx::REC_PAD) * sizeof(float) +
+                     (size_t)8 * ((K + 31) / 32) * sizeof(uint32_t);
+  static bool attr_set = false;
+  if (!attr_set) {
+    const void* fns[6] = {(const void*)k_label_sorted<3>, (const void*)k_label_sorted<4>,
+                          (const void*)k_label_sorted<5>, (const void*)k_label_sorted<6>,
+                          (const void*)k_label_sorted<7>, (const void*)k_label_sorted<8>};
+    for (const void* f : fns) {
+      const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
+      if (e != hipSuccess) return e;
+    }
+    attr_set = true;
+  }
+  const unsigned G = (unsigned)((n + SBLOCK - 1) / SBLOCK < 65536 ? (n + SBLOCK - 1) / SBLOCK : 65536);
+#define DPMM_SORTED_CASE(RB)                                                                                         \
+  case RB:                                                                                                           \
+    hipLaunchKernelGGL(k_label_sorted<RB>, dim3(G), dim3(SBLOCK), lds, s, x, n, d, packed, K, hg, perm, guess, t, seed, \
+                       z);                                                                                           \
+    break;
+  switch (mx::row_blocks(d)) {
+    DPMM_SORTED_CASE(3)
+    DPMM_SORTED_CASE(4)
+    DPMM_SORTED_CASE(5)
+    DPMM_SORTED_CASE(6)
+    DPMM_SORTED_CASE(7)
+    DPMM_SORTED_CASE(8)
+    default:
+      return hipErrorInvalidValue;
+  }
+#undef DPMM_SORTED_CASE
+  return hipGetLastError();
+}
+
+}  // namespace dpmm

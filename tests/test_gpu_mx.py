@@ -62,3 +62,34 @@ def test_stats_of_any_dimension(d, K, n):
     S.suffstats(torch.from_numpy(x).cuda(), torch.from_numpy(z).cuda(), torch.from_numpy(zs).cuda())
     _check_stats(S.get_stats(), x, z, zs, K, d)
     S.close()
+
+
+# the draw over rows sorted by a guessed cluster (48 <= d, several clusters, n K >= 250 000), with ragged last
+# steps, a word boundary of the clusters' bit sets (K = 33) and several groups of heads (K = 130); clusters apart
+# (most ruled out by their first rows) and overlapping (none)
+@pytest.mark.parametrize("d,K,n,spread", [(48, 64, 3907, 4.0), (49, 130, 2003, 0.2), (64, 20, 12545, 0.2),
+                                          (100, 12, 20999, 4.0), (113, 33, 7600, 0.5), (128, 9, 27801, 4.0)])
+def test_fp32_draw_by_guess(d, K, n, spread):
+    import torch
+
+    from paper_2204_08988_amd.sampler import Sampler
+    seed = 70 + d + K
+    params = pu.random_gauss_params(K, d, seed, spread=spread)
+    x = pu.gauss_points(params, n, seed + 1)
+    x[5] *= 100.0  # far from every cluster
+    S = Sampler("gaussian", d, K + 2, 2.0, seed, kappa=1.0, nu=d + 3.0, m=np.zeros(d), psi=np.eye(d))
+    S.set_params(params.log_pi, params.log_pisub, pu.comp_array(params))
+    xt = torch.from_numpy(x).cuda()
+    z, zs = S.sample_labels(xt, 3)
+    st = S.get_stats()
+    zn, zsn = z.cpu().numpy(), zs.cpu().numpy()
+    assert st[..., 0].sum() == n and np.array_equal(st[..., 0], np.bincount(2 * zn + zsn, minlength=2 * K).reshape(K, 2))
+    rows = np.unique(np.concatenate([np.arange(0, n, 7), np.arange(n - 70, n), [5]]))
+    model = sampler.Model("gaussian", 2.0, niw.NIWPrior(1.0, np.zeros(d), d + 3, np.eye(d)), seed=seed)
+    xs = x[rows]
+    lc, ls = sampler.loglik(model, xs.astype(np.float64), params)
+    Mc, Ms = pu.gauss_scale(xs, params)
+    bad_c, bad_s, tie_c, tie_s = pu.label_mismatches(seed, 3, zn[rows], zsn[rows], lc, ls, Mc, Ms, points=rows)
+    assert bad_c.size == 0 and bad_s.size == 0, (bad_c[:10], bad_s[:10])
+    assert tie_c <= max(2, n // 1000) and tie_s <= max(2, n // 1000)
+    S.close()
