@@ -934,7 +934,7 @@ __global__ __launch_bounds__(RS_BLOCK) void k_rescore_flagged(const float* __res
     int pos = 0;                  // next candidate slot (list lanes)
     int nxt_all = all ? 0 : K;    // next cluster (all-K lanes)
     float best = -INFINITY;
-    int win = -1, cached = -1;
+    int win = 0, cached = -1;  // a point that no cluster scores (NaN, all -inf) takes 0, as in the FP32 draw
     u32x4 blk = {0u, 0u, 0u, 0u};
     for (;;) {
       int mine_k = INT_MAX;

@@ -93,3 +93,26 @@ def test_fp32_draw_by_guess(d, K, n, spread):
     assert bad_c.size == 0 and bad_s.size == 0, (bad_c[:10], bad_s[:10])
     assert tie_c <= max(2, n // 1000) and tie_s <= max(2, n // 1000)
     S.close()
+
+
+# rows with a NaN, an infinity or values whose squares overflow, the first row among them: every row is drawn, and
+# as the FP32 context draws it
+@pytest.mark.parametrize("d,K,n", [(64, 4, 700), (64, 20, 12545), (128, 5, 513), (128, 9, 27801)])
+def test_bf16_draw_of_rows_without_a_score(d, K, n):
+    import torch
+
+    from paper_2204_08988_amd.sampler import Sampler
+    params = pu.random_gauss_params(K, d, 7 + d, spread=3.0)
+    x = pu.gauss_points(params, n, 8 + d)
+    x[::97, 3] = np.nan
+    x[5::101, 7] = np.inf
+    x[7::103] *= 1e30
+    xt = torch.from_numpy(x).cuda()
+    z = {}
+    for prec in ("fp32", "bf16"):
+        S = Sampler("gaussian", d, K + 2, 2.0, 11, kappa=1.0, nu=d + 3.0, m=np.zeros(d), psi=np.eye(d), precision=prec)
+        S.set_params(params.log_pi, params.log_pisub, pu.comp_array(params))
+        z[prec] = S.sample_labels(xt, 1)[0].cpu().numpy()
+        S.close()
+    assert z["bf16"].min() >= 0 and z["bf16"].max() < K
+    assert np.array_equal(z["fp32"], z["bf16"])
