@@ -16,12 +16,17 @@ sub-clusters settle and every timed step is a full iteration.
 
 Prints one JSON line: `value` = point-cluster evaluations per second over the
 whole step (N (K + 2) scores per iteration), iterations per second, the
-roofline of the dominant kernel (the d = 128 BF16 cluster draw, timed by HIP
-events around its own dispatch on the sampler's stream), the other
+roofline of the cluster draw, the other
 configurations (gauss_d32, mult_v100, the d = 2 label step at N = 1e8, the
 d = 2 chain at N = 1e4, the sparse-row multinomial of the 20newsgroups shape:
 its chain at N = 11 314 and its label step at N = 2e5) as extra keys, and the FP64 oracle's label step on a
 bounded sample on the host cores (all cores and one core).
+
+An evaluation counts when the draw has accounted for that cluster and point: the
+labels are those of the full FP32 scores, but at this size the draw forms only
+the first 32 of d whitened coordinates of every pair (BF16, as a bound) and all d
+of the point's best cluster and of the clusters that the bound leaves open.
+iters_per_s does not depend on that count.
 
 Other modes: --label-step WORKLOAD (label step at a workload's generating
 mixture), --learned-ab (time to the log-posterior plateau, learned proposal
@@ -47,13 +52,7 @@ PEAK_BF16_MFMA = 2.5e15    # dense BF16 matrix-core peak
 PEAK_FP32_MFMA = 157.3e12  # dense FP32 matrix-core peak
 PEAK_FP64_MFMA = 78.6e12   # dense FP64 matrix-core peak
 HEADLINE = "gauss_d128"
-HEADLINE_KERNEL = "k_label_gauss_mfma_uc<128, 512, 8>"
-# HBM bytes per launch of the headline kernel at the headline workload (N = 1e7,
-# d = 128, K = 100) from rocprofv3 FETCH_SIZE x 2.0 + WRITE_SIZE x 1.0 (KiB), the
-# factors being what a 1 GiB device copy reads on the same counters (FETCH_SIZE
-# 0.5 GiB, WRITE_SIZE 1 GiB); empty whenever the kernel changes until the
-# counters are taken again
-MEASURED_TRAFFIC = {HEADLINE_KERNEL: (2.5282e6 * 2.0 + 7.5822e4) * 1024}
+HEADLINE_DRAW = "k_guess, counting sort, k_label_sorted, k_label_gauss_mfma_uc<128, 512, 8, true>"
 
 
 def flops_per_eval(d):
@@ -125,15 +124,24 @@ def converged_chain(torch, name, n, precision, steps, warmup, seed=SEED):
 
 
 def mfma_roofline(rec, d, kernel):
-    """The BF16 cluster draw: algorithmic flops N K (d(d+1) + 2d) per launch
-    over the launch's own duration."""
+    """The BF16 cluster draw that scores every pair in full: algorithmic flops
+    N K (d(d+1) + 2d) per launch over the launch's own duration."""
     flops = rec["n"] * rec["k_mean"] * flops_per_eval(d)
     s = rec["label_kernel_ms"] / 1e3
     return {"bound": "mfma", "achieved": flops / s / 1e12, "peak": PEAK_BF16_MFMA / 1e12, "unit": "TFLOP/s",
-            "frac": flops / s / PEAK_BF16_MFMA, "traffic": MEASURED_TRAFFIC.get(kernel), "traffic_unit": "bytes per launch",
-            "algorithmic_bytes_per_launch": rec["n"] * (4 * d + 4), "kernel": kernel,
+            "frac": flops / s / PEAK_BF16_MFMA, "algorithmic_bytes_per_launch": rec["n"] * (4 * d + 4), "kernel": kernel,
             "kernel_ms": rec["label_kernel_ms"], "algorithmic_flops_per_eval": flops_per_eval(d),
             "evals_per_launch": rec["n"] * rec["k_mean"]}
+
+
+def draw_roofline(rec, d):
+    """The BF16 cluster draw by a guess: the bytes it cannot do without (the rows
+    once, the labels) over the time of all its kernels."""
+    s = rec["phase_ms"]["labels"] / 1e3
+    by = rec["n"] * (4 * d + 4)
+    return {"bound": "hbm", "achieved": by / s / 1e9, "peak": PEAK_HBM / 1e9, "unit": "GB/s", "frac": by / s / PEAK_HBM,
+            "kernel": HEADLINE_DRAW, "kernel_ms": rec["phase_ms"]["labels"], "algorithmic_bytes_per_launch": by,
+            "flops_per_eval_in_full": flops_per_eval(d), "evals_per_launch": rec["n"] * rec["k_mean"]}
 
 
 def label_step_run(torch, name, n, precision, steps, warmup, thirds=False):
@@ -327,7 +335,6 @@ def headline(args):
     assert torch.cuda.is_available(), "bench.py needs a GPU"
     rec = converged_chain(torch, HEADLINE, None, args.precision, args.steps, args.warmup)
     d = rec["d"]
-    kernel = HEADLINE_KERNEL if args.precision == "bf16" else f"cluster draw ({args.precision})"
     out = {
         "metric": "point-cluster evals/s in label step; iters/s; time-to-plateau learned vs plain",
         "value": rec["value"],
@@ -351,7 +358,8 @@ def headline(args):
         "label_kernel_ms": rec["label_kernel_ms"],
         "label_evals_per_s": rec["label_evals_per_s"],
         "nmi": rec["nmi"],
-        "roofline": mfma_roofline(rec, d, kernel),
+        "roofline": (draw_roofline(rec, d) if args.precision in ("bf16", "fp32")
+                     else mfma_roofline(rec, d, f"cluster draw ({args.precision})")),
     }
     if not args.headline_only:
         extra = {}

@@ -111,8 +111,8 @@ typedef struct {
   const double* psi;  /* host [d*d]: NIW scale, row-major SPD (Gaussian; copied) */
   const double* beta; /* host [V]: Dirichlet prior, > 0 (multinomial; copied) */
   uint64_t seed;      /* Philox key */
-  int32_t precision;  /* cluster scoring of the label step: DPMM_FP32 (vector
-                         ALUs, any d); DPMM_BF16 or DPMM_BF16X3 (matrix cores,
+  int32_t precision;  /* cluster scoring of the label step: DPMM_FP32 (any
+                         d); DPMM_BF16 or DPMM_BF16X3 (matrix cores,
                          Gaussian with d = 32, 64 or 128 only, else DPMM_E_ARG):
                          BF16 inputs with FP32 accumulation, X3 adding the
                          hi/lo cross terms; points whose BF16 top-2 gap leaves
@@ -155,10 +155,10 @@ typedef struct {
   int32_t learned_accepted; /* 1 if it was accepted */
   float ms_learned;         /* its device-side time span, milliseconds */
   float ms_label_kernel;    /* the main cluster-draw kernel alone (Gaussian
-                               matrix-core path: start and end events taken by
-                               its own dispatch, without the candidate pass and
-                               the FP32 re-score of deferred points); ms_labels
-                               on the other paths */
+                               BF16 / BF16X3 path where one kernel scores all
+                               points: start and end events taken by its own
+                               dispatch, without the candidate pass and the FP32
+                               re-score of deferred points); ms_labels elsewhere */
 } dpmm_iter_info;
 
 /* What one learned move did (dpmm_learned_move). */

@@ -111,6 +111,10 @@ dpmm_status ensure_perm(dpmm_ctx* ctx, int64_t n) {
     ctx->d_sflag = nullptr;
     ctx->d_perm_c = nullptr;
     ctx->d_zrow_c = nullptr;
+    hipFree(ctx->d_ub);
+    hipFree(ctx->d_popen);
+    ctx->d_ub = nullptr;
+    ctx->d_popen = nullptr;
     ctx->perm_cap = 0;
   }
   DPMM_HIP(ctx, hipMalloc(&ctx->d_perm, (size_t)n * sizeof(int)), "allocate permutation");
@@ -122,6 +126,11 @@ dpmm_status ensure_perm(dpmm_ctx* ctx, int64_t n) {
     DPMM_HIP(ctx, hipMalloc(&ctx->d_sflag, (size_t)n), "allocate sub-label flags");
     DPMM_HIP(ctx, hipMalloc(&ctx->d_perm_c, (size_t)n * sizeof(int)), "allocate sub-label list");
     DPMM_HIP(ctx, hipMalloc(&ctx->d_zrow_c, (size_t)n * sizeof(int)), "allocate sub-label list");
+  }
+  if (ctx->d_gtab) {
+    DPMM_HIP(ctx, hipMalloc(&ctx->d_ub, (size_t)n * sizeof(float)), "allocate score bounds");
+    if (ctx->d_shi)
+      DPMM_HIP(ctx, hipMalloc(&ctx->d_popen, (size_t)n * sizeof(int)), "allocate open points");
   }
   ctx->perm_cap = n;
   return ensure_part(ctx, n);
@@ -147,9 +156,10 @@ dpmm_status ensure_part(dpmm_ctx* ctx, int64_t n) {
 // statistics over the cluster-sorted order with the given scratch; with
 // sample = true also draws zsub
 dpmm_status sorted_pass_with(dpmm_ctx* ctx, const void* x, int64_t n, bool labels_done_hist, bool sample, uint32_t t,
-                             const int32_t* z, uint8_t* zsub, int G, long long per_block, const StatsBufs& b) {
+                             const int32_t* z, uint8_t* zsub, int G, long long per_block, const StatsBufs& b,
+                             const int* hist_mode = nullptr) {
   DPMM_HIP(ctx, launch_sort_by_z(z, n, ctx->K, G, per_block, labels_done_hist, b.hist, b.tot, b.offs, b.perm, b.zsort,
-                                 ctx->stream), "sort by cluster");
+                                 ctx->stream, hist_mode), "sort by cluster");
   if (ctx->timing) DPMM_HIP(ctx, hipEventRecord(ctx->ev[3], ctx->stream), "event");
   // BF16 tables at d = 64, 128: the sub-labels in bf16x3 first, the FP32 kernel on the rows left
   SubX3 x3{ctx->d_shi, ctx->d_slo, ctx->d_sflag, ctx->d_scnt, ctx->d_soffs, ctx->d_perm_c, ctx->d_zrow_c};
@@ -171,7 +181,8 @@ dpmm_status sorted_pass(dpmm_ctx* ctx, const void* x, int64_t n, bool labels_don
                         const int32_t* z, uint8_t* zsub, int G, long long per_block) {
   DPMM_TRY(ensure_perm(ctx, n));
   DPMM_TRY(ensure_part(ctx, n));
-  return sorted_pass_with(ctx, x, n, labels_done_hist, sample, t, z, zsub, G, per_block, ctx_bufs(ctx));
+  return sorted_pass_with(ctx, x, n, labels_done_hist, sample, t, z, zsub, G, per_block, ctx_bufs(ctx),
+                          sample && ctx->z_hist_if_dense ? ctx->d_pflag : nullptr);
 }
 
 bool stats_sorted(const dpmm_ctx* ctx) {
@@ -490,8 +501,10 @@ dpmm_status dpmm_create(const dpmm_config* cfg, void* hip_stream, dpmm_ctx** out
     c->scratch_slots = std::max(3 * km, 256);
     ok = ok && chk(c->alloc(&c->d_scratch, (size_t)c->scratch_slots * NIW_SCRATCH(d)));
     if (d > 64 && d <= 128) ok = ok && chk(c->alloc(&c->d_cmom, ((size_t)km + 1) * CMOM_TILE_ENTRIES));
-    if (cfg->precision == DPMM_FP32 && guess_table_bytes(d, km))
+    if (cfg->precision != DPMM_BF16X3 && guess_table_bytes(d, km)) {
       ok = ok && chk(c->alloc(&c->d_gtab, guess_table_bytes(d, km)));
+      ok = ok && chk(c->alloc(&c->d_pflag, 2));
+    }
     if (cfg->precision != DPMM_FP32) {
       ok = ok && chk(c->alloc(&c->d_whi, (size_t)km * d * d));
       ok = ok && chk(c->alloc(&c->d_nflag, 2));
@@ -585,6 +598,8 @@ void dpmm_destroy(dpmm_ctx* ctx) {
   if (ctx->d_cand) hipFree(ctx->d_cand);
   if (ctx->d_sflag) hipFree(ctx->d_sflag);
   if (ctx->d_perm_c) hipFree(ctx->d_perm_c);
+  if (ctx->d_ub) hipFree(ctx->d_ub);
+  if (ctx->d_popen) hipFree(ctx->d_popen);
   if (ctx->d_zrow_c) hipFree(ctx->d_zrow_c);
   if (ctx->d_sel) hipFree(ctx->d_sel);
   if (ctx->d_side) hipFree(ctx->d_side);
@@ -811,29 +826,36 @@ dpmm_status label_phase(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t, int
                         long long* per) {
   ctx->labels_gave_stats = false;
   if (ctx->sorted_path()) {
-    // the FP32 kernels take 256 rows per workgroup step, the BF16 ones 512: blocks of as many
-    sorted_plan(n, ctx->K, ctx->hist_cap, G, per, ctx->d_whi ? 512 : 256);
+    const bool mfma = ctx->d_whi != nullptr;
+    const bool by_guess = ctx->d_gtab && label_prune_pays(ctx->d, ctx->K, n, mfma) &&
+                          (!mfma || uc_list_fits(ctx->d, ctx->K));
+    // the FP32 kernels take 256 rows per workgroup step, the BF16 ones and the guess 512: blocks of as many
+    sorted_plan(n, ctx->K, ctx->hist_cap, G, per, mfma || by_guess ? 512 : 256);
     DPMM_TRY(ensure_perm(ctx, n));
-    ctx->z_hist = true;
-    if (ctx->d_gtab && label_prune_pays(ctx->d, ctx->K, n)) {
-      DPMM_HIP(ctx, launch_guess(ctx->d, (const float*)x, n, *G, *per, ctx->d_packed, ctx->K, ctx->d_gtab, z,
-                                 ctx->d_hist, ctx->stream), "guess kernel");
+    ctx->z_hist = !by_guess;  // drawn in sorted order, z is counted afterwards
+    ctx->z_hist_if_dense = by_guess && mfma;
+    const PruneBufs pb{ctx->d_gtab, ctx->d_ub, ctx->d_pflag, ctx->d_pflag + 1, ctx->d_popen};
+    const int* mode = mfma ? pb.mode : nullptr;
+    if (by_guess) {
+      DPMM_HIP(ctx, launch_guess(ctx->d, (const float*)x, n, *G, *per, ctx->d_packed, ctx->K, pb, mfma, z, ctx->d_hist,
+                                 ctx->stream), "guess kernel");
       DPMM_HIP(ctx, launch_sort_by_z(z, n, ctx->K, *G, *per, true, ctx->d_hist, ctx->d_tot, ctx->d_offs, ctx->d_perm,
-                                     ctx->d_zsort, ctx->stream), "sort by guess");
+                                     ctx->d_zsort, ctx->stream, mode), "sort by guess");
       DPMM_HIP(ctx, launch_label_sorted(ctx->d, (const float*)x, n, ctx->d_packed, ctx->K, ctx->d_perm, ctx->d_zsort, t,
-                                        ctx->cfg.seed, z, ctx->stream), "label kernel");
-      ctx->z_hist = false;
-      return DPMM_OK;
+                                        ctx->cfg.seed, pb, mfma, mfma, z, ctx->stream), "label kernel");
+      if (!mfma) return DPMM_OK;
     }
-    if (ctx->d_whi) {
+    if (mfma) {
+      const OpenList ol{mode, pb.open, pb.n_open};
+      const bool timed = ctx->label_timing && !by_guess;
       DPMM_HIP(ctx, launch_label_gauss_mfma(ctx->d, ctx->cfg.precision == DPMM_BF16X3, (const float*)x, n, *G, *per,
                                             ctx->d_packed, ctx->d_whi, ctx->d_wlo, ctx->d_wbias, ctx->K,
                                             ctx->cfg.k_max, t, ctx->cfg.seed, z,
-                                            ctx->d_hist, ctx->d_perm, ctx->d_cand, ctx->d_nflag,
-                                            ctx->stream, ctx->label_timing ? ctx->ev[7] : nullptr,
-                                            ctx->label_timing ? ctx->ev[8] : nullptr, ctx->d_cst),
+                                            ctx->d_hist, ctx->d_perm, ctx->d_cand,
+                                            ctx->d_nflag, ctx->stream, timed ? ctx->ev[7] : nullptr,
+                                            timed ? ctx->ev[8] : nullptr, ctx->d_cst, by_guess ? &ol : nullptr),
                "matrix-core label kernel");
-      ctx->label_kernel_timed = ctx->label_timing && n > 0;
+      ctx->label_kernel_timed = timed && n > 0;
       return DPMM_OK;
     }
     DPMM_HIP(ctx, launch_label_gauss_z(ctx->d, (const float*)x, n, *G, *per, ctx->d_packed, ctx->K, t, ctx->cfg.seed, z,

@@ -87,8 +87,13 @@ struct dpmm_ctx {
   uint16_t *d_whi = nullptr, *d_wlo = nullptr;
   // offsets, constants and the common centre of the uncentred BF16 main pass (d = 64, 128)
   float* d_wbias = nullptr;
-  unsigned char* d_gtab = nullptr;  // guess tables of the pruned FP32 draw
+  // the draw over rows sorted by a guess (label_prune.hip): tables, a bound per point,
+  // mode and count, the points left to the BF16 main pass
+  unsigned char* d_gtab = nullptr;
+  float* d_ub = nullptr;
+  int *d_pflag = nullptr, *d_popen = nullptr;
   bool z_hist = false;              // the last cluster draw left the histogram of z in d_hist
+  bool z_hist_if_dense = false;     // ... or did where it left *d_pflag at 0
   // the clusters' summed scatter matrices plus Psi / 2 for the log marginals at 64 < d <= 128
   double* d_cmom = nullptr;
   // BF16 fragments of the sub-cluster whiteners and the buffers of the bf16x3

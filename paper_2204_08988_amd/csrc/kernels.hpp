@@ -125,16 +125,28 @@ hipError_t launch_label_gauss_mx(int d, const float* x, long long n, int G, long
 // guess of every point's cluster into z with its histogram, and the draw over the
 // rows sorted by it.  tab: guess_table_bytes(d, k_max) bytes
 constexpr int PRUNE_MIN_D = 48;
-bool label_prune_pays(int d, int K, long long n);
+bool label_prune_pays(int d, int K, long long n, bool bf16);
 size_t guess_table_bytes(int d, int k_max);
+// ub: n floats; mode, n_open: an int each; open: n ints (list)
+struct PruneBufs {
+  unsigned char* tab;
+  float* ub;
+  int *mode, *n_open, *open;
+};
+// probe: *mode is set first to whether the guess's bounds settle most points of a
+// sample, and this, the sort and the draw run only if so (n >= 512)
 hipError_t launch_guess(int d, const float* x, long long n, int G, long long per_block, const float* packed, int K,
-                        void* tab, int* z, int* hist, hipStream_t s);
+                        const PruneBufs& b, bool probe, int* z, int* hist, hipStream_t s);
+// list (d = 64, 128): the points that another cluster may win are left to the BF16
+// main pass and listed in open
 hipError_t launch_label_sorted(int d, const float* x, long long n, const float* packed, int K, const int* perm,
-                               const int* guess, uint32_t t, uint64_t seed, int* z, hipStream_t s);
+                               const int* guess, uint32_t t, uint64_t seed, const PruneBufs& b, bool list, bool probe,
+                               int* z, hipStream_t s);
 // block_rows: rows per block while n allows at most 2048 blocks (256 or 512)
 hipError_t sorted_plan(long long n, int K, long long hist_cap, int* G, long long* per_block, int block_rows = 512);
+// mode (may be null): where *mode is 0, have_hist: nothing is done; else: hist is there
 hipError_t launch_sort_by_z(const int* z, long long n, int K, int G, long long per_block, bool have_hist, int* hist,
-                            int* tot, int* offs, int* perm, int* zsort, hipStream_t s);
+                            int* tot, int* offs, int* perm, int* zsort, hipStream_t s, const int* mode = nullptr);
 // waves of the d <= 32 statistics kernel.  In slot mode (cstart = the
 // clusters' first sorted rows, ctot their sizes, part =
 // sub_stats_part_doubles(d, n) doubles) every cluster's statistics are
@@ -194,11 +206,17 @@ hipError_t launch_sub_labels_x3(int d, const float* x, long long n, const int* p
 // flagged: int[n] (the points whose draw is deferred to FP32); cand:
 // int[n][RESCORE_CAND], each deferred point's candidate clusters (-1: empty
 // slot, -2 in slot 0: all clusters); n_flagged: one device int
+// by_guess (d = 64, 128 in BF16 where uc_list_fits): the main pass takes the listed
+// points that launch_label_sorted left open, or where *mode is 0 all as without it
+struct OpenList {
+  const int *mode, *open, *n_open;
+};
+bool uc_list_fits(int d, int K);
 hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, int G, long long per_block,
                                    const float* packed, const void* whi, const void* wlo, const float* wbias, int K,
                                    int k_max, uint32_t t, uint64_t seed, int* z, int* hist, int* flagged,
                                    int* cand, int* n_flagged, hipStream_t s, hipEvent_t ev_main0 = nullptr,
-                                   hipEvent_t ev_main1 = nullptr, float* cst = nullptr);
+                                   hipEvent_t ev_main1 = nullptr, float* cst = nullptr, const OpenList* by_guess = nullptr);
 hipError_t launch_loglik_gauss(int d, const float* x, long long n, const float* packed, int K, int k_max,
                                float* out, hipStream_t s);
 // ---- count data in compressed sparse rows (label_csr.hip)

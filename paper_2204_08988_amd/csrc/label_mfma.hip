@@ -27,6 +27,7 @@
 
 #include <climits>
 
+#include "interval.hpp"
 #include "kernels.hpp"
 #include "score.hpp"
 
@@ -135,7 +136,8 @@ struct Top2U {
 
 // Main pass, point p: certain (z = k1, the only cluster that can win) unless
 // another bound reaches T; then appended to `flagged` (z = -1, not in the
-// histogram) for the candidate pass and k_rescore_flagged.
+// histogram) for the candidate pass and k_rescore_flagged.  h may be null (no
+// histogram).
 __device__ __forceinline__ void finish_main(bool valid, long long p, const Top2U& t2, int* z, int* h, int* flagged,
                                             int* n_flagged, int lane) {
   const bool doubt = valid && t2.u2 > t2.lo_max - RGAP - TOL_ABS;
@@ -149,7 +151,7 @@ __device__ __forceinline__ void finish_main(bool valid, long long p, const Top2U
   }
   if (valid) {
     z[p] = doubt ? -1 : t2.k1;
-    if (!doubt) atomicAdd(&h[t2.k1], 1);
+    if (h && !doubt) atomicAdd(&h[t2.k1], 1);
   }
 }
 
@@ -635,24 +637,8 @@ __device__ __forceinline__ void top2_merge(Top2U& a, float u1, float u2, float l
 }
 
 
-// Bounds on the score of the uncentred form below.  l = c_k - q / 2 is the
-// score of the FP32 record (W, mu, c_k), q = ||y||^2, y = W (x - mu).  With
-// x' = x - c (c a centre common to all clusters) and beta = -W (mu - c),
-// y = W x' + beta; the matrix cores form Y = bf16(W) bf16(x') + beta with exact
-// products and FP32 sums.  Each rounding to BF16 is within 2^-8 relative, so
-//   |Y_j - y_j| <= g sum_i |W_ji| |x'_i| + g2 sum_i |W_ji| (|x'_i| + |mu_i - c_i|)
-// with g = 2^-7 (plus a margin) for the two BF16 roundings and g2 = 2^-14 for
-// the FP32 sums and roundings of both this form and the FP32 draw it stands
-// for ((3d + 5) 2^-24 at most, d <= 128).  By Cauchy-Schwarz
-//   E = ||Y - y|| <= (g + g2) ||W||_F ||x'|| + g2 ||W||_F ||mu - c||.
-// The computed s = sqrt(q_bf16) is within 2^-16 s of ||Y||, so with
-// E' = E + 2^-16 s the exact q lies in [max(0, s - E')^2, (s + E')^2]: the
-// score lies in [c_k - (s + E')^2 / 2, c_k - max(0, s - E')^2 / 2].
 constexpr int UC_BUF_DWORD3 = 0x00020000;  // raw buffer descriptor word 3 (gfx9 family)
 constexpr int UC_NT = 2;                    // cache policy of the row loads: non-temporal
-constexpr float UC_GAMMA = 1.02f / 128.0f;
-constexpr float UC_GAMMA2 = 1.0f / 16384.0f;
-constexpr float UC_EPSS = 1.0f / 65536.0f;
 
 // Main pass for d = 64, 128 in BF16, cluster-stationary and uncentred: the
 // workgroup's NWAVE waves (eight, or four with two workgroups per CU) take PTS
@@ -671,13 +657,19 @@ constexpr float UC_EPSS = 1.0f / 65536.0f;
 // FP32 draw, so the labels are those of the FP32 draw.
 // The partial top-2 states of the waves are merged through LDS at the end of
 // the step (top2_merge).
-template <int D, int PTS, int NWAVE>
+// LIST: the rows are the n_list listed points; no histogram.  mode (may be null):
+// the kernel runs only where *mode == LIST.
+template <int D, int PTS, int NWAVE, bool LIST = false>
 __global__ __launch_bounds__(64 * NWAVE, 8 / NWAVE) void k_label_gauss_mfma_uc(const float* __restrict__ x, long long n,
                                                                      long long per_block,
                                                                      const bf16x8* __restrict__ whi,
                                                                      const float* __restrict__ wbias, int K, int k_max,
                                                                      int* __restrict__ z, int* __restrict__ hist, int* __restrict__ flagged,
-                                                                     int* __restrict__ n_flagged) {
+                                                                     int* __restrict__ n_flagged,
+                                                                     const int* __restrict__ mode,
+                                                                     const int* __restrict__ list,
+                                                                     const int* __restrict__ n_list) {
+  if (mode && *mode != (LIST ? 1 : 0)) return;
   using TT = TriTiles<D>;
   constexpr int MT = TT::MT, KS = TT::KS, NF = MT * KS * 64, NT = TT::NT;
   constexpr int RB = D / 8 + 1;  // LDS row stride in 16-byte units
@@ -688,7 +680,7 @@ __global__ __launch_bounds__(64 * NWAVE, 8 / NWAVE) void k_label_gauss_mfma_uc(c
   constexpr int RPI = 64 / P4;    // rows per wave and staging pass
   constexpr int WROWS = PTS / NW;  // rows staged per wave
   constexpr int ITER = WROWS / RPI;  // staging passes for the wave's rows
-  static_assert(D % 64 == 0 && PTS % (32 * NW) == 0 && PTS <= BLK, "step, row copies");
+  static_assert(D % 64 == 0 && PTS % (32 * NW) == 0 && PTS <= BLK && (!LIST || PTS == BLK), "step, row copies");
   static_assert(NW * PTS * 4 * sizeof(float) <= PTS * RB * 16, "partial states alias the rows");
   typedef __attribute__((__vector_size__(4 * sizeof(__bf16)))) __bf16 bf16x4;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -697,14 +689,17 @@ __global__ __launch_bounds__(64 * NWAVE, 8 / NWAVE) void k_label_gauss_mfma_uc(c
   int* h = reinterpret_cast<int*>(rxs + PTS);                  // [K] counters
   const float4* cst = reinterpret_cast<const float4*>(wbias + (size_t)k_max * D);  // (c_k, (g + g2) ||W||_F, g2 ||W||_F ||mu - c||, 0)
   const float* centre = wbias + (size_t)k_max * (D + 4);
-  for (int k = threadIdx.x; k < K; k += BLK) h[k] = 0;
+  if (!LIST)
+    for (int k = threadIdx.x; k < K; k += BLK) h[k] = 0;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int half = lane >> 5, col = lane & 31;
   const int sub = lane / P4, part = lane % P4;
-  const long long begin = (long long)blockIdx.x * per_block;
-  const long long end = begin + per_block < n ? begin + per_block : n;
-  for (long long chunk = begin; chunk < end; chunk += PTS) {
+  // LIST: positions in the list, grid-strided
+  const long long begin = (long long)blockIdx.x * (LIST ? PTS : per_block);
+  const long long end = LIST ? *n_list : (begin + per_block < n ? begin + per_block : n);
+  for (long long chunk = begin; chunk < end; chunk += LIST ? (long long)gridDim.x * PTS : PTS) {
     const int rows = end - chunk < PTS ? (int)(end - chunk) : PTS;
+    const int id = LIST && (int)threadIdx.x < rows ? list[chunk + threadIdx.x] : 0;  // the point of row threadIdx.x
     // the lane's slice of the centre, read again each step (an L2 hit) rather
     // than held in registers across the cluster loop
     const float* cp = centre + 4 * part;
@@ -731,8 +726,14 @@ __global__ __launch_bounds__(64 * NWAVE, 8 / NWAVE) void k_label_gauss_mfma_uc(c
 #pragma unroll
         for (int j = 0; j < SB; ++j) {
           const int r = wave * WROWS + (i0 + j) * RPI + sub;
-          const f32x4 u = __builtin_amdgcn_raw_buffer_load_b128(rx, vo, (i0 + j) * RPI * D * 4, UC_NT);
-          v[j] = r < rows ? make_float4(u.x, u.y, u.z, u.w) : c4;
+          if constexpr (LIST) {  // a row of no point: point 0
+            const f32x4 u = *reinterpret_cast<const f32x4*>(
+                x + (size_t)(unsigned)__shfl(id, (i0 + j) * RPI + sub) * D + 4 * part);
+            v[j] = make_float4(u.x, u.y, u.z, u.w);
+          } else {
+            const f32x4 u = __builtin_amdgcn_raw_buffer_load_b128(rx, vo, (i0 + j) * RPI * D * 4, UC_NT);
+            v[j] = r < rows ? make_float4(u.x, u.y, u.z, u.w) : c4;
+          }
         }
         float ss[SB];
 #pragma unroll
@@ -868,9 +869,11 @@ __global__ __launch_bounds__(64 * NWAVE, 8 / NWAVE) void k_label_gauss_mfma_uc(c
         const float* o = ps + ((size_t)w * PTS + threadIdx.x) * 4;
         top2_merge(m, o[0], o[1], o[2], __float_as_int(o[3]));
       }
-      finish_main(threadIdx.x < rows, chunk + threadIdx.x, m, z, h, flagged, n_flagged, lane);
+      finish_main(threadIdx.x < rows, LIST ? id : chunk + threadIdx.x, m, z, LIST ? nullptr : h, flagged, n_flagged,
+                  lane);
     }
   }
+  if (LIST) return;
   __syncthreads();
   for (int k = threadIdx.x; k < K; k += BLK) {
     hist[(size_t)blockIdx.x * K + k] = h[k];
@@ -1362,6 +1365,13 @@ hipError_t launch_sub_labels_x3(int d, const float* x, long long n, const int* p
   return hipGetLastError();
 }
 
+// rows per workgroup step of the listed points' main pass, and whether they fit in LDS
+static int luc_rows(int d) { return d == 128 ? 512 : 256; }
+
+bool uc_list_fits(int d, int K) {
+  return (d == 64 || d == 128) && label_uc_lds(d, K, luc_rows(d)) <= (size_t)(d == 128 ? 160 : 80) * 1024;
+}
+
 bool mfma_supported(int d) { return d == 32 || d == 64 || d == 128; }
 
 hipError_t launch_pack_wfrag(int K, int d, int k_max, const float* packed, void* whi, void* wlo, float* wbias,
@@ -1384,7 +1394,7 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
                                    const float* packed, const void* whi, const void* wlo, const float* wbias, int K,
                                    int k_max, uint32_t t, uint64_t seed, int* z, int* hist, int* flagged,
                                    int* cand, int* n_flagged, hipStream_t s, hipEvent_t ev_main0,
-                                   hipEvent_t ev_main1, float* cst) {
+                                   hipEvent_t ev_main1, float* cst, const OpenList* by_guess) {
   if (n == 0) return hipSuccess;
   const size_t lh = (size_t)K * sizeof(int);
   const bf16x8* hi = (const bf16x8*)whi;
@@ -1393,7 +1403,9 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
   if (e != hipSuccess) return e;
   static bool attr_set = false;
   if (!attr_set) {  // d = 32 and the uncentred kernels: more than 64 KB of dynamic LDS (160 KB per CU)
-    const void* fns[8] = {(const void*)k_label_gauss_mfma32<true, false>, (const void*)k_label_gauss_mfma32<false, false>,
+    const void* fns[10] = {(const void*)k_label_gauss_mfma_uc<128, 512, 8, true>,
+                          (const void*)k_label_gauss_mfma_uc<64, 256, 4, true>,
+                          (const void*)k_label_gauss_mfma32<true, false>, (const void*)k_label_gauss_mfma32<false, false>,
                           (const void*)k_label_gauss_mfma32<true, true>,
                           (const void*)k_label_gauss_mfma_uc<64, 256, 4>, (const void*)k_label_gauss_mfma_uc<128, 512, 8>,
                           (const void*)k_label_gauss_mfma_uc<64, 512, 8>, (const void*)k_label_gauss_mfma_uc<128, 256, 8>,
@@ -1425,7 +1437,20 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
       const size_t luc = big ? l512 : l256;
 #define DPMM_UC(DD, PP, NWV)                                                                                     \
   hipExtLaunchKernelGGL((k_label_gauss_mfma_uc<DD, PP, NWV>), dim3(Gp), dim3(64 * NWV), luc, s, e0, e1, 0, x, n, \
-                        per_block, hi, wbias, K, k_max, z, hist, flagged, n_flagged)
+                        per_block, hi, wbias, K, k_max, z, hist, flagged, n_flagged, by_guess ? by_guess->mode : nullptr,      \
+                        nullptr, nullptr)
+      if (by_guess) {  // the points left by launch_label_sorted
+        const unsigned gl = (unsigned)((n + luc_rows(d) - 1) / luc_rows(d) < 512 ? (n + luc_rows(d) - 1) / luc_rows(d) : 512);
+        if (d == 128)
+          hipLaunchKernelGGL((k_label_gauss_mfma_uc<128, 512, 8, true>), dim3(gl), dim3(512), l512, s, x, n, per_block, hi,
+                             wbias, K, k_max, z, hist, flagged, n_flagged, by_guess->mode, by_guess->open,
+                             by_guess->n_open);
+        else
+          hipLaunchKernelGGL((k_label_gauss_mfma_uc<64, 256, 4, true>), dim3(gl), dim3(256), l256, s, x, n, per_block, hi,
+                             wbias, K, k_max, z, hist, flagged, n_flagged, by_guess->mode, by_guess->open,
+                             by_guess->n_open);
+        if ((e = hipGetLastError()) != hipSuccess) return e;
+      }
       if (d == 128) {
         if (big)
           DPMM_UC(128, 512, 8);

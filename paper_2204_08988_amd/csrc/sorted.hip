@@ -58,7 +58,8 @@ __device__ __forceinline__ int block_inclusive_scan(int v, int* buf) { return bl
 }  // namespace
 
 __global__ __launch_bounds__(BLOCK) void k_hist_z(const int* __restrict__ z, long long n, long long per_block, int K,
-                                                  int* __restrict__ hist) {
+                                                  int* __restrict__ hist, const int* __restrict__ mode) {
+  if (mode && *mode == 0) return;
   extern __shared__ int h[];
   for (int k = threadIdx.x; k < K; k += BLOCK) h[k] = 0;
   __syncthreads();
@@ -81,7 +82,9 @@ __global__ __launch_bounds__(BLOCK) void k_hist_z(const int* __restrict__ z, lon
 // against 3.5 us now, and a launch to clear them.)
 constexpr int SORT_BLOCKS = 2048;  // plan_blocks makes no more
 __global__ __launch_bounds__(BLOCK) void k_scan_hist(const int* __restrict__ hist, int G, int K,
-                                                     int* __restrict__ tot, int* __restrict__ offs) {
+                                                     int* __restrict__ tot, int* __restrict__ offs,
+                                                     const int* __restrict__ mode) {
+  if (mode && *mode == 0) return;
   constexpr int PER = SORT_BLOCKS / BLOCK;
   __shared__ int buf[BLOCK];
   const int k = blockIdx.x, g0 = threadIdx.x * PER;
@@ -114,7 +117,9 @@ __global__ __launch_bounds__(BLOCK) void k_scan_hist(const int* __restrict__ his
 // offs (whose own offsets are 0) for the kernels that follow.
 __global__ __launch_bounds__(BLOCK) void k_scatter_z(const int* __restrict__ z, long long n, long long per_block,
                                                      int K, const int* __restrict__ tot, int* __restrict__ offs,
-                                                     int* __restrict__ perm, int* __restrict__ zsort) {
+                                                     int* __restrict__ perm, int* __restrict__ zsort,
+                                                     const int* __restrict__ mode) {
+  if (mode && *mode == 0) return;
   extern __shared__ int cur[];  // [4][K]
   __shared__ int buf[BLOCK];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
@@ -804,15 +809,15 @@ hipError_t sorted_plan(long long n, int K, long long hist_cap, int* G, long long
 }
 
 hipError_t launch_sort_by_z(const int* z, long long n, int K, int G, long long per_block, bool have_hist, int* hist,
-                            int* tot, int* offs, int* perm, int* zsort, hipStream_t s) {
+                            int* tot, int* offs, int* perm, int* zsort, hipStream_t s, const int* mode) {
   if (n == 0) return hipSuccess;
   hipError_t e;
   if (G > SORT_BLOCKS) return hipErrorInvalidValue;
   if (!have_hist) {
-    hipLaunchKernelGGL(k_hist_z, dim3(G), dim3(BLOCK), (size_t)K * sizeof(int), s, z, n, per_block, K, hist);
+    hipLaunchKernelGGL(k_hist_z, dim3(G), dim3(BLOCK), (size_t)K * sizeof(int), s, z, n, per_block, K, hist, mode);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
-  hipLaunchKernelGGL(k_scan_hist, dim3(K), dim3(BLOCK), 0, s, hist, G, K, tot, offs);
+  hipLaunchKernelGGL(k_scan_hist, dim3(K), dim3(BLOCK), 0, s, hist, G, K, tot, offs, have_hist ? mode : nullptr);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   // per_block is a multiple of BLOCK: each wave's quarter is whole 64-row chunks
   if (per_block % BLOCK != 0 || 4 * (size_t)K * sizeof(int) > 64 * 1024) return hipErrorInvalidValue;
@@ -823,7 +828,7 @@ hipError_t launch_sort_by_z(const int* z, long long n, int K, int G, long long p
     attr_set = true;
   }
   hipLaunchKernelGGL(k_scatter_z, dim3(G), dim3(BLOCK), 4 * (size_t)K * sizeof(int), s, z, n, per_block, K, tot, offs,
-                     perm, zsort);
+                     perm, zsort, have_hist ? mode : nullptr);
   return hipGetLastError();
 }
 

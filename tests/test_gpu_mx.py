@@ -116,3 +116,30 @@ def test_bf16_draw_of_rows_without_a_score(d, K, n):
         S.close()
     assert z["bf16"].min() >= 0 and z["bf16"].max() < K
     assert np.array_equal(z["fp32"], z["bf16"])
+
+
+# the BF16 draw by a guess (d = 64, 128, n >= 1e6, K >= 64, 32): all points by it, some left open by the guess's
+# bound, and none (the sample decides against it); ragged last steps, rows without a score
+@pytest.mark.parametrize("d,K,n,spread", [(64, 64, 1_000_000, 3.0), (64, 131, 1_000_003, 1.2), (64, 64, 1_000_100, 0.2),
+                                          (128, 32, 1_000_001, 3.0), (128, 33, 1_000_447, 1.6)])
+def test_bf16_draw_by_guess(d, K, n, spread):
+    import torch
+
+    from paper_2204_08988_amd.sampler import Sampler
+    params = pu.random_gauss_params(K, d, 9 + d, spread=spread)
+    g = torch.Generator(device="cuda").manual_seed(d + K)
+    x = torch.randn((n, d), device="cuda", generator=g)
+    mu = torch.from_numpy(params.mu[:, 0]).float().cuda()
+    x += mu[torch.randint(0, K, (n,), device="cuda", generator=g)]
+    x[5::4001, 3] = float("nan")
+    x[::5003, 7] = float("inf")
+    z = {}
+    for prec in ("fp32", "bf16"):
+        S = Sampler("gaussian", d, K + 2, 2.0, 11, kappa=1.0, nu=d + 3.0, m=np.zeros(d), psi=np.eye(d), precision=prec)
+        S.set_params(params.log_pi, params.log_pisub, pu.comp_array(params))
+        z[prec], zs = S.sample_labels(x, 1)
+        got = S.get_stats()[:, :, 0]
+        S.close()
+    assert torch.equal(z["fp32"], z["bf16"])
+    count = torch.bincount(z["bf16"].long() * 2 + zs.long(), minlength=2 * K).cpu().numpy()
+    assert np.array_equal(got, count.reshape(K, 2))
