@@ -167,10 +167,11 @@ hipError_t launch_sub_stats_w_any(int d, bool sample, const float* x, long long 
                                   const float* packed, int K, int k_max, uint32_t t, uint64_t seed, long long* counts,
                                   double* moments, const int* cstart, const int* ctot, int kbase, double* part,
                                   hipStream_t s);
-// sub-labels of cluster-sorted rows, d = 33 .. 127, FP32 on the matrix cores
+// sub-labels of cluster-sorted rows, d = 32 .. 128, FP32 on the matrix cores; n_dev
+// (d = 32, 64, 128; may be null): the length of the row list, on the device (n bounds it)
 hipError_t launch_sub_labels_mx(int d, const float* x, long long n, const int* perm, const int* z, const int* zrow,
                                 unsigned char* zsub, const float* packed, int K, int k_max, uint32_t t, uint64_t seed,
-                                hipStream_t s);
+                                hipStream_t s, const int* n_dev = nullptr);
 // statistics of a listed set of cluster k1's points split by side[i] into
 // segments slot, slot + 1 (slot >= 2 k1; d in {8, 16, 32, 64, 128});
 // cspan: device int[2] = {0, nsel}; part: sub_stats_part_doubles(d, nsel)

@@ -1021,7 +1021,7 @@ __global__ void k_pack_wfrag(int K, int d, int rec0, const float* __restrict__ p
 
 // Sub-label draw of cluster-sorted rows in bf16x3 on the BF16 matrix cores
 // (d = 64, 128), Sec. 4.1 step (f), in front of the FP32 kernel
-// k_sub_labels_mfma: the same scores (rows centred on sub-cluster 0's mean,
+// k_sub_labels_mx: the same scores (rows centred on sub-cluster 0's mean,
 // sub-cluster 1's accumulators started at W_1 (mu_0 - mu_1)) from the hi/lo
 // BF16 parts of W_h and of the centred rows, three products each (W_hi x_hi +
 // W_hi x_lo + W_lo x_hi), for about 16 mantissa bits at a sixteenth of the FP32

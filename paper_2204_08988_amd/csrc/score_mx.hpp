@@ -187,5 +187,57 @@ __device__ __forceinline__ bool sq_norm(lds_cfloat* p, int d, const float (&x)[4
   return true;
 }
 
+// Squared norm of W v + y0 for the rows v = x (already centred; d = 16 RB), W of the
+// record p, y0 the d starting values of the chains (y0 in LDS).  The rows' squares
+// are summed in two chains, those with bit 2 of the row clear and set, the order of
+// 32 x 32 accumulators.
+template <int RB>
+__device__ __forceinline__ float sq_norm_from(lds_cfloat* p, lds_cfloat* y0, const float (&x)[4][4 * RB]) {
+  constexpr int PF = 3, D = 16 * RB;
+  typedef __attribute__((address_space(3))) const f32x4 lds_f32x4;
+  const int lane = threadIdx.x & 63, g = lane >> 4, i = lane & 15;
+  float q0 = 0.0f, q1 = 0.0f;
+#pragma unroll
+  for (int rb = 0; rb < RB; ++rb) {
+    const int NS = 4 * (rb + 1), r = 16 * rb + i;
+    lds_cfloat* wr = p + 4 + D + r * (r + 1) / 2 + g;
+    const f32x4 start = *(lds_f32x4*)(y0 + 16 * rb + 4 * g);
+    float w[4 * RB];
+#pragma unroll
+    for (int s = 0; s < PF && s < NS; ++s) w[s] = wr[4 * s];
+    f32x4 a[4];
+#pragma unroll
+    for (int t = 0; t < 4; ++t) a[t] = start;
+#pragma unroll
+    for (int s = 0; s < 4 * RB; ++s) {
+      if (s >= NS) continue;
+      if (s + PF < NS) w[s + PF] = wr[4 * (s + PF)];
+      if (s >= 4 * rb) w[s] = 4 * s + g <= r ? w[s] : 0.0f;  // above the diagonal
+      __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+      for (int t = 0; t < 4; ++t) a[t] = __builtin_amdgcn_mfma_f32_16x16x4f32(w[s], x[t][s], a[t], 0, 0, 0);
+      __builtin_amdgcn_sched_barrier(0);
+    }
+#pragma unroll
+    for (int u = 0; u < 4; ++u) {
+      float v0 = a[0][u], v1 = a[1][u], v2 = a[2][u], v3 = a[3][u];
+      transpose4(v0, v1, v2, v3);
+      a[0][u] = v0;
+      a[1][u] = v1;
+      a[2][u] = v2;
+      a[3][u] = v3;
+    }
+#pragma unroll
+    for (int j = 0; j < 4; j += 2)
+#pragma unroll
+      for (int u = 0; u < 4; ++u) {
+        q0 = fmaf(a[j][u], a[j][u], q0);
+        q1 = fmaf(a[j + 1][u], a[j + 1][u], q1);
+      }
+    if (rb < RB - 1 && !Always()(q0)) break;
+  }
+  return q0 + q1;
+}
+
 }  // namespace mx
 }  // namespace dpmm

@@ -9,8 +9,8 @@
 //                sorted row, read coalesced by the kernels below).
 // Then, over the sorted order (a cluster is a run of rows):
 //   d <= 31      k_sub_stats_w: sub-labels and statistics in one pass;
-//   d = 32       k_sub_labels_mfma, then k_sub_stats_w;
-//   d = 64, 128  k_sub_labels_mfma (with BF16 tables behind the bf16x3 pass),
+//   d = 32       k_sub_labels_mx (sub_stats_any.hip), then k_sub_stats_w;
+//   d = 64, 128  k_sub_labels_mx (with BF16 tables behind the bf16x3 pass),
 //                then k_sub_stats_big;
 //   other d      k_sub_labels_mx, then k_sub_stats_big over rows padded with
 //                zero columns to 64 or 128.
@@ -253,163 +253,6 @@ constexpr int big_rows_of(int d) { return 16384 / d; }
 typedef __attribute__((address_space(3))) void lds_void;
 
 __device__ __forceinline__ int block_inclusive_scan_big(int v, int* buf) { return block_inclusive_scan_n<BIG_THREADS>(v, buf); }
-
-// Sub-label draw of sorted rows on the FP32 matrix cores (d = 32, 64, 128), Sec. 4.1
-// step (f): the scores of the two sub-clusters of the row's cluster, from
-// Y = W_h (x - mu_h) with v_mfma_f32_32x32x2_f32 (A = W_h, B = the centred
-// rows).  A workgroup walks a contiguous range of sorted rows; the two records
-// of the current cluster are staged in LDS whenever the cluster changes.  A
-// wave scores 64 rows (two 32-row tiles): a lane holds half the coordinates of
-// one row, k = 2s + h at MFMA step s (h = lane / 32).  The rows are centred
-// once on mu_0; sub-cluster 1 starts its accumulators at W_1 (mu_0 - mu_1), so
-// that both products read the same centred rows.  Row blocks of W above the
-// diagonal are skipped (k <= 32 mt + 31 for output rows 32 mt ... 32 mt + 31)
-// and the entries above the diagonal inside a block are read as zero.  With
-// n_dev the rows are the list of n_dev[0] rows that the bf16x3 pass left
-// undecided (n_sorted then only bounds the grid).
-constexpr int SUBL_BLOCK = 256;
-
-template <int D>
-__global__ __launch_bounds__(SUBL_BLOCK) __attribute__((amdgpu_waves_per_eu(2, D <= 32 ? 3 : 2))) void k_sub_labels_mfma(
-    const float* __restrict__ x, long long n_sorted, long long per_block, const int* __restrict__ perm,
-    const int* __restrict__ z, const int* __restrict__ zrow, unsigned char* __restrict__ zsub,
-    const float* __restrict__ packed, int K, int k_max, uint32_t t, uint64_t seed, const int* __restrict__ n_dev) {
-  constexpr int S = (4 + D + D * (D + 1) / 2 + 3) & ~3;
-  constexpr int MT = D / 32, HALF = D / 2, QTR = D / 4;
-  if (n_dev) {  // a row list whose length is on the device: split it evenly over the grid
-    n_sorted = *n_dev;
-    per_block = ((n_sorted + gridDim.x - 1) / gridDim.x + 63) / 64 * 64;
-  }
-  static_assert(D % 32 == 0 && D <= SUBL_BLOCK, "layout");
-  typedef float f32x16 __attribute__((ext_vector_type(16)));
-  extern __shared__ __align__(16) float s_rec[];  // records of sub-clusters 0 and 1, then W_1 (mu_0 - mu_1), mu_0 - mu_1
-  float* s_corr = s_rec + 2 * S;
-  float* s_dmu = s_corr + D;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, col = lane & 31;
-  const long long begin = (long long)blockIdx.x * per_block;
-  const long long end = begin + per_block < n_sorted ? begin + per_block : n_sorted;
-  auto kof = [&](long long g) { return __builtin_amdgcn_readfirstlane(zrow ? zrow[g] : z[perm[g]]); };
-  int staged = -1;
-  for (long long chunk = begin; chunk < end; chunk += SUBL_BLOCK) {
-    const long long cend = chunk + SUBL_BLOCK < end ? chunk + SUBL_BLOCK : end;
-    const long long base = chunk + wave * 64;
-    const long long rA = base + col, rB = base + 32 + col;
-    const bool vA = rA < cend, vB = rB < cend;
-    const long long iA = vA ? perm[rA] : 0, iB = vB ? perm[rB] : 0;
-    const int kA = vA ? (zrow ? zrow[rA] : z[iA]) : -1, kB = vB ? (zrow ? zrow[rB] : z[iB]) : -1;
-    const int kmine = h ? kB : kA;
-    float delta = 0.0f;
-    int cur = kof(chunk);
-    const int last = kof(cend - 1);
-    for (;;) {
-      if (cur != staged) {
-        __syncthreads();  // every wave is done with the previous records
-        const float4* src = reinterpret_cast<const float4*>(packed + (size_t)(k_max + 2 * cur) * S);
-        float4* dst = reinterpret_cast<float4*>(s_rec);
-        for (int j = threadIdx.x; j < 2 * S / 4; j += SUBL_BLOCK) dst[j] = src[j];
-        __syncthreads();
-        if (threadIdx.x < D) s_dmu[threadIdx.x] = s_rec[4 + threadIdx.x] - s_rec[S + 4 + threadIdx.x];
-        __syncthreads();
-        if (threadIdx.x < D) {
-          const int i = threadIdx.x;
-          const float* w1 = s_rec + S + 4 + D + i * (i + 1) / 2;
-          float c = 0.0f;
-          for (int k = 0; k <= i; ++k) c = fmaf(w1[k], s_dmu[k], c);
-          s_corr[i] = c;
-        }
-        __syncthreads();
-        staged = cur;
-      }
-      if (__ballot(kA == cur || kB == cur)) {
-        // rows of the two tiles: lane h loads coordinates [HALF h, HALF h + HALF) and the two halves
-        // trade so that ra[2j] = x[2j + h], ra[2j + 1] = x[HALF + 2j + h], centred on mu_0
-        float ra[HALF], rb[HALF];
-        const float4* pa = reinterpret_cast<const float4*>(x + (size_t)iA * D + HALF * h);
-        const float4* pb = reinterpret_cast<const float4*>(x + (size_t)iB * D + HALF * h);
-#pragma unroll
-        for (int q = 0; q < HALF / 4; ++q) {
-          const float4 va = vA ? pa[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-          const float4 vb = vB ? pb[q] : make_float4(0.f, 0.f, 0.f, 0.f);
-          ra[4 * q] = va.x, ra[4 * q + 1] = va.y, ra[4 * q + 2] = va.z, ra[4 * q + 3] = va.w;
-          rb[4 * q] = vb.x, rb[4 * q + 1] = vb.y, rb[4 * q + 2] = vb.z, rb[4 * q + 3] = vb.w;
-        }
-#pragma unroll
-        for (int j = 0; j < QTR; ++j) {
-          const float sa = __shfl_xor(h ? ra[2 * j] : ra[2 * j + 1], 32);
-          const float sb = __shfl_xor(h ? rb[2 * j] : rb[2 * j + 1], 32);
-          if (h) {
-            ra[2 * j] = sa;
-            rb[2 * j] = sb;
-          } else {
-            ra[2 * j + 1] = sa;
-            rb[2 * j + 1] = sb;
-          }
-          const float m0 = s_rec[4 + 2 * j + h], m1 = s_rec[4 + HALF + 2 * j + h];
-          ra[2 * j] -= m0;
-          rb[2 * j] -= m0;
-          ra[2 * j + 1] -= m1;
-          rb[2 * j + 1] -= m1;
-        }
-        float sc[2];
-#pragma unroll
-        for (int sub = 0; sub < 2; ++sub) {
-          const float* rec = s_rec + sub * S;
-          float qa = 0.0f, qb = 0.0f;
-#pragma unroll
-          for (int mt = 0; mt < MT; ++mt) {
-            f32x16 acca, accb;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const float c0 = sub ? s_corr[32 * mt + 8 * (r >> 2) + 4 * h + (r & 3)] : 0.0f;
-              acca[r] = c0;
-              accb[r] = c0;
-            }
-            const int i = 32 * mt + col;
-            const float* wr = rec + 4 + D + i * (i + 1) / 2 + h;
-#pragma unroll
-            for (int st = 0; st < 16 * (mt + 1); ++st) {
-              float a = wr[2 * st];
-              if (st >= 16 * mt && 2 * st + h > i) a = 0.0f;  // above the diagonal
-              const int reg = st < QTR ? 2 * st : 2 * (st - QTR) + 1;
-              acca = __builtin_amdgcn_mfma_f32_32x32x2f32(a, ra[reg], acca, 0, 0, 0);
-              accb = __builtin_amdgcn_mfma_f32_32x32x2f32(a, rb[reg], accb, 0, 0, 0);
-            }
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              qa = fmaf(acca[r], acca[r], qa);
-              qb = fmaf(accb[r], accb[r], qb);
-            }
-          }
-          qa += __shfl_xor(qa, 32);
-          qb += __shfl_xor(qb, 32);
-          sc[sub] = fmaf(-0.5f, h ? qb : qa, rec[0]);
-        }
-        if (kmine == cur) delta = sc[0] - sc[1];
-      }
-      if (cur == last) break;
-      // the next cluster: the first row of the chunk above cur (rows are sorted by cluster)
-      long long lo = chunk, hi = cend - 1;
-      while (lo < hi) {
-        const long long mid = (lo + hi) >> 1;
-        if (kof(mid) > cur)
-          hi = mid;
-        else
-          lo = mid + 1;
-      }
-      cur = kof(lo);
-    }
-    const long long rme = base + lane;
-    if (rme < cend) {
-      const int i = (int)(h ? iB : iA);
-      zsub[i] = (unsigned char)sub_label_draw(delta, seed, t, (uint32_t)i, K);
-    }
-  }
-}
-
-size_t sub_labels_mfma_lds(int d) {
-  const int S = (4 + d + d * (d + 1) / 2 + 3) & ~3;
-  return (size_t)(2 * S + 2 * d) * sizeof(float);
-}
 
 // Upper 16 x 16 block u (row-major over I <= J) of an NB x NB block grid.
 constexpr int blk_i(int u, int nb) {
@@ -870,55 +713,20 @@ hipError_t sub_stats_kernels(int d, bool sample, const float* x, long long npts,
   if (n == 0) return hipSuccess;
   const int E = d + d * (d + 1) / 2;
   const dim3 fix_grid((2 * (E + 1) + FIX_EN - 1) / FIX_EN, ncl);
-  if (sample && (d == 32 || d == 64 || d == 128)) {
-    // the sub-labels in their own pass on the FP32 matrix cores, then the statistics; at
-    // d = 128 two workgroups per CU (the staged records take 66 KB), each on a contiguous
-    // range of rows
-    {
-      static bool lattr = false;
-      const size_t llds = sub_labels_mfma_lds(d);
-      if (!lattr) {
-        e = hipFuncSetAttribute((const void*)k_sub_labels_mfma<128>, hipFuncAttributeMaxDynamicSharedMemorySize,
-                                (int)sub_labels_mfma_lds(128));
-        if (e != hipSuccess) return e;
-        lattr = true;
-      }
-      // d = 32: three waves per SIMD, all workgroups resident at once; each workgroup takes
-      // a range of whole waves' rows (64), so that the ranges differ by at most one wave
-      const long long cap = d == 128 ? 512 : (d == 64 ? 1024 : 768);
-      long long lper = (n + cap - 1) / cap;
-      lper = ((lper + 63) / 64) * 64;
-      const unsigned lg = (unsigned)((n + lper - 1) / lper);
-      // with BF16 tables (d = 64, 128) a bf16x3 pass draws most rows first and this
-      // kernel only the list it leaves
-      const int* lperm = perm;
-      const int* lz = z;
-      const int* lzrow = zrow;
-      const int* ndev = nullptr;
-      if (x3 && (d == 64 || d == 128)) {
-        e = launch_sub_labels_x3(d, x, n, perm, z, zrow, zsub, packed, K, k_max, t, seed, *x3, s);
-        if (e != hipSuccess) return e;
-        lperm = x3->perm_c;
-        lz = nullptr;
-        lzrow = x3->zrow_c;
-        ndev = x3->offs + SUBX_GROUPS;
-      }
-      if (d == 128)
-        hipLaunchKernelGGL(k_sub_labels_mfma<128>, dim3(lg), dim3(SUBL_BLOCK), llds, s, x, n, lper, lperm, lz, lzrow,
-                           zsub, packed, K, k_max, t, seed, ndev);
-      else if (d == 64)
-        hipLaunchKernelGGL(k_sub_labels_mfma<64>, dim3(lg), dim3(SUBL_BLOCK), llds, s, x, n, lper, lperm, lz, lzrow,
-                           zsub, packed, K, k_max, t, seed, ndev);
-      else
-        hipLaunchKernelGGL(k_sub_labels_mfma<32>, dim3(lg), dim3(SUBL_BLOCK), llds, s, x, n, lper, lperm, lz, lzrow,
-                           zsub, packed, K, k_max, t, seed, ndev);
-      if ((e = hipGetLastError()) != hipSuccess) return e;
+  if (sample && d >= 32) {
+    // the sub-labels in their own pass on the matrix cores, then the statistics.  With
+    // BF16 tables (d = 64, 128) a bf16x3 pass draws most rows first and the FP32 kernel
+    // only the list it leaves
+    if (x3 && (d == 64 || d == 128)) {
+      e = launch_sub_labels_x3(d, x, n, perm, z, zrow, zsub, packed, K, k_max, t, seed, *x3, s);
+      if (e != hipSuccess) return e;
+      e = launch_sub_labels_mx(d, x, n, x3->perm_c, nullptr, x3->zrow_c, zsub, packed, K, k_max, t, seed, s,
+                               x3->offs + SUBX_GROUPS);
+    } else {
+      e = launch_sub_labels_mx(d, x, n, perm, z, zrow, zsub, packed, K, k_max, t, seed, s);
     }
-    sample = false;
-  }
-  if (sample && d > 32) {
-    e = launch_sub_labels_mx(d, x, n, perm, z, zrow, zsub, packed, K, k_max, t, seed, s);
     if (e != hipSuccess) return e;
+    sample = false;
   }
   if (d > 32) {
     const int R = big_rows_of(big_dim(d));
