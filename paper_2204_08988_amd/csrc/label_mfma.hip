@@ -1080,7 +1080,10 @@ __global__ __launch_bounds__(SUBX_BLOCK, 1) void k_sub_labels_x3(
     for (;;) {
       if (cur != staged) {
         __syncthreads();  // every wave is done with the previous tables
-        for (int f = threadIdx.x; f < 4 * NFZ; f += SUBX_BLOCK) {
+        static_assert(4 * NFZ % SUBX_BLOCK == 0, "whole passes");
+#pragma unroll
+        for (int f0 = 0; f0 < 4 * NFZ; f0 += SUBX_BLOCK) {
+          const int f = f0 + threadIdx.x;
           const int part = f / NFZ, g = f - part * NFZ;  // part = 2 sub + (lo)
           const int tt = g >> 6;
           int mt = 0, o = 0;
@@ -1105,7 +1108,14 @@ __global__ __launch_bounds__(SUBX_BLOCK, 1) void k_sub_labels_x3(
           const int i = threadIdx.x;
           const float* w1 = r1 + 4 + D + i * (i + 1) / 2;
           float c = 0.0f;
-          for (int k = 0; k <= i; ++k) c = fmaf(w1[k], s_dmu[k], c);
+          // 32 reads in flight (one at a time they took 80 us at d = 128)
+          for (int k0 = 0; k0 <= i; k0 += 32) {
+            float w[32];
+#pragma unroll
+            for (int e = 0; e < 32; ++e) w[e] = w1[k0 + e <= i ? k0 + e : i];
+#pragma unroll
+            for (int e = 0; e < 32; ++e) c = k0 + e <= i ? fmaf(w[e], s_dmu[k0 + e], c) : c;
+          }
           s_corr[i] = c;
         }
         __syncthreads();
