@@ -52,7 +52,7 @@ PEAK_BF16_MFMA = 2.5e15    # dense BF16 matrix-core peak
 PEAK_FP32_MFMA = 157.3e12  # dense FP32 matrix-core peak
 PEAK_FP64_MFMA = 78.6e12   # dense FP64 matrix-core peak
 HEADLINE = "gauss_d128"
-HEADLINE_DRAW = "k_guess, counting sort, k_label_sorted, k_label_gauss_mfma_uc<128, 512, 8, true>"
+HEADLINE_DRAW = "k_guess, counting sort, k_sorted_x3<128, true>, k_label_gauss_mfma_uc<128, 512, 8, true>"
 
 
 def flops_per_eval(d):

@@ -841,9 +841,13 @@ dpmm_status label_phase(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t, int
                                  ctx->stream), "guess kernel");
       DPMM_HIP(ctx, launch_sort_by_z(z, n, ctx->K, *G, *per, true, ctx->d_hist, ctx->d_tot, ctx->d_offs, ctx->d_perm,
                                      ctx->d_zsort, ctx->stream, mode), "sort by guess");
-      DPMM_HIP(ctx, launch_label_sorted(ctx->d, (const float*)x, n, ctx->d_packed, ctx->K, ctx->d_perm, ctx->d_zsort, t,
-                                        ctx->cfg.seed, pb, mfma, mfma, z, ctx->stream), "label kernel");
-      if (!mfma) return DPMM_OK;
+      if (!mfma) {
+        DPMM_HIP(ctx, launch_label_sorted(ctx->d, (const float*)x, n, ctx->d_packed, ctx->K, ctx->d_perm, ctx->d_zsort,
+                                          t, ctx->cfg.seed, pb.ub, z, ctx->stream), "label kernel");
+        return DPMM_OK;
+      }
+      DPMM_HIP(ctx, launch_settle(ctx->d, (const float*)x, n, ctx->d_perm, ctx->d_zsort, ctx->d_packed, ctx->d_whi,
+                                  ctx->d_wlo, ctx->K, ctx->cfg.k_max, pb, z, ctx->stream), "label kernel");
     }
     if (mfma) {
       const OpenList ol{mode, pb.open, pb.n_open};

@@ -127,7 +127,7 @@ hipError_t launch_label_gauss_mx(int d, const float* x, long long n, int G, long
 constexpr int PRUNE_MIN_D = 48;
 bool label_prune_pays(int d, int K, long long n, bool bf16);
 size_t guess_table_bytes(int d, int k_max);
-// ub: n floats; mode, n_open: an int each; open: n ints (list)
+// ub: n floats; mode, n_open: an int each; open: n ints (BF16)
 struct PruneBufs {
   unsigned char* tab;
   float* ub;
@@ -137,11 +137,13 @@ struct PruneBufs {
 // sample, and this, the sort and the draw run only if so (n >= 512)
 hipError_t launch_guess(int d, const float* x, long long n, int G, long long per_block, const float* packed, int K,
                         const PruneBufs& b, bool probe, int* z, int* hist, hipStream_t s);
-// list (d = 64, 128): the points that another cluster may win are left to the BF16
-// main pass and listed in open
+// FP32: the draw over the rows sorted by the guess
 hipError_t launch_label_sorted(int d, const float* x, long long n, const float* packed, int K, const int* perm,
-                               const int* guess, uint32_t t, uint64_t seed, const PruneBufs& b, bool list, bool probe,
-                               int* z, hipStream_t s);
+                               const int* guess, uint32_t t, uint64_t seed, const float* ub, int* z, hipStream_t s);
+// BF16 (d = 64, 128): the points that no other cluster may win get their guess, the
+// others are listed in open
+hipError_t launch_settle(int d, const float* x, long long n, const int* perm, const int* guess, const float* packed,
+                         const void* whi, const void* wlo, int K, int k_max, const PruneBufs& b, int* z, hipStream_t s);
 // block_rows: rows per block while n allows at most 2048 blocks (256 or 512)
 hipError_t sorted_plan(long long n, int K, long long hist_cap, int* G, long long* per_block, int block_rows = 512);
 // mode (may be null): where *mode is 0, have_hist: nothing is done; else: hist is there
@@ -208,7 +210,7 @@ hipError_t launch_sub_labels_x3(int d, const float* x, long long n, const int* p
 // int[n][RESCORE_CAND], each deferred point's candidate clusters (-1: empty
 // slot, -2 in slot 0: all clusters); n_flagged: one device int
 // by_guess (d = 64, 128 in BF16 where uc_list_fits): the main pass takes the listed
-// points that launch_label_sorted left open, or where *mode is 0 all as without it
+// points that launch_settle left open, or where *mode is 0 all as without it
 struct OpenList {
   const int *mode, *open, *n_open;
 };

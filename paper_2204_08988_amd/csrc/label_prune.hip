@@ -11,13 +11,15 @@
 //                 same products, an upper bound of the scores of all others;
 //   the counting sort of the rows by guess (sorted.hip), so that the 64 points of a
 //                 wave share theirs;
-//   k_label_sorted  per 256 sorted rows: their guessed clusters in full in FP32, which
-//                 with the bound settles most points.  For the others of an FP32
-//                 draw every cluster's first 16 rows, then in full the clusters still
-//                 in range for some point of the wave; a BF16 draw lists them for its
-//                 main pass (label_mfma.hip).  The draw of the points (score.hpp)
+//   k_label_sorted  (FP32) per 256 sorted rows: their guessed clusters in full, which
+//                 with the bound settles most points.  For the others every
+//                 cluster's first 16 rows, then in full the clusters still in range
+//                 for some point of the wave.  The draw of the points (score.hpp)
 //                 takes the clusters in that order and gives the argmax of
-//                 l_k + g_k with the smaller k on ties, as in increasing order.
+//                 l_k + g_k with the smaller k on ties, as in increasing order;
+//   k_sorted_x3   (BF16, label_mfma.hip) the guessed clusters in full in bf16x3, which
+//                 with the bound settles most points, and a list of the others for
+//                 the main pass.
 // Scores have the bits of the kernel that forms them all (label_gauss_mx.hip), so
 // the labels are the same whatever the data.  A BF16 draw, whose main pass over all
 // points is within three times of this, first looks at 512 of the points (k_guess
@@ -28,10 +30,10 @@
 // K = 32 686 -> 246; d = 128, N = 1e5, K = 64 1589 -> 522; d = 48, N = 1e5, K = 64 348
 // -> 219.  Where nearly every cluster stays in range of every point (means
 // N(0, 0.01 I)) the extra passes cost 6 to 9% at d = 128, 13 to 19% at d = 64, 18 to
-// 25% at d = 48.  BF16: d = 128, N = 2e6, K = 100, means N(0, 9 I) 5230 -> 2900
-// (draw 3.1 -> 1.3 ms: guess 0.47, sort and probe 0.15, whole scores 0.42, open points
+// 25% at d = 48.  BF16: d = 128, N = 2e6, K = 100, means N(0, 9 I) 5230 -> 2400
+// (draw 3.1 -> 1.1 ms: guess 0.47, sort and probe 0.15, whole scores 0.26, open points
 // 0.15), N(0, 2.25 I) 5263 and 5329, N(0, 0.09 I) 7480 and 7386; d = 64, N = 2e6,
-// K = 200, N(0, 4 I) 3307 -> 2260, K = 50, N(0, 0.25 I) 1578 and 1484.
+// K = 200, N(0, 4 I) 3307 -> 2060, K = 50, N(0, 0.25 I) 1578 and 1484.
 #include "interval.hpp"
 #include "kernels.hpp"
 #include "score.hpp"
@@ -145,27 +147,30 @@ __global__ __launch_bounds__(128) void k_pack_guess(int K, int d, const float* _
 constexpr float PR_REL = 1e-6f;
 
 template <bool PROBE>
-__global__ __launch_bounds__(GBLOCK, 2) void k_guess(const float* __restrict__ x, long long n, int d,
+__global__ __launch_bounds__(PROBE ? 2 * GBLOCK : GBLOCK, 2) void k_guess(const float* __restrict__ x, long long n, int d,
                                                      long long per_block, const unsigned char* __restrict__ tab, int K,
                                                      int cg, int* __restrict__ z, int* __restrict__ hist,
                                                      float* __restrict__ ub, int* mode, long long stride) {
   typedef float f32x4u __attribute__((ext_vector_type(4), aligned(4)));
   typedef float f32x4 __attribute__((ext_vector_type(4)));
+  // 32-point tiles of a wave (the single workgroup of the probe has twice the waves)
+  constexpr int BLK = PROBE ? 2 * GBLOCK : GBLOCK, TILES = PROBE ? 2 : 4, OWN = TILES / 2;
+  static_assert(BLK / 64 * 32 * TILES == GSTEP, "points per step");
   if (!PROBE && mode && *mode != 1) return;
   extern __shared__ __align__(16) unsigned char smem_g[];
-  __shared__ int s_sure[GBLOCK / 64];
+  __shared__ int s_sure[BLK / 64];
   const bool single = cg >= K;
   unsigned char* buf0 = smem_g;
   unsigned char* buf1 = single ? smem_g : smem_g + cg * GT_BYTES;
   int* h = reinterpret_cast<int*>(smem_g + (single ? 1 : 2) * cg * GT_BYTES);
   if (!PROBE)
-    for (int k = threadIdx.x; k < K; k += GBLOCK) h[k] = 0;
+    for (int k = threadIdx.x; k < K; k += BLK) h[k] = 0;
   const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const long long begin = (long long)blockIdx.x * per_block;
   const long long end = begin + per_block < n ? begin + per_block : n;
   auto fetch = [&](unsigned char* dst, int k0, int nk) {
-    mx::stage<GBLOCK>(reinterpret_cast<float*>(dst), reinterpret_cast<const float*>(tab + (size_t)k0 * GT_BYTES),
+    mx::stage<BLK>(reinterpret_cast<float*>(dst), reinterpret_cast<const float*>(tab + (size_t)k0 * GT_BYTES),
                       nk * (GT_BYTES / 4));
   };
   float cen[2][8];
@@ -187,11 +192,11 @@ __global__ __launch_bounds__(GBLOCK, 2) void k_guess(const float* __restrict__ x
   int sure = 0;  // PROBE: the wave's points settled
   bool odd = false;
   for (long long chunk = begin; chunk < end; chunk += GSTEP) {
-    const long long base = chunk + wave * 128;
-    bf16x8 b[4][2];  // [tile][k-step]
-    float rx[4];     // the lane's half of ||x'||^2, then ||x'|| of its own two points
+    const long long base = chunk + wave * 32 * TILES;
+    bf16x8 b[TILES][2];  // [tile][k-step]
+    float rx[TILES]; // the lane's half of ||x'||^2, then ||x'|| of its own two points
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < TILES; ++t) {
       const long long p = base + 32 * t + col;
       const bool ok = p < end;
       const float* xr = x + (ok ? (size_t)(PROBE ? p * stride : p) * d : 0) + 8 * half;
@@ -209,14 +214,17 @@ __global__ __launch_bounds__(GBLOCK, 2) void k_guess(const float* __restrict__ x
         }
       }
     }
-    rx[0] = __builtin_amdgcn_sqrtf(own(rx[0], rx[1]));
-    rx[1] = __builtin_amdgcn_sqrtf(own(rx[2], rx[3]));
-    // points lane and 64 + lane of the wave: the best marginal, its cluster and its
-    // bound, and the two largest bounds
-    float best[2] = {-INFINITY, -INFINITY}, mine[2], u1[2], u2[2], est[2];
-    int arg[2] = {0, 0};
 #pragma unroll
-    for (int u = 0; u < 2; ++u) mine[u] = u1[u] = u2[u] = est[u] = -INFINITY;
+    for (int u = 0; u < OWN; ++u) rx[u] = __builtin_amdgcn_sqrtf(own(rx[2 * u], rx[2 * u + 1]));
+    // points lane (and 64 + lane) of the wave: the best marginal, its cluster and its
+    // bound, and the two largest bounds
+    float best[OWN], mine[OWN], u1[OWN], u2[OWN], est[OWN];
+    int arg[OWN];
+#pragma unroll
+    for (int u = 0; u < OWN; ++u) {
+      best[u] = mine[u] = u1[u] = u2[u] = est[u] = -INFINITY;
+      arg[u] = 0;
+    }
     for (int g0 = 0; g0 < K; g0 += cg) {
       const int nk = K - g0 < cg ? K - g0 : cg;
       if (!single) {
@@ -238,9 +246,9 @@ __global__ __launch_bounds__(GBLOCK, 2) void k_guess(const float* __restrict__ x
           for (int j = 0; j < 4; ++j) off[4 * q + j] = u[j];
         }
         const f32x4 kc = *(lds_f32x4*)(e + GT_W + GT_B);
-        float qs[4];
+        float qs[TILES];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
+        for (int t = 0; t < TILES; ++t) {
           f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b[t][0], off, 0, 0, 0);
           acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b[t][1], acc, 0, 0, 0);
           float q0 = 0.0f, q1 = 0.0f;
@@ -252,7 +260,7 @@ __global__ __launch_bounds__(GBLOCK, 2) void k_guess(const float* __restrict__ x
           qs[t] = q0 + q1;
         }
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
+        for (int u = 0; u < OWN; ++u) {
           const float q = own(qs[2 * u], qs[2 * u + 1]);
           const float l = fmaf(-0.5f, q, kc.x), sq = __builtin_amdgcn_sqrtf(q);
           const float sm = fmaxf(sq - fmaf(UC_EPSS, sq, fmaf(kc.z, rx[u], kc.w)), 0.0f), h2 = 0.5f * sm * sm;
@@ -273,7 +281,7 @@ __global__ __launch_bounds__(GBLOCK, 2) void k_guess(const float* __restrict__ x
       }
     }
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < OWN; ++u) {
       const long long p = base + 64 * u + lane;
       const float other = mine[u] == u1[u] ? u2[u] : u1[u];
       if (PROBE) {
@@ -290,12 +298,12 @@ __global__ __launch_bounds__(GBLOCK, 2) void k_guess(const float* __restrict__ x
   if (PROBE) {
     if (threadIdx.x == 0) {
       int a = 0;
-      for (int w = 0; w < GBLOCK / 64; ++w) a += s_sure[w];
+      for (int w = 0; w < BLK / 64; ++w) a += s_sure[w];
       *mode = 4 * a >= 3 * (int)(end - begin) ? 1 : 0;
     }
     return;
   }
-  for (int k = threadIdx.x; k < K; k += GBLOCK) hist[(size_t)blockIdx.x * K + k] = h[k];
+  for (int k = threadIdx.x; k < K; k += BLK) hist[(size_t)blockIdx.x * K + k] = h[k];
 }
 
 constexpr int SBLOCK = 256;
@@ -309,17 +317,12 @@ constexpr int HEAD_GROUP = 64;
 // FP32 matrix cores and the vector ALUs: per 64 points a whole evaluation (26 k
 // cycles at d = 128: N = 2e6 0.42 ms, 2.5 TB/s of rows), and for a wave with a point that the guess's bound leaves open
 // about 0.8 k cycles per cluster for the heads and the clusters in range in full.
-// LIST (BF16 draw, whose main pass scores the open points in full 15 times cheaper):
-// the open points are listed instead.
-template <int RB, bool LIST>
+template <int RB>
 __global__ __launch_bounds__(SBLOCK, 2) void k_label_sorted(const float* __restrict__ x, long long n, int d,
                                                             const float* __restrict__ packed, int K, int hg,
                                                             const int* __restrict__ perm,
                                                             const int* __restrict__ guess, uint32_t t, uint64_t seed,
-                                                            int* __restrict__ z, const float* __restrict__ ub,
-                                                            const int* __restrict__ mode, int* __restrict__ opens,
-                                                            int* __restrict__ n_open) {
-  if (LIST && mode && *mode != 1) return;
+                                                            int* __restrict__ z, const float* __restrict__ ub) {
   extern __shared__ __align__(16) float smem_s[];
   __shared__ int s_k[SBLOCK];
   const int S = gauss_rec_stride(d), NW = (K + 31) >> 5;
@@ -348,8 +351,7 @@ __global__ __launch_bounds__(SBLOCK, 2) void k_label_sorted(const float* __restr
     mx::load_rows<RB>(xr, ok, d, xv);
     __syncthreads();  // the previous rows' tables are read
     s_k[threadIdx.x] = k;
-    if (!LIST)
-      for (int w = threadIdx.x; w < 8 * NW; w += SBLOCK) need[w] = 0u;
+    for (int w = threadIdx.x; w < 8 * NW; w += SBLOCK) need[w] = 0u;
     const float other = mine < n ? ub[i] : -INFINITY;  // what no other cluster exceeds
     bool open = mine < n;                              // a cluster beside those scored may win
     __syncthreads();
@@ -378,7 +380,7 @@ __global__ __launch_bounds__(SBLOCK, 2) void k_label_sorted(const float* __restr
       bool eval;
       if (w3 < 0) {
         eval = __ballot(k == cur) != 0ull;
-        if (!LIST && eval && lane == 0) my_done[cur >> 5] |= 1u << (cur & 31);
+        if (eval && lane == 0) my_done[cur >> 5] |= 1u << (cur & 31);
       } else {
         eval = (__builtin_amdgcn_readfirstlane(my_need[cur >> 5] & ~my_done[cur >> 5]) >> (cur & 31)) & 1u;
       }
@@ -399,16 +401,6 @@ __global__ __launch_bounds__(SBLOCK, 2) void k_label_sorted(const float* __restr
           continue;
         }
         open = open && !(other <= dr.floor());
-        if (LIST) {
-          const unsigned long long om = __ballot(open);
-          if (om != 0ull) {
-            int slot = 0;
-            if (lane == 0) slot = atomicAdd(n_open, __popcll(om));
-            slot = __builtin_amdgcn_readfirstlane(slot);
-            if (open) opens[slot + __popcll(om & ((1ull << lane) - 1ull))] = i;
-          }
-          break;
-        }
         if (!__syncthreads_or(open)) break;
         // (2) the heads of all clusters
         float xh[4][4];
@@ -454,7 +446,7 @@ __global__ __launch_bounds__(SBLOCK, 2) void k_label_sorted(const float* __restr
       bits &= bits - 1;
       cur = 32 * (w3 - 1) + bit;
     }
-    if (mine < n && !(LIST && open)) z[i] = dr.finish((uint32_t)i, t, seed);
+    if (mine < n) z[i] = dr.finish((uint32_t)i, t, seed);
   }
 }
 
@@ -488,7 +480,7 @@ hipError_t launch_guess(int d, const float* x, long long n, int G, long long per
     attr_set = true;
   }
   if (probe && n >= GSTEP)
-    hipLaunchKernelGGL(k_guess<true>, dim3(1), dim3(GBLOCK), lds, s, x, (long long)GSTEP, d, (long long)GSTEP, b.tab, K,
+    hipLaunchKernelGGL(k_guess<true>, dim3(1), dim3(2 * GBLOCK), lds, s, x, (long long)GSTEP, d, (long long)GSTEP, b.tab, K,
                        cg, z, hist, b.ub, b.mode, n / GSTEP);
   hipLaunchKernelGGL(k_guess<false>, dim3(G), dim3(GBLOCK), lds, s, x, n, d, per_block, b.tab, K, cg, z, hist, b.ub,
                      probe ? b.mode : nullptr, 1ll);
@@ -496,18 +488,16 @@ hipError_t launch_guess(int d, const float* x, long long n, int G, long long per
 }
 
 hipError_t launch_label_sorted(int d, const float* x, long long n, const float* packed, int K, const int* perm,
-                               const int* guess, uint32_t t, uint64_t seed, const PruneBufs& b, bool list, bool probe,
-                               int* z, hipStream_t s) {
+                               const int* guess, uint32_t t, uint64_t seed, const float* ub, int* z, hipStream_t s) {
   if (n == 0) return hipSuccess;
-  const int hg = list ? 0 : (K < HEAD_GROUP ? K : HEAD_GROUP);
+  const int hg = K < HEAD_GROUP ? K : HEAD_GROUP;
   const size_t lds = (size_t)(gauss_rec_stride(d) + hg * HEAD_S + 2 * mx::REC_PAD) * sizeof(float) +
-                     (size_t)(list ? 0 : 8 * ((K + 31) / 32)) * sizeof(uint32_t);
+                     (size_t)8 * ((K + 31) / 32) * sizeof(uint32_t);
   static bool attr_set = false;
   if (!attr_set) {
-    const void* fns[8] = {(const void*)k_label_sorted<3, false>, (const void*)k_label_sorted<4, false>,
-                          (const void*)k_label_sorted<5, false>, (const void*)k_label_sorted<6, false>,
-                          (const void*)k_label_sorted<7, false>, (const void*)k_label_sorted<8, false>,
-                          (const void*)k_label_sorted<4, true>,  (const void*)k_label_sorted<8, true>};
+    const void* fns[6] = {(const void*)k_label_sorted<3>, (const void*)k_label_sorted<4>,
+                          (const void*)k_label_sorted<5>, (const void*)k_label_sorted<6>,
+                          (const void*)k_label_sorted<7>, (const void*)k_label_sorted<8>};
     for (const void* f : fns) {
       const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 96 * 1024);
       if (e != hipSuccess) return e;
@@ -515,25 +505,16 @@ hipError_t launch_label_sorted(int d, const float* x, long long n, const float* 
     attr_set = true;
   }
   const unsigned G = (unsigned)((n + SBLOCK - 1) / SBLOCK < 65536 ? (n + SBLOCK - 1) / SBLOCK : 65536);
-#define DPMM_SORTED(RB, LIST)                                                                                        \
-  hipLaunchKernelGGL((k_label_sorted<RB, LIST>), dim3(G), dim3(SBLOCK), lds, s, x, n, d, packed, K, hg, perm, guess, \
-                     t, seed, z, b.ub, probe ? b.mode : nullptr, b.open, b.n_open)
-  if (list) {
-    if (d == 64)
-      DPMM_SORTED(4, true);
-    else if (d == 128)
-      DPMM_SORTED(8, true);
-    else
-      return hipErrorInvalidValue;
-    return hipGetLastError();
-  }
+#define DPMM_SORTED(RB)                                                                                              \
+  hipLaunchKernelGGL(k_label_sorted<RB>, dim3(G), dim3(SBLOCK), lds, s, x, n, d, packed, K, hg, perm, guess, t, seed, \
+                     z, ub)
   switch (mx::row_blocks(d)) {
-    case 3: DPMM_SORTED(3, false); break;
-    case 4: DPMM_SORTED(4, false); break;
-    case 5: DPMM_SORTED(5, false); break;
-    case 6: DPMM_SORTED(6, false); break;
-    case 7: DPMM_SORTED(7, false); break;
-    case 8: DPMM_SORTED(8, false); break;
+    case 3: DPMM_SORTED(3); break;
+    case 4: DPMM_SORTED(4); break;
+    case 5: DPMM_SORTED(5); break;
+    case 6: DPMM_SORTED(6); break;
+    case 7: DPMM_SORTED(7); break;
+    case 8: DPMM_SORTED(8); break;
     default: return hipErrorInvalidValue;
   }
 #undef DPMM_SORTED
