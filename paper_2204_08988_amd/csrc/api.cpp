@@ -510,7 +510,7 @@ dpmm_status dpmm_create(const dpmm_config* cfg, void* hip_stream, dpmm_ctx** out
       ok = ok && chk(c->alloc(&c->d_nflag, 2));
       // low parts: the bf16x3 form, and the candidate pass of either matrix-core form
       ok = ok && chk(c->alloc(&c->d_wlo, (size_t)km * d * d));
-      if (wbias_floats(d, km)) ok = ok && chk(c->alloc(&c->d_wbias, wbias_floats(d, km)));
+      if (cfg->precision == DPMM_BF16) ok = ok && chk(c->alloc(&c->d_wbias, wbias_floats(d, km)));
       if (d == 64 || d == 128) {
         ok = ok && chk(c->alloc(&c->d_shi, (size_t)2 * km * d * d));
         ok = ok && chk(c->alloc(&c->d_slo, (size_t)2 * km * d * d));

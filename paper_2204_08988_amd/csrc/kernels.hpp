@@ -183,7 +183,7 @@ hipError_t launch_partition_stats(int d, const float* x, long long npts, const i
                                   long long* counts, double* moments, const int* cspan, double* part, hipStream_t s);
 // BF16 matrix-core cluster draw (d in {32, 64}) and its whitener fragments
 bool mfma_supported(int d);
-// wbias (d = 64, 128; may be null): [k_max][d] offsets beta = -W (mu - c) in the
+// wbias (BF16; may be null): [k_max][d] offsets beta = -W (mu - c) in the
 // accumulator layout, [k_max][4] constants, [d] the common centre c, for the
 // uncentred BF16 main pass; wbias_floats(d, k_max) floats (0 for other d)
 size_t wbias_floats(int d, int k_max);

@@ -12,8 +12,8 @@
 // BF16X3 adds the two cross terms of the hi/lo split, W_hi dx_lo + W_lo dx_hi,
 // for about 16 mantissa bits.
 //
-// The BF16 main pass at d = 64, 128 (k_label_gauss_mfma_uc) centres the points
-// once on a centre common to all clusters and starts each cluster's
+// The BF16 main passes (k_label_gauss_uc32, k_label_gauss_mfma_uc) centre the points
+// once on a centre common to all clusters and start each cluster's
 // accumulators at W_k (c - mu_k), so that the rows are rounded to BF16 once per
 // step instead of once per cluster; each of its scores carries an interval
 // that bounds the BF16 and FP32 rounding errors.
@@ -29,6 +29,7 @@
 
 #include "interval.hpp"
 #include "kernels.hpp"
+#include "score_mx.hpp"
 #include "score.hpp"
 
 namespace dpmm {
@@ -40,8 +41,7 @@ typedef __attribute__((__vector_size__(16 * sizeof(float)))) float f32x16;
 
 namespace {
 
-// allowance on |l_bf16 - l_fp32| of a score with squared norm q
-constexpr float BF16_TOL_REL = 1.0f / 32.0f;
+// allowance on |l_bf16x3 - l_fp32| of a score with squared norm q
 constexpr float BF16X3_TOL_REL = 1.0f / 4096.0f;
 constexpr float TOL_ABS = 0.05f;
 constexpr int NCAND = RESCORE_CAND;
@@ -247,7 +247,7 @@ __global__ __launch_bounds__(256) void k_cands_merge(const int* __restrict__ n_f
 
 constexpr int BLOCK32 = 512;  // threads per workgroup of the d = 32 kernel
 
-// d = 32: the whitener fragments, means and constants of a group of up to CG
+// d = 32, bf16x3 main pass and candidate pass: the whitener fragments, means and constants of a group of up to CG
 // clusters are staged in LDS once and shared by the workgroup's eight waves
 // (when K <= CG, once per workgroup).  A wave scores 64 points (two 32-point
 // tiles) against each cluster of the group: the per-cluster centring in FP32,
@@ -255,7 +255,7 @@ constexpr int BLOCK32 = 512;  // threads per workgroup of the d = 32 kernel
 // the squared norm; the top-2 update is branch-free so that two clusters'
 // work interleaves.  Points whose top-2 gap leaves any doubt are appended to
 // `flagged` (z = -1, not in the histogram) for k_rescore_flagged.
-template <bool X3, bool CANDS>
+template <bool CANDS>
 __global__ __launch_bounds__(BLOCK32) void k_label_gauss_mfma32(const float* __restrict__ x, long long n,
                                                                 long long per_block, const float* __restrict__ packed,
                                                                 const bf16x8* __restrict__ whi,
@@ -263,9 +263,9 @@ __global__ __launch_bounds__(BLOCK32) void k_label_gauss_mfma32(const float* __r
                                                                 uint64_t seed, int* __restrict__ z, int* __restrict__ hist, int* __restrict__ flagged,
                                                                 int* __restrict__ cand, int* __restrict__ n_flagged) {
   constexpr int D = 32, KS = 2, NF = KS * 64;  // 16-byte fragments per cluster and table
-  constexpr float REL = X3 ? BF16X3_TOL_REL : BF16_TOL_REL;
-  constexpr int NB = X3 ? 2 : 1;               // tables per cluster (hi, lo)
-  constexpr int CG = X3 ? 16 : 32;             // clusters per LDS stage (64 KB of fragments)
+  constexpr float REL = BF16X3_TOL_REL;
+  constexpr int NB = 2;                        // tables per cluster (hi, lo)
+  constexpr int CG = 16;                       // clusters per LDS stage (64 KB of fragments)
   constexpr int MUS = D + 4;                   // mu[D], c, padding
   constexpr int S = (4 + D + D * (D + 1) / 2 + 3) & ~3;
   extern __shared__ __align__(16) unsigned char smem[];
@@ -284,7 +284,7 @@ __global__ __launch_bounds__(BLOCK32) void k_label_gauss_mfma32(const float* __r
     for (int e = threadIdx.x; e < cnt * NB * NF; e += BLOCK32) {
       const int c = e / (NB * NF), r = e - c * (NB * NF);
       const int tb = r / NF, f = r - tb * NF;
-      s_w[e] = (X3 && tb ? wlo : whi)[(size_t)(g0 + c) * NF + f];
+      s_w[e] = (tb ? wlo : whi)[(size_t)(g0 + c) * NF + f];
     }
     for (int e = threadIdx.x; e < cnt * MUS; e += BLOCK32) {
       const int c = e / MUS, j = e - c * MUS;
@@ -343,10 +343,8 @@ __global__ __launch_bounds__(BLOCK32) void k_label_gauss_mfma32(const float* __r
             const float da = xa[ks][q] - mu[q], db = xb[ks][q] - mu[q];
             ba[ks][q] = (__bf16)da;
             bb[ks][q] = (__bf16)db;
-            if (X3) {
-              bal[ks][q] = (__bf16)(da - (float)ba[ks][q]);
-              bbl[ks][q] = (__bf16)(db - (float)bb[ks][q]);
-            }
+            bal[ks][q] = (__bf16)(da - (float)ba[ks][q]);
+            bbl[ks][q] = (__bf16)(db - (float)bb[ks][q]);
           }
         }
         f32x16 acca = {0}, accb = {0};
@@ -355,13 +353,11 @@ __global__ __launch_bounds__(BLOCK32) void k_label_gauss_mfma32(const float* __r
           const bf16x8 w = cw[ks * 64 + lane];
           acca = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, ba[ks], acca, 0, 0, 0);
           accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, bb[ks], accb, 0, 0, 0);
-          if (X3) {
-            const bf16x8 wl = cw[NF + ks * 64 + lane];
-            acca = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wl, ba[ks], acca, 0, 0, 0);
-            accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wl, bb[ks], accb, 0, 0, 0);
-            acca = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, bal[ks], acca, 0, 0, 0);
-            accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, bbl[ks], accb, 0, 0, 0);
-          }
+          const bf16x8 wl = cw[NF + ks * 64 + lane];
+          acca = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wl, ba[ks], acca, 0, 0, 0);
+          accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(wl, bb[ks], accb, 0, 0, 0);
+          acca = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, bal[ks], acca, 0, 0, 0);
+          accb = __builtin_amdgcn_mfma_f32_32x32x16_bf16(w, bbl[ks], accb, 0, 0, 0);
         }
         float qa = 0.0f, qb = 0.0f;
 #pragma unroll
@@ -425,7 +421,7 @@ constexpr int BLOCK_W32 = 512;  // threads of k_label_gauss_mfma_w32: 8 waves of
 // label kernels (the per-workgroup histogram blocks are the same).  Points
 // whose top-2 gap leaves any doubt are appended to `flagged` (z = -1, not in
 // the histogram) for the candidate pass and k_rescore_flagged.
-template <int D, bool X3, bool CANDS>
+template <int D, bool CANDS>
 __global__ __launch_bounds__(BLOCK_W32) void k_label_gauss_mfma_w32(const float* __restrict__ x, long long n,
                                                                    long long per_block, const float* __restrict__ packed,
                                                                    const bf16x8* __restrict__ whi,
@@ -440,11 +436,11 @@ __global__ __launch_bounds__(BLOCK_W32) void k_label_gauss_mfma_w32(const float*
   constexpr int MT = TT::MT, KS = TT::KS, NF = MT * KS * 64;  // fragments per cluster in global memory
   constexpr int NFZ = TT::NT * 64;                              // fragments per cluster staged (non-zero tiles)
   constexpr int NJ = (NFZ + BLOCK_W32 - 1) / BLOCK_W32;
-  constexpr float REL = X3 ? BF16X3_TOL_REL : BF16_TOL_REL;
-  constexpr int NB = X3 ? 2 : 1;  // fragment tables per cluster (hi, lo)
+  constexpr float REL = BF16X3_TOL_REL;
+  constexpr int NB = 2;           // fragment tables per cluster (hi, lo)
   constexpr int MUS = D + 4;      // mu[D], c
   constexpr int CHUNK = BLOCK_W32 / 2;
-  constexpr int CPB = X3 ? 1 : (D == 64 ? 4 : 2);  // clusters per staging buffer (per barrier)
+  constexpr int CPB = 1;           // clusters per staging buffer (per barrier)
   static_assert(D < BLOCK_W32 && CHUNK == BLOCK && NFZ % 64 == 0, "staging layout, histogram blocks");
   __shared__ __align__(16) bf16x8 s_w0[CPB * NB * NFZ], s_w1[CPB * NB * NFZ];
   __shared__ __align__(16) float s_mu0[CPB * MUS], s_mu1[CPB * MUS];
@@ -487,8 +483,7 @@ __global__ __launch_bounds__(BLOCK_W32) void k_label_gauss_mfma_w32(const float*
             if (tt >= TT::off(m)) mt = m, o = TT::off(m);
           const size_t g = (size_t)k * NF + (size_t)(mt * KS + tt - o) * 64 + (f & 63);
           __builtin_amdgcn_global_load_lds((const void*)(whi + g), (lds_void*)(dw + j * BLOCK_W32 + wbase), 16, 0, 0);
-          if (X3)
-            __builtin_amdgcn_global_load_lds((const void*)(wlo + g), (lds_void*)(dw + NFZ + j * BLOCK_W32 + wbase), 16,
+          __builtin_amdgcn_global_load_lds((const void*)(wlo + g), (lds_void*)(dw + NFZ + j * BLOCK_W32 + wbase), 16,
                                              0, 0);
         }
       }
@@ -542,7 +537,7 @@ __global__ __launch_bounds__(BLOCK_W32) void k_label_gauss_mfma_w32(const float*
         for (int q = 0; q < 8; ++q) {
           const float dv = xv[ks][q] - cmu[16 * ks + 8 * half + q];
           b[ks][q] = (__bf16)dv;
-          if (X3) bl[ks][q] = (__bf16)(dv - (float)b[ks][q]);
+          bl[ks][q] = (__bf16)(dv - (float)b[ks][q]);
         }
 #pragma unroll
       for (int mt = 0; mt < MT; ++mt) {
@@ -552,11 +547,9 @@ __global__ __launch_bounds__(BLOCK_W32) void k_label_gauss_mfma_w32(const float*
           const int tile = TT::off(mt) + ks;
           const bf16x8 a = cw[tile * 64 + lane];
           acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, b[ks], acc, 0, 0, 0);
-          if (X3) {
-            const bf16x8 al = cwl[tile * 64 + lane];
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, b[ks], acc, 0, 0, 0);
-            acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bl[ks], acc, 0, 0, 0);
-          }
+          const bf16x8 al = cwl[tile * 64 + lane];
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(al, b[ks], acc, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a, bl[ks], acc, 0, 0, 0);
         }
 #pragma unroll
         for (int e = 0; e < 16; e += 2) {
@@ -639,6 +632,147 @@ __device__ __forceinline__ void top2_merge(Top2U& a, float u1, float u2, float l
 
 constexpr int UC_BUF_DWORD3 = 0x00020000;  // raw buffer descriptor word 3 (gfx9 family)
 constexpr int UC_NT = 2;                    // cache policy of the row loads: non-temporal
+
+// Main pass for d = 32 in BF16, uncentred: a wave takes 128 points (four 32-point
+// tiles), centred once on the common centre c and rounded to BF16, and walks the
+// clusters, whose fragments, offsets beta = -W (mu - c) (the accumulators' start)
+// and constants come through LDS, eight clusters at a time in two buffers (all of
+// them at once up to sixteen).  Scores, intervals and the draw's rule as in
+// k_label_gauss_mfma_uc.  N = 1e6, K = 20: 78 -> 60 us against the
+// kernel that centred the rows on every cluster's mean, as k_label_gauss_mfma32 does.
+constexpr int U32_BLOCK = 256, U32_STEP = 512;
+
+__global__ __launch_bounds__(U32_BLOCK, 4) void k_label_gauss_uc32(const float* __restrict__ x, long long n,
+                                                                   long long per_block,
+                                                                   const bf16x8* __restrict__ whi,
+                                                                   const float* __restrict__ wbias, int K, int k_max,
+                                                                   int cg, int* __restrict__ z, int* __restrict__ hist,
+                                                                   int* __restrict__ flagged,
+                                                                   int* __restrict__ n_flagged) {
+  constexpr int D = 32, NF = 128;           // fragments of a cluster
+  constexpr int CB = NF * 16 + D * 4 + 16;  // its bytes in LDS
+  typedef float f32x4 __attribute__((ext_vector_type(4)));
+  typedef __attribute__((address_space(3))) const unsigned char lds_uchar;
+  typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
+  typedef __attribute__((address_space(3))) const f32x4 lds_f32x4;
+  extern __shared__ __align__(16) unsigned char smem[];
+  const bool single = cg >= K;
+  unsigned char* buf[2] = {smem, single ? smem : smem + cg * CB};
+  int* h = reinterpret_cast<int*>(smem + (single ? 1 : 2) * cg * CB);
+  for (int k = threadIdx.x; k < K; k += U32_BLOCK) h[k] = 0;
+  const float* cst = wbias + (size_t)k_max * D;           // [k_max][4]
+  const float* centre = wbias + (size_t)k_max * (D + 4);  // [D]
+  const int lane = threadIdx.x & 63, half = lane >> 5, col = lane & 31;
+  const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const long long begin = (long long)blockIdx.x * per_block;
+  const long long end = begin + per_block < n ? begin + per_block : n;
+  // [cg] fragments, [cg] offsets, [cg] constants
+  auto fetch = [&](unsigned char* dst, int k0, int nk) {
+    float* f = reinterpret_cast<float*>(dst);
+    mx::stage<U32_BLOCK>(f, reinterpret_cast<const float*>(whi + (size_t)k0 * NF), nk * NF * 4);
+    mx::stage<U32_BLOCK>(f + cg * NF * 4, wbias + (size_t)k0 * D, nk * D);
+    mx::stage<U32_BLOCK>(f + cg * (NF * 4 + D), cst + (size_t)k0 * 4, nk * 4);
+  };
+  float cen[2][8];
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) cen[ks][q] = centre[16 * ks + 8 * half + q];
+  if (begin < end) fetch(buf[0], 0, cg < K ? cg : K);
+  __builtin_amdgcn_s_waitcnt(0);
+  __syncthreads();
+  // both halves' sums of tiles a (lower lanes) and b (upper lanes): the lane's own point
+  auto own = [&](float a, float b) __attribute__((always_inline)) {
+    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+    return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+  };
+  bool odd = false;
+  for (long long chunk = begin; chunk < end; chunk += U32_STEP) {
+    const long long base = chunk + wave * 128;
+    bf16x8 b[4][2];  // [tile][k-step]
+    float rx[4];     // the lane's half of ||x'||^2, then ||x'|| of its own two points
+#pragma unroll
+    for (int t = 0; t < 4; ++t) {
+      const long long p = base + 32 * t + col;
+      const float4* xr = reinterpret_cast<const float4*>(x + (p < end ? (size_t)p * D : 0) + 8 * half);
+      rx[t] = 0.0f;
+#pragma unroll
+      for (int ks = 0; ks < 2; ++ks) {
+        const float4 u = xr[4 * ks], v = xr[4 * ks + 1];
+        const float f[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
+#pragma unroll
+        for (int q = 0; q < 8; ++q) {
+          const float e = f[q] - cen[ks][q];
+          rx[t] = fmaf(e, e, rx[t]);
+          b[t][ks][q] = (__bf16)e;
+        }
+      }
+    }
+    rx[0] = __builtin_amdgcn_sqrtf(own(rx[0], rx[1]));
+    rx[1] = __builtin_amdgcn_sqrtf(own(rx[2], rx[3]));
+    Top2U st[2];  // points lane and 64 + lane of the wave
+    st[0].init();
+    st[1].init();
+    for (int g0 = 0; g0 < K; g0 += cg) {
+      const int nk = K - g0 < cg ? K - g0 : cg;
+      if (!single) {
+        const bool wrap = g0 + cg >= K;
+        const int gn = wrap ? 0 : g0 + cg;
+        if (!wrap || chunk + U32_STEP < end) fetch(buf[odd ? 0 : 1], gn, K - gn < cg ? K - gn : cg);
+      }
+      lds_uchar* e = (lds_uchar*)buf[odd ? 1 : 0];
+      lds_uchar* eo = e + cg * NF * 16;
+      lds_uchar* ec = eo + cg * D * 4;
+      for (int c = 0; c < nk; ++c, e += NF * 16, eo += D * 4, ec += 16) {
+        const bf16x8 a0 = ((lds_bf16x8*)e)[lane], a1 = ((lds_bf16x8*)e)[64 + lane];
+        f32x16 off;
+#pragma unroll
+        for (int q = 0; q < 4; ++q) {
+          const f32x4 u = ((lds_f32x4*)eo)[4 * half + q];
+#pragma unroll
+          for (int j = 0; j < 4; ++j) off[4 * q + j] = u[j];
+        }
+        const f32x4 kc = *(lds_f32x4*)ec;
+        float qs[4];
+#pragma unroll
+        for (int t = 0; t < 4; ++t) {
+          f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b[t][0], off, 0, 0, 0);
+          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b[t][1], acc, 0, 0, 0);
+          float q0 = 0.0f, q1 = 0.0f;
+#pragma unroll
+          for (int r = 0; r < 16; r += 2) {
+            q0 = fmaf(acc[r], acc[r], q0);
+            q1 = fmaf(acc[r + 1], acc[r + 1], q1);
+          }
+          qs[t] = q0 + q1;
+        }
+#pragma unroll
+        for (int u = 0; u < 2; ++u) {
+          const float sq = __builtin_amdgcn_sqrtf(own(qs[2 * u], qs[2 * u + 1]));
+          const float er = fmaf(UC_EPSS, sq, fmaf(kc.y, rx[u], kc.z));
+          const float sp = sq + er, sm = fmaxf(sq - er, 0.0f);
+          const float lo = fmaf(-0.5f * sp, sp, kc.x), up = fmaf(-0.5f * sm, sm, kc.x);
+          st[u].k1 = up > st[u].u1 ? g0 + c : st[u].k1;
+          st[u].u2 = __builtin_amdgcn_fmed3f(st[u].u1, st[u].u2, up);
+          st[u].u1 = fmaxf(st[u].u1, up);
+          st[u].lo_max = fmaxf(st[u].lo_max, lo);
+        }
+      }
+      if (!single) {
+        __builtin_amdgcn_s_waitcnt(0);
+        __syncthreads();
+        odd = !odd;
+      }
+    }
+#pragma unroll
+    for (int u = 0; u < 2; ++u) {
+      const long long p = base + 64 * u + lane;
+      finish_main(p < end, p, st[u], z, h, flagged, n_flagged, lane);
+    }
+  }
+  __syncthreads();
+  for (int k = threadIdx.x; k < K; k += U32_BLOCK) hist[(size_t)blockIdx.x * K + k] = h[k];
+}
 
 // Main pass for d = 64, 128 in BF16, cluster-stationary and uncentred: the
 // workgroup's NWAVE waves (eight, or four with two workgroups per CU) take PTS
@@ -1381,9 +1515,54 @@ __global__ __launch_bounds__(D) void k_pack_bias(int K, int k_max, const float* 
   }
 }
 
+// The same table for d = 32, the centre (of the first 64 means) formed by every block.
+__global__ __launch_bounds__(64) void k_pack_bias32(int K, int k_max, const float* __restrict__ packed,
+                                                    float* __restrict__ wbias) {
+  constexpr int D = 32, S = (4 + D + D * (D + 1) / 2 + 3) & ~3;
+  __shared__ double dm[D];
+  const int k = blockIdx.x, lane = threadIdx.x, j = lane & 31, m = K < 64 ? K : 64;
+  const float* rec = packed + (size_t)k * S;
+  float s = 0.0f;
+#pragma unroll
+  for (int q = 0; q < 32; ++q) {
+    const int c = 2 * q + (lane >> 5);
+    s += c < m ? packed[(size_t)(c < m ? c : 0) * S + 4 + j] : 0.0f;
+  }
+  s += __shfl_xor(s, 32);
+  const float cen = s / (float)m;
+  if (lane < D) {
+    dm[j] = (double)rec[4 + j] - (double)cen;
+    if (k == 0) wbias[(size_t)k_max * (D + 4) + j] = cen;
+  }
+  __syncthreads();
+  const float* w = rec + 4 + D + j * (j + 1) / 2;
+  double b = 0.0, wn = 0.0, m2 = dm[j] * dm[j];
+  for (int i = 0; i <= j; ++i) {
+    const double wji = (double)w[i];
+    b = fma(wji, dm[i], b);
+    wn = fma(wji, wji, wn);
+  }
+  const int hh = (j >> 2) & 1, r = ((j >> 3) << 2) | (j & 3);
+  if (lane < D) wbias[(size_t)k * D + hh * 16 + r] = (float)(-b);
+#pragma unroll
+  for (int o = 16; o > 0; o >>= 1) {
+    wn += __shfl_xor(wn, o);
+    m2 += __shfl_xor(m2, o);
+  }
+  if (lane == 0) {
+    const double f = sqrt(wn) * (1.0 + 1e-6);
+    float4 c;
+    c.x = rec[0];
+    c.y = (float)(((double)UC_GAMMA + (double)UC_GAMMA2) * f);
+    c.z = (float)((double)UC_GAMMA2 * f * sqrt(m2) * (1.0 + 1e-6));
+    c.w = 0.0f;
+    reinterpret_cast<float4*>(wbias + (size_t)k_max * D)[k] = c;
+  }
+}
+
 }  // namespace
 
-size_t wbias_floats(int d, int k_max) { return (d == 64 || d == 128) ? (size_t)k_max * (d + 4) + d : 0; }
+size_t wbias_floats(int d, int k_max) { return mfma_supported(d) ? (size_t)k_max * (d + 4) + d : 0; }
 
 size_t sorted_x3_lds(int d, bool settle) {
   const int nt = d == 128 ? 20 : 6;
@@ -1462,7 +1641,9 @@ hipError_t launch_pack_wfrag(int K, int d, int k_max, const float* packed, void*
   hipLaunchKernelGGL(k_pack_wfrag, dim3(K), dim3(256), 0, s, K, d, 0, packed, (__bf16*)whi, (__bf16*)wlo);
   // the sub-clusters' records follow the clusters' (slot k_max + 2 k + h)
   if (shi) hipLaunchKernelGGL(k_pack_wfrag, dim3(2 * K), dim3(256), 0, s, 2 * K, d, k_max, packed, (__bf16*)shi, (__bf16*)slo);
-  if (wbias && (d == 64 || d == 128)) {
+  if (wbias && d == 32) {
+    hipLaunchKernelGGL(k_pack_bias32, dim3(K), dim3(64), 0, s, K, k_max, packed, wbias);
+  } else if (wbias) {
     hipLaunchKernelGGL(k_pack_centre, dim3(1), dim3(128), 0, s, K, d, packed, wbias + (size_t)k_max * (d + 4));
     if (d == 128)
       hipLaunchKernelGGL(k_pack_bias<128>, dim3(K), dim3(128), 0, s, K, k_max, packed, wbias);
@@ -1485,10 +1666,9 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
   if (e != hipSuccess) return e;
   static bool attr_set = false;
   if (!attr_set) {  // d = 32 and the uncentred kernels: more than 64 KB of dynamic LDS (160 KB per CU)
-    const void* fns[10] = {(const void*)k_label_gauss_mfma_uc<128, 512, 8, true>,
+    const void* fns[9] = {(const void*)k_label_gauss_mfma_uc<128, 512, 8, true>,
                           (const void*)k_label_gauss_mfma_uc<64, 256, 4, true>,
-                          (const void*)k_label_gauss_mfma32<true, false>, (const void*)k_label_gauss_mfma32<false, false>,
-                          (const void*)k_label_gauss_mfma32<true, true>,
+                          (const void*)k_label_gauss_mfma32<false>, (const void*)k_label_gauss_mfma32<true>,
                           (const void*)k_label_gauss_mfma_uc<64, 256, 4>, (const void*)k_label_gauss_mfma_uc<128, 512, 8>,
                           (const void*)k_label_gauss_mfma_uc<64, 512, 8>, (const void*)k_label_gauss_mfma_uc<128, 256, 8>,
                           (const void*)k_label_gauss_mfma_uc<64, 256, 8>};
@@ -1549,8 +1729,8 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
 #undef DPMM_UC
     } else if (d == 64 || d == 128) {
       // static staging buffers; only the histogram is dynamic
-#define DPMM_MFMA_W32(DD, XX, CC)                                                                            \
-  hipExtLaunchKernelGGL((k_label_gauss_mfma_w32<DD, XX, CC>), dim3(Gp), dim3(BLOCK_W32), lh, s, e0, e1, 0, x, n, \
+#define DPMM_MFMA_W32(DD, CC)                                                                                \
+  hipExtLaunchKernelGGL((k_label_gauss_mfma_w32<DD, CC>), dim3(Gp), dim3(BLOCK_W32), lh, s, e0, e1, 0, x, n, \
                         per_block, packed, hi, lo, K, t, seed, z, hist, flagged, cand, n_flagged, 1,        \
                         (CC) && cst ? CAND_SPLIT_CAP : 0, nullptr)
       // the candidate pass scores in bf16x3 whatever the main pass's form; while
@@ -1562,11 +1742,11 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
                                            ? (CAND_SPLIT_CAP + BLOCK_W32 / 2 - 1) / (BLOCK_W32 / 2)
                                            : Gp);
         if (d == 128)
-          hipLaunchKernelGGL((k_label_gauss_mfma_w32<128, true, true>), dim3(gx, CAND_SPLIT_NG), dim3(BLOCK_W32), lh, s,
+          hipLaunchKernelGGL((k_label_gauss_mfma_w32<128, true>), dim3(gx, CAND_SPLIT_NG), dim3(BLOCK_W32), lh, s,
                              x, n, per_block, packed, hi, lo, K, t, seed, z, hist, flagged, cand, n_flagged,
                              CAND_SPLIT_NG, CAND_SPLIT_CAP, cst);
         else
-          hipLaunchKernelGGL((k_label_gauss_mfma_w32<64, true, true>), dim3(gx, CAND_SPLIT_NG), dim3(BLOCK_W32), lh, s,
+          hipLaunchKernelGGL((k_label_gauss_mfma_w32<64, true>), dim3(gx, CAND_SPLIT_NG), dim3(BLOCK_W32), lh, s,
                              x, n, per_block, packed, hi, lo, K, t, seed, z, hist, flagged, cand, n_flagged,
                              CAND_SPLIT_NG, CAND_SPLIT_CAP, cst);
         if ((e = hipGetLastError()) != hipSuccess) return e;
@@ -1576,34 +1756,30 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
       }
       if (d == 128) {
         if (cands)
-          DPMM_MFMA_W32(128, true, true);
-        else if (x3)
-          DPMM_MFMA_W32(128, true, false);
+          DPMM_MFMA_W32(128, true);
         else
-          DPMM_MFMA_W32(128, false, false);
+          DPMM_MFMA_W32(128, false);
       } else {
         if (cands)
-          DPMM_MFMA_W32(64, true, true);
-        else if (x3)
-          DPMM_MFMA_W32(64, true, false);
+          DPMM_MFMA_W32(64, true);
         else
-          DPMM_MFMA_W32(64, false, false);
+          DPMM_MFMA_W32(64, false);
       }
 #undef DPMM_MFMA_W32
+    } else if (d == 32 && !cands && !x3 && wbias) {
+      const int cg = K <= 16 ? K : 8;
+      const size_t lu = (size_t)(K <= 16 ? 1 : 2) * cg * (128 * 16 + 32 * 4 + 16) + lh;
+      hipExtLaunchKernelGGL(k_label_gauss_uc32, dim3(Gp), dim3(U32_BLOCK), lu, s, e0, e1, 0, x, n, per_block, hi, wbias,
+                            K, k_max, cg, z, hist, flagged, n_flagged);
     } else if (d == 32) {
-      // [CG][NB][NF] fragments (64 KB), [CG][d + 4] means and constants, the histogram;
-      // the candidate pass scores in bf16x3
-      const size_t lds = (size_t)65536 + (size_t)(x3 || cands ? 16 : 32) * (d + 4) * sizeof(float) + lh;
-#define DPMM_MFMA32(XX, CC)                                                                                  \
-  hipExtLaunchKernelGGL((k_label_gauss_mfma32<XX, CC>), dim3(Gp), dim3(BLOCK32), lds, s, e0, e1, 0, x, n, per_block, \
-                        packed, hi, lo, K, t, seed, z, hist, flagged, cand, n_flagged)
+      // [CG][NB][NF] fragments (64 KB), [CG][d + 4] means and constants, the histogram
+      const size_t lds = (size_t)65536 + (size_t)16 * (d + 4) * sizeof(float) + lh;
       if (cands)
-        DPMM_MFMA32(true, true);
-      else if (x3)
-        DPMM_MFMA32(true, false);
+        hipExtLaunchKernelGGL(k_label_gauss_mfma32<true>, dim3(Gp), dim3(BLOCK32), lds, s, e0, e1, 0, x, n, per_block,
+                              packed, hi, lo, K, t, seed, z, hist, flagged, cand, n_flagged);
       else
-        DPMM_MFMA32(false, false);
-#undef DPMM_MFMA32
+        hipExtLaunchKernelGGL(k_label_gauss_mfma32<false>, dim3(Gp), dim3(BLOCK32), lds, s, e0, e1, 0, x, n, per_block,
+                              packed, hi, lo, K, t, seed, z, hist, flagged, cand, n_flagged);
     } else {
       return hipErrorInvalidValue;
     }

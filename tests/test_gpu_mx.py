@@ -97,7 +97,9 @@ def test_fp32_draw_by_guess(d, K, n, spread):
 
 # rows with a NaN, an infinity or values whose squares overflow, the first row among them: every row is drawn, and
 # as the FP32 context draws it
-@pytest.mark.parametrize("d,K,n", [(64, 4, 700), (64, 20, 12545), (128, 5, 513), (128, 9, 27801)])
+# (d = 32: one and two buffers of clusters, K = 16 | 17, ragged waves and steps)
+@pytest.mark.parametrize("d,K,n", [(64, 4, 700), (64, 20, 12545), (128, 5, 513), (128, 9, 27801), (32, 1, 1), (32, 16, 513),
+                                   (32, 17, 1025), (32, 25, 4223)])
 def test_bf16_draw_of_rows_without_a_score(d, K, n):
     import torch
 
