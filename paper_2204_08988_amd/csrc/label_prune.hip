@@ -30,9 +30,10 @@
 // 443; d = 64, N = 5e5, K = 16 631 -> 315; d = 48, N = 1e5, K = 64 349 -> 150.  Where
 // nearly every cluster stays in range of every point (means N(0, 0.01 I)) the extra
 // passes cost 6 to 8% at d = 128, 18% at d = 64, 19 to 32% at d = 48.
-// BF16: d = 128, N = 2e6, K = 100, means N(0, 9 I) 5230 -> 2400 (draw 3.1 -> 1.1 ms: guess 0.47, sort and probe 0.15, whole scores 0.26, open points
-// 0.15), N(0, 2.25 I) 5263 and 5329, N(0, 0.09 I) 7480 and 7386; d = 64, N = 2e6,
-// K = 200, N(0, 4 I) 3307 -> 2060, K = 50, N(0, 0.25 I) 1578 and 1484.
+// BF16: d = 128, N = 2e6, K = 100, means N(0, 9 I) 5230 -> 2400 (draw 3.1 -> 1.1 ms:
+// guess 0.47, sort and probe 0.15, whole scores 0.26, open points 0.15), N(0, 2.25 I)
+// 5263 and 5329, N(0, 0.09 I) 7480 and 7386; d = 64, N = 2e6, K = 200, N(0, 4 I) 3307
+// -> 2060, K = 50, N(0, 0.25 I) 1578 and 1484.
 #include "interval.hpp"
 #include "kernels.hpp"
 #include "score.hpp"
