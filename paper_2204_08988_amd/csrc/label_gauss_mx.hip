@@ -9,7 +9,8 @@
 // loads instead: at d = 128 a record of 33 KB does not stay in the 16 KB scalar
 // cache, and the draw ran at 11% of the vector ALUs' rate.
 //
-// Every score has the bits of the vector-ALU form, and the draw is the argmax
+// Every score has the bits of the vector-ALU form (a log-likelihood of a row with an
+// infinite coordinate too), and the draw is the argmax
 // of l_k + g_k (the smaller k on ties), so the labels are those of that form.
 //
 // Bound by the FP32 matrix cores and the vector ALUs together: on this chip the
@@ -152,6 +153,7 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_loglik_gauss_mx(const float* __
     const int rows = (int)(n - base < 64 ? (n - base > 0 ? n - base : 0) : 64);
     float xv[4][4 * RB];
     load_chunk<RB>(x, base, rows, d, xv);
+    bool odd_q = false;
     for (int g0 = jb; g0 < je; g0 += cg) {
       const int nj = je - g0 < cg ? je - g0 : cg;
       const bool wrap = g0 + cg >= je;
@@ -161,6 +163,7 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_loglik_gauss_mx(const float* __
       for (int c = 0; c < nj; ++c, rec += S) {
         float q;
         mx::sq_norm<RB>(rec, d, xv, q, mx::Always());
+        odd_q = odd_q || q != q;
         const int j = g0 + c, o = j % LL_GRP;
         tile[lane * (LL_GRP + 1) + o] = fmaf(-0.5f, q, rec[0]);
         if (o == LL_GRP - 1 || j == je - 1) {
@@ -180,6 +183,18 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_loglik_gauss_mx(const float* __
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
       odd = !odd;
+    }
+    // a score that is not a number: where the row has an infinity, again by the plain chain (the stores
+    // above have landed)
+    if (__ballot(odd_q)) {
+      const float* xr = x + (size_t)(base + (lane < rows ? lane : 0)) * d;
+      bool mine = false;
+      for (int c = 0; c < d; ++c) mine = mine || __builtin_isinf(xr[c]);
+      if (mine && lane < rows)
+        for (int j = jb; j < je; ++j) {
+          const float* rec = packed + (size_t)(j < K ? j : k_max + j - K) * S;
+          out[(size_t)(base + lane) * J + j] = fmaf(-0.5f, mx::sq_norm_row(rec, d, xr), rec[0]);
+        }
     }
   }
 }

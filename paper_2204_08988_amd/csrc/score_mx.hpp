@@ -7,7 +7,10 @@
 // results included).  A chain of these instructions over k is therefore the
 // chain y = fma(w[c], dx[c], y), c = 0, 1, ..., of the vector-ALU form, and the
 // zeros that pad W above its diagonal and below its last row leave a finite
-// chain unchanged (fma(0, dx, y) = y).  The squared norm q = fma(y_r, y_r, q)
+// chain unchanged (fma(0, dx, y) = y).  Times an infinite dx they give a NaN where
+// the chain over c <= r has none: a caller that returns the score takes such a row's
+// norm from sq_norm_row; a draw does not tell the two apart (a score of -inf and one
+// that is not a number both lose).  The squared norm q = fma(y_r, y_r, q)
 // runs over increasing r as there: after the rows of a 16-row block are formed,
 // a 4 x 4 transpose over the lane groups (v_permlane32_swap, v_permlane16_swap)
 // gives every lane all 16 rows of one point.
@@ -185,6 +188,21 @@ __device__ __forceinline__ bool sq_norm(lds_cfloat* p, int d, const float (&x)[4
     if (!last && !go(q)) return false;
   }
   return true;
+}
+
+// The squared norm of one row by the plain chain, row and record in memory: for rows
+// with an infinite coordinate.  Ends at the first row of W that gives a NaN.
+__device__ __forceinline__ float sq_norm_row(const float* __restrict__ p, int d, const float* __restrict__ x) {
+  const float* w = p + 4 + d;
+  float q = 0.0f;
+#pragma unroll 1
+  for (int r = 0; r < d && q == q; w += ++r) {
+    float y = 0.0f;
+#pragma unroll 1
+    for (int c = 0; c <= r; ++c) y = fmaf(w[c], x[c] - p[4 + c], y);
+    q = fmaf(y, y, q);
+  }
+  return q;
 }
 
 // Squared norm of W v + y0 for the rows v = x (already centred; d = 16 RB), W of the

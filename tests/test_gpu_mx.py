@@ -42,6 +42,35 @@ def test_fp32_draw_and_loglik(d, K, n, spread):
     S.close()
 
 
+# one infinite coordinate, at the first, a middle and the last column of a 16-row block, the last block ragged or not:
+# every whitened coordinate from it on is infinite and no other is touched, so every log-likelihood is -inf; a NaN
+# stays one, and the rows beside have the bits that they have alone
+@pytest.mark.parametrize("d", [3, 16, 17, 32, 45, 128])
+def test_loglik_of_rows_with_an_infinity(d):
+    import torch
+
+    from paper_2204_08988_amd.sampler import Sampler
+    K, n = 5, 300
+    params = pu.random_gauss_params(K, d, 60 + d, spread=2.0)
+    x = pu.gauss_points(params, n, 61 + d)
+    S = Sampler("gaussian", d, K + 2, 2.0, 3, kappa=1.0, nu=d + 3.0, m=np.zeros(d), psi=np.eye(d))
+    S.set_params(params.log_pi, params.log_pisub, pu.comp_array(params))
+    ref = S.loglik(torch.from_numpy(x).cuda()).cpu().numpy()
+    cols = sorted({c for c in (0, 1, 7, 15, 16, 23, 31, 32, 40, 44, 63, 64, 100, 127, d - 1) if c < d})
+    inf_rows = np.arange(len(cols)) * 5 + 2
+    y = x.copy()
+    for i, c in zip(inf_rows, cols):
+        y[i, c] = np.inf if c % 2 else -np.inf
+    nan_rows = np.array([0, n - 1])
+    y[nan_rows, d // 2] = np.nan
+    out = S.loglik(torch.from_numpy(y).cuda()).cpu().numpy()
+    S.close()
+    assert np.all(out[inf_rows] == -np.inf), np.argwhere(out[inf_rows] != -np.inf)[:5]
+    assert np.all(np.isnan(out[nan_rows]))
+    same = np.setdiff1d(np.arange(n), np.concatenate([inf_rows, nan_rows]))
+    assert np.all(np.isfinite(ref)) and np.array_equal(out[same], ref[same])
+
+
 # the statistics over sorted rows by themselves: on both sides of the switch from one row per lane to padded
 # tiles (32 | 33), of the padded widths (64 | 65), at the smallest and largest dimension of each, with empty
 # sub-clusters; d < 5 with more clusters than the per-lane sums hold
