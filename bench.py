@@ -364,7 +364,7 @@ def headline(args):
     if not args.headline_only:
         extra = {}
         r2 = converged_chain(torch, "gauss_d32", None, "bf16", max(args.steps, 20), args.warmup)
-        r2["roofline"] = mfma_roofline(r2, 32, "k_label_gauss_uc32")
+        r2["roofline"] = mfma_roofline(r2, 32, "k_label_gauss_b32")
         extra["gauss_d32"] = r2
         extra["mult_v100"] = label_step_run(torch, "mult_v100", None, "fp32", 20, 3)
         extra["mult_v100_chain"] = converged_chain(torch, "mult_v100", None, "fp32", 20, 3)

@@ -12,6 +12,8 @@ namespace dpmm {
 // the FP32 sums and roundings of both this form and the FP32 draw it stands
 // for ((3d + 5) 2^-24 at most, d <= 128).  By Cauchy-Schwarz
 //   E = ||Y - y|| <= (g + g2) ||W||_F ||x'|| + g2 ||W||_F ||mu - c||.
+// The share of W's rounding in g may be taken by its own norm, ||W - bf16(W)||_F in the
+// place of g / 2 ||W||_F, and rows centred on the cluster's own mean have mu - c = 0.
 // The computed s = sqrt(q_bf16) is within 2^-16 s of ||Y||, so with
 // E' = E + 2^-16 s the exact q lies in [max(0, s - E')^2, (s + E')^2]: the
 // score lies in [c_k - (s + E')^2 / 2, c_k - max(0, s - E')^2 / 2].

@@ -12,8 +12,9 @@
 // BF16X3 adds the two cross terms of the hi/lo split, W_hi dx_lo + W_lo dx_hi,
 // for about 16 mantissa bits.
 //
-// The BF16 main passes (k_label_gauss_uc32, k_label_gauss_mfma_uc) centre the points
-// once on a centre common to all clusters and start each cluster's
+// The BF16 main passes (k_label_gauss_b32, k_label_gauss_mfma_uc) centre the points
+// once on a centre common to all clusters (d = 32: or on each cluster's, for data far from
+// a common centre) and start each cluster's
 // accumulators at W_k (c - mu_k), so that the rows are rounded to BF16 once per
 // step instead of once per cluster; each of its scores carries an interval
 // that bounds the BF16 and FP32 rounding errors.
@@ -633,29 +634,103 @@ __device__ __forceinline__ void top2_merge(Top2U& a, float u1, float u2, float l
 constexpr int UC_BUF_DWORD3 = 0x00020000;  // raw buffer descriptor word 3 (gfx9 family)
 constexpr int UC_NT = 2;                    // cache policy of the row loads: non-temporal
 
-// Main pass for d = 32 in BF16, uncentred: a wave takes 128 points (four 32-point
-// tiles), centred once on the common centre c and rounded to BF16, and walks the
-// clusters, whose fragments, offsets beta = -W (mu - c) (the accumulators' start)
-// and constants come through LDS, eight clusters at a time in two buffers (all of
-// them at once up to sixteen).  Scores, intervals and the draw's rule as in
-// k_label_gauss_mfma_uc.  N = 1e6, K = 20: 78 -> 60 us against the
-// kernel that centred the rows on every cluster's mean, as k_label_gauss_mfma32 does.
-constexpr int U32_BLOCK = 256, U32_STEP = 512;
+// Main pass for d = 32 in BF16.  The clusters' fragments and constants come through
+// LDS, eight clusters at a time in two buffers (all of them at once up to sixteen), and
+// every wave walks them for its own points.  Scores, intervals and the draw's rule as in
+// k_label_gauss_mfma_uc.  Two forms:
+//   common centre (CEN = false)  a wave takes 128 points (four 32-point tiles), centred
+//       once on the common centre c and rounded to BF16; the accumulators start at
+//       beta = -W (mu - c).  Its interval grows with ||x - c||, so that points far
+//       from c are left to the candidate pass, which costs 25 us for the first of them
+//       and about 0.5 ns each beyond;
+//   own centres (CEN = true)  64 points in FP32, centred on each cluster's mean and
+//       rounded again for every cluster, the interval from ||x - mu||.
+// Bound by the vector ALUs: some 55 and 128 vector instructions per 64 points and
+// cluster beside 4 matrix ones; N = 1e6, K = 20 56 and 92 us, K = 100 231 and 420.  (Four
+// tiles per wave in the second form too, with three waves per SIMD instead of four: the
+// same, and 4 us more in the first.)  k_pack_bias32 chooses by the table.
+constexpr int U32_BLOCK = 256;
+constexpr int MARK32_MEANS = 64;  // means that a cluster is tried on
 
-__global__ __launch_bounds__(U32_BLOCK, 4) void k_label_gauss_uc32(const float* __restrict__ x, long long n,
-                                                                   long long per_block,
-                                                                   const bf16x8* __restrict__ whi,
-                                                                   const float* __restrict__ wbias, int K, int k_max,
-                                                                   int cg, int* __restrict__ z, int* __restrict__ hist,
-                                                                   int* __restrict__ flagged,
-                                                                   int* __restrict__ n_flagged) {
+// The interval of a score c - q / 2 whose whitened point is off by at most e0 (interval.hpp)
+// into the top-2 state
+__device__ __forceinline__ void push_interval(Top2U& t, float q, float e0, float c, int k) {
+  const float sq = __builtin_amdgcn_sqrtf(q);
+  const float er = fmaf(UC_EPSS, sq, e0);
+  const float sp = sq + er, sm = fmaxf(sq - er, 0.0f);
+  const float lo = fmaf(-0.5f * sp, sp, c), up = fmaf(-0.5f * sm, sm, c);
+  t.k1 = up > t.u1 ? k : t.k1;
+  t.u2 = __builtin_amdgcn_fmed3f(t.u1, t.u2, up);
+  t.u1 = fmaxf(t.u1, up);
+  t.lo_max = fmaxf(t.lo_max, lo);
+}
+
+// rows of the tile's points in the lanes' layout: dims 16 ks + 8 half + q of the lane's row
+__device__ __forceinline__ void load_row32(const float* __restrict__ xr, float (&f)[2][8]) {
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) {
+    const float4 u = reinterpret_cast<const float4*>(xr)[4 * ks], v = reinterpret_cast<const float4*>(xr)[4 * ks + 1];
+    f[ks][0] = u.x, f[ks][1] = u.y, f[ks][2] = u.z, f[ks][3] = u.w;
+    f[ks][4] = v.x, f[ks][5] = v.y, f[ks][6] = v.z, f[ks][7] = v.w;
+  }
+}
+
+// the row less cen, rounded to BF16; returns the lane's half of its squared norm
+__device__ __forceinline__ float centre_row32(const float (&f)[2][8], const float (&cen)[2][8], bf16x8 (&b)[2]) {
+  float r = 0.0f;
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int q = 0; q < 8; ++q) {
+      const float e = f[ks][q] - cen[ks][q];
+      r = fmaf(e, e, r);
+      b[ks][q] = (__bf16)e;
+    }
+  return r;
+}
+
+// the lane's half of the squared norm of a rounded row
+__device__ __forceinline__ float rounded_norm32(const bf16x8 (&b)[2]) {
+  typedef __attribute__((__vector_size__(2 * sizeof(__bf16)))) __bf16 bf16x2;
+  float r = 0.0f;
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks)
+#pragma unroll
+    for (int q = 0; q < 8; q += 2) {
+      const bf16x2 v = {b[ks][q], b[ks][q + 1]};
+      r = __builtin_amdgcn_fdot2_f32_bf16(v, v, r, false);
+    }
+  return r;
+}
+
+// the lane's half of ||W b + off||^2
+__device__ __forceinline__ float half_norm32(const bf16x8& a0, const bf16x8& a1, const bf16x8 (&b)[2], const f32x16& off) {
+  f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b[0], off, 0, 0, 0);
+  acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b[1], acc, 0, 0, 0);
+  float q0 = 0.0f, q1 = 0.0f;
+#pragma unroll
+  for (int r = 0; r < 16; r += 2) {
+    q0 = fmaf(acc[r], acc[r], q0);
+    q1 = fmaf(acc[r + 1], acc[r + 1], q1);
+  }
+  return q0 + q1;
+}
+
+template <bool CEN>
+__device__ __forceinline__ void label_b32(const float* __restrict__ x, long long n, long long per_block,
+                                          const float* __restrict__ packed, const bf16x8* __restrict__ whi,
+                                          const float* __restrict__ wbias, int K, int k_max, int cg,
+                                          int* __restrict__ z, int* __restrict__ hist, int* __restrict__ flagged,
+                                          int* __restrict__ n_flagged, unsigned char* smem) {
   constexpr int D = 32, NF = 128;           // fragments of a cluster
   constexpr int CB = NF * 16 + D * 4 + 16;  // its bytes in LDS
+  constexpr int S = (4 + D + D * (D + 1) / 2 + 3) & ~3;
+  constexpr int TILES = CEN ? 2 : 4, OWN = TILES / 2;  // 32-point tiles of a wave, points of a lane
+  constexpr int STEP = U32_BLOCK / 64 * 32 * TILES;
   typedef float f32x4 __attribute__((ext_vector_type(4)));
   typedef __attribute__((address_space(3))) const unsigned char lds_uchar;
   typedef __attribute__((address_space(3))) const bf16x8 lds_bf16x8;
   typedef __attribute__((address_space(3))) const f32x4 lds_f32x4;
-  extern __shared__ __align__(16) unsigned char smem[];
   const bool single = cg >= K;
   unsigned char* buf[2] = {smem, single ? smem : smem + cg * CB};
   int* h = reinterpret_cast<int*>(smem + (single ? 1 : 2) * cg * CB);
@@ -666,96 +741,95 @@ __global__ __launch_bounds__(U32_BLOCK, 4) void k_label_gauss_uc32(const float* 
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   const long long begin = (long long)blockIdx.x * per_block;
   const long long end = begin + per_block < n ? begin + per_block : n;
-  // [cg] fragments, [cg] offsets, [cg] constants
+  // [cg] fragments, [cg] offsets (CEN: means), [cg] constants
   auto fetch = [&](unsigned char* dst, int k0, int nk) {
     float* f = reinterpret_cast<float*>(dst);
     mx::stage<U32_BLOCK>(f, reinterpret_cast<const float*>(whi + (size_t)k0 * NF), nk * NF * 4);
-    mx::stage<U32_BLOCK>(f + cg * NF * 4, wbias + (size_t)k0 * D, nk * D);
+    float* fo = f + cg * NF * 4;
+    if constexpr (CEN) {
+      static_assert(16 * D / 4 <= U32_BLOCK, "the means of a group in one go");
+      if ((int)threadIdx.x < nk * (D / 4))
+        __builtin_amdgcn_global_load_lds(
+            (const void*)(packed + (size_t)(k0 + (threadIdx.x >> 3)) * S + 4 + 4 * (threadIdx.x & 7)),
+            (lds_void*)(fo + 4 * (threadIdx.x & ~63)), 16, 0, 0);
+    } else {
+      mx::stage<U32_BLOCK>(fo, wbias + (size_t)k0 * D, nk * D);
+    }
     mx::stage<U32_BLOCK>(f + cg * (NF * 4 + D), cst + (size_t)k0 * 4, nk * 4);
   };
   float cen[2][8];
-#pragma unroll
-  for (int ks = 0; ks < 2; ++ks)
-#pragma unroll
-    for (int q = 0; q < 8; ++q) cen[ks][q] = centre[16 * ks + 8 * half + q];
+  if constexpr (!CEN) load_row32(centre + 8 * half, cen);
   if (begin < end) fetch(buf[0], 0, cg < K ? cg : K);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  // both halves' sums of tiles a (lower lanes) and b (upper lanes): the lane's own point
-  auto own = [&](float a, float b) __attribute__((always_inline)) {
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-  };
   bool odd = false;
-  for (long long chunk = begin; chunk < end; chunk += U32_STEP) {
-    const long long base = chunk + wave * 128;
-    bf16x8 b[4][2];  // [tile][k-step]
-    float rx[4];     // the lane's half of ||x'||^2, then ||x'|| of its own two points
+  for (long long chunk = begin; chunk < end; chunk += STEP) {
+    const long long base = chunk + wave * 32 * TILES;
+    float f[TILES][2][8];  // the rows (!CEN: until they are centred)
+    bf16x8 b[TILES][2];    // [tile][k-step]
+    float rx[TILES];       // !CEN: ||x'|| of the lane's own points
 #pragma unroll
-    for (int t = 0; t < 4; ++t) {
+    for (int t = 0; t < TILES; ++t) {
       const long long p = base + 32 * t + col;
-      const float4* xr = reinterpret_cast<const float4*>(x + (p < end ? (size_t)p * D : 0) + 8 * half);
-      rx[t] = 0.0f;
-#pragma unroll
-      for (int ks = 0; ks < 2; ++ks) {
-        const float4 u = xr[4 * ks], v = xr[4 * ks + 1];
-        const float f[8] = {u.x, u.y, u.z, u.w, v.x, v.y, v.z, v.w};
-#pragma unroll
-        for (int q = 0; q < 8; ++q) {
-          const float e = f[q] - cen[ks][q];
-          rx[t] = fmaf(e, e, rx[t]);
-          b[t][ks][q] = (__bf16)e;
-        }
-      }
+      load_row32(x + (p < end ? (size_t)p * D : 0) + 8 * half, f[t]);
+      if constexpr (!CEN) rx[t] = centre_row32(f[t], cen, b[t]);
     }
-    rx[0] = __builtin_amdgcn_sqrtf(own(rx[0], rx[1]));
-    rx[1] = __builtin_amdgcn_sqrtf(own(rx[2], rx[3]));
-    Top2U st[2];  // points lane and 64 + lane of the wave
-    st[0].init();
-    st[1].init();
+    if constexpr (!CEN)
+#pragma unroll
+      for (int u = 0; u < OWN; ++u) rx[u] = __builtin_amdgcn_sqrtf(mx::half_sums(rx[2 * u], rx[2 * u + 1]));
+    Top2U st[OWN];  // points lane (and 64 + lane) of the wave
+#pragma unroll
+    for (int u = 0; u < OWN; ++u) st[u].init();
     for (int g0 = 0; g0 < K; g0 += cg) {
       const int nk = K - g0 < cg ? K - g0 : cg;
       if (!single) {
         const bool wrap = g0 + cg >= K;
         const int gn = wrap ? 0 : g0 + cg;
-        if (!wrap || chunk + U32_STEP < end) fetch(buf[odd ? 0 : 1], gn, K - gn < cg ? K - gn : cg);
+        if (!wrap || chunk + STEP < end) fetch(buf[odd ? 0 : 1], gn, K - gn < cg ? K - gn : cg);
       }
       lds_uchar* e = (lds_uchar*)buf[odd ? 1 : 0];
       lds_uchar* eo = e + cg * NF * 16;
       lds_uchar* ec = eo + cg * D * 4;
       for (int c = 0; c < nk; ++c, e += NF * 16, eo += D * 4, ec += 16) {
         const bf16x8 a0 = ((lds_bf16x8*)e)[lane], a1 = ((lds_bf16x8*)e)[64 + lane];
-        f32x16 off;
-#pragma unroll
-        for (int q = 0; q < 4; ++q) {
-          const f32x4 u = ((lds_f32x4*)eo)[4 * half + q];
-#pragma unroll
-          for (int j = 0; j < 4; ++j) off[4 * q + j] = u[j];
-        }
         const f32x4 kc = *(lds_f32x4*)ec;
-        float qs[4];
+        f32x16 off;
+        if constexpr (CEN) {
+          float mu[2][8];
 #pragma unroll
-        for (int t = 0; t < 4; ++t) {
-          f32x16 acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a0, b[t][0], off, 0, 0, 0);
-          acc = __builtin_amdgcn_mfma_f32_32x32x16_bf16(a1, b[t][1], acc, 0, 0, 0);
-          float q0 = 0.0f, q1 = 0.0f;
+          for (int ks = 0; ks < 2; ++ks)
 #pragma unroll
-          for (int r = 0; r < 16; r += 2) {
-            q0 = fmaf(acc[r], acc[r], q0);
-            q1 = fmaf(acc[r + 1], acc[r + 1], q1);
+            for (int j = 0; j < 2; ++j) {
+              const f32x4 u = ((lds_f32x4*)eo)[4 * ks + 2 * half + j];
+              mu[ks][4 * j] = u.x, mu[ks][4 * j + 1] = u.y, mu[ks][4 * j + 2] = u.z, mu[ks][4 * j + 3] = u.w;
+            }
+#pragma unroll
+          for (int t = 0; t < TILES; ++t) {
+            centre_row32(f[t], mu, b[t]);
+            rx[t] = rounded_norm32(b[t]);
           }
-          qs[t] = q0 + q1;
-        }
 #pragma unroll
-        for (int u = 0; u < 2; ++u) {
-          const float sq = __builtin_amdgcn_sqrtf(own(qs[2 * u], qs[2 * u + 1]));
-          const float er = fmaf(UC_EPSS, sq, fmaf(kc.y, rx[u], kc.z));
-          const float sp = sq + er, sm = fmaxf(sq - er, 0.0f);
-          const float lo = fmaf(-0.5f * sp, sp, kc.x), up = fmaf(-0.5f * sm, sm, kc.x);
-          st[u].k1 = up > st[u].u1 ? g0 + c : st[u].k1;
-          st[u].u2 = __builtin_amdgcn_fmed3f(st[u].u1, st[u].u2, up);
-          st[u].u1 = fmaxf(st[u].u1, up);
-          st[u].lo_max = fmaxf(st[u].lo_max, lo);
+          for (int j = 0; j < 16; ++j) off[j] = 0.0f;
+        } else {
+#pragma unroll
+          for (int q = 0; q < 4; ++q) {
+            const f32x4 u = ((lds_f32x4*)eo)[4 * half + q];
+#pragma unroll
+            for (int j = 0; j < 4; ++j) off[4 * q + j] = u[j];
+          }
+        }
+        float qs[TILES];
+#pragma unroll
+        for (int t = 0; t < TILES; ++t) qs[t] = half_norm32(a0, a1, b[t], off);
+#pragma unroll
+        for (int u = 0; u < OWN; ++u) {
+          const float q = mx::half_sums(qs[2 * u], qs[2 * u + 1]);
+          if constexpr (CEN)
+            // (the norm of the rounded row, within 2^-8 of the row's)
+            push_interval(st[u], q, kc.y * 1.005f * __builtin_amdgcn_sqrtf(mx::half_sums(rx[2 * u], rx[2 * u + 1])), kc.x,
+                          g0 + c);
+          else
+            push_interval(st[u], q, fmaf(kc.y, rx[u], kc.z), kc.x, g0 + c);
         }
       }
       if (!single) {
@@ -765,13 +839,33 @@ __global__ __launch_bounds__(U32_BLOCK, 4) void k_label_gauss_uc32(const float* 
       }
     }
 #pragma unroll
-    for (int u = 0; u < 2; ++u) {
+    for (int u = 0; u < OWN; ++u) {
       const long long p = base + 64 * u + lane;
       finish_main(p < end, p, st[u], z, h, flagged, n_flagged, lane);
     }
   }
   __syncthreads();
   for (int k = threadIdx.x; k < K; k += U32_BLOCK) hist[(size_t)blockIdx.x * K + k] = h[k];
+}
+
+__global__ __launch_bounds__(U32_BLOCK, 4) void k_label_gauss_b32(const float* __restrict__ x, long long n,
+                                                                  long long per_block,
+                                                                  const float* __restrict__ packed,
+                                                                  const bf16x8* __restrict__ whi,
+                                                                  const float* __restrict__ wbias, int K, int k_max,
+                                                                  int cg, int* __restrict__ z, int* __restrict__ hist,
+                                                                  int* __restrict__ flagged,
+                                                                  int* __restrict__ n_flagged) {
+  extern __shared__ __align__(16) unsigned char smem[];
+  const float* cst = wbias + (size_t)k_max * 32;
+  float pairs = 0.0f;
+  for (int k = threadIdx.x & 63; k < K; k += 64) pairs += cst[4 * k + 3];
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) pairs += __shfl_xor(pairs, o);
+  if (__builtin_amdgcn_readfirstlane((int)pairs) * 32 > (K < MARK32_MEANS ? K : MARK32_MEANS))
+    label_b32<true>(x, n, per_block, packed, whi, wbias, K, k_max, cg, z, hist, flagged, n_flagged, smem);
+  else
+    label_b32<false>(x, n, per_block, packed, whi, wbias, K, k_max, cg, z, hist, flagged, n_flagged, smem);
 }
 
 // Main pass for d = 64, 128 in BF16, cluster-stationary and uncentred: the
@@ -1515,49 +1609,103 @@ __global__ __launch_bounds__(D) void k_pack_bias(int K, int k_max, const float* 
   }
 }
 
-// The same table for d = 32, the centre (of the first 64 means) formed by every block.
+// The same table for d = 32, the centre (of the first 64 means) formed by every block,
+// W's rounding by its own norm, and in the fourth constant how many of up to 64 other
+// clusters' means (spread over all, one per lane) the common centre leaves in doubt
+// against this cluster and the clusters' own centres would not (k_label_gauss_b32).
+// A point at the mean mu_i has s^2 = ||W (mu_i - mu)||^2 + d here (the points' own
+// spread, as if the covariances were alike), sqrt(d) under its own cluster, and the
+// E that the form bounds in both; it is in doubt where the two intervals come within
+// the Gumbel range.  Only where mu_i is further from the common centre than from mu.
+//
+// The own centres' form runs where more than 1 / 32 of the means are in doubt: a few in a
+// hundred points left to the candidate pass cost what it takes longer.  N = 1e6, K = 20,
+// means N(0, 25 I), Wishart(d + 2, I / d) covariances, label step in us with the common
+// centre alone and so: groups of clusters +-10 apart in every coordinate 206 and 181 (the
+// common centre, with W's rounding by its norm), +-20 363 and 218, +-50 606 and 217, one
+// cluster 1000 off 607 and 217; centred 181 and 181.  K = 100: +-10 520 and 495, +-50 1190
+// and 553, centred 362 to 489 and 364 to 488.
 __global__ __launch_bounds__(64) void k_pack_bias32(int K, int k_max, const float* __restrict__ packed,
                                                     float* __restrict__ wbias) {
   constexpr int D = 32, S = (4 + D + D * (D + 1) / 2 + 3) & ~3;
   __shared__ double dm[D];
+  __shared__ __align__(16) float s_rec[S], s_cen[D];
   const int k = blockIdx.x, lane = threadIdx.x, j = lane & 31, m = K < 64 ? K : 64;
   const float* rec = packed + (size_t)k * S;
+  // the mean and constant of the lane's cluster among the sampled ones
+  const int mi = K < MARK32_MEANS ? K : MARK32_MEANS;
+  const int ki = lane < mi ? (int)((long long)lane * K / mi) : k;
+  const float* ri = packed + (size_t)ki * S;
+  float4 mu4[D / 4];
+#pragma unroll
+  for (int q = 0; q < D / 4; ++q) mu4[q] = reinterpret_cast<const float4*>(ri + 4)[q];
+  const float ci = ri[0];
   float s = 0.0f;
 #pragma unroll
   for (int q = 0; q < 32; ++q) {
     const int c = 2 * q + (lane >> 5);
     s += c < m ? packed[(size_t)(c < m ? c : 0) * S + 4 + j] : 0.0f;
   }
+#pragma unroll
+  for (int q = 0; q < (S + 63) / 64; ++q)
+    if (64 * q + lane < S) s_rec[64 * q + lane] = rec[64 * q + lane];
   s += __shfl_xor(s, 32);
   const float cen = s / (float)m;
   if (lane < D) {
+    s_cen[j] = cen;
     dm[j] = (double)rec[4 + j] - (double)cen;
     if (k == 0) wbias[(size_t)k_max * (D + 4) + j] = cen;
   }
   __syncthreads();
-  const float* w = rec + 4 + D + j * (j + 1) / 2;
-  double b = 0.0, wn = 0.0, m2 = dm[j] * dm[j];
+  const float* w = s_rec + 4 + D + j * (j + 1) / 2;
+  double b = 0.0, wn = 0.0, en = 0.0, m2 = dm[j] * dm[j];
   for (int i = 0; i <= j; ++i) {
-    const double wji = (double)w[i];
+    const double wji = (double)w[i], er = wji - (double)(float)(__bf16)w[i];
     b = fma(wji, dm[i], b);
     wn = fma(wji, wji, wn);
+    en = fma(er, er, en);
   }
   const int hh = (j >> 2) & 1, r = ((j >> 3) << 2) | (j & 3);
   if (lane < D) wbias[(size_t)k * D + hh * 16 + r] = (float)(-b);
 #pragma unroll
   for (int o = 16; o > 0; o >>= 1) {
     wn += __shfl_xor(wn, o);
+    en += __shfl_xor(en, o);
     m2 += __shfl_xor(m2, o);
   }
-  if (lane == 0) {
-    const double f = sqrt(wn) * (1.0 + 1e-6);
-    float4 c;
-    c.x = rec[0];
-    c.y = (float)(((double)UC_GAMMA + (double)UC_GAMMA2) * f);
-    c.z = (float)((double)UC_GAMMA2 * f * sqrt(m2) * (1.0 + 1e-6));
-    c.w = 0.0f;
-    reinterpret_cast<float4*>(wbias + (size_t)k_max * D)[k] = c;
+  const double f = sqrt(wn) * (1.0 + 1e-6);
+  float4 c;
+  c.x = s_rec[0];
+  // W's rounding by its own norm in the place of 2^-8 ||W||_F (0.4 of it where W is full)
+  c.y = (float)((((double)UC_GAMMA / 2 + (double)UC_GAMMA2) * f + sqrt(en)) * (1.0 + 1e-6));
+  c.z = (float)((double)UC_GAMMA2 * f * sqrt(m2) * (1.0 + 1e-6));
+  float dx[D], near = 0.0f, far = 0.0f, q2 = (float)D;
+#pragma unroll
+  for (int q = 0; q < D / 4; ++q) {
+    const float v[4] = {mu4[q].x, mu4[q].y, mu4[q].z, mu4[q].w};
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float d = v[e] - s_cen[4 * q + e];
+      dx[4 * q + e] = v[e] - s_rec[4 + 4 * q + e];
+      far = fmaf(d, d, far);
+      near = fmaf(dx[4 * q + e], dx[4 * q + e], near);
+    }
   }
+#pragma unroll
+  for (int row = 0; row < D; ++row) {
+    float y = 0.0f;
+#pragma unroll
+    for (int e = 0; e <= row; ++e) y = fmaf(s_rec[4 + D + row * (row + 1) / 2 + e], dx[e], y);
+    q2 = fmaf(y, y, q2);
+  }
+  const float sq = sqrtf(q2), own = sqrtf((float)D), room = 2.0f * (RGAP + TOL_ABS + c.x - ci);
+  auto doubt = [&](float e, float e_own) {
+    const float lo = fmaxf(sq - e, 0.0f), hi = own + e_own;
+    return lo * lo < fmaf(hi, hi, room);
+  };
+  const float ef = fmaf(c.y, sqrtf(far), c.z), eo = c.y * sqrtf(near);
+  c.w = (float)__popcll(__ballot(lane < mi && ki != k && far > near && doubt(ef, ef) && !doubt(eo, 0.0f)));
+  if (lane == 0) reinterpret_cast<float4*>(wbias + (size_t)k_max * D)[k] = c;
 }
 
 }  // namespace
@@ -1769,8 +1917,8 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
     } else if (d == 32 && !cands && !x3 && wbias) {
       const int cg = K <= 16 ? K : 8;
       const size_t lu = (size_t)(K <= 16 ? 1 : 2) * cg * (128 * 16 + 32 * 4 + 16) + lh;
-      hipExtLaunchKernelGGL(k_label_gauss_uc32, dim3(Gp), dim3(U32_BLOCK), lu, s, e0, e1, 0, x, n, per_block, hi, wbias,
-                            K, k_max, cg, z, hist, flagged, n_flagged);
+      hipExtLaunchKernelGGL(k_label_gauss_b32, dim3(Gp), dim3(U32_BLOCK), lu, s, e0, e1, 0, x, n, per_block, packed, hi,
+                            wbias, K, k_max, cg, z, hist, flagged, n_flagged);
     } else if (d == 32) {
       // [CG][NB][NF] fragments (64 KB), [CG][d + 4] means and constants, the histogram
       const size_t lds = (size_t)65536 + (size_t)16 * (d + 4) * sizeof(float) + lh;

@@ -186,11 +186,6 @@ __global__ __launch_bounds__(PROBE ? 2 * GBLOCK : GBLOCK, 2) void k_guess(const 
   if (begin < end) fetch(buf0, 0, cg < K ? cg : K);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
-  // both halves' sums of tiles a (lower lanes) and b (upper lanes): the lane's own point
-  auto own = [&](float a, float b) __attribute__((always_inline)) {
-    const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
-    return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
-  };
   int sure = 0;  // PROBE: the wave's points settled
   bool odd = false;
   for (long long chunk = begin; chunk < end; chunk += GSTEP) {
@@ -217,7 +212,7 @@ __global__ __launch_bounds__(PROBE ? 2 * GBLOCK : GBLOCK, 2) void k_guess(const 
       }
     }
 #pragma unroll
-    for (int u = 0; u < OWN; ++u) rx[u] = __builtin_amdgcn_sqrtf(own(rx[2 * u], rx[2 * u + 1]));
+    for (int u = 0; u < OWN; ++u) rx[u] = __builtin_amdgcn_sqrtf(mx::half_sums(rx[2 * u], rx[2 * u + 1]));
     // points lane (and 64 + lane) of the wave: the best marginal, its cluster and its
     // bound, and the two largest bounds
     float best[OWN], mine[OWN], u1[OWN], u2[OWN], est[OWN];
@@ -263,7 +258,7 @@ __global__ __launch_bounds__(PROBE ? 2 * GBLOCK : GBLOCK, 2) void k_guess(const 
         }
 #pragma unroll
         for (int u = 0; u < OWN; ++u) {
-          const float q = own(qs[2 * u], qs[2 * u + 1]);
+          const float q = mx::half_sums(qs[2 * u], qs[2 * u + 1]);
           const float l = fmaf(-0.5f, q, kc.x), sq = __builtin_amdgcn_sqrtf(q);
           const float sm = fmaxf(sq - fmaf(UC_EPSS, sq, fmaf(kc.z, rx[u], kc.w)), 0.0f), h2 = 0.5f * sm * sm;
           const float up = fmaf(PR_REL, h2 + fabsf(kc.y), kc.y - h2);

@@ -64,6 +64,14 @@ __device__ __forceinline__ void transpose4(float& v0, float& v1, float& v2, floa
   v3 = __uint_as_float(f[1]);
 }
 
+// a and b: sums over half the coordinates, of point l % 32 of one 32-point tile and of
+// the next, the other half of them in lane l ^ 32.  The whole sum of the lane's own point
+// (lanes 0-31 the first tile's, 32-63 the second's).
+__device__ __forceinline__ float half_sums(float a, float b) {
+  const auto sw = __builtin_amdgcn_permlane32_swap(__float_as_uint(a), __float_as_uint(b), false, false);
+  return __uint_as_float(sw[0]) + __uint_as_float(sw[1]);
+}
+
 // x[t][s] of the rows xr[t] (the lane's row 16 t + c of each tile), zero where !ok[t]
 // (xr[t] must be readable all the same) and past the dimension.  The four lanes
 // of a row read 64 consecutive bytes of it at a time and trade them by

@@ -187,6 +187,78 @@ def test_bf16_labels_far_from_origin(d, K, n, shift):
     S.close()
 
 
+def _shifted(params, shift):
+    """The mixture moved as a whole, split into two groups of clusters, or with one cluster moved away."""
+    K, _, d = params.mu.shape
+    off = np.zeros((K, 1, d))
+    if shift[0] == "common":
+        off[:] = shift[1]
+    elif shift[0] == "split":
+        off[: K // 2], off[K // 2:] = shift[1], -shift[1]
+    elif shift[0] == "one":
+        off[0] = shift[1]
+    return sampler.Params(params.log_pi, params.log_pisub, mu=params.mu + off, sigma=params.sigma)
+
+
+# d = 32: K on both sides of one and two LDS groups and of the 64 means that a cluster is tried on, ragged steps
+@pytest.mark.parametrize("K,n,scale,shift", [(2, 700, 5.0, ("split", 50.0)), (6, 4000, 5.0, ("common", 1000.0)),
+                                             (16, 1025, 5.0, ("one", 1000.0)), (17, 1023, 5.0, ("split", 200.0)),
+                                             (20, 513, 1.0, ("split", 20.0)), (65, 4097, 3.0, ("split", 50.0)),
+                                             (130, 255, 5.0, ("one", 3000.0)), (20, 4000, 0.5, ("none",))])
+def test_bf16_d32_far_from_a_common_centre(K, n, scale, shift):
+    """d = 32 in BF16 where the points lie far from the mean of the cluster means:
+    the labels and sub-labels of the FP32 sampler."""
+    import torch
+    from paper_2204_08988_amd.sampler import Sampler
+    d = 32
+    params = _shifted(_wishart_params(K, d, 4500 + K, mean_scale=scale), shift)
+    xt = torch.from_numpy(pu.gauss_points(params, n, 4600 + K)).cuda()
+    out = {}
+    for prec in ("bf16", "fp32"):
+        S = Sampler("gaussian", d, K + 2, 2.0, 9, m=np.zeros(d), psi=np.eye(d), precision=prec)
+        S.set_params(params.log_pi, params.log_pisub, pu.comp_array(params))
+        out[prec] = [a.cpu().numpy() for t in (2, 3) for a in S.sample_labels(xt, t)]
+        counts = S.get_stats()[:, :, 0].sum(axis=1)
+        assert np.array_equal(counts, np.bincount(out[prec][2], minlength=K))
+        S.close()
+    for a, b in zip(out["bf16"], out["fp32"]):
+        assert np.array_equal(a, b), np.nonzero(a != b)[0][:10]
+
+
+def test_bf16_d32_time_far_from_a_common_centre():
+    """Two groups of clusters far apart take much the time of the same clusters around
+    one centre (1.2 times it; 3.3 times it with every point left to the candidate pass)."""
+    import torch
+    from paper_2204_08988_amd.sampler import Sampler
+    d, K, n = 32, 20, 1_000_000
+    base = _wishart_params(K, d, 4700, mean_scale=5.0)
+    g = torch.Generator(device="cuda").manual_seed(5)
+    lab = torch.randint(0, K, (n,), device="cuda", generator=g)
+    e = torch.randn((n, d), device="cuda", generator=g)
+    best = {}
+    for name, shift in (("centred", ("none",)), ("split", ("split", 50.0))):
+        params = _shifted(base, shift)
+        L = torch.from_numpy(np.linalg.cholesky(params.sigma[:, 0])).float().cuda()
+        x = torch.from_numpy(params.mu[:, 0]).float().cuda()[lab]
+        for k in range(K):
+            x[lab == k] += e[lab == k] @ L[k].T.contiguous()
+        S = Sampler("gaussian", d, K + 2, 2.0, 9, m=np.zeros(d), psi=np.eye(d), precision="bf16")
+        S.set_params(params.log_pi, params.log_pisub, pu.comp_array(params))
+        z, zs = S.sample_labels(x, 1)
+        times = []
+        for t in range(12):
+            a, b = (torch.cuda.Event(enable_timing=True) for _ in range(2))
+            a.record()
+            for u in range(5):
+                S.sample_labels(x, 2 + u, z, zs)
+            b.record()
+            torch.cuda.synchronize()
+            times.append(a.elapsed_time(b))
+        best[name] = min(times)
+        S.close()
+    assert best["split"] <= 2.0 * best["centred"], best
+
+
 @pytest.mark.parametrize("d,K,n,offset", [(64, 7, 6000, 0.0), (128, 6, 3000, 0.0), (128, 5, 2000, 300.0)])
 def test_bf16_draw_equals_fp32_draw(d, K, n, offset):
     """The matrix-core forms promise the FP32 form's labels: a point is drawn
