@@ -847,7 +847,8 @@ dpmm_status label_phase(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t, int
         return DPMM_OK;
       }
       DPMM_HIP(ctx, launch_settle(ctx->d, (const float*)x, n, ctx->d_perm, ctx->d_zsort, ctx->d_packed, ctx->d_whi,
-                                  ctx->d_wlo, ctx->K, ctx->cfg.k_max, pb, z, ctx->stream), "label kernel");
+                                  ctx->d_wlo, ctx->d_wbias, ctx->K, ctx->cfg.k_max, pb, z, ctx->stream),
+               "label kernel");
     }
     if (mfma) {
       const OpenList ol{mode, pb.open, pb.n_open};

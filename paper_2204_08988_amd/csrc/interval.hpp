@@ -23,4 +23,18 @@ constexpr float UC_GAMMA = 1.02f / 128.0f;
 constexpr float UC_GAMMA2 = 1.0f / 16384.0f;
 constexpr float UC_EPSS = 1.0f / 65536.0f;
 
+// The same for a bf16x3 score of a row centred on the cluster's own mean, v = x - mu:
+// W = W_hi + W_lo and v = v_hi + v_lo up to 2^-16 relative, and the kernel forms
+// W_hi v_hi + W_hi v_lo + W_lo v_hi.  Left out are W_lo v_lo and the two remainders, 3 * 2^-16
+// sum_i |W_ji| |v_i|; the 3 d products are added in FP32 (3 d 2^-23 at most, d <= 128,
+// should each sum be cut off), and the FP32 draw's d as well: 2^-13.3 in all, so
+//   ||Y - y|| <= g3 ||W||_F ||v||,  g3 = 2^-13.
+constexpr float X3_GAMMA = 1.0f / 8192.0f;
+// A lower bound of the FP32 score c - q / 2 of a row with bf16x3 norm s = sqrt(q) and
+// wv >= ||W||_F ||v||, the rounding of both scores and of the bound itself included.
+constexpr float x3_lower(float c, float s, float wv) {
+  const float e = s + (X3_GAMMA * wv + UC_EPSS * s), h = 0.5f * e * e;
+  return c - h - 1e-6f * (h + (c < 0.0f ? -c : c));
+}
+
 }  // namespace dpmm

@@ -143,7 +143,8 @@ hipError_t launch_label_sorted(int d, const float* x, long long n, const float* 
 // BF16 (d = 64, 128): the points that no other cluster may win get their guess, the
 // others are listed in open
 hipError_t launch_settle(int d, const float* x, long long n, const int* perm, const int* guess, const float* packed,
-                         const void* whi, const void* wlo, int K, int k_max, const PruneBufs& b, int* z, hipStream_t s);
+                         const void* whi, const void* wlo, const float* wbias, int K, int k_max, const PruneBufs& b, int* z,
+                         hipStream_t s);
 // block_rows: rows per block while n allows at most 2048 blocks (256 or 512)
 hipError_t sorted_plan(long long n, int K, long long hist_cap, int* G, long long* per_block, int block_rows = 512);
 // mode (may be null): where *mode is 0, have_hist: nothing is done; else: hist is there

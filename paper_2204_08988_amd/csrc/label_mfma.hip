@@ -1276,17 +1276,20 @@ __device__ __forceinline__ int logistic_pick(float delta, float u) {
 }
 
 // SETTLE: the rows are sorted by a guessed cluster (zrow), whose score the kernel
-// forms in the same way from the clusters' own tables.  Where no other cluster's
-// score exceeds its lower end by more than the Gumbel range (ub, from the guess) the
+// forms in the same way from the clusters' own tables, with its lower bound
+// (interval.hpp; cst: the constants of the BF16 main pass, for ||W||_F).  Where no other
+// cluster's score (ub, from the guess) comes within the Gumbel range of that bound the
 // point has that label; the others are listed in open.  Runs where *mode is 1.
-// d = 128, N = 2e6 262 us (the same scores in FP32, 64 rows at a time 419), d = 64 152 (175).
+// d = 128, N = 2e6 265 us (the same scores in FP32, 64 rows at a time 419), d = 64
+// 153 (175).
 template <int D, bool SETTLE>
 __global__ __launch_bounds__(SUBX_BLOCK, 1) void k_sorted_x3(
     const float* __restrict__ x, long long n_sorted, long long per_block, const int* __restrict__ perm,
     int* __restrict__ z, const int* __restrict__ zrow, unsigned char* __restrict__ zsub,
     const float* __restrict__ packed, const bf16x8* __restrict__ shi, const bf16x8* __restrict__ slo, int K,
     int k_max, uint32_t t, uint64_t seed, unsigned char* __restrict__ flag, int* __restrict__ cnt,
-    const float* __restrict__ ub, const int* __restrict__ mode, int* __restrict__ open) {
+    const float* __restrict__ ub, const float4* __restrict__ cst, const int* __restrict__ mode,
+    int* __restrict__ open) {
   if (SETTLE && *mode != 1) return;
   using TT = TriTiles<D>;
   constexpr int S = (4 + D + D * (D + 1) / 2 + 3) & ~3;
@@ -1298,7 +1301,7 @@ __global__ __launch_bounds__(SUBX_BLOCK, 1) void k_sorted_x3(
   float* s_mu0 = reinterpret_cast<float*>(s_fr + 2 * NS * NFZ);
   float* s_dmu = s_mu0 + D;
   float* s_corr = s_dmu + D;  // W_1 (mu_0 - mu_1)
-  float* s_c = s_corr + D;    // c_0, c_1
+  float* s_c = s_corr + D;    // c_0, c_1 (SETTLE: c, ||W||_F)
   int* s_cnt = reinterpret_cast<int*>(s_c + 4);
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, h = lane >> 5, col = lane & 31;
   if (threadIdx.x == 0) *s_cnt = 0;
@@ -1365,7 +1368,7 @@ __global__ __launch_bounds__(SUBX_BLOCK, 1) void k_sorted_x3(
         }
         if (threadIdx.x == 0) {
           s_c[0] = r0[0];
-          if (!SETTLE) s_c[1] = r1[0];
+          s_c[1] = SETTLE ? cst[cur].y * (1.00001f / (UC_GAMMA + UC_GAMMA2)) : r1[0];
         }
         __syncthreads();
         if (!SETTLE && threadIdx.x < D) {
@@ -1387,6 +1390,7 @@ __global__ __launch_bounds__(SUBX_BLOCK, 1) void k_sorted_x3(
       }
       const bool has = __ballot(now.k == cur) != 0ull;
       bf16x8 xh[KS], xl[KS];  // the row centred on mu_0, hi and lo parts
+      float vv = 0.0f;        // SETTLE: the lane's half of its squared norm
       if (has) {
 #pragma unroll
         for (int ks = 0; ks < KS; ++ks) {
@@ -1395,6 +1399,7 @@ __global__ __launch_bounds__(SUBX_BLOCK, 1) void k_sorted_x3(
 #pragma unroll
           for (int q = 0; q < 8; ++q) {
             const float e = v[q] - s_mu0[16 * ks + 8 * h + q];
+            if (SETTLE) vv = fmaf(e, e, vv);
             xh[ks][q] = (__bf16)e;
             xl[ks][q] = (__bf16)(e - (float)xh[ks][q]);
           }
@@ -1443,9 +1448,10 @@ __global__ __launch_bounds__(SUBX_BLOCK, 1) void k_sorted_x3(
           qq[sub] = q;
           sc[sub] = fmaf(-0.5f, q, s_c[sub]);
         }
+        if (SETTLE) vv += __shfl_xor(vv, 32);
         if (now.k == cur) {
-          delta = SETTLE ? sc[0] : sc[0] - sc[NS - 1];
-          allow = fmaf(BF16X3_TOL_REL, SETTLE ? qq[0] : qq[0] + qq[NS - 1], TOL_ABS);
+          delta = SETTLE ? x3_lower(s_c[0], sqrtf(qq[0]), s_c[1] * sqrtf(vv)) : sc[0] - sc[NS - 1];
+          if (!SETTLE) allow = fmaf(BF16X3_TOL_REL, qq[0] + qq[NS - 1], TOL_ABS);
         }
       }
       if (cur == last) break;
@@ -1462,7 +1468,7 @@ __global__ __launch_bounds__(SUBX_BLOCK, 1) void k_sorted_x3(
     const long long rme = chunk + wave * 32 + col;
     if (SETTLE) {
       const bool mine = h == 0 && rme < cend;
-      const bool left = mine && !(ub[now.i] <= delta - allow - RGAP);
+      const bool left = mine && !(ub[now.i] <= delta - RGAP - TOL_ABS);
       if (mine && !left) z[now.i] = now.k;
       const unsigned long long lm = __ballot(left);
       if (lm != 0ull) {
@@ -1739,11 +1745,11 @@ hipError_t launch_sub_labels_x3(int d, const float* x, long long n, const int* p
   if (d == 128)
     hipLaunchKernelGGL((k_sorted_x3<128, false>), dim3(G), dim3(SUBX_BLOCK), lds, s, x, n, per, perm,
                        const_cast<int*>(z), zrow, zsub, packed, hi, lo, K, k_max, t, seed, b.flag, b.cnt, nullptr,
-                       nullptr, nullptr);
+                       nullptr, nullptr, nullptr);
   else if (d == 64)
     hipLaunchKernelGGL((k_sorted_x3<64, false>), dim3(G), dim3(SUBX_BLOCK), lds, s, x, n, per, perm,
                        const_cast<int*>(z), zrow, zsub, packed, hi, lo, K, k_max, t, seed, b.flag, b.cnt, nullptr,
-                       nullptr, nullptr);
+                       nullptr, nullptr, nullptr);
   else
     return hipErrorInvalidValue;
   hipError_t e = hipGetLastError();
@@ -1755,7 +1761,8 @@ hipError_t launch_sub_labels_x3(int d, const float* x, long long n, const int* p
 }
 
 hipError_t launch_settle(int d, const float* x, long long n, const int* perm, const int* guess, const float* packed,
-                         const void* whi, const void* wlo, int K, int k_max, const PruneBufs& b, int* z, hipStream_t s) {
+                         const void* whi, const void* wlo, const float* wbias, int K, int k_max, const PruneBufs& b, int* z,
+                         hipStream_t s) {
   if (n == 0) return hipSuccess;
   long long per = (n + 255) / 256;
   per = ((per + 63) / 64) * 64;
@@ -1763,7 +1770,7 @@ hipError_t launch_settle(int d, const float* x, long long n, const int* perm, co
 #define DPMM_SETTLE(DD)                                                                                              \
   hipLaunchKernelGGL((k_sorted_x3<DD, true>), dim3(G), dim3(SUBX_BLOCK), sorted_x3_lds(d, true), s, x, n, per, perm, \
                      z, guess, nullptr, packed, (const bf16x8*)whi, (const bf16x8*)wlo, K, k_max, 0u, 0ull, nullptr,  \
-                     b.n_open, b.ub, b.mode, b.open)
+                     b.n_open, b.ub, (const float4*)(wbias + (size_t)k_max * d), b.mode, b.open)
   if (d == 128)
     DPMM_SETTLE(128);
   else if (d == 64)

@@ -17,11 +17,12 @@
 //                 for some point of the wave.  The draw of the points (score.hpp)
 //                 takes the clusters in that order and gives the argmax of
 //                 l_k + g_k with the smaller k on ties, as in increasing order;
-//   k_sorted_x3   (BF16, label_mfma.hip) the guessed clusters in full in bf16x3, which
-//                 with the bound settles most points, and a list of the others for
-//                 the main pass.
-// Scores have the bits of the kernel that forms them all (label_gauss_mx.hip), so
-// the labels are the same whatever the data.  A BF16 draw, whose main pass over all
+//   k_sorted_x3   (BF16, label_mfma.hip) a lower bound of the guessed clusters' scores
+//                 from bf16x3 products, which with the upper bound settles most points,
+//                 and a list of the others for the main pass.
+// FP32 scores have the bits of the kernel that forms them all (label_gauss_mx.hip), and
+// what the bounds settle no score would change (interval.hpp), so the labels are the same
+// whatever the data.  A BF16 draw, whose main pass over all
 // points is within three times of this, first looks at 512 of the points (k_guess
 // <true>) and takes that main pass where less than 3/4 of them would be settled.
 //
