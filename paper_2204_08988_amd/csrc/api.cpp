@@ -111,10 +111,6 @@ dpmm_status ensure_perm(dpmm_ctx* ctx, int64_t n) {
     ctx->d_sflag = nullptr;
     ctx->d_perm_c = nullptr;
     ctx->d_zrow_c = nullptr;
-    hipFree(ctx->d_ub);
-    hipFree(ctx->d_popen);
-    ctx->d_ub = nullptr;
-    ctx->d_popen = nullptr;
     ctx->perm_cap = 0;
   }
   DPMM_HIP(ctx, hipMalloc(&ctx->d_perm, (size_t)n * sizeof(int)), "allocate permutation");
@@ -127,13 +123,29 @@ dpmm_status ensure_perm(dpmm_ctx* ctx, int64_t n) {
     DPMM_HIP(ctx, hipMalloc(&ctx->d_perm_c, (size_t)n * sizeof(int)), "allocate sub-label list");
     DPMM_HIP(ctx, hipMalloc(&ctx->d_zrow_c, (size_t)n * sizeof(int)), "allocate sub-label list");
   }
-  if (ctx->d_gtab) {
-    DPMM_HIP(ctx, hipMalloc(&ctx->d_ub, (size_t)n * sizeof(float)), "allocate score bounds");
-    if (ctx->d_shi)
-      DPMM_HIP(ctx, hipMalloc(&ctx->d_popen, (size_t)n * sizeof(int)), "allocate open points");
-  }
   ctx->perm_cap = n;
   return ensure_part(ctx, n);
+}
+
+// the buffers of the draw by a guess, for the contexts that come to take it; false when
+// the device has no room for them (the draw that forms every score needs none)
+bool guess_buffers(dpmm_ctx* ctx, int64_t n) {
+  if (n <= ctx->guess_cap) return true;
+  if (ctx->d_ub && hipStreamSynchronize(ctx->stream) != hipSuccess) return false;
+  hipFree(ctx->d_ub);
+  hipFree(ctx->d_popen);
+  ctx->d_ub = nullptr;
+  ctx->d_popen = nullptr;
+  ctx->guess_cap = 0;
+  if (hipMalloc(&ctx->d_ub, (size_t)n * sizeof(float)) != hipSuccess ||
+      (ctx->d_shi && hipMalloc(&ctx->d_popen, (size_t)n * sizeof(int)) != hipSuccess)) {
+    hipFree(ctx->d_ub);
+    ctx->d_ub = nullptr;
+    (void)hipGetLastError();
+    return false;
+  }
+  ctx->guess_cap = n;
+  return true;
 }
 
 // partial-slot buffer of the sorted-order statistics kernels, sized for any
@@ -827,11 +839,11 @@ dpmm_status label_phase(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t, int
   ctx->labels_gave_stats = false;
   if (ctx->sorted_path()) {
     const bool mfma = ctx->d_whi != nullptr;
+    DPMM_TRY(ensure_perm(ctx, n));
     const bool by_guess = ctx->d_gtab && label_prune_pays(ctx->d, ctx->K, n, mfma) &&
-                          (!mfma || uc_list_fits(ctx->d, ctx->K));
+                          (!mfma || uc_list_fits(ctx->d, ctx->K)) && guess_buffers(ctx, n);
     // the FP32 kernels take 256 rows per workgroup step, the BF16 ones and the guess 512: blocks of as many
     sorted_plan(n, ctx->K, ctx->hist_cap, G, per, mfma || by_guess ? 512 : 256);
-    DPMM_TRY(ensure_perm(ctx, n));
     ctx->z_hist = !by_guess;  // drawn in sorted order, z is counted afterwards
     ctx->z_hist_if_dense = by_guess && mfma;
     const PruneBufs pb{ctx->d_gtab, ctx->d_ub, ctx->d_pflag, ctx->d_pflag + 1, ctx->d_popen};

@@ -88,9 +88,11 @@ struct dpmm_ctx {
   // offsets, constants and the common centre of the uncentred BF16 main pass (d = 64, 128)
   float* d_wbias = nullptr;
   // the draw over rows sorted by a guess (label_prune.hip): tables, a bound per point,
-  // mode and count, the points left to the BF16 main pass
+  // mode and count, the points left to the BF16 main pass; d_ub and d_popen hold
+  // guess_cap points (from the first such draw on)
   unsigned char* d_gtab = nullptr;
   float* d_ub = nullptr;
+  int64_t guess_cap = 0;
   int *d_pflag = nullptr, *d_popen = nullptr;
   bool z_hist = false;              // the last cluster draw left the histogram of z in d_hist
   bool z_hist_if_dense = false;     // ... or did where it left *d_pflag at 0

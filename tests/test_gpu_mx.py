@@ -174,3 +174,30 @@ def test_bf16_draw_by_guess(d, K, n, spread):
     assert torch.equal(z["fp32"], z["bf16"])
     count = torch.bincount(z["bf16"].long() * 2 + zs.long(), minlength=2 * K).cpu().numpy()
     assert np.array_equal(got, count.reshape(K, 2))
+
+
+# the buffers of the draw by a guess belong to the contexts that take it: with K too small for it a label step
+# holds the permutation and the sorted labels, in BF16 beside the candidate lists and the sub-labels' lists
+@pytest.mark.parametrize("d,prec,per_point", [(48, "fp32", 8), (64, "bf16", 8 + 32 + 9)])
+def test_scratch_of_a_label_step_with_few_clusters(d, prec, per_point):
+    import torch
+
+    from paper_2204_08988_amd.sampler import Sampler
+    K, sizes = 2, (1_000_000, 9_000_000)
+    params = pu.random_gauss_params(K, d, 3)
+    taken = []
+    for n in sizes:
+        x = torch.zeros((n, d), device="cuda")
+        z = torch.empty(n, dtype=torch.int32, device="cuda")
+        zs = torch.empty(n, dtype=torch.uint8, device="cuda")
+        S = Sampler("gaussian", d, K, 2.0, 11, kappa=1.0, nu=d + 3.0, m=np.zeros(d), psi=np.eye(d), precision=prec)
+        S.set_params(params.log_pi, params.log_pisub, pu.comp_array(params))
+        torch.cuda.synchronize()
+        free = torch.cuda.mem_get_info()[0]
+        S.sample_labels(x, 1, z, zs)
+        torch.cuda.synchronize()
+        taken.append(free - torch.cuda.mem_get_info()[0])
+        S.close()
+        del x, z, zs
+    # (allocations are rounded up to 2 MB)
+    assert taken[1] - taken[0] <= per_point * (sizes[1] - sizes[0]) + (8 << 20), taken
