@@ -1018,8 +1018,9 @@ dpmm_status dpmm_split_merge(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t
       DPMM_TRY(logml_range(ctx, 0, first_pair));
       DPMM_HIP(ctx, launch_merge_pairs(P, ctx->d_items + first_pair, ctx->d, K, prior_dev(ctx), ctx->logdet_psi,
                                        ctx->lam_psi, ctx->d_counts, ctx->d_moments, ctx->d_logml,
-                                       ctx->d_logml + 3 * K, alpha, paper_form, seed, t, ctx->d_err, ctx->d_rb,
-                                       ctx->stream), "merge test kernel");
+                                       ctx->d_logml + 3 * K, alpha, paper_form, seed, t, ctx->d_err,
+                                       reinterpret_cast<int*>(ctx->d_logml + first_pair), ctx->d_rb, ctx->stream),
+               "merge test kernel");
     } else {
       DPMM_TRY(logml_range(ctx, 0, items.size()));
       DPMM_HIP(ctx, launch_merge_decide(P, ctx->d_items + first_pair, K, ctx->d_counts, ctx->d_logml,

@@ -283,11 +283,12 @@ hipError_t launch_logml_gauss(int n_items, const LogmlItem* items, int d, NiwPri
 // factorisation failed]
 size_t readback_bytes(int K, int P);
 // d <= MERGE_BOUND_MAX_D: the merge test of every pair, bound first (lml: the 3K
-// log marginals, logdet_half: the K bound items)
+// log marginals, logdet_half: the K bound items; list: P + 3 ints of scratch, 8-byte
+// aligned, P > 0)
 hipError_t launch_merge_pairs(int P, const LogmlItem* pairs, int d, int K, NiwPriorDev prior, double logdet_psi,
                               double lam_psi, const long long* counts, const double* moments, const double* lml,
                               const double* logdet_half, double alpha, bool paper_form, uint64_t seed, uint32_t t,
-                              const int* err, unsigned char* out, hipStream_t s);
+                              const int* err, int* list, unsigned char* out, hipStream_t s);
 // the merge test of every pair from its union marginal lml_pair (P may be 0)
 hipError_t launch_merge_decide(int P, const LogmlItem* pairs, int K, const long long* counts, const double* lml,
                                const double* lml_pair, double alpha, bool paper_form, uint64_t seed, uint32_t t,

@@ -440,7 +440,25 @@ __device__ double merge_gammas_wave(double n1, double n2, double alpha, int pape
   return g;
 }
 
-// Merge tests of the Gaussian pairs for d <= MERGE_BOUND_MAX_D, one wave per pair
+// Whether the merge bound leaves a pair to its full test, from the terms of the bound:
+// tr1, tr2 = tr C_k, dx2 = |xbar1 - xbar2|^2, lh1, lh2 = log|Psi/2 + C_k|, lmg = log
+// Gamma_d(nu_n / 2) - log Gamma_d(nu / 2), g = log H_merge without the marginals.
+__device__ __forceinline__ bool merge_open(double n1, double n2, double tr1, double tr2, double dx2, double lh1,
+                                           double lh2, double lmg, double g, double l1, double l2, double lu, int d,
+                                           const NiwPriorDev& prior, double logdet_psi, double lam_psi) {
+  const double n = n1 + n2, a = lh1 / d, c = lh2 / d;
+  const double lb = d * (fmax(a, c) + log1p(exp(-fabs(a - c)))) + log1p(n1 * n2 / n * dx2 / (lam_psi + tr1 + tr2));
+  const double nun = prior.nu + n, kn = prior.kappa + n;
+  const double ub_u = -0.5 * n * d * 1.1447298858494002 + lmg + 0.5 * prior.nu * logdet_psi - 0.5 * nun * lb +
+                      0.5 * d * (log(prior.kappa) - log(kn));
+  const double ub = g + ub_u - l1 - l2;
+  // float64 rounding of the terms above (and of the Cholesky factorisations behind them)
+  const double margin = 1e-9 * (fabs(g) + fabs(lmg) + 0.5 * nun * fabs(lb) + 0.5 * n * d * 1.15 + fabs(l1) + fabs(l2) +
+                                0.5 * prior.nu * fabs(logdet_psi)) + 1e-6;
+  return !(ub + margin < lu);
+}
+
+// Merge tests of the Gaussian pairs for d <= MERGE_BOUND_MAX_D
 // (Sec. 4.1 eq. sample_merges; with paper_form = 0 the reciprocal of the split
 // ratio of Sec. 2.3): first the merge bound, and for a pair that it leaves the
 // union's log marginal and the test itself, log u < log H_merge with u the merge
@@ -448,15 +466,42 @@ __device__ double merge_gammas_wave(double n1, double n2, double alpha, int pape
 //   Psi_n(U) >= X + Y + b b^T,  X = Psi/2 + C1, Y = Psi/2 + C2 (scatters about
 //   the clusters' means), b = sqrt(n1 n2 / n) (xbar1 - xbar2);
 //   log|X + Y| >= d log(|X|^(1/d) + |Y|^(1/d)) (Minkowski's determinant inequality),
-//   b^T (X + Y)^-1 b >= |b|^2 / (lambda_max(Psi) + tr C1 + tr C2),
+//   b^T (X + Y)^-1 b >= |b|^2 / (lam_psi + tr C1 + tr C2)
 // give a lower bound LB on log|Psi_n(U)|, so an upper bound on the NIW
 // marginal of U and on log H_merge.  A pair whose bound (plus a rounding
 // margin) lies below log u is rejected here: exactly the decision its full
 // ratio would give.  logdet_half[k] = log|Psi/2 + C_k|; lam_psi >= lambda_max(Psi).
-// Decisions: 0, 1, or 2 when the union's Cholesky failed.  Latency of one wave; a
-// thread per pair and a launch each for the bound, its survivors' marginals, their
-// test and the read-back took 22 us and five gaps at d = 2, K = 6 and 58 us at
-// d = 16, K = 8; this kernel 9 and 16 us.
+// Decisions: 0, 1, or 2 when the union's Cholesky failed.
+//
+// k_merge_pairs: a wave per pair, the terms of the bound one per lane.  Latency of one
+// wave; a thread per pair and a launch each for the bound, its survivors' marginals,
+// their test and the read-back took 22 us and five gaps at d = 2, K = 6 and 58 us at
+// d = 16, K = 8; this 9 and 16 us.
+// From MERGE_MANY pairs on the device is full of those waves, and each decision is a
+// store of one byte to the host: k_merge_bound takes a thread per pair, rejects most of
+// them and lists the others, and k_merge_listed tests those, a wave per pair.  The whole
+// phase (split_merge, no moves), us, a wave per pair and so: K = 128 (8128 pairs) 86 and
+// 81 at d = 2, 86 and 90 at d = 16; K = 181 130 and 102; K = 256 224 and 148, 231 and
+// 162; K = 1024, d = 16 3226 and 1782.
+__device__ __forceinline__ double segments_size(const long long* __restrict__ counts, int k) {
+  return (double)(counts[2 * k] + counts[2 * k + 1]);
+}
+
+__device__ __forceinline__ double merge_log_u(const LogmlItem& it, uint64_t seed, uint32_t t) {
+  return log(uniform_d(rng_block(seed, t, merge_entity(it.seg[0] >> 1, it.seg[2] >> 1), TAG_MERGE, 0).x));
+}
+
+// the test of a pair that the bound leaves, by a whole wave (sm, lg as in logml_wave)
+template <int D>
+__device__ __forceinline__ unsigned char merge_test(const LogmlItem& it, int d, const NiwPriorDev& prior,
+                                                    double logdet_psi, const long long* __restrict__ counts,
+                                                    const double* __restrict__ moments, const double* __restrict__ lml,
+                                                    double* sm, const double* lg, double g, double lu) {
+  bool ok;
+  const double lp = logml_wave<D>(it, d, prior, logdet_psi, counts, moments, sm, lg, ok);
+  return !ok ? 2 : (lu < g + lp - lml[3 * (it.seg[0] >> 1)] - lml[3 * (it.seg[2] >> 1)] ? 1 : 0);
+}
+
 template <int D>
 __global__ __launch_bounds__(BLOCK) void k_merge_pairs(int P, const LogmlItem* __restrict__ pairs, int d, int K,
                                                        NiwPriorDev prior, double logdet_psi, double lam_psi,
@@ -476,9 +521,7 @@ __global__ __launch_bounds__(BLOCK) void k_merge_pairs(int P, const LogmlItem* _
   const LogmlItem it = pairs[p];
   const int k1 = it.seg[0] >> 1, k2 = it.seg[2] >> 1;
   const int E = d + d * (d + 1) / 2;
-  const double n1 = (double)(counts[2 * k1] + counts[2 * k1 + 1]);
-  const double n2 = (double)(counts[2 * k2] + counts[2 * k2 + 1]);
-  const double n = n1 + n2;
+  const double n1 = segments_size(counts, k1), n2 = segments_size(counts, k2);
   const double* A0 = moments + (size_t)(2 * k1) * E;
   const double* A1 = A0 + E;
   const double* B0 = moments + (size_t)(2 * k2) * E;
@@ -491,27 +534,83 @@ __global__ __launch_bounds__(BLOCK) void k_merge_pairs(int P, const LogmlItem* _
   const double tr1 = fmax(wave_sum(live ? A0[di] + A1[di] : 0.0) - wave_sum(live ? s1 * s1 : 0.0) / n1, 0.0);
   const double tr2 = fmax(wave_sum(live ? B0[di] + B1[di] : 0.0) - wave_sum(live ? s2 * s2 : 0.0) / n2, 0.0);
   const double dx2 = wave_sum(live ? dd * dd : 0.0);
-  const double a = logdet_half[k1] / d, c = logdet_half[k2] / d;
-  const double lb = d * (fmax(a, c) + log1p(exp(-fabs(a - c)))) + log1p(n1 * n2 / n * dx2 / (lam_psi + tr1 + tr2));
-  const double nun = prior.nu + n, kn = prior.kappa + n;
+  const double nun = prior.nu + (n1 + n2);
   const double lmg =
       wave_sum(live ? lgamma_d(0.5 * nun - 0.5 * lane) - lgamma_d(0.5 * prior.nu - 0.5 * lane) : 0.0);
-  const double ub_u = -0.5 * n * d * 1.1447298858494002 + lmg + 0.5 * prior.nu * logdet_psi - 0.5 * nun * lb +
-                      0.5 * d * (log(prior.kappa) - log(kn));
-  const double g = merge_gammas_wave(n1, n2, alpha, paper_form);
-  const double l1 = lml[3 * k1], l2 = lml[3 * k2];
-  const double ub = g + ub_u - l1 - l2;
-  // float64 rounding of the terms above (and of the Cholesky factorisations behind them)
-  const double margin = 1e-9 * (fabs(g) + fabs(lmg) + 0.5 * nun * fabs(lb) + 0.5 * n * d * 1.15 + fabs(l1) + fabs(l2) +
-                                0.5 * prior.nu * fabs(logdet_psi)) + 1e-6;
-  const double lu = log(uniform_d(rng_block(seed, t, merge_entity(k1, k2), TAG_MERGE, 0).x));
+  const double g = merge_gammas_wave(n1, n2, alpha, paper_form), lu = merge_log_u(it, seed, t);
   unsigned char dec = 0;
-  if (!(ub + margin < lu)) {  // the same for every lane
-    bool ok;
-    const double lp = logml_wave<D>(it, d, prior, logdet_psi, counts, moments, ssum[wave], &lmg, ok);
-    dec = !ok ? 2 : (lu < g + lp - l1 - l2 ? 1 : 0);
-  }
+  if (merge_open(n1, n2, tr1, tr2, dx2, logdet_half[k1], logdet_half[k2], lmg, g, lml[3 * k1], lml[3 * k2], lu, d, prior,
+                 logdet_psi, lam_psi))  // the same for every lane
+    dec = merge_test<D>(it, d, prior, logdet_psi, counts, moments, lml, ssum[wave], &lmg, g, lu);
   if (lane == 0) out[8 + 40 * (size_t)K + p] = dec;
+}
+
+// list: the pairs left, *n_list of them (cleared before); the others' decisions are 0.  (A
+// pair with an empty cluster is rejected: the round starts over without that cluster.)
+__global__ __launch_bounds__(BLOCK) void k_merge_bound(int P, const LogmlItem* __restrict__ pairs, int d, int K,
+                                                       NiwPriorDev prior, double logdet_psi, double lam_psi,
+                                                       const long long* __restrict__ counts,
+                                                       const double* __restrict__ moments,
+                                                       const double* __restrict__ lml,
+                                                       const double* __restrict__ logdet_half, double alpha,
+                                                       int paper_form, uint64_t seed, uint32_t t,
+                                                       const int* __restrict__ err, int* __restrict__ list,
+                                                       int* __restrict__ n_list, unsigned char* __restrict__ out) {
+  const int p = blockIdx.x * BLOCK + threadIdx.x;
+  for (int i = p; i < 5 * K; i += gridDim.x * BLOCK) pack_readback(i, K, counts, lml, err, out);
+  if (p >= P) return;
+  const LogmlItem it = pairs[p];
+  const int k1 = it.seg[0] >> 1, k2 = it.seg[2] >> 1;
+  const int E = d + d * (d + 1) / 2;
+  const double n1 = segments_size(counts, k1), n2 = segments_size(counts, k2);
+  out[8 + 40 * (size_t)K + p] = 0;
+  if (n1 == 0.0 || n2 == 0.0) return;
+  const double* A0 = moments + (size_t)(2 * k1) * E;
+  const double* A1 = A0 + E;
+  const double* B0 = moments + (size_t)(2 * k2) * E;
+  const double* B1 = B0 + E;
+  double tr1 = 0.0, tr2 = 0.0, ss1 = 0.0, ss2 = 0.0, dx2 = 0.0, lmg = 0.0;
+  for (int i = 0; i < d; ++i) {
+    const int di = d + tri_index(i, i, d);
+    const double s1 = A0[i] + A1[i], s2 = B0[i] + B1[i], dd = s1 / n1 - s2 / n2;
+    tr1 += A0[di] + A1[di];
+    tr2 += B0[di] + B1[di];
+    ss1 += s1 * s1;
+    ss2 += s2 * s2;
+    dx2 += dd * dd;
+    lmg += lgamma_d(0.5 * (prior.nu + (n1 + n2)) - 0.5 * i) - lgamma_d(0.5 * prior.nu - 0.5 * i);
+  }
+  double g = lgamma_d(n1 + n2) - log(alpha) - lgamma_d(n1) - lgamma_d(n2);
+  if (paper_form)
+    g += lgamma_d(alpha) - lgamma_d(alpha + n1 + n2) + lgamma_d(0.5 * alpha + n1) + lgamma_d(0.5 * alpha + n2) -
+         2.0 * lgamma_d(0.5 * alpha);
+  if (merge_open(n1, n2, fmax(tr1 - ss1 / n1, 0.0), fmax(tr2 - ss2 / n2, 0.0), dx2, logdet_half[k1], logdet_half[k2], lmg,
+                 g, lml[3 * k1], lml[3 * k2], merge_log_u(it, seed, t), d, prior, logdet_psi, lam_psi))
+    list[atomicAdd(n_list, 1)] = p;  // the order of the list does not matter: one result per pair
+}
+
+template <int D>
+__global__ __launch_bounds__(BLOCK) void k_merge_listed(const LogmlItem* __restrict__ pairs, int d, int K,
+                                                        NiwPriorDev prior, double logdet_psi,
+                                                        const long long* __restrict__ counts,
+                                                        const double* __restrict__ moments,
+                                                        const double* __restrict__ lml, double alpha, int paper_form,
+                                                        uint64_t seed, uint32_t t, const int* __restrict__ list,
+                                                        const int* __restrict__ n_list,
+                                                        unsigned char* __restrict__ out) {
+  constexpr int ED = D + D * (D + 1) / 2;
+  __shared__ double ssum[BLOCK / 64][ED];
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, n = *n_list;
+  for (int q = blockIdx.x * (BLOCK / 64) + wave; q < n; q += gridDim.x * (BLOCK / 64)) {
+    const int p = list[q];
+    const LogmlItem it = pairs[p];
+    const double g = merge_gammas_wave(segments_size(counts, it.seg[0] >> 1), segments_size(counts, it.seg[2] >> 1), alpha,
+                                       paper_form);
+    wave_sync();  // the previous pair's statistics are read
+    const unsigned char dec = merge_test<D>(it, d, prior, logdet_psi, counts, moments, lml, ssum[wave], nullptr, g,
+                                            merge_log_u(it, seed, t));
+    if (lane == 0) out[8 + 40 * (size_t)K + p] = dec;
+  }
 }
 
 // The merge test of every pair from the union marginals of a launch before
@@ -705,15 +804,28 @@ hipError_t launch_logml_gauss(int n_items, const LogmlItem* items, int d, NiwPri
   return hipGetLastError();
 }
 
+constexpr int MERGE_MANY = 8192;
+
 hipError_t launch_merge_pairs(int P, const LogmlItem* pairs, int d, int K, NiwPriorDev prior, double logdet_psi,
                               double lam_psi, const long long* counts, const double* moments, const double* lml,
                               const double* logdet_half, double alpha, bool paper_form, uint64_t seed, uint32_t t,
-                              const int* err, unsigned char* out, hipStream_t s) {
-  if (d > MERGE_BOUND_MAX_D) return hipErrorInvalidValue;
-  const int waves = BLOCK / 64;
-  hipLaunchKernelGGL(k_merge_pairs<MERGE_BOUND_MAX_D>, dim3((P + waves - 1) / waves), dim3(BLOCK), 0, s, P, pairs, d, K,
-                     prior, logdet_psi, lam_psi, counts, moments, lml, logdet_half, alpha, paper_form ? 1 : 0, seed, t,
-                     err, out);
+                              const int* err, int* list, unsigned char* out, hipStream_t s) {
+  constexpr int D = MERGE_BOUND_MAX_D, WAVES = BLOCK / 64;
+  if (d > D) return hipErrorInvalidValue;
+  const int form = paper_form ? 1 : 0;
+  if (P < MERGE_MANY) {
+    hipLaunchKernelGGL(k_merge_pairs<D>, dim3((P + WAVES - 1) / WAVES), dim3(BLOCK), 0, s, P, pairs, d, K, prior,
+                       logdet_psi, lam_psi, counts, moments, lml, logdet_half, alpha, form, seed, t, err, out);
+    return hipGetLastError();
+  }
+  int* n_list = list + P + (P & 1);  // 8-byte aligned
+  hipError_t e = launch_zero64(n_list, 1, s);
+  if (e != hipSuccess) return e;
+  hipLaunchKernelGGL(k_merge_bound, dim3((P + BLOCK - 1) / BLOCK), dim3(BLOCK), 0, s, P, pairs, d, K, prior, logdet_psi,
+                     lam_psi, counts, moments, lml, logdet_half, alpha, form, seed, t, err, list, n_list, out);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_merge_listed<D>, dim3(2048), dim3(BLOCK), 0, s, pairs, d, K, prior, logdet_psi, counts, moments,
+                     lml, alpha, form, seed, t, list, n_list, out);
   return hipGetLastError();
 }
 

@@ -78,3 +78,34 @@ def test_merge_tests_of_close_and_distant_pairs(d, K, form):
     assert (info["K"], info["splits"], info["merges"]) == (ref.K, ri.splits, ri.merges) and info["merges"] > 0
     assert np.array_equal(zt.cpu().numpy(), ref.z) and np.array_equal(zst.cpu().numpy(), ref.zsub)
     S.close()
+
+
+# from 8192 pairs on a bound per thread and a wave for each pair that it leaves; some clusters coincide, one is empty
+@pytest.mark.parametrize("d,K,form", [(1, 130, "paper"), (2, 141, "inverse_split"), (16, 130, "paper")])
+def test_merge_tests_of_many_pairs(d, K, form):
+    import torch
+
+    from paper_2204_08988_amd.sampler import Sampler
+    seed = 5 + d + K
+    g = np.random.Generator(np.random.PCG64(seed))
+    n = 40 * K
+    z = np.arange(n) % K
+    z[z == K // 2] = 1
+    centre = np.where(np.arange(K) % 16 == 3, 0.0, 9.0 * np.arange(K))  # every sixteenth cluster in one place
+    x = (g.standard_normal((n, d)) + centre[z][:, None]).astype(np.float32)
+    zs = g.integers(0, 2, n)
+    model = sampler.Model("gaussian", 2.0, niw.NIWPrior(1.0, np.zeros(d), d + 3.0, np.eye(d)), seed=seed, burn_out=0,
+                          merge_form=form)
+    S = Sampler("gaussian", d, 2 * K + 4, 2.0, seed, kappa=1.0, nu=d + 3.0, m=np.zeros(d), psi=np.eye(d), burn_out=0,
+                merge_form=form)
+    xt, zt = torch.from_numpy(x).cuda(), torch.from_numpy(z.astype(np.int32)).cuda()
+    zst = torch.from_numpy(zs.astype(np.uint8)).cuda()
+    S.set_state(K, [3] * K)
+    S.suffstats(xt, zt, zst)
+    info = S.split_merge(xt, 4, zt, zst)
+    st, stats = sampler.drop_empty(model, x, sampler.State(K, z.astype(np.int64), zs.astype(np.int64), np.full(K, 3)))
+    ref, ri = sampler.split_merge(model, st, stats, 4)
+    assert (info["K"], info["splits"], info["merges"]) == (ref.K, ri.splits, ri.merges)
+    assert info["merges"] > 0 and info["removed"] == 1
+    assert np.array_equal(zt.cpu().numpy(), ref.z) and np.array_equal(zst.cpu().numpy(), ref.zsub)
+    S.close()
