@@ -104,22 +104,28 @@ __global__ __launch_bounds__(BLOCK) void k_label_mult(const int* __restrict__ x,
 // clusters 4 g .. 4 g + 3 of every 16 for point c.
 //
 // Clusters within the Gumbel range of the running maximum are listed per wave in
-// LDS (point, cluster, score); with a single group only those of points that have
-// several.  The list's Gumbels are drawn one entry per lane, whatever points they
-// belong to, and each point's winner (largest l_k + g_k, smaller k on ties) is a
-// 64-bit LDS maximum: a wave with a few doubtful points pays for their clusters,
-// not for every cluster of 64 points.  The sub-label needs the point's whole row
-// on one lane: a 4 x 4 lane transpose of the registers.  The two sub-cluster
-// records come from LDS while they fit beside the clusters'.
+// LDS by fours (point, the clusters of one random block and their scores); with a
+// single group only those of points that have several.  A lane draws the Gumbels of
+// one entry, whatever point it belongs to, and each point's winner (largest l_k +
+// g_k, smaller k on ties) is a 64-bit LDS maximum: a wave with a few doubtful points
+// pays for their clusters, not for every cluster of 64 points, and one whose clusters
+// are nearly all in range for one random block per four of them.  The sub-label needs
+// the point's whole row on one lane: a 4 x 4 lane transpose of the registers.  The two
+// sub-cluster records come from LDS while they fit beside the clusters'.
 //
 // Bound by the FP32 matrix cores, and HBM behind them.  N = 1e6, V = 100, K = 50:
 // 646 us (32-row tiles, rows read with a stride, the whole wave scored twice for
-// one doubtful point, sub-cluster records gathered from memory) -> 196 us; its 400
-// matrix instructions per 64 points take 95.
-constexpr int MM_BLOCK = 512;
-constexpr int MM_LIST = 1024;  // candidates listed per wave: those of one tile and group always fit
-constexpr int MM_WAVES = MM_BLOCK / 64;
+// one doubtful point, sub-cluster records gathered from memory) -> 186 us; its 400
+// matrix instructions per 64 points take 95.  With nearly every cluster in range (counts
+// of one law) V = 7, K = 200, N = 3e5: 233 us that way, 365 with the candidates listed
+// one by one and a random block for each, 182 so; V = 64, K = 300, N = 5e4: 130, 210, 94.
+constexpr int MM_BLOCK = 512;  // threads at most
+constexpr int MM_LIST = 256;  // fours of candidates listed per wave: those of one tile and group always fit
 constexpr size_t MM_LDS_MAX = 150 * 1024;
+// up to here workgroups of half as many threads, so that no more than one per CU
+// still leaves fewer CUs idle: V = 100, K = 50, us with 256 and 512 threads: n = 2e4 30 and
+// 39, 5e4 31 and 40, 1e5 58 and 43; V = 32, K = 600: n = 5e4 150 and 192, 1e5 285 and 200
+constexpr long long MM_SMALL_N = 65536;
 
 __host__ __device__ constexpr int mm_ldv(int V) { return 4 * (((V + 3) / 4) | 1); }
 
@@ -135,17 +141,18 @@ __global__ __launch_bounds__(MM_BLOCK, 2) void k_label_mult_mfma(const int* __re
                                                                  uint32_t t, uint64_t seed,
                                                                  int* __restrict__ z, unsigned char* __restrict__ zsub) {
   typedef float f32x4 __attribute__((ext_vector_type(4)));
+  const int nt = blockDim.x, nw = nt / 64;
   const int S = mult_rec_stride(V), LDV = mm_ldv(V), Q = LDV / 4;
   extern __shared__ __align__(16) float th[];  // [K][LDV] clusters, then (SUB) [2K][LDV] sub-clusters
   float* cw = th + (size_t)(SUB ? 3 : 1) * K * LDV;  // [K rounded up to 64] log w (-inf past K), [2K] sub-clusters'
   const int KP = (K + 63) & ~63;
-  float* csub = cw + KP;
-  unsigned long long* best_all = reinterpret_cast<unsigned long long*>(cw + KP + 2 * K);  // [waves][64]
-  float* lists = reinterpret_cast<float*>(best_all + MM_WAVES * 64);  // [waves][MM_LIST] scores
-  unsigned short* listk = reinterpret_cast<unsigned short*>(lists + MM_WAVES * MM_LIST);  // point << 10 | cluster
+  f32x4* lists = reinterpret_cast<f32x4*>(cw + KP);  // [waves][MM_LIST] scores of clusters k .. k + 3
+  unsigned long long* best_all = reinterpret_cast<unsigned long long*>(lists + nw * MM_LIST);  // [waves][64]
+  float* csub = reinterpret_cast<float*>(best_all + nw * 64);
+  unsigned short* listk = reinterpret_cast<unsigned short*>(csub + 2 * K);  // [waves][MM_LIST] point << 10 | k
   {
     const int rows = SUB ? 3 * K : K;
-    for (int e = threadIdx.x; e < rows * Q; e += MM_BLOCK) {
+    for (int e = threadIdx.x; e < rows * Q; e += nt) {
       const int r = e / Q, q = e - r * Q;
       const float* src = packed + (size_t)(r < K ? r : k_max + (r - K)) * S + 4;
       float4 v = make_float4(0.f, 0.f, 0.f, 0.f);
@@ -156,14 +163,14 @@ __global__ __launch_bounds__(MM_BLOCK, 2) void k_label_mult_mfma(const int* __re
       v.w = 4 * q + 3 < V ? v.w : 0.0f;
       *reinterpret_cast<float4*>(th + (size_t)r * LDV + 4 * q) = v;
     }
-    for (int k = threadIdx.x; k < KP; k += MM_BLOCK) cw[k] = k < K ? packed[(size_t)k * S] : -INFINITY;
-    for (int k = threadIdx.x; k < 2 * K; k += MM_BLOCK) csub[k] = packed[(size_t)(k_max + k) * S];
+    for (int k = threadIdx.x; k < KP; k += nt) cw[k] = k < K ? packed[(size_t)k * S] : -INFINITY;
+    for (int k = threadIdx.x; k < 2 * K; k += nt) csub[k] = packed[(size_t)(k_max + k) * S];
   }
   __syncthreads();
   const int lane = threadIdx.x & 63, g = lane >> 4, c = lane & 15;
   const int wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
   unsigned long long* best = best_all + wave * 64;
-  float* ll = lists + wave * MM_LIST;
+  f32x4* ll = lists + wave * MM_LIST;
   unsigned short* lk = listk + wave * MM_LIST;
   const int ext = V - 16 * (RB - 1);  // words of the last 16
   // Gumbels of the listed candidates above their point's floor; the winners into best
@@ -171,21 +178,29 @@ __global__ __launch_bounds__(MM_BLOCK, 2) void k_label_mult_mfma(const int* __re
     wave_sync();
     for (int e0 = 0; e0 < cnt; e0 += 64) {
       const int e = e0 + lane;
-      const float l = ll[e < cnt ? e : 0];
+      const f32x4 l = ll[e < cnt ? e : 0];
       const int pk = lk[e < cnt ? e : 0], p = pk >> 10, k = pk & 1023;
       // the floor of point p: lane p % 16 holds it for tile p / 16
       const float f0 = __shfl(fl[0], p & 15), f1 = __shfl(fl[1], p & 15), f2 = __shfl(fl[2], p & 15),
                   f3 = __shfl(fl[3], p & 15);
       const float f = p < 32 ? (p < 16 ? f0 : f1) : (p < 48 ? f2 : f3);
-      if (e < cnt && l > f) {
+      if (e < cnt && (l[0] > f || l[1] > f || l[2] > f || l[3] > f)) {
         const u32x4 blk = rng_block(seed, t, (uint32_t)(base + p), TAG_GUMBEL, (uint32_t)(k >> 2));
-        const float sv = l + gumbel_f(word_of(blk, k & 3));
-        atomicMax(&best[p], (unsigned long long)order_key(sv) << 32 | (uint32_t)(0x7fffffff - k));
+        float sv = -INFINITY;
+        int w = 0;
+#pragma unroll
+        for (int u = 0; u < 4; ++u)
+          if (l[u] > f) {
+            const float v = l[u] + gumbel_f(word_of(blk, u));
+            w = v > sv ? u : w;  // the smaller k on ties
+            sv = fmaxf(sv, v);
+          }
+        atomicMax(&best[p], (unsigned long long)order_key(sv) << 32 | (uint32_t)(0x7fffffff - (k + w)));
       }
     }
     wave_sync();
   };
-  for (long long chunk = (long long)blockIdx.x * MM_BLOCK; chunk < n; chunk += (long long)gridDim.x * MM_BLOCK) {
+  for (long long chunk = (long long)blockIdx.x * nt; chunk < n; chunk += (long long)gridDim.x * nt) {
     const long long base = chunk + wave * 64;
     if (base >= n) continue;  // (no workgroup barrier in the loop)
     float xv[4][4 * RB];
@@ -272,28 +287,28 @@ __global__ __launch_bounds__(MM_BLOCK, 2) void k_label_mult_mfma(const int* __re
         }
         const bool list_it = many[q] && in > 0 && base + 16 * q + c < n;
         if (__ballot(list_it)) {
+          bool up[4];
           int add = 0;
 #pragma unroll
-          for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) add += __popcll(__ballot(list_it && a[rb][q][u] > fl[q]));
+          for (int rb = 0; rb < 4; ++rb) {
+            const f32x4 v = a[rb][q];
+            up[rb] = list_it && (v[0] > fl[q] || v[1] > fl[q] || v[2] > fl[q] || v[3] > fl[q]);
+            add += __popcll(__ballot(up[rb]));
+          }
           if (cnt + add > MM_LIST) {
             draw_list(cnt, fl, base);
             cnt = 0;
           }
 #pragma unroll
-          for (int rb = 0; rb < 4; ++rb)
-#pragma unroll
-            for (int u = 0; u < 4; ++u) {
-              const bool up = list_it && a[rb][q][u] > fl[q];
-              const unsigned long long m = __ballot(up);
-              if (up) {
-                const int o = cnt + __popcll(m & ((1ull << lane) - 1ull));
-                ll[o] = a[rb][q][u];
-                lk[o] = (unsigned short)((16 * q + c) << 10 | (k0 + 16 * rb + 4 * g + u));
-              }
-              cnt += __popcll(m);
+          for (int rb = 0; rb < 4; ++rb) {
+            const unsigned long long m = __ballot(up[rb]);
+            if (up[rb]) {
+              const int o = cnt + __popcll(m & ((1ull << lane) - 1ull));
+              ll[o] = a[rb][q];
+              lk[o] = (unsigned short)((16 * q + c) << 10 | (k0 + 16 * rb + 4 * g));
             }
+            cnt += __popcll(m);
+          }
         }
       }
     }
@@ -349,9 +364,9 @@ __global__ __launch_bounds__(MM_BLOCK, 2) void k_label_mult_mfma(const int* __re
   }
 }
 
-size_t label_mult_mfma_lds(int V, int K, bool sub) {
+size_t label_mult_mfma_lds(int V, int K, bool sub, int nt) {
   return ((size_t)(sub ? 3 : 1) * K * mm_ldv(V) + ((K + 63) & ~63) + 2 * (size_t)K) * sizeof(float) +
-         (size_t)MM_WAVES * (64 * sizeof(unsigned long long) + MM_LIST * (sizeof(float) + sizeof(unsigned short)));
+         (size_t)(nt / 64) * (64 * sizeof(unsigned long long) + MM_LIST * (4 * sizeof(float) + sizeof(unsigned short)));
 }
 
 // The matrix-core draw takes the calls whose log theta, in rows of 32, 64 or 128
@@ -395,8 +410,9 @@ hipError_t launch_label_mult(int V, const int* x, long long n, const float* pack
                              uint32_t t, uint64_t seed, int* z, unsigned char* zsub, hipStream_t s) {
   if (n == 0) return hipSuccess;
   if (mult_on_matrix_cores(V, K)) {
-    const bool sub = label_mult_mfma_lds(V, K, true) <= MM_LDS_MAX;
-    const size_t lds = label_mult_mfma_lds(V, K, sub);
+    const int nt = n <= MM_SMALL_N ? MM_BLOCK / 2 : MM_BLOCK;
+    const bool sub = label_mult_mfma_lds(V, K, true, nt) <= MM_LDS_MAX;
+    const size_t lds = label_mult_mfma_lds(V, K, sub, nt);
     static bool attr_set = false;
     if (!attr_set) {
       const void* fns[16] = {
@@ -414,16 +430,16 @@ hipError_t launch_label_mult(int V, const int* x, long long n, const float* pack
       }
       attr_set = true;
     }
-    // one workgroup of eight waves per CU, which stages the tables once
-    long long g = (n + MM_BLOCK - 1) / MM_BLOCK;
+    // one workgroup per CU, which stages the tables once
+    long long g = (n + nt - 1) / nt;
     if (g > 256) g = 256;
 #define DPMM_MM_CASE(RB)                                                                                              \
   case RB:                                                                                                            \
     if (sub)                                                                                                          \
-      hipLaunchKernelGGL((k_label_mult_mfma<RB, true>), dim3(g), dim3(MM_BLOCK), lds, s, x, n, V, packed, K, k_max, t, \
+      hipLaunchKernelGGL((k_label_mult_mfma<RB, true>), dim3(g), dim3(nt), lds, s, x, n, V, packed, K, k_max, t, \
                          seed, z, zsub);                                                                              \
     else                                                                                                              \
-      hipLaunchKernelGGL((k_label_mult_mfma<RB, false>), dim3(g), dim3(MM_BLOCK), lds, s, x, n, V, packed, K, k_max, t, \
+      hipLaunchKernelGGL((k_label_mult_mfma<RB, false>), dim3(g), dim3(nt), lds, s, x, n, V, packed, K, k_max, t, \
                          seed, z, zsub);                                                                              \
     break;
     switch (mx::row_blocks(V)) {

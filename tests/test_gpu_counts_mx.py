@@ -61,3 +61,32 @@ def test_large_counts_do_not_overflow_a_partial_sum():
     st = S.get_stats()
     assert np.array_equal(st[0, 0], np.concatenate([[n], np.full(V, n * 250_000)])) and not st[0, 1].any()
     S.close()
+
+
+# workgroups of 256 and of 512 threads (n up to 65 536 and beyond), most clusters of a point in range, one and two groups
+# of clusters: the candidates of a tile fill the list more than once
+@pytest.mark.parametrize("V,K,n", [(3, 64, 65_536), (3, 65, 65_537), (30, 200, 511), (30, 701, 70_001)])
+def test_draw_with_every_cluster_in_range(V, K, n):
+    import torch
+
+    from paper_2204_08988_amd.sampler import Sampler
+    seed = 3 * V + K
+    g = np.random.Generator(np.random.PCG64(seed))
+    th = 1.0 + 0.2 * g.random((K, 3, V))
+    th /= th.sum(2, keepdims=True)
+    params = sampler.Params(np.log(g.dirichlet(np.full(K, 20.0))), np.log(g.dirichlet(np.ones(2), size=K)),
+                            log_theta=np.log(th))
+    x = g.poisson(0.7, (n, V)).astype(np.int32)
+    S = Sampler("multinomial", V, K + 2, 2.0, seed, beta=np.ones(V))
+    S.set_params(params.log_pi, params.log_pisub, pu.comp_array(params))
+    z, zs = S.sample_labels(torch.from_numpy(x).cuda(), 3)
+    zn, zsn = z.cpu().numpy(), zs.cpu().numpy()
+    S.close()
+    rows = np.unique(np.concatenate([np.arange(0, n, 1 + n // 1500), np.arange(max(0, n - 130), n)]))
+    model = sampler.Model("multinomial", 2.0, dirmult.DirPrior(np.ones(V)), seed=seed)
+    lc, ls = sampler.loglik(model, x[rows], params)
+    Mc, Ms = pu.mult_scale(x[rows], params)
+    bad_c, bad_s, tie_c, tie_s = pu.label_mismatches(seed, 3, zn[rows], zsn[rows], lc, ls, Mc, Ms, points=rows)
+    assert bad_c.size == 0 and bad_s.size == 0, (bad_c[:10], bad_s[:10])
+    assert tie_c <= 4 and tie_s <= 4
+    assert np.unique(zn).size > K // 2
