@@ -586,9 +586,10 @@ __global__ __launch_bounds__(128) void k_niw_draw_wave(int K, int d, int k_max, 
     __syncthreads();
     // the log weight, while wave 0 works: from k_weights, or (own_weights, K <= 63)
     // drawn here with its draws, sums and order, one log-gamma draw per lane
-    double lw;
+    double lw = 0.0;
     if (!own_weights) {
-      lw = c == 0 ? log_pi[k] : log_pisub[2 * k + (c - 1)];
+      // (read below.  This wave is done and makes room for the next workgroup's: waiting
+      // for wave 0 it cost 10 to 20% at K = 500)
     } else if (c == 0) {
       double lg = -INFINITY;
       if (lane <= K)
@@ -611,10 +612,10 @@ __global__ __launch_bounds__(128) void k_niw_draw_wave(int K, int d, int k_max, 
     }
     if (lane == 0) s_lw = lw;
   }
-  __syncthreads();
+  if (own_weights) __syncthreads();
   if (wave != 0) return;
   const double ld = 2.0 * wave_sum(live ? log(diag) : 0.0);
-  const double lw = s_lw;
+  const double lw = own_weights ? s_lw : (c == 0 ? log_pi[k] : log_pisub[2 * k + (c - 1)]);
   const int stride = gauss_rec_stride(d);
   float* rec = packed + (size_t)record_slot(k, c, k_max) * stride;
   if (lane == 0) {
