@@ -22,9 +22,9 @@
 // max_k l_k + g_k, smaller k on ties) and the sub-label draw follow as in the
 // dense kernels.  Every index read from the rows is checked: an entry out of
 // range sets bit ERR_SPARSE_INPUT of the error flag and the row is skipped.
-// Table reads are issued eight (four in the sub-label pass) per lane at a time, the
-// next nonzeros loaded meanwhile: 97 -> 90 us at N = 11 314, V = 20 000, K = 20, where
-// the lines of the tables from L2 (0.6 GB) are most of the time.
+// Long rows issue their table reads eight (four in the sub-label pass) per lane at a
+// time, the next nonzeros loaded meanwhile: 97 -> 90 us at N = 11 314, V = 20 000,
+// K = 20, where the lines of the tables from L2 (0.6 GB) are most of the time.
 #include "kernels.hpp"
 
 namespace dpmm {
@@ -33,7 +33,6 @@ namespace {
 
 constexpr int BLOCK = 256;
 constexpr int WAVES = BLOCK / 64;
-constexpr int UN = 8, US = 4;  // table reads of a lane in flight: scores, sub-scores
 constexpr float RGAP = GUMBEL_MAX_F - GUMBEL_MIN_F;
 
 __device__ __forceinline__ void wave_lds_sync() {
@@ -76,12 +75,15 @@ __device__ __forceinline__ void load_batch(const int* __restrict__ col, const in
   }
 }
 
+// LONG: several table reads of a lane in flight, also past a row's end
+template <bool LONG>
 __global__ __launch_bounds__(BLOCK) void k_label_csr(const long long* __restrict__ rp, const int* __restrict__ col,
                                                      const int* __restrict__ val, long long nnz, long long n, int V,
                                                      const float* __restrict__ tcl, const float* __restrict__ tsub,
                                                      const float* __restrict__ cw, int K, int lg_qp, uint32_t t,
                                                      uint64_t seed, int* __restrict__ z,
                                                      unsigned char* __restrict__ zsub, int* __restrict__ err) {
+  constexpr int UN = LONG ? 8 : 1, US = LONG ? 4 : 1;  // table reads of a lane in flight: scores, sub-scores
   extern __shared__ float sc_all[];
   const int lane = threadIdx.x & 63, w = threadIdx.x >> 6;
   float* sc = sc_all + (size_t)w * K;
@@ -97,15 +99,16 @@ __global__ __launch_bounds__(BLOCK) void k_label_csr(const long long* __restrict
     for (int c = 0; c < NC; ++c) {
       const int q = 64 * c + ql;
       float4 acc = make_float4(0.0f, 0.0f, 0.0f, 0.0f);
-      int cn;
-      float vn;
-      load_batch(col, val, e0, (int)min(64LL, e1 - e0), V, lane, cn, vn, err);
+      int cn = 0;
+      float vn = 0.0f;
+      if (LONG) load_batch(col, val, e0, (int)min(64LL, e1 - e0), V, lane, cn, vn, err);
       for (long long b = e0; b < e1; b += 64) {
         const int m = (int)min(64LL, e1 - b);
+        if (!LONG) load_batch(col, val, b, m, V, lane, cn, vn, err);
         const int cl = cn;
         const float vl = vn;
         // the next batch's entries and UN table reads per lane in flight
-        load_batch(col, val, b + 64, (int)max(0LL, min(64LL, e1 - b - 64)), V, lane, cn, vn, err);
+        if (LONG) load_batch(col, val, b + 64, (int)max(0LL, min(64LL, e1 - b - 64)), V, lane, cn, vn, err);
         const int qc = q < Q ? q : Q - 1;
         // uniform trip count: every lane takes part in each broadcast
         for (int u0 = 0; u0 < m; u0 += G * UN) {
@@ -345,8 +348,13 @@ hipError_t launch_label_csr(const SparseRows& x, long long n, int V, const float
   int lg = 0;
   while ((1 << lg) < Q && lg < 6) ++lg;
   const size_t lds = (size_t)WAVES * K * sizeof(float);
-  hipLaunchKernelGGL(k_label_csr, dim3(waves_grid(n)), dim3(BLOCK), lds, s, x.row_ptr, x.col, x.val, x.nnz, n, V, tcl,
-                     tsub, cw, K, lg, t, seed, z, zsub, err);
+  // one read takes 64 >> lg nonzeros of a row; long rows are those where eight reads in
+  // flight come twice on average.  Us one read at a time and so: K = 20, 160 nonzeros per
+  // row 39.1 and 37.6, 60 20.9 and 21.3, 5 53 and 63; K = 4, 160 24.2 and 25.9; K = 30, 33
+  // 25.8 and 28.5; K = 100, 60 78.8 and 74.6; K = 200, 400 160 and 144
+  auto kernel = x.nnz / n >= (16 << 6 >> lg) ? k_label_csr<true> : k_label_csr<false>;
+  hipLaunchKernelGGL(kernel, dim3(waves_grid(n)), dim3(BLOCK), lds, s, x.row_ptr, x.col, x.val, x.nnz, n, V, tcl, tsub, cw,
+                     K, lg, t, seed, z, zsub, err);
   return hipGetLastError();
 }
 

@@ -293,3 +293,31 @@ def test_sparse_bad_rows_raise():
             S.split_merge(xs, 1, z, zs)
         assert e.value.status == -1, e.value
         S.close()
+
+
+@pytest.mark.parametrize("K", [1, 4, 20, 65, 130])
+def test_short_and_long_rows_draw_alike(K):
+    """The draw's two forms (by the mean row length): the same rows by themselves and beside one row
+    long enough for the other form, whose entries end at no multiple of 64."""
+    torch = _torch()
+    from paper_2204_08988_amd.sampler import Sampler, SparseCounts
+    V, n, seed = 300, 600, 70 + K
+    g = np.random.Generator(np.random.PCG64(seed))
+    params = _mult_params(K, V, seed, True)
+    lens = g.integers(0, 40, n)
+    lens[[3, 5, 7, 9, 11]] = 63, 64, 65, 513, 200
+    lens = np.concatenate([lens, [1025 * n + 7]])
+    ptr = np.concatenate([[0], np.cumsum(lens)])
+    col = g.integers(0, V, ptr[-1]).astype(np.int32)
+    val = g.integers(1, 4, ptr[-1]).astype(np.int32)
+    out = []
+    for rows in (n, n + 1):
+        e = ptr[rows]
+        x = SparseCounts.from_numpy(ptr[:rows + 1], col[:e], val[:e], V)
+        S = Sampler("multinomial", V, K + 2, 2.0, seed, beta=np.ones(V), sparse=True)
+        S.set_params(params.log_pi, params.log_pisub, pu.comp_array(params))
+        z, zs = S.sample_labels(x, 3)
+        out.append((z.cpu().numpy()[:n], zs.cpu().numpy()[:n]))
+        S.close()
+    assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
+    assert K == 1 or np.unique(out[0][0]).size > 1
