@@ -170,7 +170,7 @@ __global__ __launch_bounds__(BLOCK) void k_label_csr(const long long* __restrict
       }
       m2 = s2;
     }
-    int zi = arg;
+    int zi = arg < K ? arg : 0;  // a row that no cluster scores (all -inf) takes 0, as the dense draws
     if (m2 > m1 - RGAP) {
       // exact draw over the clusters within the Gumbel range of the leader
       const float th = m1 - RGAP;

@@ -321,3 +321,28 @@ def test_short_and_long_rows_draw_alike(K):
         S.close()
     assert np.array_equal(out[0][0], out[1][0]) and np.array_equal(out[0][1], out[1][1])
     assert K == 1 or np.unique(out[0][0]).size > 1
+
+
+def test_rows_that_no_cluster_scores():
+    """A word whose probability is 0 in float32 under every component: its rows take cluster 0,
+    as the dense draw's do, and the others are drawn as they are without them."""
+    torch = _torch()
+    from paper_2204_08988_amd.sampler import Sampler, SparseCounts
+    K, V, n, seed = 9, 40, 300, 3
+    g = np.random.Generator(np.random.PCG64(seed))
+    params = _mult_params(K, V, seed, True)
+    params.log_theta[:, :, 17] = -1e300
+    x = g.poisson(0.3, (n, V)).astype(np.int32)
+    x[:, 17] = 0
+    x[::7, 17] = 2
+    ptr = np.concatenate([[0], np.cumsum((x > 0).sum(1))])
+    r, c = np.nonzero(x)
+    got = {}
+    for sparse in (True, False):
+        S = Sampler("multinomial", V, K, 2.0, seed, beta=np.ones(V), sparse=sparse)
+        S.set_params(params.log_pi, params.log_pisub, pu.comp_array(params))
+        xt = SparseCounts.from_numpy(ptr, c.astype(np.int32), x[r, c], V) if sparse else torch.from_numpy(x).cuda()
+        got[sparse] = S.sample_labels(xt, 2)[0].cpu().numpy()
+        S.close()
+    assert np.all(got[True][::7] == 0) and np.all(got[False][::7] == 0)
+    assert got[True].min() >= 0 and got[True].max() < K and np.unique(got[True]).size > 1
