@@ -421,7 +421,7 @@ dpmm_status dpmm_create(const dpmm_config* cfg, void* hip_stream, dpmm_ctx** out
     return bad(DPMM_E_ARG, cfg->sparse ? "vocabulary size must lie in [1, 2^20]" : "vocabulary size must lie in [1, 128]");
   if (cfg->family == DPMM_POISSON && (cfg->d < 1 || cfg->d > max_v))
     return bad(DPMM_E_ARG, cfg->sparse ? "Poisson dimension must lie in [1, 2^20]" : "Poisson dimension must lie in [1, 128]");
-  if (cfg->k_max < 1 || cfg->k_max > 4096) return bad(DPMM_E_ARG, "k_max must lie in [1, 4096]");
+  if (cfg->k_max < 1 || cfg->k_max > K_MAX) return bad(DPMM_E_ARG, "k_max must lie in [1, 4096]");
   if (cfg->burn_out < 0) return bad(DPMM_E_ARG, "burn_out must be >= 0");
   if (!(cfg->alpha > 0.0) || !std::isfinite(cfg->alpha)) return bad(DPMM_E_ARG, "alpha must be > 0");
   if (cfg->precision != DPMM_FP32 && cfg->precision != DPMM_BF16 && cfg->precision != DPMM_BF16X3)
@@ -840,8 +840,7 @@ dpmm_status label_phase(dpmm_ctx* ctx, const void* x, int64_t n, uint32_t t, int
   if (ctx->sorted_path()) {
     const bool mfma = ctx->d_whi != nullptr;
     DPMM_TRY(ensure_perm(ctx, n));
-    const bool by_guess = ctx->d_gtab && label_prune_pays(ctx->d, ctx->K, n, mfma) &&
-                          (!mfma || uc_list_fits(ctx->d, ctx->K)) && guess_buffers(ctx, n);
+    const bool by_guess = ctx->d_gtab && label_prune_pays(ctx->d, ctx->K, n, mfma) && guess_buffers(ctx, n);
     // the FP32 kernels take 256 rows per workgroup step, the BF16 ones and the guess 512: blocks of as many
     sorted_plan(n, ctx->K, ctx->hist_cap, G, per, mfma || by_guess ? 512 : 256);
     ctx->z_hist = !by_guess;  // drawn in sorted order, z is counted afterwards

@@ -4,6 +4,8 @@
 
 namespace dpmm {
 
+constexpr int K_MAX = 4096;  // clusters of a context at most
+
 #define NIW_SCRATCH(d) ((size_t)3 * (d) * (d) + (d))
 // float64 workspaces of the per-component kernels live in LDS up to this d
 // candidate clusters kept per point by the matrix-core label kernels
@@ -210,12 +212,11 @@ hipError_t launch_sub_labels_x3(int d, const float* x, long long n, const int* p
 // flagged: int[n] (the points whose draw is deferred to FP32); cand:
 // int[n][RESCORE_CAND], each deferred point's candidate clusters (-1: empty
 // slot, -2 in slot 0: all clusters); n_flagged: one device int
-// by_guess (d = 64, 128 in BF16 where uc_list_fits): the main pass takes the listed
+// by_guess (d = 64, 128 in BF16): the main pass takes the listed
 // points that launch_settle left open, or where *mode is 0 all as without it
 struct OpenList {
   const int *mode, *open, *n_open;
 };
-bool uc_list_fits(int d, int K);
 hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, int G, long long per_block,
                                    const float* packed, const void* whi, const void* wlo, const float* wbias, int K,
                                    int k_max, uint32_t t, uint64_t seed, int* z, int* hist, int* flagged,

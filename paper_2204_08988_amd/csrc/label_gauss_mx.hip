@@ -215,23 +215,23 @@ hipError_t launch_label_gauss_mx(int d, const float* x, long long n, int G, long
   const size_t lds = rec * cg * bufs + mx::REC_PAD * sizeof(float) + (size_t)K * sizeof(int);
   static bool attr_set = false;
   if (!attr_set) {
-    const void* fns[8] = {(const void*)k_label_gauss_mx<1>, (const void*)k_label_gauss_mx<2>,
-                          (const void*)k_label_gauss_mx<3>, (const void*)k_label_gauss_mx<4>,
-                          (const void*)k_label_gauss_mx<5>, (const void*)k_label_gauss_mx<6>,
-                          (const void*)k_label_gauss_mx<7>, (const void*)k_label_gauss_mx<8>};
+    const void* fns[7] = {(const void*)k_label_gauss_mx<2>, (const void*)k_label_gauss_mx<3>,
+                          (const void*)k_label_gauss_mx<4>, (const void*)k_label_gauss_mx<5>,
+                          (const void*)k_label_gauss_mx<6>, (const void*)k_label_gauss_mx<7>,
+                          (const void*)k_label_gauss_mx<8>};
     for (const void* f : fns) {
       const hipError_t e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, MX_LDS_MAX);
       if (e != hipSuccess) return e;
     }
     attr_set = true;
   }
+  static_assert(mx::row_blocks(MX_MIN_D) == 2, "the smallest form");
 #define DPMM_MX_CASE(RB)                                                                                          \
   case RB:                                                                                                        \
     hipLaunchKernelGGL(k_label_gauss_mx<RB>, dim3(G), dim3(MX_BLOCK), lds, s, x, n, d, per_block, packed, K, cg, t, \
                        seed, z, hist);                                                                       \
     break;
   switch (mx::row_blocks(d)) {
-    DPMM_MX_CASE(1)
     DPMM_MX_CASE(2)
     DPMM_MX_CASE(3)
     DPMM_MX_CASE(4)

@@ -26,6 +26,7 @@
 // can win and the leader is the label.
 #include <hip/hip_ext.h>
 
+#include <algorithm>
 #include <climits>
 
 #include "interval.hpp"
@@ -406,13 +407,10 @@ constexpr int BLOCK_W32 = 512;  // threads of k_label_gauss_mfma_w32: 8 waves of
 
 // d = 64, 128 in bf16x3, and the candidate pass of either form (the BF16
 // main pass is k_label_gauss_mfma_uc below): a cluster's non-zero whitener
-// tiles (only those on or below
-// the diagonal), its mean and its constant are copied from global memory
-// straight into LDS (global_load_lds, no registers) into one of two
-// statically allocated buffers, while the workgroup scores its points against
-// the previous clusters from the other (in BF16 four clusters per buffer and
-// barrier at d = 64, two at d = 128; one in bf16x3, whose tables are twice as
-// large); the matrix cores
+// tiles (only those on or below the diagonal), its mean and its constant are
+// copied from global memory straight into LDS (global_load_lds, no registers)
+// into one of two statically allocated buffers, while the workgroup scores its
+// points against the previous cluster from the other; the matrix cores
 // execute 1.25 d^2 instead of 2 d^2 flops per point-cluster at d = 128.  A
 // wave scores a single 32-point tile: lanes l and l + 32 hold the two halves
 // of the K slice of point l % 32, so a lane keeps d / 2 FP32 coordinates and
@@ -441,10 +439,9 @@ __global__ __launch_bounds__(BLOCK_W32) void k_label_gauss_mfma_w32(const float*
   constexpr int NB = 2;           // fragment tables per cluster (hi, lo)
   constexpr int MUS = D + 4;      // mu[D], c
   constexpr int CHUNK = BLOCK_W32 / 2;
-  constexpr int CPB = 1;           // clusters per staging buffer (per barrier)
   static_assert(D < BLOCK_W32 && CHUNK == BLOCK && NFZ % 64 == 0, "staging layout, histogram blocks");
-  __shared__ __align__(16) bf16x8 s_w0[CPB * NB * NFZ], s_w1[CPB * NB * NFZ];
-  __shared__ __align__(16) float s_mu0[CPB * MUS], s_mu1[CPB * MUS];
+  __shared__ __align__(16) bf16x8 s_w0[NB * NFZ], s_w1[NB * NFZ];
+  __shared__ __align__(16) float s_mu0[MUS], s_mu1[MUS];
   extern __shared__ int h[];  // K counters
   for (int k = threadIdx.x; k < K; k += BLOCK_W32) h[k] = 0;
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -463,43 +460,34 @@ __global__ __launch_bounds__(BLOCK_W32) void k_label_gauss_mfma_w32(const float*
   const long long begin = CANDS ? (long long)blockIdx.x * CHUNK : (long long)blockIdx.x * per_block;
   const long long end = CANDS ? nf : (begin + per_block < n ? begin + per_block : n);
   const long long step = CANDS ? (long long)gridDim.x * CHUNK : CHUNK;
-  // copies of clusters k0 ... k0 + nk - 1 into slots 0 ... nk - 1 of (dw, dmu): fragment
-  // f of a slot's table is tile f / 64 in (row block, ks) order, lane f % 64; each wave
-  // fills 64 consecutive entries
-  auto stage = [&](bf16x8* dws, float* dmus, int k0, int nk) {
+  // copy of cluster k into (dw, dmu): fragment f of a table is tile f / 64 in (row block,
+  // ks) order, lane f % 64; each wave fills 64 consecutive entries
+  auto stage = [&](bf16x8* dw, float* dmu, int k) {
 #pragma unroll
-    for (int c = 0; c < CPB; ++c) {
-      if (c >= nk) break;
-      const int k = k0 + c;
-      bf16x8* dw = dws + c * NB * NFZ;
-      float* dmu = dmus + c * MUS;
+    for (int j = 0; j < NJ; ++j) {
+      const int f = j * BLOCK_W32 + threadIdx.x;
+      if (f < NFZ) {
+        const int tt = f >> 6;
+        int mt = 0, o = 0;
 #pragma unroll
-      for (int j = 0; j < NJ; ++j) {
-        const int f = j * BLOCK_W32 + threadIdx.x;
-        if (f < NFZ) {
-          const int tt = f >> 6;
-          int mt = 0, o = 0;
-#pragma unroll
-          for (int m = 1; m < MT; ++m)
-            if (tt >= TT::off(m)) mt = m, o = TT::off(m);
-          const size_t g = (size_t)k * NF + (size_t)(mt * KS + tt - o) * 64 + (f & 63);
-          __builtin_amdgcn_global_load_lds((const void*)(whi + g), (lds_void*)(dw + j * BLOCK_W32 + wbase), 16, 0, 0);
-          __builtin_amdgcn_global_load_lds((const void*)(wlo + g), (lds_void*)(dw + NFZ + j * BLOCK_W32 + wbase), 16,
-                                             0, 0);
-        }
-      }
-      if (threadIdx.x <= D) {
-        const float* rec = packed + (size_t)k * S;
-        __builtin_amdgcn_global_load_lds((const void*)(threadIdx.x < D ? rec + 4 + threadIdx.x : rec),
-                                         (lds_void*)(dmu + wbase), 4, 0, 0);
+        for (int m = 1; m < MT; ++m)
+          if (tt >= TT::off(m)) mt = m, o = TT::off(m);
+        const size_t g = (size_t)k * NF + (size_t)(mt * KS + tt - o) * 64 + (f & 63);
+        __builtin_amdgcn_global_load_lds((const void*)(whi + g), (lds_void*)(dw + j * BLOCK_W32 + wbase), 16, 0, 0);
+        __builtin_amdgcn_global_load_lds((const void*)(wlo + g), (lds_void*)(dw + NFZ + j * BLOCK_W32 + wbase), 16, 0, 0);
       }
     }
+    if (threadIdx.x <= D) {
+      const float* rec = packed + (size_t)k * S;
+      __builtin_amdgcn_global_load_lds((const void*)(threadIdx.x < D ? rec + 4 + threadIdx.x : rec),
+                                       (lds_void*)(dmu + wbase), 4, 0, 0);
+    }
   };
-  if (begin < end && kb0 < kb1) stage(s_w0, s_mu0, kb0, kb1 - kb0 < CPB ? kb1 - kb0 : CPB);
+  if (begin < end && kb0 < kb1) stage(s_w0, s_mu0, kb0);
   __builtin_amdgcn_s_waitcnt(0);
   __syncthreads();
   int buf = 0;
-  // every wave runs the same number of chunks and clusters: one barrier per CPB clusters
+  // every wave runs the same number of chunks and clusters: one barrier per cluster
   for (long long chunk = begin; chunk < end; chunk += step) {
     const long long r = chunk + wave * 32 + col;
     const bool ok = r < end;
@@ -567,28 +555,20 @@ __global__ __launch_bounds__(BLOCK_W32) void k_label_gauss_mfma_w32(const float*
       else
         t2.push(l, qm, REL, k);
     };
-    // score clusters k0 ... k0 + nk - 1 from (cw, cmu) while the next group (kn, nkn)
-    // is copied into (nw, nmu)
-    auto group = [&](const bf16x8* cw, const float* cmu, bf16x8* nw, float* nmu, int k0, int nk, bool next, int kn,
-                     int nkn) {
-      if (next) stage(nw, nmu, kn, nkn);
-#pragma unroll
-      for (int c = 0; c < CPB; ++c)
-        if (c < nk) score(cw + c * NB * NFZ, cmu + c * MUS, k0 + c);
+    // score cluster k from (cw, cmu) while the next one is copied into (nw, nmu)
+    auto group = [&](const bf16x8* cw, const float* cmu, bf16x8* nw, float* nmu, int k) {
+      const bool last = k + 1 == kb1;
+      if (!last || more) stage(nw, nmu, last ? kb0 : k + 1);
+      score(cw, cmu, k);
       // this wave's copies into the other buffer have landed; after the barrier all have
       __builtin_amdgcn_s_waitcnt(0);
       __syncthreads();
     };
-    for (int k = kb0; k < kb1; k += CPB) {
-      const int nk = kb1 - k < CPB ? kb1 - k : CPB;
-      const bool last = k + CPB >= kb1;
-      const bool next = !last || more;
-      const int kn = last ? kb0 : k + CPB;
-      const int nkn = last ? (kb1 - kb0 < CPB ? kb1 - kb0 : CPB) : (kb1 - kn < CPB ? kb1 - kn : CPB);
+    for (int k = kb0; k < kb1; ++k) {
       if (buf == 0)
-        group(s_w0, s_mu0, s_w1, s_mu1, k, nk, next, kn, nkn);
+        group(s_w0, s_mu0, s_w1, s_mu1, k);
       else
-        group(s_w1, s_mu1, s_w0, s_mu0, k, nk, next, kn, nkn);
+        group(s_w1, s_mu1, s_w0, s_mu0, k);
       buf ^= 1;
     }
     // lanes 0-31 own the points (lanes 32-63 hold the same state)
@@ -1108,9 +1088,14 @@ __global__ __launch_bounds__(64 * NWAVE, 8 / NWAVE) void k_label_gauss_mfma_uc(c
   }
 }
 
-size_t label_uc_lds(int d, int K, int pts) {
-  return (size_t)pts * (d / 8 + 1) * 16 + (size_t)pts * sizeof(float) + (size_t)K * sizeof(int);
+// rows per workgroup step and waves of a workgroup: at d = 64 two workgroups of four
+// waves per CU, so that one copies its rows while the other runs its matrix-core work;
+// at d = 128 one of eight.  Both fit for every K
+constexpr int uc_rows(int d) { return d == 128 ? 512 : 256; }
+constexpr size_t label_uc_lds(int d, int K) {
+  return (size_t)uc_rows(d) * ((d / 8 + 1) * 16 + sizeof(float)) + (size_t)K * sizeof(int);
 }
+static_assert(label_uc_lds(128, K_MAX) <= 160 * 1024 && 2 * label_uc_lds(64, K_MAX) <= 160 * 1024, "LDS of a CU");
 
 constexpr int RS_BLOCK = 256;
 
@@ -1781,13 +1766,6 @@ hipError_t launch_settle(int d, const float* x, long long n, const int* perm, co
   return hipGetLastError();
 }
 
-// rows per workgroup step of the listed points' main pass, and whether they fit in LDS
-static int luc_rows(int d) { return d == 128 ? 512 : 256; }
-
-bool uc_list_fits(int d, int K) {
-  return (d == 64 || d == 128) && label_uc_lds(d, K, luc_rows(d)) <= (size_t)(d == 128 ? 160 : 80) * 1024;
-}
-
 bool mfma_supported(int d) { return d == 32 || d == 64 || d == 128; }
 
 hipError_t launch_pack_wfrag(int K, int d, int k_max, const float* packed, void* whi, void* wlo, float* wbias,
@@ -1821,12 +1799,10 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
   if (e != hipSuccess) return e;
   static bool attr_set = false;
   if (!attr_set) {  // d = 32 and the uncentred kernels: more than 64 KB of dynamic LDS (160 KB per CU)
-    const void* fns[9] = {(const void*)k_label_gauss_mfma_uc<128, 512, 8, true>,
-                          (const void*)k_label_gauss_mfma_uc<64, 256, 4, true>,
-                          (const void*)k_label_gauss_mfma32<false>, (const void*)k_label_gauss_mfma32<true>,
-                          (const void*)k_label_gauss_mfma_uc<64, 256, 4>, (const void*)k_label_gauss_mfma_uc<128, 512, 8>,
-                          (const void*)k_label_gauss_mfma_uc<64, 512, 8>, (const void*)k_label_gauss_mfma_uc<128, 256, 8>,
-                          (const void*)k_label_gauss_mfma_uc<64, 256, 8>};
+    const void* fns[6] = {
+        (const void*)k_label_gauss_mfma_uc<128, 512, 8, true>, (const void*)k_label_gauss_mfma_uc<64, 256, 4, true>,
+        (const void*)k_label_gauss_mfma_uc<128, 512, 8>,       (const void*)k_label_gauss_mfma_uc<64, 256, 4>,
+        (const void*)k_label_gauss_mfma32<false>,              (const void*)k_label_gauss_mfma32<true>};
     for (const void* f : fns) {
       e = hipFuncSetAttribute(f, hipFuncAttributeMaxDynamicSharedMemorySize, 160 * 1024);
       if (e != hipSuccess) return e;
@@ -1842,45 +1818,25 @@ hipError_t launch_label_gauss_mfma(int d, bool x3, const float* x, long long n, 
     // time stamps, for timing it alone without extra queue packets)
     hipEvent_t e0 = cands ? nullptr : ev_main0, e1 = cands ? nullptr : ev_main1;
     if ((d == 64 || d == 128) && !cands && !x3 && wbias) {
-      // BF16 main pass, uncentred: the rows centred once on the common centre.  At
-      // d = 64, two workgroups of four waves per CU (256 rows per step each) while
-      // both fit in LDS, so that one copies its rows while the other runs its
-      // matrix-core work; at d = 128 (and for larger K at d = 64) one workgroup of
-      // eight waves, 512 rows per step while they and the counters fit in LDS
-      // (fewer fragment fetches and merges per point), else 256
-      const size_t l256 = label_uc_lds(d, K, 256), l512 = label_uc_lds(d, K, 512);
-      const bool two = d == 64 && 2 * l256 <= (size_t)160 * 1024;
-      const bool big = !two && l512 <= (size_t)160 * 1024;
-      const size_t luc = big ? l512 : l256;
-#define DPMM_UC(DD, PP, NWV)                                                                                     \
-  hipExtLaunchKernelGGL((k_label_gauss_mfma_uc<DD, PP, NWV>), dim3(Gp), dim3(64 * NWV), luc, s, e0, e1, 0, x, n, \
-                        per_block, hi, wbias, K, k_max, z, hist, flagged, n_flagged, by_guess ? by_guess->mode : nullptr,      \
-                        nullptr, nullptr)
-      if (by_guess) {  // the points left by launch_settle
-        const unsigned gl = (unsigned)((n + luc_rows(d) - 1) / luc_rows(d) < 512 ? (n + luc_rows(d) - 1) / luc_rows(d) : 512);
-        if (d == 128)
-          hipLaunchKernelGGL((k_label_gauss_mfma_uc<128, 512, 8, true>), dim3(gl), dim3(512), l512, s, x, n, per_block, hi,
-                             wbias, K, k_max, z, hist, flagged, n_flagged, by_guess->mode, by_guess->open,
-                             by_guess->n_open);
-        else
-          hipLaunchKernelGGL((k_label_gauss_mfma_uc<64, 256, 4, true>), dim3(gl), dim3(256), l256, s, x, n, per_block, hi,
-                             wbias, K, k_max, z, hist, flagged, n_flagged, by_guess->mode, by_guess->open,
-                             by_guess->n_open);
-        if ((e = hipGetLastError()) != hipSuccess) return e;
-      }
-      if (d == 128) {
-        if (big)
-          DPMM_UC(128, 512, 8);
-        else
-          DPMM_UC(128, 256, 8);
-      } else {
-        if (two)
-          DPMM_UC(64, 256, 4);
-        else if (big)
-          DPMM_UC(64, 512, 8);
-        else
-          DPMM_UC(64, 256, 8);
-      }
+      // BF16 main pass, uncentred: the rows centred once on the common centre; where the
+      // points were guessed first, the ones that launch_settle left
+      const size_t luc = label_uc_lds(d, K);
+      const unsigned gl = (unsigned)std::min<long long>((n + uc_rows(d) - 1) / uc_rows(d), 512);
+#define DPMM_UC(DD, PP, NWV)                                                                                         \
+  do {                                                                                                               \
+    if (by_guess)                                                                                                    \
+      hipLaunchKernelGGL((k_label_gauss_mfma_uc<DD, PP, NWV, true>), dim3(gl), dim3(64 * NWV), luc, s, x, n, per_block, \
+                         hi, wbias, K, k_max, z, hist, flagged, n_flagged, by_guess->mode, by_guess->open,           \
+                         by_guess->n_open);                                                                          \
+    if ((e = hipGetLastError()) != hipSuccess) return e;                                                             \
+    hipExtLaunchKernelGGL((k_label_gauss_mfma_uc<DD, PP, NWV>), dim3(Gp), dim3(64 * NWV), luc, s, e0, e1, 0, x, n,   \
+                          per_block, hi, wbias, K, k_max, z, hist, flagged, n_flagged,                               \
+                          by_guess ? by_guess->mode : nullptr, nullptr, nullptr);                                    \
+  } while (0)
+      if (d == 128)
+        DPMM_UC(128, uc_rows(128), 8);
+      else
+        DPMM_UC(64, uc_rows(64), 4);
 #undef DPMM_UC
     } else if (d == 64 || d == 128) {
       // static staging buffers; only the histogram is dynamic
