@@ -201,3 +201,34 @@ def test_scratch_of_a_label_step_with_few_clusters(d, prec, per_point):
         del x, z, zs
     # (allocations are rounded up to 2 MB)
     assert taken[1] - taken[0] <= per_point * (sizes[1] - sizes[0]) + (8 << 20), taken
+
+
+# the draw by a guess against the draw that forms every score: as many of the first rows as stay below the guess's
+# range (n K < 250 000, BF16 n < 1e6) have the labels that they have among all; covariances of condition 10 and 1e6,
+# data about one centre, far from it, and in two groups
+@pytest.mark.parametrize("d,K,prec", [(48, 12, "fp32"), (64, 40, "fp32"), (100, 130, "fp32"), (128, 9, "fp32"),
+                                      (64, 70, "bf16"), (128, 34, "bf16")])
+@pytest.mark.parametrize("cond,shift", [(10.0, 0.0), (1e6, 0.0), (1e6, 500.0), (10.0, 40.0)])
+def test_draw_by_guess_equals_the_full_draw(d, K, prec, cond, shift):
+    import torch
+
+    from paper_2204_08988_amd.sampler import Sampler
+    n = 1_000_100 if prec == "bf16" else 20_000 + 400_000 // K
+    few = 249_999 // K if prec == "fp32" else 60_000
+    params = pu.random_gauss_params(K, d, 21 + d + K, spread=1.5, cond=cond)
+    params.mu[: K // 2] += shift
+    params.mu[K // 2:] += -shift if shift == 40.0 else shift
+    g = torch.Generator(device="cuda").manual_seed(d + K)
+    x = torch.randn((n, d), device="cuda", generator=g)
+    lab = torch.randint(0, K, (n,), device="cuda", generator=g)
+    L = torch.from_numpy(np.linalg.cholesky(params.sigma[:, 0])).float().cuda()
+    for k in range(K):
+        x[lab == k] = x[lab == k] @ L[k].T.contiguous()
+    x += torch.from_numpy(params.mu[:, 0]).float().cuda()[lab]
+    S = Sampler("gaussian", d, K + 2, 2.0, 11, kappa=1.0, nu=d + 3.0, m=np.zeros(d), psi=np.eye(d), precision=prec)
+    S.set_params(params.log_pi, params.log_pisub, pu.comp_array(params))
+    z, zs = S.sample_labels(x, 3)
+    zf, zsf = S.sample_labels(x[:few].contiguous(), 3)
+    S.close()
+    assert torch.equal(z[:few], zf) and torch.equal(zs[:few], zsf)
+    assert torch.unique(zf).numel() > K // 2

@@ -1,9 +1,10 @@
-"""The lower bound of a bf16x3 score against the FP32 score it stands for, on the
+"""The bounds of BF16 and bf16x3 scores against the FP32 scores they stand for, on the
 CPU: both forms rounded as the kernels round them (BF16 parts to nearest even, FP32
 sums one after the other, in both directions of the sum for the matrix form), the
 bound from the library's own header.  (A fixed share of the squared norm, q / 4096 +
 0.05, misses by 0.2 and 0.6 at condition 1e10.)"""
 import os
+import re
 import shutil
 import subprocess
 
@@ -80,3 +81,58 @@ def test_x3_lower_bound(driver, d, cond):
             low = np.array(out, dtype=np.float64)
             assert low.shape == (n,)
             assert np.all(low <= l32), (kind, rev, np.max(low - l32))
+
+
+def _constants():
+    text = open(os.path.join(HERE, "..", "paper_2204_08988_amd", "csrc", "interval.hpp")).read()
+    return {k: eval(v.replace("f", "")) for k, v in re.findall(r"constexpr float (UC_\w+) = ([^;]+);", text)}
+
+
+@pytest.mark.parametrize("r,d", [(32, 64), (32, 128), (32, 32), (64, 64), (128, 128)])
+@pytest.mark.parametrize("cond,offset", [(10.0, 0.0), (1e6, 0.0), (1e6, 300.0), (1e8, 30.0)])
+def test_bf16_interval(r, d, cond, offset):
+    """The first r rows of W, the rows centred on a common centre: the upper end bounds the FP32 score of all d
+    rows (the guess's bound of the clusters that it leaves out), with r = d the lower end bounds it from below;
+    rows near the cluster, near another one and anywhere."""
+    c = _constants()
+    g0, g2, eps = c["UC_GAMMA"], c["UC_GAMMA2"], c["UC_EPSS"]
+    g = np.random.Generator(np.random.PCG64(int(np.log10(cond)) + d + r))
+    n = 120
+    for _ in range(2):
+        q, _r = np.linalg.qr(g.standard_normal((d, d)))
+        lam = np.exp(g.uniform(-0.5, 0.5, d) * np.log(cond))
+        lam[0], lam[1] = cond ** 0.5, cond ** -0.5
+        L = np.linalg.cholesky((q * lam) @ q.T + 1e-16 * np.eye(d))
+        W = np.linalg.inv(L).astype(F)
+        mu = (offset + 3.0 * g.standard_normal(d)).astype(F)
+        cen = (0.3 * offset + 0.1 * g.standard_normal(d)).astype(F)
+        e = g.standard_normal((n, d))
+        x = np.concatenate([mu + e @ L.T, mu + 20.0 * e, offset * g.choice([-1.0, 1.0], (n, 1)) + 3.0 * e]).astype(F)
+        const = F(np.log(np.abs(np.diag(W).astype(np.float64))).sum())
+        l32, _s = _scores(W, (x - mu).astype(F), const, False)
+        # the BF16 form of the first r rows
+        xc = (x[:, :r] - cen[:r]).astype(F)
+        W64 = W.astype(np.float64)[:r, :r]
+        beta = (-W64 @ (mu[:r].astype(np.float64) - cen[:r])).astype(F)
+        wb, xb = _bf16(W[:r, :r]), _bf16(xc)
+        s2 = np.zeros(x.shape[0], F)
+        for j in range(r):
+            y = np.full(x.shape[0], beta[j], F)
+            for i in range(j + 1):
+                y = (y.astype(np.float64) + wb[j, i].astype(np.float64) * xb[:, i]).astype(F)
+            s2 = (s2.astype(np.float64) + y.astype(np.float64) ** 2).astype(F)
+        s = np.sqrt(s2).astype(np.float64)
+        f = np.sqrt((W64 ** 2).sum())
+        rx = np.sqrt((xc.astype(np.float64) ** 2).sum(axis=1))
+        m = np.sqrt(((mu[:r].astype(np.float64) - cen[:r]) ** 2).sum())
+        # E with W's rounding bounded by 2^-8, and by its own norm
+        own = np.sqrt(((W[:r, :r] - wb).astype(np.float64) ** 2).sum())
+        for ew in ((g0 + g2) * f, (0.5 * g0 + g2) * f + own):
+            E = ew * rx + g2 * f * m + eps * s
+            up = const - 0.5 * np.maximum(s - E, 0.0) ** 2
+            up = up + 1e-6 * (np.abs(const - up) + np.abs(const))
+            assert np.all(l32 <= up), np.max(l32 - up)
+            if r == d:
+                low = const - 0.5 * (s + E) ** 2
+                low = low - 1e-6 * (np.abs(const - low) + np.abs(const))
+                assert np.all(low <= l32), np.max(low - l32)
