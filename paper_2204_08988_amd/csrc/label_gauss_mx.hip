@@ -10,12 +10,12 @@
 // cache, and the draw ran at 11% of the vector ALUs' rate.
 //
 // Every score has the bits of the vector-ALU form (a log-likelihood of a row with an
-// infinite coordinate too), and the draw is the argmax
-// of l_k + g_k (the smaller k on ties), so the labels are those of that form.
+// infinite coordinate too), and the draw is the argmax of l_k + g_k (the smaller k on
+// ties), so the labels are those of that form.
 //
 // Bound by the FP32 matrix cores and the vector ALUs together: on this chip the
 // two do not overlap (four MFMAs 147 cycles, with 16 vector FMAs 200, at two
-// waves per SIMD).  Measured against the vector-ALU kernels that this one
+// waves per SIMD; the log-likelihoods of larger d run at one).  Measured against the vector-ALU kernels that this one
 // replaced: d = 128, N = 1e6, K = 32: 61.9 -> 5.6 ms (9 -> 97 TFLOP/s of
 // algorithmic work, 120 executed); d = 100, N = 1e5, K = 32: 15.2 -> 0.56 ms;
 // log-likelihoods at d = 32, N = 1e5, K = 20: 1.89 -> 0.15 ms.
@@ -199,7 +199,9 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_loglik_gauss_mx(const float* __
   }
 }
 
-constexpr size_t MX_LDS_RECORDS = 72 * 1024;  // staged records: two workgroups per CU
+// staged records of a draw: two workgroups per CU.  (The log-likelihoods' output tile
+// comes on top: from d = 29 or so on, wherever the groups are the widest, one per CU)
+constexpr size_t MX_LDS_RECORDS = 72 * 1024;
 constexpr int MX_LDS_MAX = 160 * 1024;
 
 }  // namespace

@@ -13,11 +13,11 @@
 // for about 16 mantissa bits.
 //
 // The BF16 main passes (k_label_gauss_b32, k_label_gauss_mfma_uc) centre the points
-// once on a centre common to all clusters (d = 32: or on each cluster's, for data far from
-// a common centre) and start each cluster's
-// accumulators at W_k (c - mu_k), so that the rows are rounded to BF16 once per
-// step instead of once per cluster; each of its scores carries an interval
-// that bounds the BF16 and FP32 rounding errors.
+// once on a centre common to all clusters and start each cluster's accumulators at
+// W_k (c - mu_k), so that the rows are rounded to BF16 once per step instead of once
+// per cluster (d = 32: or on each cluster's mean, for data far from a common centre);
+// each of their scores carries an interval that bounds the BF16 and FP32 rounding
+// errors.
 //
 // Precision guard: if the runner-up is within the Gumbel range of the leader,
 // widened by an allowance for the BF16 rounding of both scores, the point is

@@ -1,12 +1,14 @@
-// Multinomial label step, float32 VALU path: Sec. 4.1 steps (e) and (f)
-// with multinomial components (Sec. 2.1).
+// Label step of dense counts in float32: Sec. 4.1 steps (e) and (f) with
+// multinomial components (Sec. 2.1; Poisson ones score alike).
 //
 // Score of a component: l = log w + sum_v x_v log theta_v (the multinomial
-// coefficient is the same for every component and is left out).  One lane per
-// point; the count row is converted to float32 once (counts below 2^24 are
-// exact) and held in registers, the uniform cluster loop reads log theta with
-// scalar loads.  Label and sub-label draws as in the Gaussian kernel: top-2
-// screen, lazy Gumbel-max, logistic skipped outside its range.
+// coefficient is the same for every component and is left out).  Two kernels:
+// k_label_mult_mfma on the FP32 matrix cores while log theta of all clusters fits
+// in LDS, and for more of them k_label_mult, one lane per point: the count row is
+// converted to float32 once (counts below 2^24 are exact) and held in registers, the
+// uniform cluster loop reads log theta with scalar loads; label and sub-label draws as in
+// the Gaussian kernel: top-2 screen, lazy Gumbel-max, logistic skipped outside its
+// range.
 #include "kernels.hpp"
 #include "score_mx.hpp"
 

@@ -22,19 +22,20 @@
 //                 and a list of the others for the main pass.
 // FP32 scores have the bits of the kernel that forms them all (label_gauss_mx.hip), and
 // what the bounds settle no score would change (interval.hpp), so the labels are the same
-// whatever the data.  A BF16 draw, whose main pass over all
-// points is within three times of this, first looks at 512 of the points (k_guess
-// <true>) and takes that main pass where less than 3/4 of them would be settled.
+// whatever the data.  A BF16 draw, whose main pass over all points is within three times
+// of this, first looks at 512 of the points (k_guess<true>) and takes that main pass
+// where less than 3/4 of them would be settled.
 //
 // Label step (with sub-labels and statistics), all rows of every cluster -> so, us.
-// FP32, means N(0, 9 I): d = 128, N = 1e6, K = 32 6165 -> 1306, N = 1e5, K = 64 1596 ->
-// 443; d = 64, N = 5e5, K = 16 631 -> 315; d = 48, N = 1e5, K = 64 349 -> 150.  Where
+// FP32, means N(0, 9 I): d = 128, N = 1e6, K = 32 6080 -> 1233, N = 1e5, K = 64 1556 ->
+// 393; d = 64, N = 5e5, K = 16 613 -> 308; d = 48, N = 1e5, K = 64 337 -> 144.  Where
 // nearly every cluster stays in range of every point (means N(0, 0.01 I)) the extra
-// passes cost 6 to 8% at d = 128, 18% at d = 64, 19 to 32% at d = 48.
-// BF16: d = 128, N = 2e6, K = 100, means N(0, 9 I) 5230 -> 2400 (draw 3.1 -> 1.1 ms:
-// guess 0.47, sort and probe 0.15, whole scores 0.26, open points 0.15), N(0, 2.25 I)
-// 5263 and 5329, N(0, 0.09 I) 7480 and 7386; d = 64, N = 2e6, K = 200, N(0, 4 I) 3307
-// -> 2060, K = 50, N(0, 0.25 I) 1578 and 1484.
+// passes cost 6% at d = 128, 21% at d = 64, 36% at d = 48.
+// BF16: d = 128, N = 2e6, K = 100, means N(0, 9 I) 5414 -> 2630 (draw 3.3 -> 1.1 ms:
+// guess 0.47, sort and probe 0.15, whole scores 0.27, open points 0.15), N(0, 2.25 I)
+// 5854 and 5832, N(0, 0.09 I) 7234 and 7237; d = 64, N = 2e6, K = 200, N(0, 4 I) 3358
+// -> 2240, N(0, 0.25 I) 4063 and 4051; N = 1e6, N(0, 0.25 I), where the look at the sample
+// is 3 to 4%: K = 200 2190 and 2256, K = 64 984 and 1026.
 #include "interval.hpp"
 #include "kernels.hpp"
 #include "score.hpp"

@@ -1,12 +1,15 @@
-// Sub-labels and statistics of the dimensions without a kernel of their own in
-// sorted.hip: Sec. 4.1 step (f) and Sec. 4.4 over cluster-sorted rows.
+// Sub-labels of cluster-sorted rows from d = 32 on, sub-labels and statistics of the
+// smaller dimensions without a launch of their own in sorted.hip: Sec. 4.1 step (f) and
+// Sec. 4.4.
 //
-//   d <= 31       k_sub_stats_w, one instantiation per dimension (the generic
-//                 kernel before it read both operands of every FMA from LDS:
-//                 N = 5e5, K = 16: d = 6 551 -> 30 us, 20 742 -> 61, 31 1035 -> 120);
-//   33 <= d < 128 k_sub_labels_mx: the two sub-cluster scores of a row on the
-//                 FP32 matrix cores (score_mx.hpp), with the bits of the
-//                 vector-ALU form.  The statistics follow in k_sub_stats_big.
+//   d <= 31   k_sub_stats_w, one instantiation per dimension (the generic
+//             kernel before it read both operands of every FMA from LDS:
+//             N = 5e5, K = 16: d = 6 551 -> 30 us, 20 742 -> 61, 31 1035 -> 120);
+//   d >= 32   k_sub_labels_mx: the two sub-cluster scores of a row on the
+//             FP32 matrix cores (score_mx.hpp), with the bits of the
+//             vector-ALU form (d = 64, 128 with BF16 tables: on the rows that the bf16x3
+//             pass leaves).  The statistics follow in k_sub_stats_w (d = 32) or
+//             k_sub_stats_big.
 #include "kernels.hpp"
 #include "score.hpp"
 #include "score_mx.hpp"
