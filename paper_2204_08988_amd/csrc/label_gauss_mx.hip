@@ -153,7 +153,7 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_loglik_gauss_mx(const float* __
     const int rows = (int)(n - base < 64 ? (n - base > 0 ? n - base : 0) : 64);
     float xv[4][4 * RB];
     load_chunk<RB>(x, base, rows, d, xv);
-    bool odd_q = false;
+    float q = 0.0f;
     for (int g0 = jb; g0 < je; g0 += cg) {
       const int nj = je - g0 < cg ? je - g0 : cg;
       const bool wrap = g0 + cg >= je;
@@ -161,9 +161,7 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_loglik_gauss_mx(const float* __
       if (!wrap || chunk + step < n) fetch(odd ? buf0 : buf1, gn, je - gn < cg ? je - gn : cg);
       mx::lds_cfloat* rec = (mx::lds_cfloat*)(odd ? buf1 : buf0);
       for (int c = 0; c < nj; ++c, rec += S) {
-        float q;
         mx::sq_norm<RB>(rec, d, xv, q, mx::Always());
-        odd_q = odd_q || q != q;
         const int j = g0 + c, o = j % LL_GRP;
         tile[lane * (LL_GRP + 1) + o] = fmaf(-0.5f, q, rec[0]);
         if (o == LL_GRP - 1 || j == je - 1) {
@@ -184,9 +182,9 @@ __global__ __launch_bounds__(MX_BLOCK, 2) void k_loglik_gauss_mx(const float* __
       __syncthreads();
       odd = !odd;
     }
-    // a score that is not a number: where the row has an infinity, again by the plain chain (the stores
-    // above have landed)
-    if (__ballot(odd_q)) {
+    // a score that is not a number (the last stands for all: an infinity meets the zeros above every W's
+    // diagonal): where the row has an infinity, again by the plain chain (the stores above have landed)
+    if (__ballot(q != q)) {
       const float* xr = x + (size_t)(base + (lane < rows ? lane : 0)) * d;
       bool mine = false;
       for (int c = 0; c < d; ++c) mine = mine || __builtin_isinf(xr[c]);
