@@ -352,6 +352,8 @@ def headline(args):
                                "means N(0,9I), covariances Wishart(d+2, I/d), weights Dir(1); converged state "
                                f"(generating labels); cluster scoring {args.precision} with the FP32 guard, "
                                "sub-labels bf16x3 with the FP32 guard, statistics and parameters FP64",
+                   "evaluations": "N (K + 2) per iteration; the draw settles most point-cluster pairs by a bound of "
+                                  "their first 32 whitened coordinates, the labels being those of the full scores",
                    "n": rec["n"], "d": d, "k_mean": rec["k_mean"], "alpha": ALPHA, "parallelism": "single GPU"},
         "iters_per_s": rec["iters_per_s"],
         "phase_ms": rec["phase_ms"],
